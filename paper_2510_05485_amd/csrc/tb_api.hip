@@ -332,7 +332,8 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
       // per-sentence work is done by the fused kernel; only the batch sums remain
       Problem quiet = c.pb;
       quiet.status = nullptr;
-      return hip_rc(launch_finalize(quiet, c.st, c.sp, false, true, corpus, out_bleu, c.stream));
+      return hip_rc(launch_finalize(quiet, c.st, c.sp, false, true, corpus, out_bleu, c.stream,
+                                    nullptr, true));
     }
     return TB_OK;
   }

@@ -74,8 +74,9 @@ __device__ __forceinline__ float bleu_from_stats(const IntT* clipped, const IntT
 
 // The same score, bit for bit, computed by one wavefront: lane n < N holds the statistics of
 // order n + 1, the four logarithms run side by side and so do the two exponentials.  All 64
-// lanes must be active; the result is valid in every lane.
-__device__ __forceinline__ float bleu_from_stats_wave(int cn, int tn, int c, int r,
+// lanes must be active; c and r are the same in every lane; the result is valid in every lane.
+template <typename IntT>
+__device__ __forceinline__ float bleu_from_stats_wave(IntT cn, IntT tn, IntT c, IntT r,
                                                       const ScoreParams& sp) {
   const int lane = threadIdx.x & (kWave - 1);
   const bool order_lane = lane < sp.N;
@@ -86,9 +87,8 @@ __device__ __forceinline__ float bleu_from_stats_wave(int cn, int tn, int c, int
   for (int n = 1; n < 8; ++n) w = (lane == n) ? sp.w[n] : w;
   bool dead = false;
   float t = 0.0f;
-  if (order_lane) t = order_log_term<int>(lane + 1, cn, tn, zeros_seen, sp, w, &dead);
+  if (order_lane) t = order_log_term<IntT>(lane + 1, cn, tn, zeros_seen, sp, w, &dead);
   const bool any_dead = __builtin_amdgcn_ballot_w64(dead) != 0ull;
-  const int first_clipped = lane_value(cn, 0);
   float logsum = 0.0f;
 #pragma unroll
   for (int n = 0; n < 8; ++n)
@@ -97,7 +97,7 @@ __device__ __forceinline__ float bleu_from_stats_wave(int cn, int tn, int c, int
   const float y = expf(x);
   const float e0 = __int_as_float(lane_value(__float_as_int(y), 0));
   const float e1 = __int_as_float(lane_value(__float_as_int(y), 1));
-  if (c == 0 || first_clipped == 0 || any_dead) return 0.0f;
+  if (c == 0 || (zero_mask & 1ull) || any_dead) return 0.0f;
   return ((c > r) ? 1.0f : e1) * e0;
 }
 
