@@ -113,7 +113,6 @@ struct Plans {
   tb_layout_t layout;
   DictPlan dict;
   CountPlan count;
-  FusedPlan fused;
   BigPlan big;
   PartPlan part;
   HierPlan hier;
@@ -158,7 +157,7 @@ int make_plans(int32_t B, int32_t R, int64_t cand_stride, int64_t ref_stride,
   L.global_tables_in_hbm = p->use_big ? 1 : 0;
   L.global_partitions = p->use_part ? (1 << p->part.log2_parts) : 0;
   L.global_candidate_first = p->use_hier ? 1 : 0;
-  L.fused_ok = plan_fused(cand_stride, ref_stride, R, N, L.bits, &p->fused);
+  L.fused_ok = fused_path_takes(cand_stride, ref_stride, R, L.bits);
   int path = cfg->force_path;
   if (path == TB_PATH_AUTO) path = L.fused_ok ? TB_PATH_FUSED : TB_PATH_GLOBAL;
   if (path == TB_PATH_FUSED && !L.fused_ok) return TB_ERR_UNSUPPORTED;
@@ -315,6 +314,22 @@ hipError_t run_count_clip(const Call& c, const ScoreTail* tail = nullptr) {
                          : launch_count_clip(c.pb, c.ws, c.plans.count, c.st, c.stream);
 }
 
+// Whether the call runs on the fused kernel: on its own path, and on AUTO also for longer shapes
+// that its plan covers.  (In a workspace that is larger than it needs.  The statistic group_distinct
+// is the size of the group's dictionary there, which only the staged kernels build.)  The partitioned
+// kernels spread a group over the chip, the fused one gives it one compute unit: with 6400 tokens a
+// sequence they take 30 us for one group, 40 for 32 and 82 for 128, the fused kernel 38, 40 and 41.
+bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
+                 FusedPlan* plan) {
+  const Problem& pb = c.pb;
+  if (c.plans.layout.path != TB_PATH_FUSED) {
+    if (cfg->force_path != TB_PATH_AUTO || cfg->workspace_tables) return false;
+    if (stats && stats->group_distinct) return false;
+    if (c.plans.use_part && pb.B < 32) return false;
+  }
+  return plan_fused(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.bits, rouge, plan);
+}
+
 int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
             const void* refs, int64_t ref_stride, const int32_t* ref_len, int32_t B, int32_t R,
             const tb_config_t* cfg, void* out_bleu, const tb_stats_t* stats, void* workspace,
@@ -324,9 +339,11 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
                    workspace, workspace_bytes, hip_stream, true, TB_PATH_AUTO, &c);
   if (rc != TB_OK || B == 0) return rc;
   if (!out_bleu) return TB_ERR_INVALID_ARG;
-  if (c.plans.layout.path == TB_PATH_FUSED) {
-    rc = hip_rc(launch_fused(c.pb, c.plans.fused, c.st, c.sp, corpus ? nullptr : out_bleu,
-                             c.stream));
+  FusedPlan plan;
+  const bool fused = takes_fused(c, cfg, stats, false, &plan);
+  if (!fused && c.plans.layout.path == TB_PATH_FUSED) return TB_ERR_UNSUPPORTED;
+  if (fused) {
+    rc = hip_rc(launch_fused(c.pb, plan, c.st, c.sp, corpus ? nullptr : out_bleu, c.stream));
     if (rc != TB_OK) return rc;
     if (corpus || c.want_corpus_stats) {
       // per-sentence work is done by the fused kernel; only the batch sums remain
@@ -411,8 +428,10 @@ int tensorrouge_n(const void* cand, int64_t cand_stride, const int32_t* cand_len
   c.st.total = reinterpret_cast<int32_t*>(w + L.total_off);
   c.st.closest = reinterpret_cast<int32_t*>(w + L.closest_off);
   c.st.distinct = reinterpret_cast<int32_t*>(w + L.distinct_off);
-  if (L.path == TB_PATH_FUSED)
-    return hip_rc(launch_fused(c.pb, c.plans.fused, c.st, c.sp, nullptr, c.stream, &ro));
+  FusedPlan plan;
+  if (takes_fused(c, cfg, nullptr, true, &plan))
+    return hip_rc(launch_fused(c.pb, plan, c.st, c.sp, nullptr, c.stream, &ro));
+  if (L.path == TB_PATH_FUSED) return TB_ERR_UNSUPPORTED;
   // GLOBAL: pack and dictionary as for BLEU (the keys of order n build on the ids of the orders
   // below), then the count pass for order n alone, which also sums the per-reference overlaps
   // (the packed-key LDS count kernels are BLEU-only: such a shape is served with

@@ -1,22 +1,53 @@
-// FUSED path: the whole per-sentence pipeline in one kernel, one workgroup per sentence group.
+// FUSED kernel: the whole per-sentence pipeline for one sentence group in one workgroup.
 //
-// Tokens of the candidate and its references are read from HBM once and staged in LDS; then, for
-// each order n, the workgroup
-//   1. inserts the candidate's n-grams into an LDS open-addressing table (the dictionary of
-//      Section 3.2, restricted to the candidate: an n-gram that the candidate lacks cannot
-//      contribute to min(candidate count, reference count)); the id of a distinct n-gram is the
-//      candidate position whose insertion created its entry,
-//   2. looks the reference n-grams up and bumps the 16-bit counter field that belongs to
-//      (id, reference) -- one field per sequence keeps the sequences' counts apart, which is what
-//      the offset of Section 3.3 step 1 achieves,
-//   3. lets the thread that created an entry take the maximum over the reference fields and the
-//      minimum with the candidate field (Section 3.3 step 3) and sum it,
-// and finally wavefront 0 forms the brevity penalty, smoothing and geometric mean (Section 3.4),
-// one order per lane.  HBM traffic is the tokens in and one score (plus optional integer
-// statistics) out.  The same kernel, instantiated with ROUGE = true, scores ROUGE-N instead.
+// Tokens are read from HBM once; dictionary and counters never leave LDS; one score (plus optional
+// integer statistics) goes out.  What bounds it: instruction issue.  A lone small group pays seven or
+// eight cycles per instruction of its longest wavefront; a full chip is limited by the vector unit
+// (1.5 simple instructions per cycle and compute unit) and just as much by the one scalar unit (1.0),
+// which loops, masks and bookkeeping keep busy.  LDS is not the limit (a random 16-byte read takes
+// 12.5 cycles per wavefront, a 4-byte one 6.5, a compare-and-swap 12).  So:
+//   * Symbols.  Order 1 turns every token into the candidate position that holds its first
+//     occurrence there (its "symbol"), or into "absent" (-1).  An n-gram of order n >= 2 is then
+//     named by (id of the (n-1)-gram that starts at the same position, symbol of its last token):
+//     at most 2 * log2(candidate stride) bits whatever n and the vocabulary are.  Once the symbols
+//     of all positions are in LDS, a thread walks all orders of its positions on its own: a
+//     candidate position enters its n-grams one order after the other (an id is known as soon as
+//     the entry is), a reference position looks its n-grams up until one is absent (a candidate
+//     n-gram extends only prefixes the candidate contains).  No barrier lies between the orders.
+//   * Entries that carry the id.  A table entry is one 32-bit word (remainder | probe count | id).
+//     The key is multiplied by an odd constant modulo 2^key_bits (a bijection); the top bits of the
+//     product pick the home bucket and the remaining bits are stored.  Bucket and probe count give
+//     back the home bucket (the probe step depends on the remainder only), so (bucket, remainder,
+//     probe count) identifies the key exactly, and one LDS read answers both "is it this key" and
+//     "what is its id": no second array and no second dependent read.
+//   * Buckets of four slots, filled front to back.  A look-up reads a bucket with one request and
+//     is straight-line code: only a full bucket without the key makes it go on.
+//   * A group's positions are dealt to the wavefronts in blocks of 64 that lie in one sequence, so
+//     sequence, row, counter word and addend of a block are scalars.
+//   * The orders of a pass put their number into the key and share one table, each with counters of
+//     its own.  How many orders that are is the plan's choice: all of them (fewest barriers), or
+//     fewer where LDS is short (table and counters are then swept and cleared in between).
+//
+// Counters: one 16-bit field per sequence and candidate id (the offset of Section 3.3 step 1 keeps
+// sequences apart the same way); the sweep takes the maximum over the reference fields and the
+// minimum with the candidate's (step 3).  Wavefront 0 forms brevity penalty, smoothing and geometric
+// mean (Section 3.4), one order per lane.  With ROUGE = true the kernel scores ROUGE-N for n = N.
+//
+// Measured on gfx950 (us of GPU time, 4 orders; in brackets the kernel that had one barrier per
+// insertion and look-up of each order, 64-bit-wide slots and a list of live positions in LDS):
+// 16 x 256 tokens with one reference 7.0 (9.5), 256 x 1088 10.1 (12.8), 512 x 1024 with four
+// references 20.2 (22.8), 4096 x 512 with two 47.7 (50.5), 4096 x 2048 with two 152 (171), 1000 x 96
+// with up to eight 11.3 (13.7), ROUGE-2 of 512 x 512 with three 11.0 (12.5); 128 x 5000 with one
+// 31 (55, on three staged kernels), 128 x 8192 52 (98, on the partitioned ones).
+#include <type_traits>
+
 #include "tb_kernels.h"
 #include "tb_score.h"
 
+#ifdef TB_TUNE
+#include <cstdio>
+#include <cstdlib>
+#endif
 // Phase time stamps for tuning builds only (-DTB_STAMPS), as in the hierarchical kernels.
 #ifdef TB_STAMPS
 __device__ unsigned long long tb_fused_stamps[8192 * 32];
@@ -31,426 +62,491 @@ extern "C" int tb_debug_stamps_fused(unsigned long long* host, int count) {
 
 namespace tb {
 
-constexpr int kMaxFusedSeqs = kWave;  // candidate + references handled by one lane each
-constexpr uint32_t kEmptySlot = 0xFFFFFFFFu;
-constexpr size_t kLdsForTwoWorkgroups = 78 * 1024;  // per workgroup, so that two share a CU
+namespace {
+
+constexpr int kMaxSeqs = kWave;     // candidate + references, one lane each
+constexpr int kPadSymbols = 8;      // absent symbols behind every sequence: orders up to 8
+constexpr int kMaxBlocks = 24;      // per wavefront
 
 struct FusedArgs {
   Problem pb;
   StatPtrs st;
   ScoreParams sp;
-  void* out;            // per-sentence scores (fp32 or bfloat16: sp.out_bf16), or null
-  // ROUGE-N mode (fused_kernel<.., true>): order N = pb.N only
-  void* rouge_prf;      // [B, 3] precision, recall, F of the best reference (same type)
+  void* out;               // per-sentence scores (fp32 or bfloat16: sp.out_bf16), or null
+  void* rouge_prf;         // ROUGE-N (order N = pb.N): [B, 3] (same type)
   int32_t* rouge_overlap;  // [B, R] or null
-  int32_t* rouge_best;  // [B] or null
-  float beta2;          // beta squared
-  int table_slots;      // power of two
-  int table_shift;      // 32 - log2(table_slots)
-  int words;            // 32-bit counter words per id: ceil((R + 1) / 2)
-  int list_per_wave;    // work-list entries reserved for each wavefront
-  int progress_priority;  // 1: wavefronts of a workgroup that is behind get the higher priority
-  uint32_t off_ids, off_cnt, off_cstate, off_tok, off_list;
+  int32_t* rouge_best;     // [B] or null
+  float beta2;             // beta squared
+  uint32_t pass_ends;      // bits 4(n - 1)..: last order of the pass that starts with order n >= 2;
+                           // bits 0..3: 1 if order 1 is a pass of its own, else 0
+  int cand_stride, ref_stride;
+  int log2_slots, log2_waves;
+  int id_bits;             // ids (candidate positions) are below 2^id_bits
+  int first_payload, first_key_bits;  // payload bits and key bits (order within the pass | payload)
+                                      // of the table that order 1 is in
+  int later_payload, later_key_bits;  // ... of the passes behind it
+  int words;               // 32-bit counter words per id; field 0: candidate, field 1 + j: reference j
+  int set_words;           // counter words of one order
+  int table_and_counters;  // 16-byte units of table and counters together
+  uint32_t off_sym, off_sums;
+  int progress_priority;   // 1: wavefronts of a workgroup that is behind get the higher priority
 };
 
-static size_t fused_layout(int slots, int64_t cand_stride, int64_t cap, int list_total, int words,
-                           int tok_bytes, FusedPlan* plan) {
-  size_t off = size_t(slots) * 4;
-  plan->off_ids = off;
-  off += size_t(slots) * 2;
-  plan->off_cnt = off;
-  off += (size_t(cand_stride) * words * 4 + 15) & ~size_t(15);  // cleared in 16-byte stores
-  plan->off_cstate = off;
-  off += size_t(cand_stride) * 4;
-  plan->off_tok = off;
-  off += (size_t(cap + 4) * tok_bytes + 3) & ~size_t(3);
-  plan->off_list = off;
-  off += size_t(list_total) * 4;
-  return off;
+// LDS by byte offset.  (The kernel has dynamic LDS only, which starts at offset 0; going through the
+// array's name would cost an addition of that 0 per access.)
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lds(uint32_t offset) {
+  typedef __attribute__((address_space(3))) T* Ptr;
+  return (Ptr)(uintptr_t)(offset);
+}
+__device__ __forceinline__ uint32_t lds_cas(uint32_t at, uint32_t desired) {  // expects 0
+  uint32_t expected = 0u;
+  __hip_atomic_compare_exchange_strong((uint32_t*)lds<uint32_t>(at), &expected, desired,
+                                       __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                       __HIP_MEMORY_SCOPE_WORKGROUP);
+  return expected;
+}
+__device__ __forceinline__ void lds_add(uint32_t at, uint32_t v) {
+  __hip_atomic_fetch_add((uint32_t*)lds<uint32_t>(at), v, __ATOMIC_RELAXED,
+                         __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-bool plan_fused(int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
-                FusedPlan* plan) {
-  (void)N;
-  if (R + 1 > kMaxFusedSeqs) return false;
-  const int64_t cap = cand_stride + int64_t(R) * ref_stride;
-  // list entries pack position (14 bits), id (12 bits) and sequence index (6 bits)
-  if (cap > 12 * 1024 || cand_stride > 4096 || ref_stride > 65535) return false;
-  // key = id * 2^bits + token, id < cand_stride, must stay below the all-ones empty marker
-  if (bits > 31 || (uint64_t(cand_stride) << bits) > 0xFFFFFFFFull) return false;
-  int t = 256;
-  while (t < 1024 && cap > 4 * t) t *= 2;
-  plan->threads = t;
-  const int need = int((cap + t - 1) / t);
-  plan->items = need <= 2 ? 2 : need <= 4 ? 4 : need <= 6 ? 6 : need <= 8 ? 8 : 12;
-  plan->words = (R + 2) / 2;
-  plan->tok_bytes = bits <= 16 ? 2 : 4;
-  const int nwaves = t / kWave;
-  const int64_t list_cap = int64_t(R) * ref_stride;
-  plan->list_per_wave = int((list_cap + nwaves - 1) / nwaves);
-  plan->list_per_wave = (plan->list_per_wave + kWave - 1) / kWave * kWave;
-  const int list_total = plan->list_per_wave * nwaves;
-  int base = 256;
-  while (int64_t(base) * 3 < cand_stride * 4) base <<= 1;
-  // the emptier the table the fewer probes; take the largest of 4x, 2x, 1x the minimum size
-  // that still lets two workgroups share a compute unit, else the minimum size
-  plan->table_slots = base;
-  plan->lds_bytes =
-      fused_layout(base, cand_stride, cap, list_total, plan->words, plan->tok_bytes, plan);
-  for (int mult = 4; mult >= 2; mult >>= 1) {
-    FusedPlan trial = *plan;
-    const size_t bytes = fused_layout(base * mult, cand_stride, cap, list_total, plan->words,
-                                      plan->tok_bytes, &trial);
-    if (bytes + 1024 <= kLdsForTwoWorkgroups && base * mult <= 65536) {
-      *plan = trial;
-      plan->table_slots = base * mult;
-      plan->lds_bytes = bytes;
-      break;
-    }
+// The table of one pass, at LDS offset 0: buckets of four slots, filled front to back.  0: free slot;
+// probe counts start at 1, so no entry is 0 (nor below id_limit).
+struct SymbolTable {
+  uint32_t bucket_mask;  // byte offsets of buckets
+  int home_shift;        // 30 - log2(slots)
+  int log2_buckets;
+  uint32_t multiplier;   // odd << (32 - key bits)
+  uint32_t id_limit;     // 1 << id_bits
+  uint32_t longest;      // largest probe count an entry can hold, << id_bits
+  uint32_t lost_at;      // LDS word set to 1 when a probe sequence reaches that count
+
+  // (an odd number of buckets further, from the remainder alone)
+  __device__ __forceinline__ uint32_t step(uint32_t remainder) const {
+    return ((remainder >> 16) & ~31u) | 16u;
   }
-  return plan->lds_bytes + 1024 <= size_t(kLdsBudget);
-}
-
-// The candidate's dictionary of one order: an open-addressing table of 32-bit keys with double
-// hashing.  One 32-bit multiply hashes the key: the top bits of the product pick the slot, lower
-// bits the (odd) probe step, so a probe sequence reaches every slot of the power-of-two table.
-// A probe loop ends at the key or at an empty slot and needs no round limit: the odd step visits
-// every slot of the power-of-two table, which is at most 3/4 full (only candidate n-grams are
-// inserted, at most cand_stride of them) and written by this workgroup alone after clearing it.
-// The loops have a single exit (one condition, no break):
-// that halves the instructions the compiler emits per probe round.  (Measured on this hardware:
-// plain divergent loops beat
-// variants that keep all lanes in lock step until the slowest is done, and probing slot pairs
-// or 4-slot buckets with wider LDS reads did not pay either.)
-struct ProbeTable {
-  uint32_t* slots;
-  uint32_t mask;  // slots - 1
-  int shift;      // 32 - log2(slots)
-
-  static constexpr uint32_t kNotFound = 0xFFFFFFFFu;
-
-  // Slot of `key`, or kNotFound.  Lanes with active == false return kNotFound.
-  __device__ __forceinline__ uint32_t find(uint32_t key, bool active) const {
-    uint32_t found = kNotFound;
-    if (active) {
-      const uint32_t h = key * 0x9E3779B1u;
-      const uint32_t step = (h >> 3) | 1u;
-      uint32_t s = h >> shift;
-      uint32_t e = slots[s];
-      while (int(e != key) & int(e != kEmptySlot)) {
-        s = (s + step) & mask;
-        e = slots[s];
-      }
-      found = (e == key) ? s : kNotFound;
+  // Id of the key with product h, entered as `id` where it is not there: tries the slots of its
+  // buckets one after the other.  Ends: the odd step visits every bucket, the plan keeps the table
+  // at most 3/4 full, and only this workgroup writes it.
+  __device__ __forceinline__ uint32_t claim(uint32_t h, uint32_t id) const {
+    uint32_t s = (h >> home_shift) & bucket_mask;
+    const uint32_t remainder = h << log2_buckets;
+    uint32_t mine = remainder + id_limit;
+    uint32_t old = lds_cas(s, mine + id);
+    uint32_t x = old ^ mine;
+    while (min(old, x) >= id_limit) {  // neither free nor the key
+      s += 4u;
+      const bool leaves = (s & 15u) == 0u;  // (selects, no branch)
+      const uint32_t jump = (s - 16u + step(remainder)) & bucket_mask;
+      s = leaves ? jump : s;
+      mine = min(mine + (leaves ? id_limit : 0u), remainder + longest);
+      old = lds_cas(s, mine + id);
+      x = old ^ mine;
     }
-    return found;
+    if (__builtin_expect(mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
+    return old == 0u ? id : x;
   }
-
-  // Claim-or-find for active lanes.  Returns the slot; *won is set where this call created
-  // the entry.
-  __device__ __forceinline__ uint32_t insert(uint32_t key, bool active, bool* won) const {
-    uint32_t slot = 0;
-    bool created = false;
-    if (active) {
-      const uint32_t h = key * 0x9E3779B1u;
-      const uint32_t step = (h >> 3) | 1u;
-      uint32_t s = h >> shift;
-      uint32_t old = atomicCAS(&slots[s], kEmptySlot, key);
-      while (int(old != kEmptySlot) & int(old != key)) {
-        s = (s + step) & mask;
-        old = atomicCAS(&slots[s], kEmptySlot, key);
-      }
-      created = old == kEmptySlot;
-      slot = s;
+  __device__ __forceinline__ static uint32_t match(const uint4& e, uint32_t mine) {
+    return min(min(min(e.x ^ mine, e.y ^ mine), e.z ^ mine), e.w ^ mine);
+  }
+  __device__ __forceinline__ static uint4 bucket(uint32_t at) {
+    typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+    const Quad q = *lds<Quad>(at);
+    return make_uint4(q.x, q.y, q.z, q.w);
+  }
+  // Id of the key, or a value of at least id_limit: one 16-byte request answers unless the bucket
+  // is full and does not hold the key.
+  __device__ __forceinline__ uint32_t find(uint32_t h) const {
+    uint32_t s = (h >> home_shift) & bucket_mask;
+    const uint32_t remainder = h << log2_buckets;
+    uint32_t mine = remainder + id_limit;
+    uint4 e = bucket(s);
+    uint32_t x = match(e, mine);
+    if (min(x, e.w) >= id_limit) {
+      do {
+        s = (s + step(remainder)) & bucket_mask;
+        mine = min(mine + id_limit, remainder + longest);
+        e = bucket(s);
+        x = match(e, mine);
+      } while (min(x, e.w) >= id_limit);
+      if (__builtin_expect(mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
     }
-    *won = created;
-    return slot;
+    return x;
   }
 };
 
-// One workgroup per sentence group.
-//
-// Keys are hierarchical: the order-n key of a position is (id of its (n-1)-gram prefix) * 2^bits
-// + the n-th token, where the id of a distinct candidate n-gram is the candidate position that
-// created its table entry (order-0 ids are 0).  By induction two positions carry the same
-// order-n key exactly when their n-grams are equal, so the key never needs more than
-// log2(cand_stride) + bits bits whatever n is, and one 32-bit LDS compare-and-swap claims a slot.
-//
-// A reference position whose n-gram is not in the candidate's table cannot match at any higher
-// order either (a candidate n-gram extends only prefixes the candidate contains), so it is
-// dropped.  Each wavefront owns a slice of the reference positions and keeps the survivors --
-// position, id, sequence index packed in one word -- compacted in its own LDS work list, so the
-// next order runs over full wavefronts; reading and appending stay inside the wavefront and
-// need neither atomics nor extra barriers.
-// SITEMS: token positions per thread (workgroup size * SITEMS >= tokens of a group).
-// The scalar-register cap matters for occupancy: two 1024-thread workgroups per compute unit are
-// eight wavefronts per SIMD, and on this hardware a kernel that allocates more than 80 scalar
-// registers gets only seven (measured: the same kernel at 96 runs one workgroup per compute
-// unit and takes 34 us instead of 25 us at the headline shape).
-// ROUGE: the same pipeline scores ROUGE-N for n = N instead of BLEU: at the last order the
-// creator of an entry adds min(candidate count, reference j's count) to an overlap sum per
-// reference, and the tail turns the sums into precision, recall and F.
-template <typename TokT, int SITEMS, bool ROUGE>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_num_sgpr(80)))
-void fused_kernel(FusedArgs a) {
-  extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  __shared__ int s_part[8];              // per order: clipped sum (low 16) | distinct count (high 16)
-  __shared__ int s_end[kMaxFusedSeqs];   // end of each sequence in back-to-back token indices
-  __shared__ int s_overlap[ROUGE ? kMaxFusedSeqs : 1];  // ROUGE: overlap with each reference
+// BLOCKS: blocks of 64 positions per wavefront.  KEEP: a pass starts above order 2, with the ids of
+// the order below.  WIDE: int64 token ids.
+// (The scalar-register cap keeps two 1024-thread workgroups on a compute unit: eight wavefronts per
+// SIMD need at most 80 scalar registers each on this hardware.)
+template <int BLOCKS, bool KEEP, bool WIDE, bool ROUGE>
+__global__ __launch_bounds__(1024, 8) __attribute__((amdgpu_num_sgpr(80)))
+void fused_kernel(FusedArgs by_value) {
+  // The arguments are read through the kernel-argument segment where they are used: loads of a
+  // by-value parameter all stand at the entry and would occupy scalar registers throughout.
+  (void)by_value;
+  const FusedArgs& a = *(const FusedArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  typedef std::conditional_t<WIDE, long long, int32_t> Token;
+  typedef std::conditional_t<WIDE, unsigned long long, uint32_t> UToken;
+  typedef uint32_t Quad __attribute__((ext_vector_type(4)));
   const Problem& pb = a.pb;
-  const int nt = blockDim.x, tid = threadIdx.x;
-  const int lane = tid & (kWave - 1), nwaves = nt / kWave;
-  // the wavefront's index as a scalar: loop bounds derived from it stay in scalar registers
+  const int nt = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int g = blockIdx.x;
-  const int R = pb.R, N = pb.N, T = a.table_slots;
-  const uint32_t W = uint32_t(a.words);
-  uint32_t* table = reinterpret_cast<uint32_t*>(smem);
-  uint16_t* ids = reinterpret_cast<uint16_t*>(smem + a.off_ids);
-  uint32_t* cnt = reinterpret_cast<uint32_t*>(smem + a.off_cnt);
-  uint32_t* cstate = reinterpret_cast<uint32_t*>(smem + a.off_cstate);
-  TokT* tok = reinterpret_cast<TokT*>(smem + a.off_tok);
-  uint32_t* my_list = reinterpret_cast<uint32_t*>(smem + a.off_list) + wave * a.list_per_wave;
-  const ProbeTable dict{table, uint32_t(T) - 1u, a.table_shift};
-  const int bits = pb.bits;
-  TB_FSTAMP(0);
-  if (a.progress_priority) __builtin_amdgcn_s_setprio(3);  // staging: as the first order, below
+  const int g = blockIdx.x, R = pb.R, N = pb.N;
+  // (in scalar registers: a select between two argument fields would otherwise become a vector
+  // load from a selected address)
+  const int cs = __builtin_amdgcn_readfirstlane(a.cand_stride);
+  const int rs = __builtin_amdgcn_readfirstlane(a.ref_stride);
+  const int log2_waves = a.log2_waves, nwaves = 1 << log2_waves;
+  const int lg = a.log2_slots, id_bits = a.id_bits;
+  const uint32_t sym_at = a.off_sym;
+  // per order and wavefront (16 words an order): clipped sum (low 16) | distinct count (high 16)
+  const uint32_t part_at = a.off_sums;
+  const uint32_t lost_at = part_at + 8 * 16 * 4;  // non-zero: a probe sequence was too long to be counted
+  const uint32_t overlap_at = lost_at + 4;        // ROUGE: overlap with each reference
+  const bool prio = a.progress_priority;
 
-  // lane j of every wavefront: length of sequence j and the inclusive prefix of lengths
-  // (a reference beyond the candidate's reference count has length 0 and no say in the closest
-  // reference length)
+  TB_FSTAMP(0);
+  if (prio) __builtin_amdgcn_s_setprio(3);
+
+  // lane j of every wavefront: length of sequence j (0 for a reference not in use), where its row
+  // is, and the prefix of the sequences' block counts
   const RefRows rr = ref_rows(pb, g, tid == 0);
   const int used = rr.used;
-  int my_len = 0;
-  if (lane <= used) {
-    my_len = (lane == 0)
-        ? clamped_len(pb.cand_len[g], pb.cand_stride, wave == 0 ? pb.status : nullptr)
-        : clamped_len(pb.ref_len[rr.row0 + lane - 1], pb.ref_stride,
-                      wave == 0 ? pb.status : nullptr);
+  const int raw_cand = uniform_load(pb.cand_len, g);
+  int raw_ref = 0;
+  if (lane >= 1 && lane <= used) raw_ref = pb.ref_len[rr.row0 + lane - 1];
+  const Token* const cand_row = static_cast<const Token*>(pb.cand) + uint64_t(g) * uint32_t(cs);
+  const Token* const ref_row =
+      static_cast<const Token*>(pb.refs) + uint64_t(rr.row0) * uint32_t(rs);
+  uint64_t row_at = reinterpret_cast<uint64_t>(ref_row) +
+                    uint64_t(uint32_t(lane - 1) * uint32_t(rs)) * sizeof(Token);
+  row_at = lane == 0 ? reinterpret_cast<uint64_t>(cand_row) : row_at;
+  const int raw_len = lane == 0 ? raw_cand : raw_ref;
+  const int my_len = min(max(raw_len, 0), lane == 0 ? cs : rs);
+  if (__builtin_amdgcn_ballot_w64(my_len != raw_len)) {  // uniform
+    if (wave == 0 && my_len != raw_len && pb.status) atomicOr(pb.status, TB_DEV_LENGTH_RANGE);
   }
-  const int incl = wave_inclusive_scan(my_len);
-  if (wave == 0 && lane <= R) {
-    s_end[lane] = incl;
-  }
-  if (tid < 8) s_part[tid] = 0;
-  if (ROUGE && tid < kMaxFusedSeqs) s_overlap[tid] = 0;
-  const int total_tokens = min(lane_value(incl, R), SITEMS * nt);
   const int cand_len = lane_value(my_len, 0);
+  const int my_seq_blocks = (my_len + kWave - 1) >> 6;
+  const int block_ends = wave_inclusive_scan(my_seq_blocks);
+  const int block_begins = block_ends - my_seq_blocks;
+  const int ends = lane <= R ? block_ends : 0x7FFFFFFF;
+  const int blocks = min(lane_value(block_ends, kWave - 1), BLOCKS << log2_waves);
+  const int cand_blocks = lane_value(block_ends, 0);
+  auto sequence_of = [&](int b) {  // of block b < blocks
+    return int(__popcll(__builtin_amdgcn_ballot_w64(ends <= b)));
+  };
 
+  // This wavefront's blocks are wave, wave + nwaves, ... (the candidate's come first).  val[i]: the
+  // token, then the symbol, of the lane's position (KEEP: then the id of the last finished order).
+  int32_t val[BLOCKS];
   {
-    // 16-byte stores (table and counters start on 16-byte boundaries and the counters' area is
-    // a whole number of them)
-    uint4* t4 = reinterpret_cast<uint4*>(table);
-    for (int q = tid; q < T / 4; q += nt)
-      t4[q] = make_uint4(kEmptySlot, kEmptySlot, kEmptySlot, kEmptySlot);
-    uint4* c4 = reinterpret_cast<uint4*>(cnt);
-    for (int q = tid; q < (cand_len * int(W) + 3) / 4; q += nt) c4[q] = make_uint4(0u, 0u, 0u, 0u);
-    for (int s = tid; s < cand_len; s += nt) cstate[s] = 0;
-  }
-
-  // stage the tokens back to back: candidate, reference 0, reference 1, ...  All of a thread's
-  // loads are issued before the first one is consumed (one round trip to memory, not one per
-  // position).
-  {
-    // sequence of each position and where it begins: the 64 positions of a wavefront usually
-    // lie in one sequence, which one ballot over the lanes holding the sequence ends finds
-    int seq[SITEMS], begin[SITEMS];
-    {
-      const int ends = (lane <= R) ? incl : 0x7FFFFFFF;
-      const int wave_first = __builtin_amdgcn_readfirstlane(tid - lane);
+    Token raw[BLOCKS];
+    int left[BLOCKS];  // positions of the block inside the sequence
 #pragma unroll
-      for (int i = 0; i < SITEMS; ++i) {
-        const int k0 = wave_first + i * nt;
-        const int f0 = min(int(__popcll(__builtin_amdgcn_ballot_w64(ends <= k0))), R);
-        int sq = f0, bg = f0 > 0 ? __builtin_amdgcn_readlane(incl, max(f0 - 1, 0)) : 0;
-        if (k0 + kWave > __builtin_amdgcn_readlane(incl, f0)) {  // uniform: the block straddles
-          const int f1 =
-              min(int(__popcll(__builtin_amdgcn_ballot_w64(ends <= k0 + kWave - 1))), R);
-          for (int q = f0; q < f1; ++q) {
-            const int e = __builtin_amdgcn_readlane(incl, q);
-            const bool ge = k0 + lane >= e;
-            sq = ge ? q + 1 : sq;
-            bg = ge ? e : bg;
-          }
-        }
-        seq[i] = sq;
-        begin[i] = bg;
+    for (int i = 0; i < BLOCKS; ++i) {
+      const int b = wave + (i << log2_waves);
+      raw[i] = 0;
+      left[i] = 0;
+      if (b < blocks) {  // uniform
+        const int f = sequence_of(b);
+        const int first = (b - __builtin_amdgcn_readlane(block_begins, f)) << 6;
+        left[i] = __builtin_amdgcn_readlane(my_len, f) - first;
+        const uint64_t row =
+            (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(row_at >> 32), f))) << 32) |
+            uint32_t(__builtin_amdgcn_readlane(int(uint32_t(row_at)), f));
+        typedef const Token __attribute__((address_space(1)))* GlobalToken;
+        GlobalToken p = reinterpret_cast<GlobalToken>(row) + uint32_t(first);
+        raw[i] = p[uint32_t(min(lane, left[i] - 1))];
       }
     }
-    const int64_t cand_row = int64_t(g) * pb.cand_stride;
-    const int64_t ref_rows = rr.row0 * pb.ref_stride;
-    int32_t t[SITEMS];
-#pragma unroll
-    for (int i = 0; i < SITEMS; ++i) {
-      const int k = tid + i * nt;
-      t[i] = 0;
-      if (k < total_tokens) {
-        const int p = k - begin[i];
-        t[i] = (seq[i] == 0)
-            ? load_token(pb.cand, cand_row + p, pb.tok64)
-            : load_token(pb.refs, ref_rows + int64_t(seq[i] - 1) * pb.ref_stride + p, pb.tok64);
-      }
-    }
+    // meanwhile: table slots free, counters zero, symbols behind the sequences absent
+    for (uint32_t q = tid; q < uint32_t(a.table_and_counters); q += nt)
+      *lds<Quad>(16u * q) = Quad(0u);
+    if (wave == 0 && lane <= R)
+      *lds<Quad>(sym_at + uint32_t(2 * kWave) * block_ends + uint32_t(2 * kPadSymbols) * lane) =
+          Quad(~0u);
+    if (tid == 0) *lds<uint32_t>(lost_at) = 0u;
+    if (ROUGE && tid < kMaxSeqs) *lds<uint32_t>(overlap_at + 4 * tid) = 0u;
+    const UToken vocab = UToken(uint32_t(pb.vocab));
     bool bad = false;
 #pragma unroll
-    for (int i = 0; i < SITEMS; ++i) {
-      const int k = tid + i * nt;
-      if (k < total_tokens) {
-        // a token outside the vocabulary is reported and staged as 0, so that every key formed
-        // from the staged tokens stays below the empty-slot marker
-        const bool outside = uint32_t(t[i]) >= uint32_t(pb.vocab);
-        tok[k] = TokT(outside ? 0 : t[i]);
-        bad |= outside;
-      }
+    for (int i = 0; i < BLOCKS; ++i) {
+      // a token outside the vocabulary is reported and taken as 0
+      const bool outside = UToken(raw[i]) >= vocab;
+      const bool here = lane < left[i];
+      bad |= outside & here;
+      val[i] = here ? (outside ? 0 : int32_t(raw[i])) : -1;
     }
-    if (bad && pb.status) atomicOr(pb.status, TB_DEV_TOKEN_RANGE);
-  }
-  // this wavefront's slice of the reference positions (order 1 reads it directly), and the
-  // range of sequences the slice touches
-  const int nref = total_tokens - cand_len;
-  const int slice = min((nref + nwaves - 1) / nwaves, a.list_per_wave);
-  const int slice_begin = cand_len + wave * slice;
-  int todo = max(min(slice, total_tokens - slice_begin), 0);  // entries in this wave's list
-  int f_lo = 0, f_hi = 0;
-  for (int m = 1; m <= R; ++m) {
-    const int bm = lane_value(incl, m - 1);
-    f_lo += (slice_begin >= bm) ? 1 : 0;
-    f_hi += (slice_begin + todo - 1 >= bm) ? 1 : 0;
+    if (__builtin_amdgcn_ballot_w64(bad)) {  // uniform
+      if (bad && pb.status) atomicOr(pb.status, TB_DEV_TOKEN_RANGE);
+    }
   }
   __syncthreads();
   TB_FSTAMP(1);
 
+  // val[0] is the block at hand, finished blocks rotate to the end (a register array cannot be
+  // indexed by a loop counter, and unrolled loops would multiply the code).
+  auto rotate_in = [&](int32_t v) {
+#pragma unroll
+    for (int i = 0; i + 1 < BLOCKS; ++i) val[i] = val[i + 1];
+    val[BLOCKS - 1] = v;
+  };
+
+  SymbolTable table;
+  table.bucket_mask = (((1u << lg) - 1u) << 2) & ~15u;
+  table.home_shift = 30 - lg;
+  table.log2_buckets = lg - 2;
+  table.id_limit = 1u << id_bits;
+  table.lost_at = lost_at;
+  const uint32_t id_limit = table.id_limit;
+  auto set_key_bits = [&](int key_bits) {
+    const int count_bits = min(32 - key_bits + lg - 2 - id_bits, 32 - id_bits);
+    table.multiplier = 0x9E3779B1u << (32 - key_bits);
+    table.longest = ((1u << count_bits) - 1u) << id_bits;
+  };
+  const uint32_t cnt_at = 4u << lg;
+  const uint32_t W4 = 4u * uint32_t(a.words), set_bytes = 4u * uint32_t(a.set_words);
+  const int my_cand_blocks = (max(cand_blocks - wave, 0) + nwaves - 1) >> log2_waves;
+  const int my_blocks = (max(blocks - wave, 0) + nwaves - 1) >> log2_waves;
+  // byte offset of the symbol of this lane's position in the wavefront's first block, and from
+  // block to block (behind sequence f lie kPadSymbols * f more)
+  const uint32_t first_sym = sym_at + 2u * uint32_t(kWave * wave + lane);
+  const uint32_t sym_stride = 2u * uint32_t(nt);
+
+  // ---- order 1: tokens become symbols
+  set_key_bits(a.first_key_bits);
+  {
+    int i = 0, b = wave;
+    uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
 #pragma unroll 1
-  for (int n = 1; n <= N; ++n) {
-    // Two workgroups share a compute unit, and its arbiter serves the older wavefronts first:
-    // left alone, the workgroup dispatched first finishes early and the other one then runs
-    // alone on a half-empty unit.  A workgroup that is behind (a lower order) therefore gets
-    // the higher priority, which keeps the two within an order of each other.  (Only for
-    // batches of at most two rounds of workgroups: with more, fresh workgroups at the highest
-    // priority would hold up the nearly finished ones whose slots the next round waits for.)
-    if (a.progress_priority) {
-      switch (n) {
-        case 1: __builtin_amdgcn_s_setprio(3); break;
-        case 2: __builtin_amdgcn_s_setprio(2); break;
-        case 3: __builtin_amdgcn_s_setprio(1); break;
-        default: __builtin_amdgcn_s_setprio(0); break;
+    for (; i < my_cand_blocks; ++i, id += nt, s += sym_stride, b += nwaves) {
+      int32_t got = -1;
+      if (val[0] >= 0) {
+        got = int32_t(table.claim(uint32_t(val[0]) * table.multiplier, id));
+        if (!ROUGE || N == 1) lds_add(cnt_at + __umul24(uint32_t(got), W4), 1u);
       }
-    }
-    if (n >= 2) __syncthreads();  // every slot of the previous order has been emptied
-
-    // ---- A: candidate n-grams claim or find their entry
-    for (int k = tid; k + n <= cand_len; k += nt) {
-      const uint32_t pid = (cstate[k] >> 16) & 0xFFFu;
-      const uint32_t key = (pid << bits) | uint32_t(tok[k + n - 1]);
-      bool won;
-      const uint32_t s = dict.insert(key, true, &won);
-      if (won) ids[s] = uint16_t(k);
-      cstate[k] = s | (won ? 0x80000000u : 0u);
+      *lds<int16_t>(s) = int16_t(got);
+      rotate_in(got);
     }
     __syncthreads();
-    TB_FSTAMP(2 + (n - 1) * 3);
-
-    // ---- B: candidate counts (field 0 of the entry's id) ...
-    for (int k = tid; k + n <= cand_len; k += nt) {
-      const uint32_t st = cstate[k];
-      const uint32_t id = ids[st & 0xFFFFu];
-      atomicAdd(&cnt[__umul24(id, W)], 1u);
-      cstate[k] = (st & 0x8000FFFFu) | (id << 16);
+    TB_FSTAMP(2);
+#pragma unroll 1
+    for (; i < my_blocks; ++i, s += sym_stride, b += nwaves) {
+      const int f = sequence_of(b);
+      // (a lane without a token asks like the others; its sign bit then hides the answer)
+      const uint32_t x = table.find(uint32_t(val[0]) * table.multiplier) |
+                         (uint32_t(val[0]) & 0x80000000u);
+      const bool hit = x < id_limit;
+      const int32_t got = hit ? int32_t(x) : -1;
+      if (hit && (!ROUGE || N == 1))
+        lds_add(cnt_at + 4u * uint32_t(f >> 1) + __umul24(x, W4), (f & 1) ? 0x10000u : 1u);
+      *lds<int16_t>(s + uint32_t(2 * kPadSymbols) * f) = int16_t(got);
+      rotate_in(got);
     }
-    // ... and this wavefront's reference positions: look up, count in the reference's field,
-    // keep the ones that can still match at the next order
-    int kept = 0;
-    for (int e0 = 0; e0 < todo; e0 += kWave) {
-      const int e = e0 + lane;
-      const bool active = e < todo;
-      uint32_t q, pid, f;
-      if (n == 1) {
-        q = uint32_t(min(slice_begin + e, total_tokens - 1));
-        pid = 0;
-        f = uint32_t(f_lo);
-        for (int m = f_lo + 1; m <= f_hi; ++m)
-          f += (q >= uint32_t(lane_value(incl, m - 1))) ? 1u : 0u;
-      } else {
-        const uint32_t ent = my_list[active ? e : 0];
-        q = ent & 0x3FFFu;
-        pid = (ent >> 14) & 0xFFFu;
-        f = ent >> 26;
-      }
-      const uint32_t key = (pid << bits) | uint32_t(tok[q + uint32_t(n) - 1]);
-      const uint32_t s = dict.find(key, active);
-      uint32_t next = 0xFFFFFFFFu;
-      if (s != ProbeTable::kNotFound) {
-        const uint32_t id = ids[s];
-        atomicAdd(&cnt[__umul24(id, W) + (f >> 1)], (f & 1u) ? 0x10000u : 1u);
-        const bool more = n < N && uint32_t(s_end[f]) >= q + uint32_t(n) + 1u;
-        next = more ? (q | (id << 14) | (f << 26)) : next;
-      }
-      // in-place compaction: the write cursor never passes the entries still to be read
-      const unsigned long long m = __builtin_amdgcn_ballot_w64(next != 0xFFFFFFFFu);
-      const uint32_t rank =
-          __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-      if (next != 0xFFFFFFFFu) my_list[kept + int(rank)] = next;
-      kept += int(__builtin_popcountll(m));
+    if (KEEP) {
+#pragma unroll 1
+      for (; i < BLOCKS; ++i) rotate_in(val[0]);
     }
-    todo = kept;
-    __syncthreads();
-    TB_FSTAMP(3 + (n - 1) * 3);
+  }
+  TB_FSTAMP(3);
 
-    // ---- C: the position that created an entry clips it (max over the reference fields, min
-    // with the candidate field), zeroes its counters and empties its slot
-    int part = 0;
-    for (int k = tid; k + n <= cand_len; k += nt) {
-      const uint32_t st = cstate[k];
-      if (st >> 31) {
-        const uint32_t base = __umul24(uint32_t(k), W);
-        const uint32_t w0 = cnt[base];
-        const uint32_t cc = w0 & 0xFFFFu;  // candidate count; reference j is field j + 1
-        uint32_t mx = w0 >> 16;
-        cnt[base] = 0;
-        if (ROUGE && n == N && min(cc, mx)) atomicAdd(&s_overlap[0], int(min(cc, mx)));
-        for (uint32_t w = 1; w < W; ++w) {
-          const uint32_t x = cnt[base + w];
-          mx = max(mx, max(x & 0xFFFFu, x >> 16));
-          cnt[base + w] = 0;
-          if (ROUGE && n == N) {  // per reference: min(candidate count, its own count)
-            const uint32_t m_lo = min(cc, x & 0xFFFFu), m_hi = min(cc, x >> 16);
-            if (m_lo) atomicAdd(&s_overlap[2 * w - 1], int(m_lo));
-            if (m_hi) atomicAdd(&s_overlap[2 * w], int(m_hi));
+  int swept = 0, hi = 1;
+  bool pass_ends = a.pass_ends & 1u;
+#pragma unroll 1
+  while (true) {
+    if (pass_ends) {
+      if (hi == N && prio) __builtin_amdgcn_s_setprio(0);
+      __syncthreads();
+      // ---- counters of the pass's orders: maximum over the references, minimum with the
+      // candidate, sum
+      uint32_t at = cnt_at;
+#pragma unroll 1
+      for (int n = ROUGE ? N : swept + 1; n <= hi; ++n) {
+        uint32_t part = 0;
+        uint32_t e = at + __umul24(uint32_t(tid), W4);
+#pragma unroll 1
+        for (int k = tid; k < cand_len; k += nt, e += __umul24(uint32_t(nt), W4)) {
+          const uint32_t first = *lds<uint32_t>(e);
+          const uint32_t cc = first & 0xFFFFu;
+          uint32_t mx = first >> 16;
+          for (uint32_t w = 4; w < W4; w += 4) {
+            const uint32_t v = *lds<uint32_t>(e + w);
+            mx = max(mx, max(v & 0xFFFFu, v >> 16));
+          }
+          part += min(cc, mx) + (cc ? 0x10000u : 0u);
+          if (ROUGE && cc) {
+            for (int j = 1; j <= R; ++j) {
+              const uint32_t v = *lds<uint32_t>(e + 4u * uint32_t(j >> 1));
+              const uint32_t both = min(cc, (j & 1) ? v >> 16 : v & 0xFFFFu);
+              if (both) lds_add(overlap_at + 4u * uint32_t(j - 1), both);
+            }
           }
         }
-        part += int(min(cc, mx)) + 0x10000;
-        table[st & 0xFFFFu] = kEmptySlot;
+        part = uint32_t(wave_inclusive_scan(int(part)));
+        if (lane == kWave - 1) *lds<uint32_t>(part_at + 64u * uint32_t(n - 1) + 4u * wave) = part;
+        at += set_bytes;
+      }
+      __syncthreads();
+      if (hi == N) break;
+      for (uint32_t q = tid; q < uint32_t(a.table_and_counters); q += nt)
+        *lds<Quad>(16u * q) = Quad(0u);
+      __syncthreads();
+      swept = hi;
+      set_key_bits(a.later_key_bits);
+    }
+    // ---- orders lo..hi
+    const int lo = hi + 1;
+    hi = int((a.pass_ends >> (4 * hi)) & 15u);
+    pass_ends = true;
+    // Two workgroups share a compute unit and its arbiter serves the older wavefronts first: left
+    // alone, the one dispatched first finishes early and its mate runs alone on a half-empty unit.
+    // The workgroup that is behind therefore gets the higher priority.
+    if (prio) {
+      if (lo == 2)
+        __builtin_amdgcn_s_setprio(2);
+      else
+        __builtin_amdgcn_s_setprio(1);
+    }
+    // the order within the pass is the key's top bits: a constant added to the product
+    const int payload = swept == 0 ? __builtin_amdgcn_readfirstlane(a.first_payload)
+                                   : __builtin_amdgcn_readfirstlane(a.later_payload);
+    const uint32_t tag_unit = table.multiplier << payload;
+    const uint32_t first_tag = uint32_t(lo - 1 - swept) * tag_unit;
+    const uint32_t first_count = cnt_at + (ROUGE ? 0u : uint32_t(lo - 1 - swept) * set_bytes);
+    int i = 0, b = wave;
+    uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
+#pragma unroll 1
+    for (; i < my_cand_blocks; ++i, id += nt, s += sym_stride, b += nwaves) {
+      int32_t cur = KEEP ? val[0] : int32_t(*lds<int16_t>(s));
+      uint32_t tag = first_tag, count = first_count, next = s + 2u * uint32_t(lo - 1);
+      int n = lo;
+      auto enter = [&](int offset) {
+        // (an absent symbol makes the key negative: no n-gram here)
+        const int32_t key =
+            int32_t(uint32_t(cur) << id_bits) | int32_t(*lds<int16_t>(next + uint32_t(offset)));
+        cur = -1;
+        if (key >= 0) {
+          cur = int32_t(table.claim(uint32_t(key) * table.multiplier + tag, id));
+          if (!ROUGE || n == N) lds_add(count + __umul24(uint32_t(cur), W4), 1u);
+        }
+        tag += tag_unit;
+        if (!ROUGE) count += set_bytes;
+        ++n;
+      };
+      enter(0);
+#pragma unroll 1
+      while (n <= hi) {
+        enter(2);
+        next += 2u;
+      }
+      if (KEEP) rotate_in(cur);
+    }
+    __syncthreads();
+    TB_FSTAMP(2 * lo);
+#pragma unroll 1
+    for (; i < my_blocks; ++i, s += sym_stride, b += nwaves) {
+      const int f = sequence_of(b);
+      const uint32_t addend = (f & 1) ? 0x10000u : 1u;
+      const uint32_t own = s + uint32_t(2 * kPadSymbols) * f;
+      int32_t cur = KEEP ? val[0] : int32_t(*lds<int16_t>(own));
+      uint32_t next = own + 2u * uint32_t(lo - 1);
+      uint32_t tag = first_tag, count = first_count + 4u * uint32_t(f >> 1);
+#pragma unroll 1
+      for (int n = lo;; ++n) {
+        const int32_t key = int32_t(uint32_t(cur) << id_bits) | int32_t(*lds<int16_t>(next));
+        cur = -1;
+        if (!__builtin_amdgcn_ballot_w64(key >= 0)) break;  // uniform: nothing to extend
+        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag) |
+                           (uint32_t(key) & 0x80000000u);
+        const bool hit = x < id_limit;
+        cur = hit ? int32_t(x) : -1;
+        if (hit && (!ROUGE || n == N)) lds_add(count + __umul24(x, W4), addend);
+        tag += tag_unit;
+        if (!ROUGE) count += set_bytes;
+        next += 2u;
+        if (n >= hi) break;  // uniform
+      }
+      if (KEEP) rotate_in(cur);
+    }
+    if (KEEP) {
+#pragma unroll 1
+      for (; i < BLOCKS; ++i) rotate_in(val[0]);
+    }
+    TB_FSTAMP(2 * lo + 1);
+  }
+  TB_FSTAMP(20);
+  if (*lds<uint32_t>(lost_at)) {
+    // Token ids chosen to collide: count by comparing n-grams, without a table.
+    __syncthreads();
+    if (tid < 8 * 16) *lds<uint32_t>(part_at + 4 * tid) = 0u;
+    if (nt < 8 * 16 && tid < 64) *lds<uint32_t>(part_at + 4 * (tid + 64)) = 0u;
+    if (ROUGE && tid < kMaxSeqs) *lds<uint32_t>(overlap_at + 4 * tid) = 0u;
+    __syncthreads();
+    auto token = [&](const Token* row, int i) {
+      const Token t = row[i];
+      return UToken(t) >= UToken(uint32_t(pb.vocab)) ? 0 : int32_t(t);
+    };
+#pragma unroll 1
+    for (int n = ROUGE ? N : 1; n <= N; ++n) {
+#pragma unroll 1
+      for (int k = tid; k + n <= cand_len; k += nt) {
+        // occurrences in row[0 .. len - 1] of the n-gram at candidate position k (at most one is
+        // wanted with `once`)
+        auto occurrences = [&](const Token* row, int len, bool once) {
+          int found = 0;
+#pragma unroll 1
+          for (int i = 0; i + n <= len && !(once && found); ++i) {
+            int j = 0;
+            while (j < n && token(row, i + j) == token(cand_row, k + j)) ++j;
+            found += j == n ? 1 : 0;
+          }
+          return found;
+        };
+        if (occurrences(cand_row, k + n - 1, true)) continue;  // not its first occurrence
+        const int cc = occurrences(cand_row, cand_len, false);
+        int mx = 0;
+#pragma unroll 1
+        for (int j = 0; j < used; ++j) {
+          const int len = min(max(pb.ref_len[rr.row0 + j], 0), rs);
+          const int c = occurrences(
+              ref_row + int64_t(j) * rs, len, false);
+          mx = max(mx, c);
+          if (ROUGE && c) lds_add(overlap_at + 4u * j, uint32_t(min(cc, c)));
+        }
+        lds_add(part_at + 64u * (n - 1), uint32_t(min(cc, mx) + 0x10000));
       }
     }
-    part = wave_sum(part);
-    if (lane == 0 && part != 0) atomicAdd(&s_part[n - 1], part);
-    TB_FSTAMP(4 + (n - 1) * 3);
+    __syncthreads();
   }
-  __syncthreads();
-  TB_FSTAMP(2 + N * 3);
 
   // wavefront 0: lane n < N owns order n + 1 (statistics out, one logarithm each)
   if (wave == 0) {
     const int c = cand_len;
-    const int sum = (lane < N) ? s_part[lane & 7] : 0;
+    uint32_t sums = 0;
+    for (int w = 0; w < nwaves; ++w) sums += *lds<uint32_t>(part_at + 64u * uint32_t(lane & 7) + 4u * w);
+    const int sum = (lane < N) ? int(sums) : 0;
     const int cn = sum & 0xFFFF;
     const int tn = max(c - lane, 0);
-    if (lane < N) {
-      a.st.clipped[int64_t(g) * N + lane] = cn;
-      a.st.total[int64_t(g) * N + lane] = tn;
-      a.st.distinct[int64_t(g) * N + lane] = int(uint32_t(sum) >> 16);
-    }
-    // closest reference length, the shorter one on ties (lane j holds the length of sequence j)
-    int best = lane_value(my_len, 1), bd = abs(best - c);
-    for (int j = 2; j <= used; ++j) {
-      const int l = lane_value(my_len, j), d = abs(l - c);
-      if (d < bd || (d == bd && l < best)) {
-        best = l;
-        bd = d;
-      }
-    }
     if (!ROUGE) {
-      const float score = bleu_from_stats_wave(cn, tn, c, best, a.sp);
+      if (lane < N) {
+        a.st.clipped[int64_t(g) * N + lane] = cn;
+        a.st.total[int64_t(g) * N + lane] = tn;
+        a.st.distinct[int64_t(g) * N + lane] = int(uint32_t(sum) >> 16);
+      }
+      // closest reference length, the shorter one on ties (lane j holds the length of sequence j;
+      // no reference at all: 0)
+      int best = lane_value(my_len, 1), bd = abs(best - c);
+      for (int j = 2; j <= used; ++j) {
+        const int l = lane_value(my_len, j), d = abs(l - c);
+        if (d < bd || (d == bd && l < best)) {
+          best = l;
+          bd = d;
+        }
+      }
+      const float score = bleu_from_stats_wave<int>(cn, tn, c, best, a.sp);
       if (lane == 0) {
         a.st.closest[g] = best;
         if (a.out) store_score(a.out, g, score, a.sp.out_bf16);
@@ -459,7 +555,7 @@ void fused_kernel(FusedArgs a) {
       // lane j = 1..used: reference j - 1.  F is proportional to overlap / (cand + beta^2 ref)
       // n-grams; the best reference is the first one with the largest such quotient.
       const bool ref_lane = lane >= 1 && lane <= used;
-      const int ov = ref_lane ? s_overlap[(lane - 1) & (kMaxFusedSeqs - 1)] : 0;
+      const int ov = ref_lane ? int(*lds<uint32_t>(overlap_at + 4 * ((lane - 1) & (kMaxSeqs - 1)))) : 0;
       const float ct = float(max(c - N + 1, 0)), rt = float(max(my_len - N + 1, 0));
       const float key = (ref_lane && ov > 0) ? float(ov) / __fmaf_rn(a.beta2, rt, ct) : 0.0f;
       if (a.rouge_overlap && lane >= 1 && lane <= R)
@@ -484,36 +580,162 @@ void fused_kernel(FusedArgs a) {
       }
     }
   }
+  TB_FSTAMP(21);
 }
 
-template <typename TokT, int SITEMS, bool ROUGE>
-hipError_t launch_fused_mode(const FusedArgs& a, const FusedPlan& plan, int blocks,
-                             hipStream_t s) {
-  hipError_t e = grant_dynamic_lds(
-      reinterpret_cast<const void*>(fused_kernel<TokT, SITEMS, ROUGE>), plan.lds_bytes);
+int log2_ceil(int64_t v) {
+  int b = 0;
+  while ((int64_t(1) << b) < v) ++b;
+  return b;
+}
+
+template <int BLOCKS, bool KEEP, bool WIDE, bool ROUGE>
+hipError_t launch_shape(const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
+  const auto kernel = fused_kernel<BLOCKS, KEEP, WIDE, ROUGE>;
+  hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), plan.lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((fused_kernel<TokT, SITEMS, ROUGE>), dim3(blocks), dim3(plan.threads),
-                     plan.lds_bytes, s, a);
+  hipLaunchKernelGGL(kernel, dim3(uint32_t(a.pb.B)), dim3(plan.threads), plan.lds_bytes, s, a);
   return hipGetLastError();
 }
-template <typename TokT, int SITEMS>
-hipError_t launch_fused_items(const FusedArgs& a, const FusedPlan& plan, int blocks,
-                              hipStream_t s) {
-  return a.rouge_prf ? launch_fused_mode<TokT, SITEMS, true>(a, plan, blocks, s)
-                     : launch_fused_mode<TokT, SITEMS, false>(a, plan, blocks, s);
+template <int BLOCKS, bool KEEP>
+hipError_t launch_keep(const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
+  if (a.pb.tok64)
+    return a.rouge_prf ? launch_shape<BLOCKS, KEEP, true, true>(a, plan, s)
+                       : launch_shape<BLOCKS, KEEP, true, false>(a, plan, s);
+  return a.rouge_prf ? launch_shape<BLOCKS, KEEP, false, true>(a, plan, s)
+                     : launch_shape<BLOCKS, KEEP, false, false>(a, plan, s);
+}
+template <int BLOCKS>
+hipError_t launch_blocks(const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
+  return plan.keep ? launch_keep<BLOCKS, true>(a, plan, s) : launch_keep<BLOCKS, false>(a, plan, s);
 }
 
-template <typename TokT>
-hipError_t launch_fused_tok(const FusedArgs& a, const FusedPlan& plan, int blocks,
-                            hipStream_t s) {
-  switch (plan.items) {
-    case 2: return launch_fused_items<TokT, 2>(a, plan, blocks, s);
-    case 4: return launch_fused_items<TokT, 4>(a, plan, blocks, s);
-    case 6: return launch_fused_items<TokT, 6>(a, plan, blocks, s);
-    case 8: return launch_fused_items<TokT, 8>(a, plan, blocks, s);
-    case 12: return launch_fused_items<TokT, 12>(a, plan, blocks, s);
-    default: return hipErrorInvalidValue;
+constexpr size_t kSumsBytes = 8 * 16 * 4 + 16 + kMaxSeqs * 4;
+
+}  // namespace
+
+bool fused_path_takes(int64_t cand_stride, int64_t ref_stride, int R, int bits) {
+  if (R + 1 > kMaxSeqs) return false;
+  const int64_t cap = cand_stride + int64_t(R) * ref_stride;
+  if (cap > 12 * 1024 || cand_stride > 4096 || ref_stride > 65535) return false;
+  if (bits > 31 || (uint64_t(cand_stride) << bits) > 0xFFFFFFFFull) return false;
+  int64_t slots = 256;
+  while (slots * 3 < cand_stride * 4) slots *= 2;
+  const int64_t nwaves = cap <= 1024 ? 4 : cap <= 2048 ? 8 : 16;
+  const int64_t list = ((R * ref_stride + nwaves - 1) / nwaves + kWave - 1) / kWave * kWave * nwaves;
+  const int64_t bytes = slots * 6 + ((cand_stride * ((R + 2) / 2) * 4 + 15) & ~int64_t(15)) +
+                        cand_stride * 4 + (((cap + 4) * (bits <= 16 ? 2 : 4) + 3) & ~int64_t(3)) +
+                        list * 4;
+  return bytes + 1024 <= kLdsBudget;
+}
+
+namespace {
+
+// Passes of a plan: 0: all orders share a table; 1: order 1 on its own, then the others; 2: pairs;
+// 3: every order on its own.  Fills in pass_ends and the key widths; false: the key is too wide.
+bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pass) {
+  FusedPlan& p = *plan;
+  static const uint32_t kEnds[4] = {0u, 1u << 1, 0x154u, ~0u};  // bit n: a pass ends with order n
+  p.pass_ends = (N == 1 || (kEnds[passes] & 2u)) ? 1u : 0u;
+  for (int n = 2; n <= N; ++n) {
+    int end = n;
+    while (end < N && !((kEnds[passes] >> end) & 1u)) ++end;
+    p.pass_ends |= uint32_t(end) << (4 * (n - 1));
   }
+  static const int kOrders[4] = {8, 7, 2, 1};
+  const int most = passes == 1 && N > 1 ? N - 1 : N;
+  *orders_per_pass = kOrders[passes] < most ? kOrders[passes] : most;
+  const int tag_bits = log2_ceil(*orders_per_pass);
+  p.later_payload = 2 * p.id_bits;
+  p.later_key_bits = p.later_payload + tag_bits;
+  p.first_payload = p.first_key_bits = bits;
+  if (!(p.pass_ends & 1u)) {
+    p.first_payload = bits > p.later_payload ? bits : p.later_payload;
+    p.first_key_bits = p.first_payload + tag_bits;
+  }
+  p.keep = passes >= 2 && N > 2;
+  return p.first_key_bits <= 32 && p.later_key_bits <= 32;
+}
+
+}  // namespace
+
+// What the choice weighs (times of kernels over some hundred plans and forty shapes):
+//   * A table that is nearly full costs more than anything else: probe sequences of the wavefront's
+//     slowest lane grow from 1 to 4 requests between a quarter and three quarters (twice the time).
+//   * A pass costs its barriers and the block loop again, but takes table and counters of its orders
+//     only: with few large workgroups on a unit fewer passes win, with many small ones (whose
+//     barriers the others fill) and short block loops (few references) more passes in less LDS do.
+//   * 32 wavefronts a unit hide latency; a workgroup with fewer blocks than wavefronts idles, and
+//     with two blocks or less per wavefront its prologue outweighs them.
+bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
+                bool rouge, FusedPlan* plan) {
+  if (R + 1 > kMaxSeqs || cand_stride > 12288 || ref_stride > 65535 || bits > 31) return false;
+  const int64_t blocks =
+      (cand_stride + kWave - 1) / kWave + R * ((ref_stride + kWave - 1) / kWave);
+  if (blocks > kMaxBlocks * 16) return false;
+  FusedPlan& p = *plan;
+  p.id_bits = cand_stride > 1 ? log2_ceil(cand_stride) : 1;
+  p.words = (R + 2) / 2;
+  p.set_words = (int(cand_stride) * p.words + 3) & ~3;
+  const size_t sym_bytes = (size_t(blocks * kWave + (R + 1) * kPadSymbols) * 2 + 15) & ~size_t(15);
+
+  int want_passes = -1, want_lg = 0, want_threads = 0;
+#ifdef TB_TUNE
+  if (const char* e = getenv("TB_FUSED")) sscanf(e, "%d,%d,%d", &want_passes, &want_lg, &want_threads);
+#endif
+  // workgroups a compute unit gets, and with it its share of LDS and wavefronts
+  int resident = 1;
+  while (resident < 32 && B > 256 * resident) resident *= 2;
+  // share of the slots that may be taken if every row is full, in twelfths; the last resort comes
+  // after all numbers of workgroups have been tried with the others
+  static const int kTwelfths[3] = {5, 6, 9};
+  for (int last_resort = 0; last_resort < 2; ++last_resort) {
+    for (int r = resident; r >= 1; r /= 2) {
+      int waves = 1;
+      if (resident == 1) {  // the chip is not full: a wavefront for (nearly) each block
+        while (waves < 16 && 4 * waves < 3 * blocks) waves *= 2;
+      } else {
+        while (waves < 16 && waves < 32 / r && blocks > waves * (waves < 4 ? 1 : waves < 8 ? 2 : 4))
+          waves *= 2;
+      }
+      if (want_threads) waves = want_threads / kWave;
+      while (waves < 16 && blocks > int64_t(kMaxBlocks) * waves) waves *= 2;
+      p.blocks = int((blocks + waves - 1) / waves);
+      p.threads = waves * kWave;
+      for (int level = last_resort ? 2 : 0; level < (last_resort ? 3 : 2); ++level) {
+        if (level == 1 && r >= 4 && R > 2 && want_passes < 0) continue;  // (fewer workgroups first)
+        for (int passes = 0; passes < 4; ++passes) {
+          int orders;
+          if (want_passes >= 0 && passes != want_passes) continue;
+          if (!set_passes(passes, N, bits, plan, &orders)) continue;
+          if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2) && want_passes < 0) continue;
+          const int64_t entries = orders * cand_stride;
+          const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
+          int lg_min = 6;
+          while ((int64_t(kTwelfths[level]) << lg_min) < 12 * entries) ++lg_min;
+          // bits for the probe count: sequences of ordinary tokens stay below fifteen
+          while (32 - widest + lg_min - 2 - p.id_bits < 4) ++lg_min;
+          int lg = lg_min;  // (a larger table than this costs more to clear than it saves)
+          while ((int64_t(1) << lg) < (r == 1 ? 6 : 4) * entries) ++lg;
+          if (want_lg) {
+            if (!last_resort || want_lg < lg_min) continue;
+            lg = lg_min = want_lg;
+          }
+          for (; lg >= lg_min; --lg) {
+            const size_t front = (size_t(4) << lg) + size_t(rouge ? 1 : orders) * p.set_words * 4;
+            p.lds_bytes = front + sym_bytes + kSumsBytes;
+            if (p.lds_bytes > size_t(kLdsBudget) / (want_lg ? 1 : r)) continue;
+            p.log2_slots = lg;
+            p.table_and_counters = int(front / 16);
+            p.off_sym = uint32_t(front);
+            p.off_sums = uint32_t(front + sym_bytes);
+            return true;
+          }
+        }
+      }
+    }
+  }
+  return false;
 }
 
 hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs& st,
@@ -528,26 +750,41 @@ hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs
   a.rouge_overlap = rouge ? rouge->overlap : nullptr;
   a.rouge_best = rouge ? rouge->best : nullptr;
   a.beta2 = rouge ? rouge->beta2 : 1.0f;
-  a.table_slots = plan.table_slots;
-  int lg = 0;
-  while ((1 << lg) < plan.table_slots) ++lg;
-  a.table_shift = 32 - lg;
+  a.pass_ends = plan.pass_ends;
+  a.log2_slots = plan.log2_slots;
+  a.id_bits = plan.id_bits;
+  a.first_payload = plan.first_payload;
+  a.first_key_bits = plan.first_key_bits;
+  a.later_payload = plan.later_payload;
+  a.later_key_bits = plan.later_key_bits;
   a.words = plan.words;
-  a.list_per_wave = plan.list_per_wave;
-  {
-    // workgroups a compute unit holds at once (2048 threads, 160 KB of LDS), times 256 units
-    const int by_threads = 2048 / plan.threads;
-    const int by_lds = int(size_t(kLdsBudget) / (plan.lds_bytes + 512));
-    const int resident = 256 * (by_threads < by_lds ? by_threads : (by_lds < 1 ? 1 : by_lds));
-    a.progress_priority = pb.B <= 2 * resident ? 1 : 0;
-  }
-  a.off_ids = uint32_t(plan.off_ids);
-  a.off_cnt = uint32_t(plan.off_cnt);
-  a.off_cstate = uint32_t(plan.off_cstate);
-  a.off_tok = uint32_t(plan.off_tok);
-  a.off_list = uint32_t(plan.off_list);
-  return plan.tok_bytes == 2 ? launch_fused_tok<uint16_t>(a, plan, pb.B, s)
-                             : launch_fused_tok<int32_t>(a, plan, pb.B, s);
+  a.set_words = plan.set_words;
+  a.table_and_counters = plan.table_and_counters;
+  a.off_sym = plan.off_sym;
+  a.off_sums = plan.off_sums;
+  a.cand_stride = int(pb.cand_stride);
+  a.ref_stride = int(pb.ref_stride);
+  a.log2_waves = log2_ceil(plan.threads / kWave);
+  const int by_threads = 2048 / plan.threads;
+  const int by_lds = int(size_t(kLdsBudget) / plan.lds_bytes);
+  const int resident = 256 * (by_threads < by_lds ? by_threads : (by_lds < 1 ? 1 : by_lds));
+  a.progress_priority = pb.B <= 2 * resident ? 1 : 0;
+#ifdef TB_TUNE
+  if (const char* e = getenv("TB_PRIO")) a.progress_priority = atoi(e);
+  if (getenv("TB_PLAN"))
+    fprintf(stderr, "fused cut %x lg %d threads %d blocks %d keep %d lds %zu prio %d\n", plan.pass_ends,
+            plan.log2_slots, plan.threads, plan.blocks, plan.keep, plan.lds_bytes, a.progress_priority);
+#endif
+  if (plan.blocks <= 1) return launch_blocks<1>(a, plan, s);
+  if (plan.blocks <= 2) return launch_blocks<2>(a, plan, s);
+  if (plan.blocks <= 3) return launch_blocks<3>(a, plan, s);
+  if (plan.blocks <= 4) return launch_blocks<4>(a, plan, s);
+  if (plan.blocks <= 5) return launch_blocks<5>(a, plan, s);
+  if (plan.blocks <= 6) return launch_blocks<6>(a, plan, s);
+  if (plan.blocks <= 8) return launch_blocks<8>(a, plan, s);
+  if (plan.blocks <= 12) return launch_blocks<12>(a, plan, s);
+  if (plan.blocks <= 16) return launch_blocks<16>(a, plan, s);
+  return launch_blocks<kMaxBlocks>(a, plan, s);
 }
 
 }  // namespace tb

@@ -58,13 +58,15 @@ struct CountPlan {
   size_t lds_bytes;
 };
 struct FusedPlan {
-  int threads;         // workgroup size
-  int items;           // token positions staged per thread: 2, 4, 6, 8 or 12
-  int table_slots;     // power of two >= 4/3 * cand_stride (larger when LDS allows)
-  int words;           // 32-bit counter words per id (two 16-bit sequence fields each)
-  int tok_bytes;       // staged tokens are 2 bytes when bits <= 16, else 4
-  int list_per_wave;   // work-list entries reserved per wavefront (multiple of 64)
-  size_t lds_bytes, off_ids, off_cnt, off_cstate, off_tok, off_list;
+  int threads, blocks;     // workgroup size; blocks of 64 positions per wavefront
+  int keep;                // 1: a pass starts above order 2
+  uint32_t pass_ends;      // see FusedArgs
+  int log2_slots, id_bits;
+  int first_payload, first_key_bits, later_payload, later_key_bits;
+  int words, set_words;
+  int table_and_counters;  // 16-byte units
+  uint32_t off_sym, off_sums;
+  size_t lds_bytes;
 };
 
 // Groups within one LDS table whose (prefix id, last token) keys fit 31 bits: one workgroup per
@@ -143,8 +145,12 @@ bool plan_dictionary(int64_t group_cap, const int32_t* key_bytes, int N, int bit
                      DictPlan* plan);
 bool plan_count(int64_t group_cap, int64_t cand_stride, int64_t ref_stride, int R,
                 CountPlan* plan);
-bool plan_fused(int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
-                FusedPlan* plan);
+// Whether TB_PATH_AUTO resolves a shape to the FUSED path.  (The kernel itself takes larger groups:
+// plan_fused.  The line stays where callers know it, because what a path reports as group_distinct
+// depends on it.)
+bool fused_path_takes(int64_t cand_stride, int64_t ref_stride, int R, int bits);
+bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
+                bool rouge, FusedPlan* plan);
 
 hipError_t launch_pack(const Problem& pb, const GlobalWs& ws, hipStream_t s);
 hipError_t launch_dictionary(const Problem& pb, const GlobalWs& ws, const DictPlan& plan,

@@ -1,0 +1,82 @@
+"""The fused kernel at the edges of its blocks of 64 positions, of its plans (how many orders share
+a table, how many workgroups share a compute unit) and of its table, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_05485_amd as tb
+import synth_inputs as syn
+from rouge_validity import check_rouge
+
+pytestmark = pytest.mark.gpu
+TOL = 1e-5
+DEV = "cuda:0"
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def check(w, N, int64=False, rouge=True):
+    cand, refs = dev(w.cand), dev(w.refs)
+    if int64:
+        cand, refs = cand.long(), refs.long()
+    cl, rl = dev(w.cand_len), dev(w.ref_len)
+    ref = oracle.bleu(w.cand, w.cand_len, w.refs, w.ref_len, max_n=N, smoothing="exp", threads=8)
+    cfg = tb.make_config(max_n=N, smoothing="exp", vocab_size=w.vocab)
+    stats = tb.Stats.allocate(w.B, N, DEV)
+    stats.group_distinct = None  # (asking for it keeps long shapes on the staged kernels)
+    out = tb.tensorbleu_sentence(cand, cl, refs, rl, cfg, stats=stats)
+    torch.cuda.synchronize()
+    assert stats.device_status.item() == 0
+    np.testing.assert_array_equal(stats.clipped.cpu().numpy(), ref.clipped)
+    np.testing.assert_array_equal(stats.total.cpu().numpy(), ref.total)
+    np.testing.assert_array_equal(stats.closest_ref_len.cpu().numpy(), ref.closest_ref_len)
+    assert np.abs(out.cpu().numpy().astype(np.float64) - ref.bleu).max() <= TOL
+    if rouge:
+        n = min(N, 2)
+        want = oracle.rouge_n(w.cand, w.cand_len, w.refs, w.ref_len, n=n)
+        prf, overlap, best = tb.tensorrouge_n(cand, cl, refs, rl, n=n, vocab_size=w.vocab,
+                                              want_overlap=True, want_best=True)
+        check_rouge(want, overlap.cpu().numpy(), best.cpu().numpy(), prf.cpu().numpy(), TOL)
+
+
+@pytest.mark.parametrize("N", [1, 2, 4, 8])
+@pytest.mark.parametrize("L,Lr", [(1, 1), (3, 2), (63, 65), (64, 64), (65, 63), (128, 191)])
+def test_block_edges(N, L, Lr):
+    # rows of every length around a block's end, short of the order, and empty
+    w = syn.random_small(601 + L, B=24, R=3, vocab=5, max_len=min(L, Lr), cand_stride=L,
+                         ref_stride=Lr)
+    for i in range(0, w.B, 2):
+        w.cand_len[i], w.ref_len[i] = max(L - i // 4, 0), max(Lr - i // 8, 0)
+        w.cand[i, :w.cand_len[i]] = (np.arange(w.cand_len[i]) * 7 + i) % 5
+        w.refs[i, :, :max(Lr - i // 8, 0)] = (np.arange(max(Lr - i // 8, 0)) * 7 + i + i // 6) % 5
+    check(w, N, int64=L % 2 == 1)
+
+
+@pytest.mark.parametrize("B,R,L,vocab,N", [
+    (300, 1, 90, 40, 4),        # two workgroups on a unit
+    (1300, 1, 1000, 300, 4),    # every order on its own
+    (1300, 4, 300, 50, 4),      # pairs
+    (9000, 1, 40, 30, 4),       # as many workgroups as a unit takes
+    (40, 2, 2700, 50257, 4),    # order 1 apart from the others
+    (600, 1, 4096, 2, 3),       # long runs: counters near their limit
+    (70, 1, 7000, 50257, 4),    # longer than the path's own shapes
+    (33, 1, 8192, 3, 8),
+])
+def test_plans(B, R, L, vocab, N):
+    check(syn.random_small(B + L, B=B, R=R, vocab=vocab, max_len=L, min_len=L // 3), N)
+
+
+@pytest.mark.parametrize("N", [1, 4])
+def test_tokens_chosen_to_collide(N):
+    # 150 token ids whose products with the table's multiplier are the smallest there are: all of
+    # them walk the same sequence of buckets, further than an entry can count
+    vocab = (1 << 31) - 1
+    inverse = pow(0x9E3779B1, -1, 1 << 31)
+    ids = np.array([(k * inverse) % (1 << 31) for k in range(150)], dtype=np.int64)
+    ids = ids[ids < vocab].astype(np.int32)
+    w = syn.random_small(631, B=6, R=2, vocab=len(ids), max_len=400, min_len=300)
+    w.cand, w.refs, w.vocab = ids[w.cand], ids[w.refs], vocab
+    check(w, N)
