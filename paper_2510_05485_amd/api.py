@@ -88,6 +88,11 @@ class BleuScorer:
         self.cfg.ref_count = t.data_ptr()
 
     def __call__(self, cand, cand_len, refs, ref_len, ref_count=None) -> torch.Tensor:
+        score = _b.native().bleu(False, cand, cand_len, refs, ref_len, self.cfg, self.out,
+                                 self.stats, self.workspace, self.shape, ref_count)
+        if score is not None:
+            self._ref_count = ref_count
+            return score
         refs = _refs3d(refs)
         self._check(cand, refs)
         self._set_ref_count(ref_count)
@@ -95,6 +100,11 @@ class BleuScorer:
                                       out=self.out, stats=self.stats, workspace=self.workspace)
 
     def corpus(self, cand, cand_len, refs, ref_len, ref_count=None) -> torch.Tensor:
+        score = _b.native().bleu(True, cand, cand_len, refs, ref_len, self.cfg, self.corpus_out,
+                                 self.stats, self.workspace, self.shape, ref_count)
+        if score is not None:
+            self._ref_count = ref_count
+            return score
         refs = _refs3d(refs)
         self._check(cand, refs)
         self._set_ref_count(ref_count)
@@ -103,20 +113,30 @@ class BleuScorer:
                                     workspace=self.workspace)
 
 
+def _one_shot(corpus: bool, cand, cand_len, refs, ref_len, vocab_size: int, max_n: int = 4,
+              smoothing: str = "none", smooth_param: float = 0.0,
+              score_dtype: torch.dtype = torch.float32, **kw) -> torch.Tensor:
+    refs = _refs3d(refs)
+    if not kw and score_dtype in (torch.float32, torch.bfloat16):
+        score = _b.native().once(corpus, cand, cand_len, refs, ref_len, max_n,
+                                 _b.SMOOTHING.get(smoothing, smoothing), smooth_param, vocab_size,
+                                 score_dtype == torch.bfloat16)
+        if score is not None:
+            return score
+    s = BleuScorer(cand.shape[0], refs.shape[1], cand.shape[1], refs.shape[2],
+                   vocab_size=vocab_size, device=cand.device, max_n=max_n, smoothing=smoothing,
+                   smooth_param=smooth_param, score_dtype=score_dtype, **kw)
+    return (s.corpus if corpus else s)(cand, cand_len, refs, ref_len).clone()
+
+
 def sentence_bleu(cand, cand_len, refs, ref_len, *, vocab_size: int, **kw) -> torch.Tensor:
     """One-shot per-sentence BLEU (allocates its buffers; use BleuScorer inside a loop)."""
-    refs = _refs3d(refs)
-    s = BleuScorer(cand.shape[0], refs.shape[1], cand.shape[1], refs.shape[2],
-                   vocab_size=vocab_size, device=cand.device, **kw)
-    return s(cand, cand_len, refs, ref_len).clone()
+    return _one_shot(False, cand, cand_len, refs, ref_len, vocab_size, **kw)
 
 
 def corpus_bleu(cand, cand_len, refs, ref_len, *, vocab_size: int, **kw) -> torch.Tensor:
     """One-shot corpus-level BLEU over the batch."""
-    refs = _refs3d(refs)
-    s = BleuScorer(cand.shape[0], refs.shape[1], cand.shape[1], refs.shape[2],
-                   vocab_size=vocab_size, device=cand.device, **kw)
-    return s.corpus(cand, cand_len, refs, ref_len).clone()
+    return _one_shot(True, cand, cand_len, refs, ref_len, vocab_size, **kw)
 
 
 def rouge_n(cand, cand_len, refs, ref_len, *, n: int = 2, beta: float = 1.0, vocab_size: int,

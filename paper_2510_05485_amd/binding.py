@@ -1,6 +1,7 @@
-"""ctypes binding of libtensorbleu.so: argument marshalling only.
+"""Binding of libtensorbleu.so: argument marshalling only.
 
-Every function here has the name of the C entry point it calls (see include/tensorbleu.h).
+Every function here has the name of the C entry point it calls (see include/tensorbleu.h).  The
+usual calls are marshalled natively (csrc/tb_host.cpp, see `native`), the others with ctypes.
 PyTorch supplies device memory and the current HIP stream; every step of the computation runs
 in the library's kernels.  There is no CPU fallback: if the library is missing or no GPU is
 present the calls raise.
@@ -107,6 +108,24 @@ def load_library() -> ctypes.CDLL:
     lib.tensorbleu_status_string.argtypes = [ctypes.c_int]
     _lib = lib
     return lib
+
+
+_host = None
+
+
+def native():
+    """The native marshalling module (built with the library; raises if it has not been).  Its
+    functions return None, having done nothing, for what they leave to the code here."""
+    global _host
+    if _host is None:
+        load_library()
+        try:
+            from . import _host as module
+        except ImportError as e:
+            raise TensorBLEUError("the module _host does not load: run `python -m "
+                                  f"paper_2510_05485_amd.build` first ({e})") from e
+        _host = module
+    return _host
 
 
 def tensorbleu_status_string(status: int) -> str:
@@ -297,6 +316,10 @@ def tensorbleu_sentence(cand, cand_len, refs, ref_len, cfg: tb_config_t,
                         out: Optional[torch.Tensor] = None, stats: Optional[Stats] = None,
                         workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """float32 (or bfloat16, see make_config) [B]: one BLEU score per candidate."""
+    if stream is None:
+        r = native().bleu(False, cand, cand_len, refs, ref_len, cfg, out, stats, workspace)
+        if r is not None:
+            return r
     out = _score_out(out, cfg, (cand.shape[0],), cand.device)
     return _full("tensorbleu_sentence", cand, cand_len, refs, ref_len, cfg, out, stats,
                  workspace, stream)
@@ -326,6 +349,10 @@ def tensorbleu_corpus(cand, cand_len, refs, ref_len, cfg: tb_config_t,
                       out: Optional[torch.Tensor] = None, stats: Optional[Stats] = None,
                       workspace: Optional[torch.Tensor] = None, stream=None) -> torch.Tensor:
     """float32 (or bfloat16) [1]: one BLEU score for the batch."""
+    if stream is None:
+        r = native().bleu(True, cand, cand_len, refs, ref_len, cfg, out, stats, workspace)
+        if r is not None:
+            return r
     out = _score_out(out, cfg, (1,), cand.device)
     return _full("tensorbleu_corpus", cand, cand_len, refs, ref_len, cfg, out, stats, workspace,
                  stream)
@@ -342,6 +369,13 @@ def tensorrouge_n(cand, cand_len, refs, ref_len, n: int = 2, beta: float = 1.0, 
     recall, F of the best reference), plus overlap int32 [B, R] and best-reference index int32 [B]
     on request (returned as a tuple then).  Without a workspace argument, a shape that the GLOBAL
     path would serve with its BLEU-only packed-key kernels is run with workspace_tables set."""
+    if workspace is None and stats is None and stream is None and ref_offsets is None and \
+            path == "auto" and not (want_overlap or want_best or workspace_tables) and \
+            score_dtype in (torch.float32, torch.bfloat16):
+        r = native().rouge(cand, cand_len, refs, ref_len, n, beta, vocab_size, ref_count,
+                           score_dtype == torch.bfloat16)
+        if r is not None:
+            return r
     cfg = make_config(max_n=n, smooth_param=beta, vocab_size=vocab_size, path=path,
                       ref_count=ref_count, score_dtype=score_dtype, ref_offsets=ref_offsets,
                       max_refs=max_refs, workspace_tables=workspace_tables)

@@ -1,8 +1,9 @@
-"""Build the gfx950 shared library (libtensorbleu.so) in-tree with hipcc.
+"""Build the gfx950 shared library (libtensorbleu.so) and the Python module that calls it in-tree.
 
 `python -m paper_2510_05485_amd.build` compiles every HIP translation unit under csrc/ for
-gfx950 and links them into one C-ABI library next to this file.  hipcc cross-compiles without a
-GPU, so this runs anywhere the ROCm toolchain is installed.
+gfx950 and links them into one C-ABI library next to this file, and csrc/tb_host.cpp (host code,
+against PyTorch's headers) into the module _host.  hipcc cross-compiles without a GPU, so this runs
+anywhere the ROCm toolchain is installed.
 """
 from __future__ import annotations
 
@@ -16,6 +17,8 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libtensorbleu.so")
+HOST_SRC = os.path.join(CSRC, "tb_host.cpp")
+HOST_LIB = os.path.join(PKG, "_host.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
@@ -30,10 +33,10 @@ def sources():
 
 
 def needs_build() -> bool:
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(HOST_LIB):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
+    t = min(os.path.getmtime(LIB), os.path.getmtime(HOST_LIB))
+    deps = sources() + [HOST_SRC] + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
     return any(os.path.getmtime(d) > t for d in deps)
 
 
@@ -45,7 +48,32 @@ def build(verbose: bool = True) -> str:
         print(" ".join(cmd), flush=True)
     subprocess.check_call(cmd)
     os.replace(tmp, LIB)
+    build_host(verbose)
     return LIB
+
+
+def build_host(verbose: bool = True) -> str:
+    """The module _host: links against the library and PyTorch."""
+    import sysconfig
+
+    import torch
+    from torch.utils import cpp_extension
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    torch_lib = os.path.join(os.path.dirname(torch.__file__), "lib")
+    include = [INCLUDE, *cpp_extension.include_paths(), os.path.join(rocm, "include"),
+               sysconfig.get_paths()["include"]]
+    tmp = HOST_LIB + f".tmp{os.getpid()}"
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[f"-isystem{d}" for d in include], "-o", tmp, HOST_SRC, "-L", PKG, "-ltensorbleu",
+           "-L", torch_lib, "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip",
+           "-Wl,-rpath,$ORIGIN"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.check_call(cmd)
+    os.replace(tmp, HOST_LIB)
+    return HOST_LIB
 
 
 EXAMPLE_SRC = os.path.join(PKG, "example", "c_caller.c")
