@@ -314,18 +314,35 @@ hipError_t run_count_clip(const Call& c, const ScoreTail* tail = nullptr) {
                          : launch_count_clip(c.pb, c.ws, c.plans.count, c.st, c.stream);
 }
 
+// Whether a call on groups beyond one LDS table runs on the sorted-run kernels.  (A caller who forces
+// the GLOBAL path gets the kernels that its passes run one by one.)
+bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_distinct,
+                RunsPlan* plan) {
+  if (!c.plans.use_part || cfg->force_path != TB_PATH_AUTO) return false;
+  const Problem& pb = c.pb;
+  return plan_runs(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.bits, rouge, group_distinct,
+                   plan);
+}
+
 // Whether the call runs on the fused kernel: on its own path, and on AUTO also for longer shapes
 // that its plan covers.  (In a workspace that is larger than it needs.  The statistic group_distinct
-// is the size of the group's dictionary there, which only the staged kernels build.)  The partitioned
-// kernels spread a group over the chip, the fused one gives it one compute unit: with 6400 tokens a
-// sequence they take 30 us for one group, 40 for 32 and 82 for 128, the fused kernel 38, 40 and 41.
+// is the size of the group's dictionary there, which only the kernels of the GLOBAL path build.)
+// The sorted-run kernels spread a group over the chip, the fused one gives it one compute unit, whose
+// time does not depend on the number of groups until each unit has one.  Measured (us, sorted runs /
+// fused): one reference of 8192 tokens, 32 groups 35.5 / 52.0, 48 46.6 / 52.2, 64 54.9 / 52.1; of 6200
+// tokens 32 29.8 / 39.2, 48 39.7 / 39.3; three of 4200 32 40.4 / 45.0, 48 54.5 / 45.4; seven of 1800
+// 32 36.8 / 30.3, 16 24.1 / -.  ROUGE-2, which needs the sorted runs of one order only: one reference of
+// 8192 64 25.2 / 30.4, 96 34.8 / 30.8; two of 6000 64 29.1 / 33.9, 96 40.2 / 34.2.
 bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
                  FusedPlan* plan) {
   const Problem& pb = c.pb;
   if (c.plans.layout.path != TB_PATH_FUSED) {
     if (cfg->force_path != TB_PATH_AUTO || cfg->workspace_tables) return false;
     if (stats && stats->group_distinct) return false;
-    if (c.plans.use_part && pb.B < 32) return false;
+    RunsPlan runs;
+    int few = 32;  // (against the partitioned kernels)
+    if (takes_runs(c, cfg, rouge, false, &runs)) few = rouge ? 80 : pb.R < 4 ? 52 - 6 * pb.R : 28;
+    if (c.plans.use_part && pb.B < few) return false;
   }
   return plan_fused(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.bits, rouge, plan);
 }
@@ -353,6 +370,15 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
                                     nullptr, true));
     }
     return TB_OK;
+  }
+  const bool group_distinct = stats && stats->group_distinct;
+  RunsPlan runs;
+  if (takes_runs(c, cfg, false, group_distinct, &runs)) {
+    rc = hip_rc(launch_runs(c.pb, runs, runs_buffers(c.pb, c.ws, c.plans.part), c.st,
+                            group_distinct, nullptr, c.stream));
+    if (rc != TB_OK) return rc;
+    return hip_rc(launch_finalize(c.pb, c.st, c.sp, !corpus, corpus || c.want_corpus_stats, corpus,
+                                  out_bleu, c.stream, c.ws.overflow));
   }
   if (!c.plans.use_part && (rc = hip_rc(launch_pack(c.pb, c.ws, c.stream))) != TB_OK) return rc;
   if ((rc = hip_rc(run_dictionary(c, true, true))) != TB_OK) return rc;
@@ -438,6 +464,13 @@ int tensorrouge_n(const void* cand, int64_t cand_stride, const int32_t* cand_len
   // cfg->workspace_tables set)
   if (!c.plans.use_hier && !c.plans.use_part && !c.plans.use_big) return TB_ERR_UNSUPPORTED;
   int32_t* ov = reinterpret_cast<int32_t*>(w + L.overlap_off);
+  RunsPlan runs;
+  if (takes_runs(c, cfg, true, false, &runs)) {
+    rc = hip_rc(launch_runs(c.pb, runs, runs_buffers(c.pb, c.ws, c.plans.part), c.st, false, ov,
+                            c.stream));
+    if (rc != TB_OK) return rc;
+    return hip_rc(launch_rouge_finalize(c.pb, c.sp, ov, ro, c.stream));
+  }
   if (!c.plans.use_part && (rc = hip_rc(launch_pack(c.pb, c.ws, c.stream))) != TB_OK) return rc;
   if ((rc = hip_rc(run_dictionary(c, false, true))) != TB_OK) return rc;
   rc = hip_rc(c.plans.use_hier

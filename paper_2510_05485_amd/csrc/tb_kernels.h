@@ -133,6 +133,34 @@ hipError_t launch_part_count_clip(const Problem& pb, const GlobalWs& ws, const P
                                   const StatPtrs& st, hipStream_t s,
                                   int32_t* rouge_overlap = nullptr);
 
+// Whole calls on the same groups: equal n-grams of a chunk merged before they are dealt out to
+// partitions, tables with the candidate's n-grams only (tb_runs.hip).  group_distinct: the caller
+// wants the dictionary sizes (the references' n-grams are then entered, too).
+struct RunsPlan {
+  int items;                    // positions per thread of the sorting kernel: 1, 2 or 4
+  int num_orders;               // 1..N, or order N alone (ROUGE-N)
+  int log2_parts, sub_bits, log2_slots;
+  int cand_chunks, ref_chunks, chunks;
+  int words, wide_fields;
+  uint32_t off_counters, off_prefix, off_runs;
+  size_t lds_bytes;
+};
+bool plan_runs(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
+               bool rouge, bool group_distinct, RunsPlan* plan);
+// its share of the partitioned kernels' workspace: N * B * group_cap keys of 8 bytes,
+// multiplicities of (at least) 2 and places of 4
+struct RunsBuffers {
+  uint64_t* keys;
+  uint16_t* times;
+  uint32_t* places;
+  int32_t* overflow;  // [B]
+};
+RunsBuffers runs_buffers(const Problem& pb, const GlobalWs& ws, const PartPlan& plan);
+// rouge_overlap != null: ROUGE-N, as for launch_hier_count_clip
+hipError_t launch_runs(const Problem& pb, const RunsPlan& plan, const RunsBuffers& buffers,
+                       const StatPtrs& st, bool group_distinct, int32_t* rouge_overlap,
+                       hipStream_t s);
+
 bool plan_big(int64_t group_cap, int N, BigPlan* plan);
 hipError_t launch_big_dictionary(const Problem& pb, const GlobalWs& ws, const BigPlan& plan,
                                  const StatPtrs& st, hipStream_t s);

@@ -1140,6 +1140,16 @@ size_t part_workspace_bytes(int64_t B, int N, int64_t group_cap, const PartPlan&
          round256(((size_t(B) * N * chunks) << plan.log2_parts) * 4);
 }
 
+RunsBuffers runs_buffers(const Problem& pb, const GlobalWs& ws, const PartPlan& plan) {
+  const PartArgs a = make_args(pb, ws, plan, StatPtrs{});
+  RunsBuffers b;
+  b.keys = a.member_key;
+  b.times = reinterpret_cast<uint16_t*>(a.member_slot);
+  b.places = a.member_id;
+  b.overflow = ws.overflow;
+  return b;
+}
+
 bool plan_part(int64_t group_cap, int64_t cand_stride, int64_t ref_stride, int R, int N,
                const int32_t* key_bytes, PartPlan* plan) {
   (void)key_bytes;  // orders with 16-byte keys are keyed by (prefix id, last token) instead
