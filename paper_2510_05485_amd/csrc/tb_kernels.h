@@ -139,7 +139,9 @@ hipError_t launch_part_count_clip(const Problem& pb, const GlobalWs& ws, const P
 struct RunsPlan {
   int items;                    // positions per thread of the sorting kernel: 1, 2 or 4
   int num_orders;               // 1..N, or order N alone (ROUGE-N)
-  int log2_parts, sub_bits, log2_slots;
+  int orders_each;              // orders a sorting workgroup takes one after the other
+  int parts, log2_slots;
+  int beyond, log2_parts, sub_bits;  // n-grams of more than 64 bits
   int cand_chunks, ref_chunks, chunks;
   int words, wide_fields;
   uint32_t off_counters, off_prefix, off_runs;

@@ -27,9 +27,11 @@
 //     plan has fewer partitions than that takes, up to four more bits choose a part of the table.
 //
 // Measured (us a call, before on the partitioned kernels -> now): one text of 262 144 tokens with its
-// reference 110.7 -> 32.9 (sorting 14, counting 15, score 3); 16 groups of two times 8192 36 -> 23; 100 of
-// two times 20 000 276 -> 172; 300 of nine times 4096 1111 -> 382; 20 of nine times 4096 with 18-bit
-// tokens 147 -> 49; ROUGE-2 of one text of 100 000 80 -> 20.
+// reference 110.7 -> 32.9 (sorting 14, counting 15, score 3); 16 groups of two times 8192 36 -> 22; 100 of
+// two times 20 000 276 -> 137 (sorting 55, counting 80); 300 of nine times 4096 1111 -> 354; 20 of nine
+// times 4096 with 18-bit tokens 147 -> 48; ROUGE-2 of one text of 100 000 80 -> 20.  The number of
+// partitions is as many as the tables need, filled up to whole rounds of 512 workgroups (a power of two
+// only with longer n-grams): counting 110 us before, with 16 tables a third full, for the 100 groups.
 //
 // Keys are exact.  A table that is full (more than twice the expected n-grams in one partition:
 // tokens chosen to collide) is reported through TB_DEV_TABLE_OVERFLOW and scored NaN.
@@ -54,8 +56,11 @@ struct RunsArgs {
   uint32_t* run_at;         // [num_orders][B][chunks][P]: first of the run within its chunk | size << 16
   int32_t* overflow;        // [B]
   int32_t* rouge_overlap;   // [B, R] or null
-  int orders[8], num_orders;
-  int log2_parts, sub_bits, log2_slots;
+  int first_order, num_orders;
+  int orders_each;          // orders a sorting workgroup handles one after the other
+  int parts, log2_slots;
+  int log2_parts, sub_bits; // with n-grams of more than 64 bits, where parts = 1 << log2_parts
+  int beyond;               // 1: there are some
   int cand_chunks, ref_chunks, chunks;  // of the candidate, of one reference, of a group
   int words, wide_fields;   // counter words per entry; 1: 32-bit counters, 0: two of 16 bits a word
   int enter_refs;           // 1: the references' n-grams are entered, too, and distinct ones counted
@@ -69,9 +74,7 @@ __device__ __forceinline__ uint32_t run_hash(uint64_t key) {
   return h ^ (h >> 15);
 }
 // (independent of the top bits of h, which pick the table slot, and of the probe step)
-__device__ __forceinline__ uint32_t run_part(uint32_t h, int log2_parts) {
-  return (h * 0x85EBCA6Bu + 0x27D4EB2Fu) >> (32 - log2_parts);
-}
+__device__ __forceinline__ uint32_t second_hash(uint32_t h) { return h * 0x85EBCA6Bu + 0x27D4EB2Fu; }
 
 // Chunk c of a group: its sequence and first position.
 struct Chunk {
@@ -81,7 +84,7 @@ template <int CHUNK>
 __device__ __forceinline__ Chunk chunk_of(const RunsArgs& a, int c) {
   Chunk k;
   const int q = max(c - a.cand_chunks, 0);
-  const int j = q / a.ref_chunks;
+  const int j = a.pb.R > 1 ? q / a.ref_chunks : 0;
   k.seq = c < a.cand_chunks ? 0 : 1 + j;
   k.first = (c < a.cand_chunks ? c : q - j * a.ref_chunks) * CHUNK;
   return k;
@@ -92,21 +95,26 @@ __device__ __forceinline__ int chunk_base(const RunsArgs& a, const Chunk& k) {
 }
 
 // ITEMS: positions per thread.  68 KB of LDS with four: two workgroups on a compute unit.
+//
+// Bound by latency: 2.5 of a workgroup's 6.6 us pass until the tokens are there, and six barriers
+// follow.  Where there are more workgroups than the chip holds, each therefore takes several orders of
+// its chunk (100 groups of two times 20 000 tokens: 63 us, then 55).
 template <int ITEMS>
 __global__ __launch_bounds__(kRunThreads, 8) void runs_sort_kernel(RunsArgs a) {
   constexpr int kChunk = ITEMS * kRunThreads;
   constexpr int kLog2Chunk = ITEMS == 4 ? 12 : ITEMS == 2 ? 11 : 10;
   static_assert((1 << kLog2Chunk) == kChunk, "chunk");
   __shared__ uint64_t key[kChunk];
-  __shared__ uint32_t token[kChunk + 8];  // in the end: what run_times receives
-  __shared__ uint32_t kept[kChunk];       // by hash: position kept there | its duplicates << 12
+  __shared__ uint32_t token[kChunk + 8];
+  __shared__ uint32_t kept[kChunk];       // by hash: position kept there | its duplicates << 12; in
+                                          // the end: what run_times receives
   __shared__ int in_part[kMaxRunParts], first_of[kMaxRunParts];
   __shared__ int scan_scratch[17];
   const Problem& pb = a.pb;
-  const int tid = threadIdx.x, parts = 1 << a.log2_parts;
-  const int c = int(blockIdx.x) % a.chunks, gn = int(blockIdx.x) / a.chunks;
-  const int idx = gn % a.num_orders, g = gn / a.num_orders;
-  const int n = a.orders[idx];
+  const int tid = threadIdx.x, parts = a.parts;
+  const int c = blockIdx.x, g = blockIdx.z;
+  const int idx_begin = int(blockIdx.y) * a.orders_each;
+  const int idx_end = min(idx_begin + a.orders_each, a.num_orders);
   const Chunk me = chunk_of<kChunk>(a, c);
 
   const RefRows rr = ref_rows(pb, g);
@@ -124,8 +132,8 @@ __global__ __launch_bounds__(kRunThreads, 8) void runs_sort_kernel(RunsArgs a) {
     row = r * pb.ref_stride;
   }
   row += me.first;
-  const int count = min(max(len - n + 1 - me.first, 0), kChunk);
-  const int staged = min(max(len - me.first, 0), kChunk + n - 1);
+  // (every token inside the length is looked at, also where no n-gram starts)
+  const int staged = min(max(len - me.first, 0), kChunk + a.first_order + idx_end - 2);
 
   bool bad = false;
   auto put = [&](int i, int32_t t) {
@@ -145,95 +153,108 @@ __global__ __launch_bounds__(kRunThreads, 8) void runs_sort_kernel(RunsArgs a) {
   }
   if (tid < kMaxRunParts) in_part[tid] = 0;
   if (c == 0) {  // what the partitions' workgroups add to
-    if (tid == 0) {
-      a.st.clipped[int64_t(g) * pb.N + n - 1] = 0;
-      a.st.distinct[int64_t(g) * pb.N + n - 1] = 0;
-      if (idx == 0) a.overflow[g] = 0;
+    if (tid >= idx_begin && tid < idx_end) {
+      const int64_t stat = int64_t(g) * pb.N + a.first_order + tid - 1;
+      a.st.clipped[stat] = 0;
+      a.st.distinct[stat] = 0;
     }
-    if (a.rouge_overlap && idx == 0 && tid < pb.R) a.rouge_overlap[int64_t(g) * pb.R + tid] = 0;
+    if (idx_begin == 0 && tid == 0) a.overflow[g] = 0;
+    if (a.rouge_overlap && idx_begin == 0 && tid < pb.R)
+      a.rouge_overlap[int64_t(g) * pb.R + tid] = 0;
   }
   if (bad && pb.status) atomicOr(pb.status, TB_DEV_TOKEN_RANGE);
   __syncthreads();
 
   const int bits = pb.bits;
-  const bool wide = n * bits > 64;
   uint64_t lo[ITEMS];
-  uint32_t above[ITEMS];  // the bits beyond 64; then the partition (and part of the table)
+  uint32_t hi[ITEMS];  // the bits beyond 64
 #pragma unroll
-  for (int u = 0; u < ITEMS; ++u) lo[u] = 0, above[u] = 0;
+  for (int u = 0; u < ITEMS; ++u) lo[u] = 0, hi[u] = 0;
+  int built = 0;  // tokens in lo and hi
 #pragma unroll 1
-  for (int j = 0; j < n; ++j) {
+  for (int idx = idx_begin; idx < idx_end; ++idx) {
+    const int n = a.first_order + idx;
+    const int count = min(max(len - n + 1 - me.first, 0), kChunk);
+    const bool wide = n * bits > 64;
+#pragma unroll 1
+    for (; built < n; ++built) {
+#pragma unroll
+      for (int u = 0; u < ITEMS; ++u) {
+        if (wide) hi[u] = (hi[u] << bits) | uint32_t(lo[u] >> (64 - bits));
+        lo[u] = (lo[u] << bits) | token[u * kRunThreads + tid + built];  // (beyond `count`: not used)
+      }
+    }
+    uint32_t h[ITEMS], where[ITEMS];  // where: partition (| part of the table << log2_parts)
 #pragma unroll
     for (int u = 0; u < ITEMS; ++u) {
-      if (wide) above[u] = (above[u] << bits) | uint32_t(lo[u] >> (64 - bits));
-      lo[u] = (lo[u] << bits) | token[u * kRunThreads + tid + j];  // (beyond `count`: not used)
+      const int k = u * kRunThreads + tid;
+      h[u] = run_hash(lo[u]);
+      const uint32_t h2 = second_hash(h[u]);
+      where[u] = a.beyond ? (h2 >> (32 - a.log2_parts - a.sub_bits)) ^ hi[u]
+                          : __umulhi(h2, uint32_t(parts));
+      if (k < count) {
+        key[k] = lo[u];
+        kept[h[u] >> (32 - kLog2Chunk)] = uint32_t(k);
+      }
     }
-  }
-  uint32_t h[ITEMS];
+    auto part_at = [&](int u) { return a.beyond ? where[u] & uint32_t(parts - 1) : where[u]; };
+    __syncthreads();
+    int rank[ITEMS];  // -1: merged into another position
 #pragma unroll
-  for (int u = 0; u < ITEMS; ++u) {
-    const int k = u * kRunThreads + tid;
-    h[u] = run_hash(lo[u]);
-    above[u] ^= run_part(h[u], a.log2_parts + a.sub_bits);
-    if (k < count) {
-      key[k] = lo[u];
-      kept[h[u] >> (32 - kLog2Chunk)] = uint32_t(k);
+    for (int u = 0; u < ITEMS; ++u) {
+      const int k = u * kRunThreads + tid;
+      rank[u] = -1;
+      if (k < count) {
+        uint32_t* const word = &kept[h[u] >> (32 - kLog2Chunk)];
+        const int w = int(*word & 0xFFFu);
+        // (the bits beyond 64 belong to the first token)
+        if (w != k && key[w] == lo[u] && (!wide || token[w] == token[k]))
+          atomicAdd(word, 0x1000u);
+        else
+          rank[u] = atomicAdd(&in_part[part_at(u)], 1);
+      }
     }
-  }
-  __syncthreads();
-  int rank[ITEMS];  // -1: merged into another position
+    __syncthreads();
+    uint32_t times[ITEMS];
 #pragma unroll
-  for (int u = 0; u < ITEMS; ++u) {
-    const int k = u * kRunThreads + tid;
-    rank[u] = -1;
-    if (k < count) {
-      uint32_t* const word = &kept[h[u] >> (32 - kLog2Chunk)];
-      const int w = int(*word & 0xFFFu);
-      // (the bits beyond 64 belong to the first token)
-      if (w != k && key[w] == lo[u] && (!wide || token[w] == token[k]))
-        atomicAdd(word, 0x1000u);
-      else
-        rank[u] = atomicAdd(&in_part[above[u] & uint32_t(parts - 1)], 1);
+    for (int u = 0; u < ITEMS; ++u) {
+      const int k = u * kRunThreads + tid;
+      times[u] = 0u;
+      if (rank[u] >= 0) {
+        const uint32_t word = kept[h[u] >> (32 - kLog2Chunk)];
+        if (int(word & 0xFFFu) == k) times[u] = word >> 12;
+        if (a.beyond) times[u] |= (where[u] >> a.log2_parts) << 12;
+      }
     }
-  }
-  __syncthreads();
-  uint32_t times[ITEMS];
+    const int mine = tid < parts ? in_part[tid] : 0;
+    int total;
+    const int first = block_exclusive_scan(mine, scan_scratch, &total);
+    if (tid < parts) {
+      first_of[tid] = first;
+      in_part[tid] = 0;
+      a.run_at[((int64_t(idx) * pb.B + g) * a.chunks + c) * parts + tid] =
+          uint32_t(first) | (uint32_t(mine) << 16);
+    }
+    __syncthreads();
 #pragma unroll
-  for (int u = 0; u < ITEMS; ++u) {
-    const int k = u * kRunThreads + tid;
-    times[u] = 0u;
-    if (rank[u] >= 0) {
-      const uint32_t word = kept[h[u] >> (32 - kLog2Chunk)];
-      if (int(word & 0xFFFu) == k) times[u] = word >> 12;
-      times[u] |= (above[u] >> a.log2_parts) << 12;
+    for (int u = 0; u < ITEMS; ++u) {
+      if (rank[u] >= 0) {
+        const int at = first_of[part_at(u)] + rank[u];
+        key[at] = lo[u];
+        kept[at] = times[u];
+      }
     }
-  }
-  const int mine = tid < parts ? in_part[tid] : 0;
-  int total;
-  const int first = block_exclusive_scan(mine, scan_scratch, &total);
-  if (tid < parts) {
-    first_of[tid] = first;
-    a.run_at[((int64_t(idx) * pb.B + g) * a.chunks + c) * parts + tid] =
-        uint32_t(first) | (uint32_t(mine) << 16);
-  }
-  __syncthreads();
+    __syncthreads();
+    const int64_t out = (int64_t(idx) * pb.B + g) * pb.group_cap + chunk_base(a, me);
 #pragma unroll
-  for (int u = 0; u < ITEMS; ++u) {
-    if (rank[u] >= 0) {
-      const int at = first_of[above[u] & uint32_t(parts - 1)] + rank[u];
-      key[at] = lo[u];
-      token[at] = times[u];
+    for (int u = 0; u < ITEMS; ++u) {
+      const int i = u * kRunThreads + tid;
+      if (i < total) {
+        a.run_key[out + i] = key[i];
+        a.run_times[out + i] = uint16_t(kept[i]);
+      }
     }
-  }
-  __syncthreads();
-  const int64_t out = (int64_t(idx) * pb.B + g) * pb.group_cap + chunk_base(a, me);
-#pragma unroll
-  for (int u = 0; u < ITEMS; ++u) {
-    const int i = u * kRunThreads + tid;
-    if (i < total) {
-      a.run_key[out + i] = key[i];
-      a.run_times[out + i] = uint16_t(token[i]);
-    }
+    if (idx + 1 < idx_end) __syncthreads();  // key and kept are written again
   }
 }
 
@@ -245,10 +266,9 @@ __global__ __launch_bounds__(kRunThreads, 8) void runs_count_kernel(RunsArgs a) 
   __shared__ int s_overlap[kWave];  // ROUGE-N: this partition's overlap with each reference
   const Problem& pb = a.pb;
   const int tid = threadIdx.x, nt = kRunThreads;
-  const int parts = 1 << a.log2_parts;
-  const int p = int(blockIdx.x) & (parts - 1), gn = int(blockIdx.x >> a.log2_parts);
-  const int idx = gn % a.num_orders, g = gn / a.num_orders;
-  const int n = a.orders[idx];
+  const int parts = a.parts;
+  const int p = blockIdx.x, idx = blockIdx.y, g = blockIdx.z;
+  const int n = a.first_order + idx;
   const int T = 1 << a.log2_slots, W = a.words;
   unsigned long long* const table = reinterpret_cast<unsigned long long*>(smem);  // T, and for the
   // key that looks like a free slot one entry for each part of the table behind them
@@ -401,7 +421,14 @@ __global__ __launch_bounds__(kRunThreads, 8) void runs_count_kernel(RunsArgs a) 
 
   // maximum over the references, minimum with the candidate, sum
   int part = 0;
-  for (int s = tid; s < T + kSubs; s += nt) {
+  if (W == 1) {  // one reference: four entries a request
+    for (int q = tid; q < (T + kSubs) / 4; q += nt) {
+      const uint4 e = reinterpret_cast<const uint4*>(counters)[q];
+      part += int(min(e.x & 0xFFFFu, e.x >> 16) + min(e.y & 0xFFFFu, e.y >> 16) +
+                  min(e.z & 0xFFFFu, e.z >> 16) + min(e.w & 0xFFFFu, e.w >> 16));
+    }
+  }
+  for (int s = tid; W > 1 && s < T + kSubs; s += nt) {
     const uint32_t* const e = counters + __umul24(uint32_t(s), uint32_t(W));
     const uint32_t w0 = e[0];
     const uint32_t cc = a.wide_fields ? w0 : w0 & 0xFFFFu;
@@ -420,8 +447,10 @@ __global__ __launch_bounds__(kRunThreads, 8) void runs_count_kernel(RunsArgs a) 
     }
   }
   const int clipped = block_sum(part, scan_scratch);  // (its barriers complete s_overlap)
-  if (a.rouge_overlap && tid < pb.R && s_overlap[tid])
-    atomicAdd(&a.rouge_overlap[int64_t(g) * pb.R + tid], s_overlap[tid]);
+  if (a.rouge_overlap && tid < pb.R) {
+    const int both = W == 1 ? clipped : s_overlap[tid];
+    if (both) atomicAdd(&a.rouge_overlap[int64_t(g) * pb.R + tid], both);
+  }
   const int64_t stat = int64_t(g) * pb.N + n - 1;
   if (a.enter_refs) {
     __syncthreads();  // (scan_scratch is used again)
@@ -439,17 +468,15 @@ __global__ __launch_bounds__(kRunThreads, 8) void runs_count_kernel(RunsArgs a) 
 
 template <int ITEMS>
 hipError_t launch_items(const RunsArgs& a, const RunsPlan& plan, hipStream_t s) {
-  const int64_t pairs = int64_t(a.pb.B) * a.num_orders;
-  if (pairs * a.chunks > 0x7FFFFFFF || (pairs << a.log2_parts) > 0x7FFFFFFF)
-    return hipErrorInvalidValue;
   const auto count = runs_count_kernel<ITEMS * kRunThreads>;
   hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(count), plan.lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(runs_sort_kernel<ITEMS>, dim3(uint32_t(pairs * a.chunks)), dim3(kRunThreads),
-                     0, s, a);
+  const int shares = (a.num_orders + a.orders_each - 1) / a.orders_each;
+  hipLaunchKernelGGL(runs_sort_kernel<ITEMS>, dim3(a.chunks, shares, a.pb.B), dim3(kRunThreads), 0,
+                     s, a);
   e = hipGetLastError();
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(count, dim3(uint32_t(pairs << a.log2_parts)), dim3(kRunThreads),
+  hipLaunchKernelGGL(count, dim3(a.parts, a.num_orders, a.pb.B), dim3(kRunThreads),
                      plan.lds_bytes, s, a);
   return hipGetLastError();
 }
@@ -460,7 +487,7 @@ bool plan_runs(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
                bool rouge, bool group_distinct, RunsPlan* plan) {
   RunsPlan& p = *plan;
   const int64_t cap = cand_stride + R * ref_stride;
-  if (R >= kWave || cap > int64_t(4096) * kMaxRunParts) return false;
+  if (R >= kWave || cap > int64_t(4096) * kMaxRunParts || B > 65535) return false;
   p.wide_fields = cand_stride > 65535 || ref_stride > 65535;
   p.words = p.wide_fields ? R + 1 : (R + 2) / 2;
   p.num_orders = rouge ? 1 : N;
@@ -496,22 +523,39 @@ bool plan_runs(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   while (log2_slots > 10 && lds_for(log2_slots) > size_t(kLdsBudget) / 2) --log2_slots;
   while (log2_slots < 13 && (entries >> (log2_slots - 1)) >= kMaxRunParts) ++log2_slots;
   if (lds_for(log2_slots) > size_t(kLdsBudget)) return false;
-  int lg = 1;
-  while ((int64_t(1) << (lg + log2_slots - 1)) < entries) ++lg;
-  // few groups: more partitions than the tables ask for, until the chip has two workgroups a unit
-  while (lg < 9 && (pairs << lg) < 512 && (entries >> lg) > 512) ++lg;
+  const int64_t half_full = int64_t(1) << (log2_slots - 1);
+  int64_t parts = (entries + half_full - 1) / half_full;
+  // the chip holds 512 workgroups of the counting kernel: more partitions than the tables ask for, until
+  // the last round of workgroups is a full one, but none of less than 512 n-grams
+  const int64_t rounds = (pairs * parts + 511) / 512;
+  const int64_t fill = rounds * 512 / pairs, most = entries / 512;
+  const int64_t more = fill < most ? fill : most;
+  parts = more > parts ? more : parts;
+  if (parts > kMaxRunParts && half_full * kMaxRunParts >= entries) parts = kMaxRunParts;
+  if (parts < 2) parts = 2;
   // bits of an n-gram beyond 64 (they have to lie in its first token)
   const int beyond = N * bits - 64;
-  if (beyond > 0) {
+  p.beyond = beyond > 0;
+  p.log2_parts = p.sub_bits = 0;
+  if (p.beyond) {
     if (beyond > bits) return false;
+    int lg = 1;
+    while ((int64_t(1) << lg) < parts) ++lg;
     while (lg + kSubBits < beyond) ++lg;
-    if ((entries >> lg) < 64) return false;  // partitions of a few n-grams: not worth it
+    parts = int64_t(1) << lg;
+    if (entries / parts < 64) return false;  // partitions of a few n-grams: not worth it
+    p.log2_parts = lg;
+    p.sub_bits = beyond > lg ? beyond - lg : 0;
   }
-  if ((1 << lg) > kMaxRunParts) return false;
-  p.log2_parts = lg;
-  p.sub_bits = beyond > lg ? beyond - lg : 0;
+  if (parts > kMaxRunParts) return false;
+  p.parts = int(parts);
+  // orders a sorting workgroup takes: as many as leave the chip two full rounds of workgroups
+  p.orders_each = p.num_orders;
+  while (p.orders_each > 1 &&
+         B * ((p.num_orders + p.orders_each - 1) / p.orders_each) * chunks < 1024)
+    p.orders_each = (p.orders_each + 1) / 2;
   // the runs' places lie where the partitioned kernels keep the ids of a group's slots
-  return (chunks << lg) <= cap;
+  return chunks * parts <= cap;
 }
 
 hipError_t launch_runs(const Problem& pb, const RunsPlan& plan, const RunsBuffers& buffers,
@@ -526,9 +570,12 @@ hipError_t launch_runs(const Problem& pb, const RunsPlan& plan, const RunsBuffer
   a.overflow = buffers.overflow;
   a.rouge_overlap = rouge_overlap;
   a.num_orders = plan.num_orders;
-  for (int k = 0; k < 8; ++k) a.orders[k] = rouge_overlap ? pb.N : k + 1;
+  a.first_order = rouge_overlap ? pb.N : 1;
+  a.orders_each = plan.orders_each;
+  a.parts = plan.parts;
   a.log2_parts = plan.log2_parts;
   a.sub_bits = plan.sub_bits;
+  a.beyond = plan.beyond;
   a.log2_slots = plan.log2_slots;
   a.cand_chunks = plan.cand_chunks;
   a.ref_chunks = plan.ref_chunks;
