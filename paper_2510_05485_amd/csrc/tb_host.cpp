@@ -213,10 +213,14 @@ bool take_int(PyObject* o, int32_t* to) {
   return !overflow && v == *to;
 }
 bool take_float(PyObject* o, float* to) {
-  const double v = PyFloat_CheckExact(o) ? PyFloat_AS_DOUBLE(o)
-                   : PyLong_CheckExact(o) ? double(PyLong_AsLong(o)) : 0.0;
+  if (!PyFloat_CheckExact(o) && !PyLong_CheckExact(o)) return false;
+  const double v = PyFloat_AsDouble(o);
+  if (PyErr_Occurred()) {  // an integer beyond a double's range
+    PyErr_Clear();
+    return false;
+  }
   *to = float(v);
-  return PyFloat_CheckExact(o) || PyLong_CheckExact(o);
+  return true;
 }
 
 // once(corpus, cand, cand_len, refs, ref_len, max_n, smoothing, smooth_param, vocab_size,
@@ -252,7 +256,7 @@ PyObject* rouge(PyObject*, PyObject* const* args, Py_ssize_t n) {
   if (!take_batch(args, &cfg, nullptr, &b)) Py_RETURN_NONE;
   if (args[7] != Py_None) {
     const at::Tensor* t = tensor(args[7]);
-    if (!plain(t, 1, at::kInt)) Py_RETURN_NONE;
+    if (!plain(t, 1, at::kInt) || t->size(0) != b.B) Py_RETURN_NONE;
     cfg.ref_count = t->data_ptr<int32_t>();
   }
   tb_layout_t layout;
