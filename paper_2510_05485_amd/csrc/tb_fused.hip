@@ -301,12 +301,35 @@ void fused_kernel(FusedArgs by_value) {
   __syncthreads();
   TB_FSTAMP(1);
 
-  // val[0] is the block at hand, finished blocks rotate to the end (a register array cannot be
-  // indexed by a loop counter, and unrolled loops would multiply the code).
-  auto rotate_in = [&](int32_t v) {
+  // The blocks at hand are val[0], ..., finished ones rotate to the end (a register array cannot be
+  // indexed by a loop counter).  A rotation moves all of them, so they are taken in groups of up to
+  // four, as far as full ones go: 128 x 8192 48.5 -> 46.7 us, 128 x 5000 29.5 -> 28.7.
+  constexpr int GROUP = BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
+  auto rotate = [&](auto by) {
+    constexpr int n = decltype(by)::value;
+    int32_t first[n];
 #pragma unroll
-    for (int i = 0; i + 1 < BLOCKS; ++i) val[i] = val[i + 1];
-    val[BLOCKS - 1] = v;
+    for (int u = 0; u < n; ++u) first[u] = val[u];
+#pragma unroll
+    for (int i = 0; i + n < BLOCKS; ++i) val[i] = val[i + n];
+#pragma unroll
+    for (int u = 0; u < n; ++u) val[BLOCKS - n + u] = first[u];
+  };
+  // f(val[k]) for the blocks from i to `end`; f may change the value
+  auto each_block = [&](int& i, int end, auto&& f) __attribute__((always_inline)) {
+    if (GROUP > 1) {
+#pragma unroll 1
+      for (; i + GROUP <= end; i += GROUP) {
+#pragma unroll
+        for (int u = 0; u < GROUP; ++u) f(val[u]);
+        rotate(std::integral_constant<int, GROUP>{});
+      }
+    }
+#pragma unroll 1
+    for (; i < end; ++i) {
+      f(val[0]);
+      rotate(std::integral_constant<int, 1>{});
+    }
   };
 
   SymbolTable table;
@@ -335,34 +358,36 @@ void fused_kernel(FusedArgs by_value) {
   {
     int i = 0, b = wave;
     uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
-#pragma unroll 1
-    for (; i < my_cand_blocks; ++i, id += nt, s += sym_stride, b += nwaves) {
+    each_block(i, my_cand_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       int32_t got = -1;
-      if (val[0] >= 0) {
-        got = int32_t(table.claim<KEEP>(uint32_t(val[0]) * table.multiplier, id));
+      if (v >= 0) {
+        got = int32_t(table.claim<KEEP>(uint32_t(v) * table.multiplier, id));
         if (!ROUGE || N == 1) lds_add(cnt_at + __umul24(uint32_t(got), W4), 1u);
       }
       *lds<int16_t>(s) = int16_t(got);
-      rotate_in(got);
-    }
+      v = got;
+      id += nt;
+      s += sym_stride;
+      b += nwaves;
+    });
     __syncthreads();
     TB_FSTAMP(2);
-#pragma unroll 1
-    for (; i < my_blocks; ++i, s += sym_stride, b += nwaves) {
+    each_block(i, my_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       const int f = sequence_of(b);
       // (a lane without a token asks like the others; its sign bit then hides the answer)
-      const uint32_t x = table.find(uint32_t(val[0]) * table.multiplier) |
-                         (uint32_t(val[0]) & 0x80000000u);
+      const uint32_t x = table.find(uint32_t(v) * table.multiplier) | (uint32_t(v) & 0x80000000u);
       const bool hit = x < id_limit;
       const int32_t got = hit ? int32_t(x) : -1;
       if (hit && (!ROUGE || N == 1))
         lds_add(cnt_at + 4u * uint32_t(f >> 1) + __umul24(x, W4), (f & 1) ? 0x10000u : 1u);
       *lds<int16_t>(s + uint32_t(2 * kPadSymbols) * f) = int16_t(got);
-      rotate_in(got);
-    }
+      v = got;
+      s += sym_stride;
+      b += nwaves;
+    });
     if (KEEP) {
 #pragma unroll 1
-      for (; i < BLOCKS; ++i) rotate_in(val[0]);
+      for (; i < BLOCKS; ++i) rotate(std::integral_constant<int, 1>{});
     }
   }
   TB_FSTAMP(3);
@@ -432,9 +457,8 @@ void fused_kernel(FusedArgs by_value) {
     const uint32_t first_count = cnt_at + (ROUGE ? 0u : uint32_t(lo - 1 - swept) * set_bytes);
     int i = 0, b = wave;
     uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
-#pragma unroll 1
-    for (; i < my_cand_blocks; ++i, id += nt, s += sym_stride, b += nwaves) {
-      int32_t cur = KEEP ? val[0] : int32_t(*lds<int16_t>(s));
+    auto enter_block = [&](int32_t& v) __attribute__((always_inline)) {
+      int32_t cur = KEEP ? v : int32_t(*lds<int16_t>(s));
       uint32_t tag = first_tag, count = first_count, next = s + 2u * uint32_t(lo - 1);
       int n = lo;
       auto enter = [&](int offset) {
@@ -456,16 +480,16 @@ void fused_kernel(FusedArgs by_value) {
         enter(2);
         next += 2u;
       }
-      if (KEEP) rotate_in(cur);
-    }
-    __syncthreads();
-    TB_FSTAMP(2 * lo);
-#pragma unroll 1
-    for (; i < my_blocks; ++i, s += sym_stride, b += nwaves) {
+      if (KEEP) v = cur;
+      id += nt;
+      s += sym_stride;
+      b += nwaves;
+    };
+    auto look_up_block = [&](int32_t& v) __attribute__((always_inline)) {
       const int f = sequence_of(b);
       const uint32_t addend = (f & 1) ? 0x10000u : 1u;
       const uint32_t own = s + uint32_t(2 * kPadSymbols) * f;
-      int32_t cur = KEEP ? val[0] : int32_t(*lds<int16_t>(own));
+      int32_t cur = KEEP ? v : int32_t(*lds<int16_t>(own));
       uint32_t next = own + 2u * uint32_t(lo - 1);
       uint32_t tag = first_tag, count = first_count + 4u * uint32_t(f >> 1);
 #pragma unroll 1
@@ -483,11 +507,25 @@ void fused_kernel(FusedArgs by_value) {
         next += 2u;
         if (n >= hi) break;  // uniform
       }
-      if (KEEP) rotate_in(cur);
-    }
+      if (KEEP) v = cur;
+      s += sym_stride;
+      b += nwaves;
+    };
     if (KEEP) {
+      each_block(i, my_cand_blocks, enter_block);
+    } else {
 #pragma unroll 1
-      for (; i < BLOCKS; ++i) rotate_in(val[0]);
+      for (; i < my_cand_blocks; ++i) enter_block(val[0]);
+    }
+    __syncthreads();
+    TB_FSTAMP(2 * lo);
+    if (KEEP) {
+      each_block(i, my_blocks, look_up_block);
+#pragma unroll 1
+      for (; i < BLOCKS; ++i) rotate(std::integral_constant<int, 1>{});
+    } else {
+#pragma unroll 1
+      for (; i < my_blocks; ++i) look_up_block(val[0]);
     }
     TB_FSTAMP(2 * lo + 1);
   }
