@@ -46,16 +46,22 @@ __device__ __forceinline__ int dpp_or_zero(int v) {
   return __builtin_amdgcn_update_dpp(0, v, kCtrl, kRowMask, kBankMask, false);
 }
 
-// Inclusive prefix sum across the 64 lanes of a wavefront.  All 64 lanes must be active.
-// Row-local shifts build the scan inside each row of 16 lanes; two row broadcasts (lane 15 of a
-// row into the next row, lane 31 into the upper half) carry it across rows.
-__device__ __forceinline__ int wave_inclusive_scan(int v) {
+// Inclusive prefix sum across each row of 16 lanes.  All 64 lanes must be active.
+__device__ __forceinline__ int row_inclusive_scan(int v) {
   int x = v;
   x += dpp_or_zero<0x111, 0xf, 0xf>(v);  // row_shr:1
   x += dpp_or_zero<0x112, 0xf, 0xf>(v);  // row_shr:2
   x += dpp_or_zero<0x113, 0xf, 0xf>(v);  // row_shr:3
   x += dpp_or_zero<0x114, 0xf, 0xe>(x);  // row_shr:4, lanes 4..15 of each row
   x += dpp_or_zero<0x118, 0xf, 0xc>(x);  // row_shr:8, lanes 8..15 of each row
+  return x;
+}
+
+// Inclusive prefix sum across the 64 lanes of a wavefront.  All 64 lanes must be active.
+// Row-local shifts build the scan inside each row of 16 lanes; two row broadcasts (lane 15 of a
+// row into the next row, lane 31 into the upper half) carry it across rows.
+__device__ __forceinline__ int wave_inclusive_scan(int v) {
+  int x = row_inclusive_scan(v);
   x += dpp_or_zero<0x142, 0xa, 0xf>(x);  // row_bcast:15 into rows 1 and 3
   x += dpp_or_zero<0x143, 0xc, 0xf>(x);  // row_bcast:31 into rows 2 and 3
   return x;
