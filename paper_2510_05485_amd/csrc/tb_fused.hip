@@ -304,7 +304,7 @@ void fused_kernel(FusedArgs by_value) {
   // The blocks at hand are val[0], ..., finished ones rotate to the end (a register array cannot be
   // indexed by a loop counter).  A rotation moves all of them, so they are taken in groups of up to
   // four, as far as full ones go: 128 x 8192 48.5 -> 46.7 us, 128 x 5000 29.5 -> 28.7.
-  constexpr int GROUP = BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
+  constexpr int GROUP = !KEEP ? 1 : BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
   auto rotate = [&](auto by) {
     constexpr int n = decltype(by)::value;
     int32_t first[n];
