@@ -780,6 +780,10 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
   // workgroups a compute unit gets, and with it its share of LDS and wavefronts
   int resident = 1;
   while (resident < 32 && B > 256 * resident) resident *= 2;
+  // a little more than eight a unit, short rows: tables for sixteen would be half as large as there is
+  // room for (2398 x 227 20.8 -> 15.9 us, 2295 x 223 with two references 22.1 -> 17.5; with longer rows,
+  // more references or other numbers of groups the power of two is the better choice)
+  if (resident == 16 && B <= 2560 && cand_stride <= 256 && R <= 2) resident = 10;
   // share of the slots that may be taken if every row is full, in twelfths; the last resort comes
   // after all numbers of workgroups have been tried with the others
   static const int kTwelfths[3] = {5, 6, 9};
@@ -789,7 +793,7 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
       if (resident == 1) {  // the chip is not full: a wavefront for (nearly) each block
         while (waves < 16 && 4 * waves < 3 * blocks) waves *= 2;
       } else {
-        while (waves < 16 && waves < 32 / r && blocks > waves * (waves < 4 ? 1 : waves < 8 ? 2 : 4))
+        while (waves < 16 && 2 * waves <= 32 / r && blocks > waves * (waves < 4 ? 1 : waves < 8 ? 2 : 4))
           waves *= 2;
       }
       if (want_threads) waves = want_threads / kWave;
@@ -802,6 +806,8 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           int orders;
           if (want_passes >= 0 && passes != want_passes) continue;
           if (!set_passes(passes, N, bits, plan, &orders)) continue;
+          // (1561 x 283 with three references 19.5 us, in pairs 17.2)
+          if (passes == 1 && r == 8 && R == 3 && N > 2 && want_passes < 0) continue;
           if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2) && want_passes < 0) continue;
           const int64_t entries = orders * cand_stride;
           const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;

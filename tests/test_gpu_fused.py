@@ -59,6 +59,8 @@ def test_block_edges(N, L, Lr):
     (300, 1, 90, 40, 4),        # two workgroups on a unit
     (1300, 1, 1000, 300, 4),    # every order on its own
     (1300, 4, 300, 50, 4),      # pairs
+    (2300, 2, 200, 500, 4),     # ten workgroups on a unit
+    (1600, 3, 280, 3000, 4),    # pairs, eight on a unit
     (9000, 1, 40, 30, 4),       # as many workgroups as a unit takes
     (40, 2, 2700, 50257, 4),    # order 1 apart from the others
     (600, 1, 4096, 2, 3),       # long runs: counters near their limit
