@@ -24,7 +24,9 @@
 //     references), so two workgroups of 1024 threads share a compute unit.
 //   * n-grams of more than 64 bits: the partition number is (hash of the low 64 bits) xor (the bits
 //     above them), so partition and low bits identify the n-gram and the key stays 8 bytes.  Where the
-//     plan has fewer partitions than that takes, up to four more bits choose a part of the table.
+//     plan has fewer partitions than that takes, up to four more bits choose a part of the table.  Such a
+//     part is a table of its own, of 64 slots at the least: the plan has to leave it room for more than
+//     its share (has_room).
 //
 // Measured (us a call, before on the partitioned kernels -> now): one text of 262 144 tokens with its
 // reference 110.7 -> 32.9 (sorting 14, counting 15, score 3); 16 groups of two times 8192 36 -> 22; 100 of
@@ -33,8 +35,10 @@
 // partitions is as many as the tables need, filled up to whole rounds of 512 workgroups (a power of two
 // only with longer n-grams): counting 110 us before, with 16 tables a third full, for the 100 groups.
 //
-// Keys are exact.  A table that is full (more than twice the expected n-grams in one partition:
-// tokens chosen to collide) is reported through TB_DEV_TABLE_OVERFLOW and scored NaN.
+// Keys are exact.  A table that is full (which takes tokens chosen to collide: see has_room) is reported
+// through TB_DEV_TABLE_OVERFLOW and scored NaN.
+#include <cmath>
+
 #include "tb_kernels.h"
 
 namespace tb {
@@ -481,6 +485,15 @@ hipError_t launch_items(const RunsArgs& a, const RunsPlan& plan, hipStream_t s) 
   return hipGetLastError();
 }
 
+// Whether a table (or part of one) of `slots` slots holds what a hash sends to it of `entries` distinct
+// n-grams dealt to `tables` of them.  The number is binomial; that it reaches k is less likely than
+// exp(k - mean - k log(k / mean)) (Chernoff), here exp(-40): with 2^31 tables in a call, 1e-8.  Half full
+// on average is room enough from 256 slots on; 128 may expect 52, 64 may expect 16.
+bool has_room(int64_t entries, int64_t tables, int64_t slots) {
+  const double mean = double(entries) / double(tables), k = double(slots);
+  return mean < k && k - mean - k * std::log(k / mean) <= -40.0;
+}
+
 }  // namespace
 
 bool plan_runs(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
@@ -542,10 +555,20 @@ bool plan_runs(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
     int lg = 1;
     while ((int64_t(1) << lg) < parts) ++lg;
     while (lg + kSubBits < beyond) ++lg;
+    // one partition more instead of one part of a table: the parts keep their n-grams and get twice the
+    // slots.  (8192 tokens of 18 bits with 16 references: 32 n-grams in 64 slots, now in 128.)  Where
+    // partitions would become too many or too small, larger tables.
+    auto sub_bits = [&] { return beyond > lg ? beyond - lg : 0; };
+    while (!has_room(entries, int64_t(1) << (lg + sub_bits()), int64_t(1) << (log2_slots - sub_bits()))) {
+      if ((int64_t(2) << lg) <= kMaxRunParts && entries >> (lg + 1) >= 64)
+        ++lg;
+      else if (++log2_slots > 13 || lds_for(log2_slots) > size_t(kLdsBudget))
+        return false;
+    }
     parts = int64_t(1) << lg;
     if (entries / parts < 64) return false;  // partitions of a few n-grams: not worth it
     p.log2_parts = lg;
-    p.sub_bits = beyond > lg ? beyond - lg : 0;
+    p.sub_bits = sub_bits();
   }
   if (parts > kMaxRunParts) return false;
   p.parts = int(parts);

@@ -1,0 +1,19 @@
+// The library's plans, callable from Python (compiled and loaded by test_plans.py).
+#include "tb_kernels.h"
+
+extern "C" {
+
+// tables an order's n-grams are dealt to, slots of one, partitions; false: no such plan
+bool runs_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits, bool rouge,
+               bool group_distinct, int64_t* out) {
+  tb::RunsPlan p;
+  if (!tb::plan_runs(B, cand_stride, ref_stride, R, N, bits, rouge, group_distinct, &p)) return false;
+  out[0] = int64_t(p.parts) << p.sub_bits;
+  out[1] = int64_t(1) << (p.log2_slots - p.sub_bits);
+  out[2] = p.parts;
+  out[3] = p.chunks;
+  out[4] = int64_t(p.lds_bytes);
+  return true;
+}
+
+}  // extern "C"

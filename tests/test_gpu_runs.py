@@ -79,6 +79,22 @@ def test_shapes(B, R, L, Lr, vocab, N):
     check(w, N, int64=B % 2 == 0, rouge_n=N if vocab == 10000 else 2)
 
 
+@pytest.mark.parametrize("B,R,L,Lr,vocab,N", [
+    (2, 16, 4096, 700, 262144, 4),     # parts of 64 slots, the smallest
+    (1, 16, 8192, 1000, 262144, 4),    # of 128
+])
+def test_parts_of_a_table(B, R, L, Lr, vocab, N):
+    # every n-gram another one: the table's parts as full as the plan reckons with
+    w = syn.random_small(871, B=B, R=R, vocab=vocab, max_len=min(L, Lr), min_len=min(L, Lr),
+                         cand_stride=L, ref_stride=Lr)
+    rng = np.random.default_rng(871)
+    for i in range(B):
+        w.cand[i], w.cand_len[i] = rng.permutation(vocab)[:L], L
+        for j in range(R):
+            w.refs[i, j] = w.cand[i, 64 * j:64 * j + Lr]
+    check(w, N)
+
+
 @pytest.mark.parametrize("length", [1024, 1025, 4095, 8192])
 def test_chunk_edges(length):
     # the length ends a chunk, starts one, or leaves fewer positions than an n-gram has
