@@ -170,8 +170,9 @@ struct SymbolTable {
     return make_uint4(q.x, q.y, q.z, q.w);
   }
   // Id of the key, or a value of at least id_limit: one 16-byte request answers unless the bucket
-  // is full and does not hold the key.
-  __device__ __forceinline__ uint32_t find(uint32_t h) const {
+  // is full and does not hold the key.  live: the lane has a key (the others ask like it, and their
+  // sequences must not be taken for one that was too long).
+  __device__ __forceinline__ uint32_t find(uint32_t h, bool live) const {
     uint32_t s = (h >> home_shift) & bucket_mask;
     const uint32_t remainder = h << log2_buckets;
     uint32_t mine = remainder + id_limit;
@@ -184,7 +185,7 @@ struct SymbolTable {
         e = bucket(s);
         x = match(e, mine);
       } while (min(x, e.w) >= id_limit);
-      if (__builtin_expect(mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
+      if (__builtin_expect(live && mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
     }
     return x;
   }
@@ -375,7 +376,7 @@ void fused_kernel(FusedArgs by_value) {
     each_block(i, my_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       const int f = sequence_of(b);
       // (a lane without a token asks like the others; its sign bit then hides the answer)
-      const uint32_t x = table.find(uint32_t(v) * table.multiplier) | (uint32_t(v) & 0x80000000u);
+      const uint32_t x = table.find(uint32_t(v) * table.multiplier, v >= 0) | (uint32_t(v) & 0x80000000u);
       const bool hit = x < id_limit;
       const int32_t got = hit ? int32_t(x) : -1;
       if (hit && (!ROUGE || N == 1))
@@ -524,7 +525,7 @@ void fused_kernel(FusedArgs by_value) {
         const int32_t key = int32_t(uint32_t(cur) << id_bits) | int32_t(*lds<int16_t>(next));
         cur = -1;
         if (!__builtin_amdgcn_ballot_w64(key >= 0)) break;  // uniform: nothing to extend
-        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag) |
+        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag, key >= 0) |
                            (uint32_t(key) & 0x80000000u);
         const bool hit = x < id_limit;
         cur = hit ? int32_t(x) : -1;
@@ -813,8 +814,13 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
           int lg_min = 6;
           while ((int64_t(kTwelfths[level]) << lg_min) < 12 * entries) ++lg_min;
-          // bits for the probe count: sequences of ordinary tokens stay below fifteen
-          while (32 - widest + lg_min - 2 - p.id_bits < 4) ++lg_min;
+          // bits for the probe count.  A sequence that reaches the largest count sends the whole
+          // workgroup to the loop without a table, so ordinary tokens must not get there.  Every bucket
+          // further is reached by an eighth of the sequences at half load, by 0.43 of them at three
+          // quarters (look-ups and insertions of 128 x 8192 and 64 x 6144 Zipf-distributed tokens counted
+          // on the CPU): fifteen buckets were reached by 1e-9 of the groups and by one in twenty, sixty-three
+          // would be by 1e-19.
+          while (32 - widest + lg_min - 2 - p.id_bits < (level < 2 ? 4 : 6)) ++lg_min;
           int lg = lg_min;  // (a larger table than this costs more to clear than it saves)
           while ((int64_t(1) << lg) < (r == 1 ? 6 : 4) * entries) ++lg;
           if (want_lg) {

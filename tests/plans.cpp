@@ -16,4 +16,21 @@ bool runs_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   return true;
 }
 
+// log2 of the slots; bits of an id and of the widest key; pass_ends; LDS bytes; false: no such plan
+bool fused_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits, bool rouge,
+                int64_t* out) {
+  tb::FusedPlan p;
+  if (!tb::plan_fused(B, cand_stride, ref_stride, R, N, bits, rouge, &p)) return false;
+  out[0] = p.log2_slots;
+  out[1] = p.id_bits;
+  out[2] = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
+  out[3] = p.pass_ends;
+  out[4] = int64_t(p.lds_bytes);
+  return true;
+}
+
+bool fused_path(int64_t cand_stride, int64_t ref_stride, int R, int bits) {
+  return tb::fused_path_takes(cand_stride, ref_stride, R, bits);
+}
+
 }  // extern "C"

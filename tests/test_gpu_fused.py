@@ -71,6 +71,24 @@ def test_plans(B, R, L, vocab, N):
     check(syn.random_small(B + L, B=B, R=R, vocab=vocab, max_len=L, min_len=L // 3), N)
 
 
+@pytest.mark.parametrize("B,R,L,Lr,vocab,N", [
+    (30, 16, 2984, 895, 1 << 23, 4),   # a table of 4096 slots 0.73 full, six bits for the probe count
+    (12, 62, 1059, 105, 2000, 4),      # of 2048 slots 0.52 full
+    (30, 4, 6144, 2000, 50257, 4),     # would be 0.75 full with four bits: not for this kernel
+    (28, 3, 6144, 6144, 50257, 4),
+])
+def test_full_tables(B, R, L, Lr, vocab, N):
+    w = syn.random_small(641 + L, B=B, R=R, vocab=vocab, max_len=min(L, Lr), min_len=min(L, Lr),
+                         cand_stride=L, ref_stride=Lr)
+    rng = np.random.default_rng(641)
+    for i in range(B):
+        w.cand[i], w.cand_len[i] = rng.integers(0, vocab, L), L
+        for j in range(R):
+            w.refs[i, j] = np.where(rng.random(Lr) < 0.2, w.refs[i, j], w.cand[i, j:j + Lr] if L >= j + Lr
+                                    else w.cand[i, :Lr])
+    check(w, N)
+
+
 @pytest.mark.parametrize("N", [1, 4])
 def test_tokens_chosen_to_collide(N):
     # 150 token ids whose products with the table's multiplier are the smallest there are: all of

@@ -28,7 +28,21 @@ def plans(tmp_path_factory):
     i64, i32, flag = ctypes.c_int64, ctypes.c_int, ctypes.c_bool
     lib.runs_plan.restype = flag
     lib.runs_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, flag, ctypes.POINTER(i64)]
+    lib.fused_plan.restype = lib.fused_path.restype = flag
+    lib.fused_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, ctypes.POINTER(i64)]
+    lib.fused_path.argtypes = [i64, i64, i32, i32]
     return lib
+
+
+def orders_in_a_pass(N, pass_ends):
+    """The largest number of orders that share a table (see FusedArgs::pass_ends)."""
+    most = swept = 0
+    end = 1 if pass_ends & 1 else pass_ends >> 4 & 15 if N > 1 else 1
+    while True:
+        most, swept = max(most, end - swept), end
+        if swept >= N:
+            return most
+        end = pass_ends >> 4 * end & 15
 
 
 def test_sorted_runs_leave_their_tables_room(plans):
@@ -57,3 +71,32 @@ def test_sorted_runs_leave_their_tables_room(plans):
     chance = stats.binom.logsf(slots, entries, 1.0 / np.array(tables, dtype=np.float64))
     worst = int(np.argmax(chance))
     assert chance[worst] <= -40.0, (shapes[worst], tables[worst], slots[worst], chance[worst])
+
+
+def fused_table(plans, *shape):
+    """Share of the table's slots that are taken if no n-gram repeats, and bits of an entry's probe
+    count (what the remainder of the key and the id leave of 32); None: no such plan."""
+    out = (ctypes.c_int64 * 5)()
+    if not plans.fused_plan(*shape, out):
+        return None
+    lg, id_bits, key_bits, pass_ends, lds = out
+    assert lds <= LDS, shape
+    load = orders_in_a_pass(shape[4], pass_ends) * shape[1] / 2 ** lg
+    return load, min(32 - key_bits + lg - 2, 32) - id_bits
+
+
+def test_fused_tables_count_far_enough(plans):
+    # A probe sequence of ordinary tokens must not reach the largest count of an entry.  The share of
+    # the sequences that go one bucket further is an eighth at half load and 0.43 at three quarters.
+    seen = {False: 0, True: 0}
+    for R, cs, of, (N, bits), B in itertools.product(
+            (1, 2, 3, 4, 5, 7, 8, 12, 16, 31, 62), list(range(1024, 8193, 128)) + [1, 5, 60, 500, 5600],
+            (0.1, 0.3, 0.8, 1.0, 1.2), ((1, 8), (2, 14), (4, 16), (4, 23), (8, 12)), (1, 40, 700, 4096)):
+        for rouge in (False, True):
+            shape = (B, cs, max(int(of * cs), 1), R, N, bits, rouge)
+            table = fused_table(plans, *shape)
+            if table:
+                load, count_bits = table
+                assert load <= 0.75 and count_bits >= (4 if load <= 0.5 else 6), (shape, table)
+                seen[load > 0.5] += 1
+    assert min(seen.values()) > 10, seen
