@@ -124,6 +124,16 @@ __device__ __forceinline__ int block_sum(int v, int* scratch) {
   return scratch[16];
 }
 
+// Where an insertion goes on that has read a bucket of four slots (x, y, z and one more; 0: free) while
+// others swap into it: the byte offset of the first slot it saw free, of the last one where it saw
+// none of the first three free.  Nothing keeps the words of a 16-byte LDS read together: a slot may be
+// seen free and a later one taken, although buckets are filled front to back.  Slots before the first
+// free one hold other keys; the slot itself, whatever it has become since, is tried with a
+// compare-and-swap, and so is every one behind it.
+__host__ __device__ __forceinline__ uint32_t first_free_slot(uint32_t x, uint32_t y, uint32_t z) {
+  return !x ? 0u : !y ? 4u : !z ? 8u : 12u;
+}
+
 // Problem description handed to every kernel (device pointers + shapes).
 struct Problem {
   const void* cand;      // int32 or int64 token ids (tok64)

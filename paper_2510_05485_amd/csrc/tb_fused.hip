@@ -145,7 +145,7 @@ struct SymbolTable {
       const uint4 e = bucket(s);
       x = match(e, mine);
       if (x < id_limit) return x;
-      s += e.z ? 12u : e.y ? 8u : e.x ? 4u : 0u;  // (a full one: its last slot, then the next bucket)
+      s += first_free_slot(e.x, e.y, e.z);  // (a full one: its last slot, then the next bucket)
     }
     uint32_t old = lds_cas(s, mine + id);
     x = old ^ mine;

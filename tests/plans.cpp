@@ -1,4 +1,5 @@
-// The library's plans, callable from Python (compiled and loaded by test_plans.py).
+// The library's plans and what else of it runs on the host, callable from Python (compiled and loaded
+// by test_plans.py).
 #include "tb_kernels.h"
 
 extern "C" {
@@ -32,5 +33,7 @@ bool fused_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
 bool fused_path(int64_t cand_stride, int64_t ref_stride, int R, int bits) {
   return tb::fused_path_takes(cand_stride, ref_stride, R, bits);
 }
+
+uint32_t first_free_slot(uint32_t x, uint32_t y, uint32_t z) { return tb::first_free_slot(x, y, z); }
 
 }  // extern "C"

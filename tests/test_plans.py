@@ -31,6 +31,8 @@ def plans(tmp_path_factory):
     lib.fused_plan.restype = lib.fused_path.restype = flag
     lib.fused_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, ctypes.POINTER(i64)]
     lib.fused_path.argtypes = [i64, i64, i32, i32]
+    lib.first_free_slot.restype = ctypes.c_uint32
+    lib.first_free_slot.argtypes = [ctypes.c_uint32] * 3
     return lib
 
 
@@ -100,3 +102,16 @@ def test_fused_tables_count_far_enough(plans):
                 assert load <= 0.75 and count_bits >= (4 if load <= 0.5 else 6), (shape, table)
                 seen[load > 0.5] += 1
     assert min(seen.values()) > 10, seen
+
+
+def test_an_insertion_skips_no_slot_it_saw_free(plans):
+    # `before` and `after`: how many slots of the bucket are taken, front to back, when a 16-byte read
+    # of it begins and ends.  Each word comes from some moment in between.  The key may be in any slot
+    # that was filled meanwhile, so the insertion has to begin at or before the first slot seen free.
+    for before in range(5):
+        for after in range(before, 5):
+            for seen in itertools.product((0, 7), repeat=4):
+                if all(seen[:before]) and not any(seen[after:]):
+                    free = [k for k in range(4) if not seen[k]]
+                    at = plans.first_free_slot(*seen[:3])
+                    assert at == 4 * (free[0] if free else 3), (before, after, seen)
