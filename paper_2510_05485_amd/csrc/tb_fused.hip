@@ -44,10 +44,6 @@
 #include "tb_kernels.h"
 #include "tb_score.h"
 
-#ifdef TB_TUNE
-#include <cstdio>
-#include <cstdlib>
-#endif
 // Phase time stamps for tuning builds only (-DTB_STAMPS), as in the hierarchical kernels.
 #ifdef TB_STAMPS
 __device__ unsigned long long tb_fused_stamps[8192 * 32];
@@ -774,10 +770,6 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
   p.set_words = (int(cand_stride) * p.words + 3) & ~3;
   const size_t sym_bytes = (size_t(blocks * kWave + (R + 1) * kPadSymbols) * 2 + 15) & ~size_t(15);
 
-  int want_passes = -1, want_lg = 0, want_threads = 0;
-#ifdef TB_TUNE
-  if (const char* e = getenv("TB_FUSED")) sscanf(e, "%d,%d,%d", &want_passes, &want_lg, &want_threads);
-#endif
   // workgroups a compute unit gets, and with it its share of LDS and wavefronts
   int resident = 1;
   while (resident < 32 && B > 256 * resident) resident *= 2;
@@ -797,19 +789,17 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
         while (waves < 16 && 2 * waves <= 32 / r && blocks > waves * (waves < 4 ? 1 : waves < 8 ? 2 : 4))
           waves *= 2;
       }
-      if (want_threads) waves = want_threads / kWave;
       while (waves < 16 && blocks > int64_t(kMaxBlocks) * waves) waves *= 2;
       p.blocks = int((blocks + waves - 1) / waves);
       p.threads = waves * kWave;
       for (int level = last_resort ? 2 : 0; level < (last_resort ? 3 : 2); ++level) {
-        if (level == 1 && r >= 4 && R > 2 && want_passes < 0) continue;  // (fewer workgroups first)
+        if (level == 1 && r >= 4 && R > 2) continue;  // (fewer workgroups first)
         for (int passes = 0; passes < 4; ++passes) {
           int orders;
-          if (want_passes >= 0 && passes != want_passes) continue;
           if (!set_passes(passes, N, bits, plan, &orders)) continue;
           // (1561 x 283 with three references 19.5 us, in pairs 17.2)
-          if (passes == 1 && r == 8 && R == 3 && N > 2 && want_passes < 0) continue;
-          if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2) && want_passes < 0) continue;
+          if (passes == 1 && r == 8 && R == 3 && N > 2) continue;
+          if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2)) continue;
           const int64_t entries = orders * cand_stride;
           const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
           int lg_min = 6;
@@ -823,14 +813,10 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           while (32 - widest + lg_min - 2 - p.id_bits < (level < 2 ? 4 : 6)) ++lg_min;
           int lg = lg_min;  // (a larger table than this costs more to clear than it saves)
           while ((int64_t(1) << lg) < (r == 1 ? 6 : 4) * entries) ++lg;
-          if (want_lg) {
-            if (!last_resort || want_lg < lg_min) continue;
-            lg = lg_min = want_lg;
-          }
           for (; lg >= lg_min; --lg) {
             const size_t front = (size_t(4) << lg) + size_t(rouge ? 1 : orders) * p.set_words * 4;
             p.lds_bytes = front + sym_bytes + kSumsBytes;
-            if (p.lds_bytes > size_t(kLdsBudget) / (want_lg ? 1 : r)) continue;
+            if (p.lds_bytes > size_t(kLdsBudget) / r) continue;
             p.log2_slots = lg;
             p.table_and_counters = int(front / 16);
             p.off_sym = uint32_t(front);
@@ -875,12 +861,6 @@ hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs
   const int by_lds = int(size_t(kLdsBudget) / plan.lds_bytes);
   const int resident = 256 * (by_threads < by_lds ? by_threads : (by_lds < 1 ? 1 : by_lds));
   a.progress_priority = pb.B <= 2 * resident ? 1 : 0;
-#ifdef TB_TUNE
-  if (const char* e = getenv("TB_PRIO")) a.progress_priority = atoi(e);
-  if (getenv("TB_PLAN"))
-    fprintf(stderr, "fused cut %x lg %d threads %d blocks %d keep %d lds %zu prio %d\n", plan.pass_ends,
-            plan.log2_slots, plan.threads, plan.blocks, plan.keep, plan.lds_bytes, a.progress_priority);
-#endif
   if (plan.blocks <= 1) return launch_blocks<1>(a, plan, s);
   if (plan.blocks <= 2) return launch_blocks<2>(a, plan, s);
   if (plan.blocks <= 3) return launch_blocks<3>(a, plan, s);
