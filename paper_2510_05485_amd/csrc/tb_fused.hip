@@ -797,8 +797,15 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
         for (int passes = 0; passes < 4; ++passes) {
           int orders;
           if (!set_passes(passes, N, bits, plan, &orders)) continue;
-          // (1561 x 283 with three references 19.5 us, in pairs 17.2)
-          if (passes == 1 && r == 8 && R == 3 && N > 2) continue;
+          // Three references, eight a unit: pairs instead of orders 2 to 4 in one table, which full rows
+          // fill to a third or more (us: 1561 groups of 283 tokens 20.1 -> 17.7, 1887 of 236 19.8 -> 18.2,
+          // 3435 of 276 31.9 -> 27.8).  Ragged rows fill it less, and the plan does not see lengths: over
+          // 140 shapes full or nearly full rows take 0.966 of the time (0.84 to 1.05), lengths down to a
+          // tenth 1.03 (0.88 to 1.11).  Not with more orders, whose pairs are more passes (1368 of 158, six
+          // orders, 15.9 -> 17.0).  One and two references gain on full rows (1561 of 283 with two 17.9 ->
+          // 15.8) what they lose on others, four and five do not differ, eight lose (1561 of 128 15.7 ->
+          // 16.7).
+          if (passes == 1 && r == 8 && R == 3 && N > 2 && N <= 4) continue;
           if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2)) continue;
           const int64_t entries = orders * cand_stride;
           const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
