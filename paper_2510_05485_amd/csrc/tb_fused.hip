@@ -701,6 +701,7 @@ hipError_t launch_blocks(const FusedArgs& a, const FusedPlan& plan, hipStream_t 
   return plan.keep ? launch_keep<BLOCKS, true>(a, plan, s) : launch_keep<BLOCKS, false>(a, plan, s);
 }
 
+constexpr size_t kLdsUnit = 1280;  // LDS is handed out in units of this size
 constexpr size_t kSumsBytes = 8 * 16 * 4 + 16 + kMaxSeqs * 4;
 
 }  // namespace
@@ -773,15 +774,19 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
   // workgroups a compute unit gets, and with it its share of LDS and wavefronts
   int resident = 1;
   while (resident < 32 && B > 256 * resident) resident *= 2;
-  // a little more than eight a unit, short rows: tables for sixteen would be half as large as there is
-  // room for (2398 x 227 20.8 -> 15.9 us, 2295 x 223 with two references 22.1 -> 17.5; with longer rows,
-  // more references or other numbers of groups the power of two is the better choice)
-  if (resident == 16 && B <= 2560 && cand_stride <= 256 && R <= 2) resident = 10;
+  // Nine or ten a unit: LDS for as many, not for sixteen, makes the tables emptier (2300 groups, us:
+  // one reference of 200 tokens 16.9 -> 14.5, of 500 27.2 -> 23.1; two of 256 25.6 -> 19.0; three of 200
+  // 23.9 -> 19.9).  It leaves a workgroup two wavefronts, where eight a unit have four: with more than
+  // eight blocks for each that costs more (two references of 500, 24 blocks: 32.0 -> 35.8), and so it does
+  // where counters of many references take the room (six of 97: 17.5 -> 18.5, four of 200 25.1 -> 28.2).
+  // Beyond 2560 groups ten a unit are two rounds (2700, two references of 200: 22.0 -> 26.3).
+  if (resident == 16 && B <= 2560 && R <= 3 && blocks <= 16) resident = B <= 2304 ? 9 : 10;
   // share of the slots that may be taken if every row is full, in twelfths; the last resort comes
   // after all numbers of workgroups have been tried with the others
   static const int kTwelfths[3] = {5, 6, 9};
   for (int last_resort = 0; last_resort < 2; ++last_resort) {
-    for (int r = resident; r >= 1; r /= 2) {
+    for (int r = resident; r >= 1; r = r == 9 || r == 10 ? 8 : r / 2) {
+      const size_t share = size_t(kLdsBudget) / r / kLdsUnit * kLdsUnit;
       int waves = 1;
       if (resident == 1) {  // the chip is not full: a wavefront for (nearly) each block
         while (waves < 16 && 4 * waves < 3 * blocks) waves *= 2;
@@ -804,8 +809,9 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           // tenth 1.03 (0.88 to 1.11).  Not with more orders, whose pairs are more passes (1368 of 158, six
           // orders, 15.9 -> 17.0).  One and two references gain on full rows (1561 of 283 with two 17.9 ->
           // 15.8) what they lose on others, four and five do not differ, eight lose (1561 of 128 15.7 ->
-          // 16.7).
-          if (passes == 1 && r == 8 && R == 3 && N > 2 && N <= 4) continue;
+          // 16.7).  Nine or ten a unit: for one and two references, too (2264 of 276 17.3 -> 14.8, 2130 of
+          // 234 with two 20.4 -> 18.7; 150 shapes 0.85 to 1.03x).
+          if (passes == 1 && (R == 3 || r > 8) && r >= 8 && r <= 10 && N > 2 && N <= 4) continue;
           if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2)) continue;
           const int64_t entries = orders * cand_stride;
           const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
@@ -823,7 +829,7 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           for (; lg >= lg_min; --lg) {
             const size_t front = (size_t(4) << lg) + size_t(rouge ? 1 : orders) * p.set_words * 4;
             p.lds_bytes = front + sym_bytes + kSumsBytes;
-            if (p.lds_bytes > size_t(kLdsBudget) / r) continue;
+            if (p.lds_bytes > share) continue;
             p.log2_slots = lg;
             p.table_and_counters = int(front / 16);
             p.off_sym = uint32_t(front);
