@@ -328,11 +328,17 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
 // that its plan covers.  (In a workspace that is larger than it needs.  The statistic group_distinct
 // is the size of the group's dictionary there, which only the kernels of the GLOBAL path build.)
 // The sorted-run kernels spread a group over the chip, the fused one gives it one compute unit, whose
-// time does not depend on the number of groups until each unit has one.  Measured (us, sorted runs /
-// fused): one reference of 8192 tokens, 32 groups 35.5 / 52.0, 48 46.6 / 52.2, 64 54.9 / 52.1; of 6200
-// tokens 32 29.8 / 39.2, 48 39.7 / 39.3; three of 4200 32 40.4 / 45.0, 48 54.5 / 45.4; seven of 1800
-// 32 36.8 / 30.3, 16 24.1 / -.  ROUGE-2, which needs the sorted runs of one order only: one reference of
-// 8192 64 25.2 / 30.4, 96 34.8 / 30.8; two of 6000 64 29.1 / 33.9, 96 40.2 / 34.2.
+// time does not depend on the number of groups until each unit has one; it grows mostly with the
+// candidate's tokens, while the sorted runs' grows with all tokens of the batch.  Both grow with the
+// number of orders, except that ROUGE-N needs the sorted runs of one order only.  Measured (us, sorted
+// runs / fused): one reference of 8192 tokens, 40 groups 43 / 46, 56 54 / 47; of 6200 32 29 / 36, 48 39 /
+// 36; two of 4200 16 26 / 32, 32 36 / 32; four of 3500 32 40 / 42, 40 47 / 42; eight of 1500 8 28 / 27, 16
+// 31 / 28; 16 of 1400 8 36 / 46, 24 55 / 46; 62 of 250 8 58 / 44.  ROUGE-1, 2 and 4: one reference of 8192
+// 64 18 / 19, 22 / 30, 23 / 46; three of 5000 48 29 / 28, 31 / 37, 30 / 49; 24 of 900 48 51 / 51, 59 /
+// 48, 55 / 46.  The lines are linear fits to 2300 such pairs, shapes of 12 400 to 24 500 positions with 1
+// to 62 references and 4 to 130 groups, one to six orders: on average 0.4 % (ROUGE 0.9 %) behind the
+// better kernel, more than a tenth behind in 1.4 % (3.4 %) of them.
+// Against the partitioned kernels, which take what the sorted runs do not: 32.
 bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
                  FusedPlan* plan) {
   const Problem& pb = c.pb;
@@ -340,8 +346,12 @@ bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats,
     if (cfg->force_path != TB_PATH_AUTO || cfg->workspace_tables) return false;
     if (stats && stats->group_distinct) return false;
     RunsPlan runs;
-    int few = 32;  // (against the partitioned kernels)
-    if (takes_runs(c, cfg, rouge, false, &runs)) few = rouge ? 80 : pb.R < 4 ? 52 - 6 * pb.R : 28;
+    int64_t few = 32;
+    if (takes_runs(c, cfg, rouge, false, &runs)) {
+      const int64_t refs = pb.R * pb.ref_stride;
+      few = rouge ? pb.N * pb.cand_stride / 110 + refs / 240 + 2 * pb.R - pb.N * pb.R - 60
+                  : pb.cand_stride / 150 + refs / 1000 - pb.R / 4 + 5 * pb.N - 29;
+    }
     if (c.plans.use_part && pb.B < few) return false;
   }
   return plan_fused(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.bits, rouge, plan);
