@@ -104,6 +104,20 @@ def test_fused_tables_count_far_enough(plans):
     assert min(seen.values()) > 10, seen
 
 
+def test_the_fused_plan_takes_what_the_path_accepts(plans):
+    # an AUTO or forced FUSED call on a shape that the layout calls fused must not be refused later
+    accepted = 0
+    strides = sorted({1, 2, 3, 63, 64, 65, 100, 255, 256, 300, 700, 1000, 1024, 1500, 2048, 3000, 3072, 4000,
+                      4095, 4096})
+    for R, cs, rs, bits in itertools.product((1, 2, 3, 4, 7, 12, 20, 40, 62, 63), strides,
+                                             strides + [8000, 11000], (1, 6, 8, 15, 16, 18, 20, 22, 26, 31)):
+        if plans.fused_path(cs, rs, R, bits):
+            accepted += 1
+            for N, B, rouge in ((1, 1, False), (4, 1, False), (8, 300, False), (4, 2400, False), (3, 9000, True)):
+                assert fused_table(plans, B, cs, rs, R, N, bits, rouge), (B, cs, rs, R, N, bits, rouge)
+    assert accepted > 5000
+
+
 def test_an_insertion_skips_no_slot_it_saw_free(plans):
     # `before` and `after`: how many slots of the bucket are taken, front to back, when a 16-byte read
     # of it begins and ends.  Each word comes from some moment in between.  The key may be in any slot
