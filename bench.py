@@ -6,17 +6,21 @@ synthetic batch already resident in HBM.  The default workload is the headline c
 (B=512 candidates of 1024 tokens, 4 references each, vocabulary 50257).  One JSON line is
 printed: `value` = sentences/s of the whole call, `roofline` = the dominant kernel's algorithmic
 bytes per launch over its HIP-event duration against the 8 TB/s HBM peak (plus its measured HBM
-traffic and instruction counts, parsed from the committed rocprofv3 summaries under profiles/),
-`passes` = every
-kernel of the path that ran, `global_path` = the staged pipeline's passes timed one by one,
-`achievable_hbm_GBps` = plain fill / read / copy kernels in the same run, `cpu_baseline` = the CPU
+traffic and instruction counts, parsed from the committed rocprofv3 summaries under profiles/ where
+these are of the kernels that ran, built from the same sources), `kernels` = what the call launched,
+`passes` = every kernel of the path that ran, `global_path` = the staged pipeline's passes timed one
+by one, `achievable_hbm_GBps` = plain fill / read / copy kernels in the same run, `cpu_baseline` = the CPU
 oracle on a bounded sample of the same workload.
 """
 from __future__ import annotations
 
 import argparse
+import functools
+import glob
+import hashlib
 import json
 import os
+import re
 import sys
 import time
 
@@ -39,7 +43,47 @@ def algorithmic_bytes(w, lay, N, token_bytes=4):
         "count_clip": 4 * sum(G) + stats,
         "finalize": stats + 4 * w.B * (1 + w.R) + 4 * w.B,
         "fused": 4 * T + 4 * w.B + stats,
+        "sorted runs": 4 * T + 4 * w.B + stats,
     }
+
+
+def kernel_names(fn, torch):
+    """Names of the library's kernels that `fn` launches, with their template arguments, as they stand
+    in the summaries under profiles/; None where the profiler does not run.  (To be called when all
+    timing is done: the profiler stays attached.)"""
+    try:
+        from torch.profiler import ProfilerActivity, profile
+        torch.cuda.synchronize()
+        with profile(activities=[ProfilerActivity.CUDA]) as p:
+            fn()
+            torch.cuda.synchronize()
+        names = []
+        for e in p.events():
+            m = re.match(r"(?:void )?(tb::.*)\(tb::.*\)$", e.name.replace("(anonymous namespace)::", ""))
+            if m and m.group(1) not in names:
+                names.append(m.group(1))
+        return names
+    except Exception:                  # noqa: BLE001 - a missing name must not take the line with it
+        return None
+
+
+def route_of(names, layout_path):
+    """Which kernels served a call: "fused", "sorted runs" or "global" (the staged kernels)."""
+    if names and any("fused_kernel" in n for n in names):
+        return "fused"
+    if names and any("runs_count_kernel" in n for n in names):
+        return "sorted runs"
+    return "global" if names else {1: "fused", 2: "global"}[layout_path]
+
+
+def source_digest():
+    """Of the kernels' sources without comments: says which build a profile is of."""
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2510_05485_amd", "csrc", "*"))):
+        if path.endswith((".hip", ".h")):
+            code = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(path).read(), flags=re.S)
+            h.update(" ".join(code.split()).encode())
+    return h.hexdigest()[:16]
 
 
 _SLEEP_CYCLES_PER_MS = None
@@ -155,7 +199,7 @@ def other_configs(skip, steps, torch, tb, syn, np, dev):
     8192 tokens, one reference each) in short form: sentences/s of the default path and
     the three main GLOBAL passes as fractions of the HBM peak.  A failure is recorded, not
     raised: it must not take the headline line with it."""
-    rows = []
+    rows, calls = [], []
     for k in (1, 2, 3, 4, 5, "long"):   # "long": the long-generation workload of --long-form 8192
         if k == skip:
             continue
@@ -173,11 +217,12 @@ def other_configs(skip, steps, torch, tb, syn, np, dev):
             lay = tb.tensorbleu_workspace_layout(w.B, w.R, cs, rs, cfg)
             ws = tb.allocate_workspace(w.B, w.R, cs, rs, cfg, dev)
             out = torch.empty(w.B, dtype=torch.float32, device=dev)
-            fn = lambda: tb.tensorbleu_sentence(cand, cl, refs, rl, cfg, out=out, workspace=ws)
+            fn = functools.partial(tb.tensorbleu_sentence, cand, cl, refs, rl, cfg, out=out,
+                                   workspace=ws)
             for _ in range(5):
                 fn()
             ms = time_region(fn, steps, torch)
-            row = {"workload": w.name, "path": {1: "fused", 2: "global"}[lay.path],
+            row = {"workload": w.name, "path": None,
                    "us": round(ms * 1e3, 2), "sentences_per_s": round(w.B / (ms * 1e-3), 1)}
             if lay.global_ok:
                 gcfg = mk("global")
@@ -197,22 +242,12 @@ def other_configs(skip, steps, torch, tb, syn, np, dev):
                     row[name + "_frac_hbm"] = round(alg[name] / (t_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS,
                                                     4)
             rows.append(row)
-            del cand, refs, ws
+            calls.append((row, fn, lay.path))
         except Exception as err:       # noqa: BLE001 - reported in the output line
             rows.append({"config": k, "error": repr(err)})
-    return rows
+    return rows, calls
 
 
-# Which kernels implement which pass (names as they appear in the rocprofv3 summaries).
-PASS_KERNELS = {
-    "fused": ("fused_kernel",),
-    "pack": ("pack_kernel",),
-    "dictionary": ("hier_dictionary_kernel", "dictionary_narrow_kernel", "dictionary_wide_kernel",
-                   "part_dictionary_kernel", "big_dictionary_kernel"),
-    "count_clip": ("hier_count_kernel", "count_fields_kernel", "count_clip_kernel",
-                   "part_count_kernel", "big_count_kernel"),
-    "finalize": ("sentence_score_kernel",),
-}
 NUM_CUS, CLOCK_GHZ = 256, 2.4
 # Issue rates measured with micro-benchmarks on this GPU (wavefront instructions per CU-cycle at
 # full occupancy): vector ALU alone, scalar ALU alone (one scalar unit per CU), both kinds mixed.
@@ -253,35 +288,43 @@ def paper_grid(steps, torch, tb, syn, np, dev):
     return rows
 
 
-def profile_counters(workload, pass_name):
-    """Counters of the kernel that implements `pass_name`, read from the committed rocprofv3
-    summary profiles/pmc_<workload>.md (sections '## `kernel`' with '* COUNTER: value' lines;
-    values are means per launch).  Returns (kernel name, {counter: value}) or (None, {}) when no
-    summary exists for the workload or the kernel."""
+def profile_counters(workload, names):
+    """Counters of one launch of each of the kernels `names`, summed, read from the committed rocprofv3
+    summary profiles/pmc_<workload>.md (a line 'kernel sources: <digest>', sections '## `kernel`' with
+    '* COUNTER: value' lines; values are means per launch).  Returns ({counter: value}, where they come
+    from) or ({}, why there are none): the kernels have to stand there with their full names, and the
+    summary has to be of the present sources."""
     path = os.path.join(ROOT, "profiles", f"pmc_{workload}.md")
     if not os.path.exists(path):
-        return None, {}
-    best = (None, {})
-    kernel, counters = None, {}
-    for line in open(path).read().splitlines() + ["## `end`"]:
+        return {}, "no rocprofv3 summary committed for this workload"
+    if not names:
+        return {}, "which kernels ran is not known"
+    text = open(path).read()
+    if f"kernel sources: {source_digest()}" not in text:
+        return {}, f"profiles/pmc_{workload}.md is of other kernel sources"
+    sections, kernel = {}, None
+    for line in text.splitlines():
         if line.startswith("## `"):
-            if kernel and any(k in kernel for k in PASS_KERNELS[pass_name]) and \
-                    counters.get("SQ_WAVES", 0) >= best[1].get("SQ_WAVES", -1):
-                best = (kernel, counters)          # several instantiations: the largest launch
-            kernel, counters = line[4:].rstrip("`"), {}
+            kernel = line[4:].rstrip("`")
+            sections[kernel] = {}
         elif line.startswith("* ") and ":" in line and kernel:
             name, value = line[2:].split(":", 1)
-            if "traffic" in name:                  # "... = 10.89 MB"
-                try:
-                    counters["hbm_traffic_bytes"] = float(value.split("=")[-1].split()[0]) * 1e6
-                except ValueError:
-                    pass
-            else:
-                try:
-                    counters[name.strip()] = float(value.replace(",", ""))
-                except ValueError:
-                    pass
-    return best
+            try:
+                if "traffic" in name:                  # "... = 10.89 MB"
+                    sections[kernel]["hbm_traffic_bytes"] = \
+                        float(value.split("=")[-1].split()[0]) * 1e6
+                else:
+                    sections[kernel][name.strip()] = float(value.replace(",", ""))
+            except ValueError:
+                pass
+    missing = [n for n in names if n not in sections]
+    if missing:
+        return {}, f"profiles/pmc_{workload}.md does not hold {', '.join(missing)}"
+    counters = {}
+    for n in names:
+        for k, v in sections[n].items():
+            counters[k] = counters.get(k, 0.0) + v
+    return counters, f"profiles/pmc_{workload}.md ({' + '.join(names)})"
 
 
 def issue_model(counters, kernel_us):
@@ -323,6 +366,8 @@ def main():
                     help="also time the sizes the paper tabulates (L = 256 and 1024, B = 16..512)")
     ap.add_argument("--no-global-passes", action="store_true",
                     help="skip the per-pass timing of the GLOBAL path")
+    ap.add_argument("--no-kernel-names", action="store_true",
+                    help="do not ask torch's profiler which kernels ran (for runs under rocprofv3)")
     ap.add_argument("--calib-copy-mib", type=int, default=0,
                     help="launch one plain device copy of this many MiB first (a known-size "
                          "reference for the FETCH_SIZE / WRITE_SIZE counters)")
@@ -368,10 +413,11 @@ def main():
 
     cfg = config(a.path)
     lay = tb.tensorbleu_workspace_layout(w.B, w.R, cs, rs, cfg)
-    path = {1: "fused", 2: "global"}[lay.path]
     ws = tb.allocate_workspace(w.B, w.R, cs, rs, cfg, dev)
     out = torch.empty(w.B, dtype=torch.float32, device=dev)
     stats = tb.Stats.allocate(w.B, N, dev, corpus_stats=False)
+    if lay.path != tb.binding.PATHS["fused"]:
+        stats.group_distinct = None     # (asked for, it keeps long shapes off the fused kernel)
 
     def step():
         tb.tensorbleu_sentence(cand, cl, refs, rl, cfg, out=out, stats=stats, workspace=ws)
@@ -404,9 +450,9 @@ def main():
         if lay.global_ok else None
     alg = algorithmic_bytes(w, glay or lay, N, 8 if a.int64 else 4)
     global_section = None
-    if glay is not None and not (a.no_global_passes and path != "global"):
+    if glay is not None and not (a.no_global_passes and a.path != "global"):
         gcfg = config("global")
-        gws = ws if path == "global" else tb.allocate_workspace(w.B, w.R, cs, rs, gcfg, dev)
+        gws = tb.allocate_workspace(w.B, w.R, cs, rs, gcfg, dev)
         gstages = [
             ("pack", lambda: tb.tensorbleu_pack(cand, cl, refs, rl, gcfg, gws, stats)),
             ("dictionary", lambda: tb.tensorbleu_dictionary(cl, rl, cs, rs, gcfg, gws, stats)),
@@ -422,23 +468,7 @@ def main():
         g_ms = time_region(gstep, a.steps, torch)
         global_section = {"ms_per_step": round(g_ms, 5),
                           "sentences_per_s": round(w.B / (g_ms * 1e-3), 1), "passes": grows}
-    if path == "global":
-        passes = global_section["passes"]
-    else:
-        passes = time_stages([("fused", step)], alg)
-    dom = max(passes, key=lambda p: p["us"])
-    prof_kernel, counters = profile_counters(w.name, dom["kernel"])
-    traffic = a.traffic_bytes if a.traffic_bytes is not None else counters.get("hbm_traffic_bytes")
-    roofline = {"bound": "hbm", "kernel": dom["kernel"], "achieved": dom["GBps"],
-                "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": dom["frac_hbm"],
-                "traffic": traffic,
-                "traffic_source": (f"profiles/pmc_{w.name}.md ({prof_kernel})" if traffic and
-                                   a.traffic_bytes is None else
-                                   "command line" if traffic else
-                                   "no rocprofv3 summary committed for this workload")}
-    model = issue_model(counters, dom["us"])
-    if model is not None:
-        roofline["instruction_issue"] = model
+    whole_call = time_stages([("fused", step)], alg)
 
     # the paper's protocol beside it (its Section 4.2): mean wall-clock time of 5 single calls,
     # each synchronised on its own (launch and synchronisation latency included)
@@ -452,22 +482,7 @@ def main():
     paper_protocol = {"ms_mean_of_5_synchronised_calls": round(sum(runs) / 5, 5),
                       "sentences_per_s": round(w.B / (sum(runs) / 5 * 1e-3), 1)}
 
-    result = {
-        "metric": "per-sentence BLEU sentences/sec at B=512, L=1024; % HBM roofline",
-        "value": round(w.B / (ms * 1e-3), 1), "unit": "sentences/s", "n_gpus": 1,
-        "steps": a.steps, "warmup": a.warmup, "ms_per_step": round(ms, 5),
-        "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
-        "dtype": ("u32 keys / u16 counts / f32 scores" if path == "fused"
-                  else "u64 keys / u16 counts / f32 scores") + (" (int64 ids)" if a.int64 else ""),
-        "data": "synthetic",
-        "config": {"workload": w.name, "B": w.B, "R": w.R, "cand_stride": cs, "ref_stride": rs,
-                   "vocab": w.vocab, "max_n": N, "smoothing": run.smoothing, "path": path,
-                   "tokens": w.tokens},
-        "ms_per_step_events": round(ev_ms, 5), "ms_per_step_wall": round(wall_ms, 5),
-        "roofline": roofline, "passes": passes, "paper_protocol": paper_protocol,
-    }
-    if global_section is not None and path != "global":
-        result["global_path"] = global_section
+    result, calls = {}, []
     if a.paper_grid:
         result["paper_grid"] = paper_grid(a.steps, torch, tb, syn, np, dev)
     if a.rouge:
@@ -483,11 +498,51 @@ def main():
                            "sentences_per_s": round(w.B / (r_ms * 1e-3), 1),
                            "frac_hbm": round(alg["fused"] / (r_ms * 1e-3) / 1e9 / HBM_PEAK_GBPS, 4)}
     if not a.no_other_configs:
-        result["other_configs"] = other_configs("long" if (a.long_form, a.long_batch) == (8192, 128) else
+        result["other_configs"], calls = other_configs("long" if (a.long_form, a.long_batch) == (8192, 128) else
                                                 0 if a.long_form else a.config, min(a.steps, 100),
                                                 torch, tb, syn, np, dev)
     if not a.no_hbm_ceiling:
         result["achievable_hbm_GBps"] = achievable_hbm(torch, dev)
+
+    # which kernels ran (all timing is done)
+    names_of = (lambda fn: None) if a.no_kernel_names else (lambda fn: kernel_names(fn, torch))
+    names = names_of(step)
+    path = route_of(names, lay.path)
+    if path == "global" and global_section is not None:
+        passes = global_section["passes"]
+        dom = max(passes, key=lambda p: p["us"])
+        dom_names = names_of(dict(gstages)[dom["kernel"]])
+    else:
+        passes, dom_names = whole_call, names
+        dom = passes[0]
+        dom["kernel"] = path
+    for row, fn, layout_path in calls:
+        row["path"] = route_of(names_of(fn), layout_path)
+    counters, source = profile_counters(w.name, dom_names)
+    roofline = {"bound": "hbm", "kernel": dom["kernel"], "achieved": dom["GBps"],
+                "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": dom["frac_hbm"],
+                "traffic": a.traffic_bytes if a.traffic_bytes is not None else
+                counters.get("hbm_traffic_bytes"),
+                "traffic_source": "command line" if a.traffic_bytes is not None else source}
+    model = issue_model(counters, dom["us"])
+    if model is not None:
+        roofline["instruction_issue"] = model
+    result = {
+        "metric": "per-sentence BLEU sentences/sec at B=512, L=1024; % HBM roofline",
+        "value": round(w.B / (ms * 1e-3), 1), "unit": "sentences/s", "n_gpus": 1,
+        "steps": a.steps, "warmup": a.warmup, "ms_per_step": round(ms, 5),
+        "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
+        "dtype": ("u32 keys / u16 counts / f32 scores" if path == "fused"
+                  else "u64 keys / u16 counts / f32 scores") + (" (int64 ids)" if a.int64 else ""),
+        "data": "synthetic",
+        "config": {"workload": w.name, "B": w.B, "R": w.R, "cand_stride": cs, "ref_stride": rs,
+                   "vocab": w.vocab, "max_n": N, "smoothing": run.smoothing, "path": path,
+                   "tokens": w.tokens},
+        "ms_per_step_events": round(ev_ms, 5), "ms_per_step_wall": round(wall_ms, 5),
+        "roofline": roofline, "kernels": names, "passes": passes, "paper_protocol": paper_protocol,
+        **({"global_path": global_section} if global_section is not None and path != "global" else {}),
+        **result,
+    }
     if not a.no_cpu_baseline:
         step()
         torch.cuda.synchronize()
