@@ -166,9 +166,9 @@ struct SymbolTable {
     return make_uint4(q.x, q.y, q.z, q.w);
   }
   // Id of the key, or a value of at least id_limit: one 16-byte request answers unless the bucket
-  // is full and does not hold the key.  live: the lane has a key (the others ask like it, and their
-  // sequences must not be taken for one that was too long).
-  __device__ __forceinline__ uint32_t find(uint32_t h, bool live) const {
+  // is full and does not hold the key.  dead: the sign bit for a lane without a key, else 0 (such
+  // lanes ask like the others, and their sequences must not be taken for one that was too long).
+  __device__ __forceinline__ uint32_t find(uint32_t h, uint32_t dead) const {
     uint32_t s = (h >> home_shift) & bucket_mask;
     const uint32_t remainder = h << log2_buckets;
     uint32_t mine = remainder + id_limit;
@@ -181,7 +181,7 @@ struct SymbolTable {
         e = bucket(s);
         x = match(e, mine);
       } while (min(x, e.w) >= id_limit);
-      if (__builtin_expect(live && mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
+      if (__builtin_expect((mine ^ dead) == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
     }
     return x;
   }
@@ -372,7 +372,8 @@ void fused_kernel(FusedArgs by_value) {
     each_block(i, my_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       const int f = sequence_of(b);
       // (a lane without a token asks like the others; its sign bit then hides the answer)
-      const uint32_t x = table.find(uint32_t(v) * table.multiplier, v >= 0) | (uint32_t(v) & 0x80000000u);
+      const uint32_t dead = uint32_t(v) & 0x80000000u;
+      const uint32_t x = table.find(uint32_t(v) * table.multiplier, dead) | dead;
       const bool hit = x < id_limit;
       const int32_t got = hit ? int32_t(x) : -1;
       if (hit && (!ROUGE || N == 1))
@@ -521,8 +522,8 @@ void fused_kernel(FusedArgs by_value) {
         const int32_t key = int32_t(uint32_t(cur) << id_bits) | int32_t(*lds<int16_t>(next));
         cur = -1;
         if (!__builtin_amdgcn_ballot_w64(key >= 0)) break;  // uniform: nothing to extend
-        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag, key >= 0) |
-                           (uint32_t(key) & 0x80000000u);
+        const uint32_t dead = uint32_t(key) & 0x80000000u;
+        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag, dead) | dead;
         const bool hit = x < id_limit;
         cur = hit ? int32_t(x) : -1;
         if (hit && (!ROUGE || n == N)) lds_add(count + __umul24(x, W4), addend);
