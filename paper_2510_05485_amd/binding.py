@@ -115,7 +115,8 @@ _host = None
 
 def native():
     """The native marshalling module (built with the library; raises if it has not been).  Its
-    functions return None, having done nothing, for what they leave to the code here."""
+    functions return None for what they leave to the code here (and have then written nothing but
+    fields of the config that the code here sets again)."""
     global _host
     if _host is None:
         load_library()

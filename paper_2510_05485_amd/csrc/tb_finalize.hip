@@ -34,7 +34,8 @@ __global__ __launch_bounds__(256) void sentence_score_kernel(FinalArgs a) {
               a.sp.out_bf16);
 }
 
-// Sum over the wavefront of a value in [0, 2^50): two 32-bit DPP scans, no LDS round trips.
+// Sum over the wavefront of a value in [0, 2^49) (its upper part then is below 2^25, 64 of these below
+// 2^31): two 32-bit DPP scans, no LDS round trips.
 __device__ __forceinline__ long long wave_sum64(long long v) {
   const int lo = wave_sum(int(v & 0xFFFFFF));
   const int hi = wave_sum(int(v >> 24));

@@ -29,7 +29,7 @@
 //     its share (has_room).
 //
 // Measured (us a call, before on the partitioned kernels -> now): one text of 262 144 tokens with its
-// reference 110.7 -> 32.9 (sorting 14, counting 15, score 3); 16 groups of two times 8192 36 -> 22; 100 of
+// reference 110.7 -> 33 (sorting 12.5, counting 17.6, score 3); 16 groups of two times 8192 36 -> 22; 100 of
 // two times 20 000 276 -> 137 (sorting 55, counting 80); 300 of nine times 4096 1111 -> 354; 20 of nine
 // times 4096 with 18-bit tokens 147 -> 48; ROUGE-2 of one text of 100 000 80 -> 20.  The number of
 // partitions is as many as the tables need, filled up to whole rounds of 512 workgroups (a power of two
@@ -72,7 +72,8 @@ struct RunsArgs {
 };
 
 // (Both halves are multiplied: an exclusive or of shifted halves gives the same hash to all n-grams
-// whose frequent tokens, small numbers, cancel; look-ups then took 9 us of a workgroup's 21.)
+// whose frequent tokens, small numbers, cancel; the call on one text of 262 144 tokens then took 52.6 us
+// instead of 38.9.)
 __device__ __forceinline__ uint32_t run_hash(uint64_t key) {
   const uint32_t h = uint32_t(key) * 0x9E3779B1u + uint32_t(key >> 32) * 0xC2B2AE3Du;
   return h ^ (h >> 15);
@@ -100,9 +101,10 @@ __device__ __forceinline__ int chunk_base(const RunsArgs& a, const Chunk& k) {
 
 // ITEMS: positions per thread.  68 KB of LDS with four: two workgroups on a compute unit.
 //
-// Bound by latency: 2.5 of a workgroup's 6.6 us pass until the tokens are there, and six barriers
-// follow.  Where there are more workgroups than the chip holds, each therefore takes several orders of
-// its chunk (100 groups of two times 20 000 tokens: 63 us, then 55).
+// Bound by latency: 1.4 to 2.6 of a workgroup's 5.7 us pass until the tokens are there, and six barriers
+// follow (time stamps of each step, one text of 262 144 tokens).  Where there are more workgroups than
+// the chip holds, each therefore takes several orders of its chunk (100 groups of two times 20 000
+// tokens: 63 us, then 55).
 template <int ITEMS>
 __global__ __launch_bounds__(kRunThreads, 8) void runs_sort_kernel(RunsArgs a) {
   constexpr int kChunk = ITEMS * kRunThreads;
@@ -262,6 +264,9 @@ __global__ __launch_bounds__(kRunThreads, 8) void runs_sort_kernel(RunsArgs a) {
   }
 }
 
+// Bound by latency, too: 4.3 of a workgroup's 11.7 us until its runs' places and first members are there,
+// 3.8 (at most 7.9) for the candidate's entries, 1.4 for the look-ups, 1.5 for the sweep (the same time
+// stamps).
 template <int CHUNK>
 __global__ __launch_bounds__(kRunThreads, 8) void runs_count_kernel(RunsArgs a) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
