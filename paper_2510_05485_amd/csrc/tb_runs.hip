@@ -493,7 +493,7 @@ hipError_t launch_items(const RunsArgs& a, const RunsPlan& plan, hipStream_t s) 
 // Whether a table (or part of one) of `slots` slots holds what a hash sends to it of `entries` distinct
 // n-grams dealt to `tables` of them.  The number is binomial; that it reaches k is less likely than
 // exp(k - mean - k log(k / mean)) (Chernoff), here exp(-40): with 2^31 tables in a call, 1e-8.  Half full
-// on average is room enough from 256 slots on; 128 may expect 52, 64 may expect 16.
+// on average is room enough from 256 slots on; 128 may expect 51, 64 may expect 16.
 bool has_room(int64_t entries, int64_t tables, int64_t slots) {
   const double mean = double(entries) / double(tables), k = double(slots);
   return mean < k && k - mean - k * std::log(k / mean) <= -40.0;
