@@ -183,16 +183,20 @@ struct RefRows {
   int64_t row0;
   int used;
 };
+// (CSR, from the span's offsets; *odd: it had to be clamped, or is empty)
+__device__ __forceinline__ RefRows listed_rows(int64_t b, int64_t e, int64_t rows, int R, bool* odd) {
+  const int64_t row0 = min(max(b, int64_t(0)), max(rows, int64_t(0)));
+  const int64_t used = min(min(max(e - row0, int64_t(0)), int64_t(R)), rows - row0);
+  *odd = row0 != b || used != e - b || used < 1;
+  return {row0, int(max(used, int64_t(0)))};
+}
 __device__ __forceinline__ RefRows ref_rows(const Problem& pb, int g, bool flag = false) {
   RefRows r;
   if (pb.ref_offsets) {
-    const int64_t b = uniform_load(pb.ref_offsets, g), e = uniform_load(pb.ref_offsets, g + 1);
-    const int64_t row0 = min(max(b, int64_t(0)), max(pb.ref_rows, int64_t(0)));
-    const int64_t used = min(min(max(e - row0, int64_t(0)), int64_t(pb.R)), pb.ref_rows - row0);
-    if (flag && (row0 != b || used != e - b || used < 1) && pb.status)
-      atomicOr(pb.status, TB_DEV_LENGTH_RANGE);
-    r.row0 = row0;
-    r.used = int(max(used, int64_t(0)));
+    bool odd;
+    r = listed_rows(uniform_load(pb.ref_offsets, g), uniform_load(pb.ref_offsets, g + 1), pb.ref_rows,
+                    pb.R, &odd);
+    if (flag && odd && pb.status) atomicOr(pb.status, TB_DEV_LENGTH_RANGE);
     return r;
   }
   r.row0 = int64_t(g) * pb.R;

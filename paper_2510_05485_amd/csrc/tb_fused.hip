@@ -16,6 +16,14 @@
 //     candidate position enters its n-grams one order after the other (an id is known as soon as
 //     the entry is), a reference position looks its n-grams up until one is absent (a candidate
 //     n-gram extends only prefixes the candidate contains).  No barrier lies between the orders.
+//   * Implied n-grams.  An id is the candidate position of one occurrence.  The n-gram that goes on
+//     like the candidate does there (the prefix's id p, then the symbol at p + n - 1) takes the same id
+//     without an entry; only other continuations are entered and looked up.  Every (n-1)-gram but the
+//     candidate's last has one implied continuation, so the entries of orders lo..hi are at most the
+//     distinct n-grams of order hi less those of order lo - 1, plus one an order: never more than
+//     candidate positions, where four orders used to enter up to four times as many.  Tables take a
+//     quarter of the room or fill a quarter as far, from order 3 on few lanes enter anything at all
+//     (1024 x 2048 43.8 -> 35.7 us, 128 x 8192 46.5 -> 37.5, 4096 x 2048 with two references 143 -> 127).
 //   * Entries that carry the id.  A table entry is one 32-bit word (remainder | probe count | id).
 //     The key is multiplied by an odd constant modulo 2^key_bits (a bijection); the top bits of the
 //     product pick the home bucket and the remaining bits are stored.  Bucket and probe count give
@@ -65,29 +73,35 @@ namespace {
 constexpr int kMaxSeqs = kWave;     // candidate + references, one lane each
 constexpr int kPadSymbols = 8;      // absent symbols behind every sequence: orders up to 8
 constexpr int kMaxBlocks = 24;      // per wavefront
+constexpr int kRegisterArgs = 56;   // bytes of the arguments before the struct
 
+// The eight plain arguments before it come in scalar registers (the build asks for 56 bytes), so that
+// the lengths are requested at once; what else is read before the tokens arrive stands first here and
+// is read in one request meanwhile.  Before, the prologue waited for the argument segment six times in
+// turn: 16 x 256 6.74 -> 6.64 us, 39 x 336 with two references, two orders, 6.31 -> 6.21.
 struct FusedArgs {
-  Problem pb;
-  StatPtrs st;
-  ScoreParams sp;
-  void* out;               // per-sentence scores (fp32 or bfloat16: sp.out_bf16), or null
-  void* rouge_prf;         // ROUGE-N (order N = pb.N): [B, 3] (same type)
-  int32_t* rouge_overlap;  // [B, R] or null
-  int32_t* rouge_best;     // [B] or null
-  float beta2;             // beta squared
+  int32_t* status;         // may be null
+  int vocab;
+  int table_and_counters;  // 16-byte units of table and counters together
+  uint32_t off_sym, off_sums;
+  int progress_priority;   // 1: wavefronts of a workgroup that is behind get the higher priority
+  int log2_slots;
+  int id_bits;             // ids (candidate positions) are below 2^id_bits
+  int64_t ref_rows;        // CSR lists: number of reference rows
   uint32_t pass_ends;      // bits 4(n - 1)..: last order of the pass that starts with order n >= 2;
                            // bits 0..3: 1 if order 1 is a pass of its own, else 0
-  int cand_stride, ref_stride;
-  int log2_slots, log2_waves;
-  int id_bits;             // ids (candidate positions) are below 2^id_bits
   int first_payload, first_key_bits;  // payload bits and key bits (order within the pass | payload)
                                       // of the table that order 1 is in
   int later_payload, later_key_bits;  // ... of the passes behind it
   int words;               // 32-bit counter words per id; field 0: candidate, field 1 + j: reference j
   int set_words;           // counter words of one order
-  int table_and_counters;  // 16-byte units of table and counters together
-  uint32_t off_sym, off_sums;
-  int progress_priority;   // 1: wavefronts of a workgroup that is behind get the higher priority
+  float beta2;             // ROUGE-N: beta squared
+  StatPtrs st;
+  ScoreParams sp;
+  void* out;               // per-sentence scores (fp32 or bfloat16: sp.out_bf16), or null
+  void* rouge_prf;         // ROUGE-N of order N: [B, 3] (same type)
+  int32_t* rouge_overlap;  // [B, R] or null
+  int32_t* rouge_best;     // [B] or null
 };
 
 // LDS by byte offset.  (The kernel has dynamic LDS only, which starts at offset 0; going through the
@@ -112,6 +126,7 @@ __device__ __forceinline__ void lds_add(uint32_t at, uint32_t v) {
 // The table of one pass, at LDS offset 0: buckets of four slots, filled front to back.  0: free slot;
 // probe counts start at 1, so no entry is 0 (nor below id_limit).
 struct SymbolTable {
+  __device__ __forceinline__ uint32_t home(uint32_t h) const { return (h >> home_shift) & bucket_mask; }
   uint32_t bucket_mask;  // byte offsets of buckets
   int home_shift;        // 30 - log2(slots)
   int log2_buckets;
@@ -127,20 +142,18 @@ struct SymbolTable {
   // Id of the key with product h, entered as `id` where it is not there: tries the slots of its
   // buckets one after the other.  Ends: the odd step visits every bucket, the plan keeps the table
   // at most 3/4 full, and only this workgroup writes it.
-  // LOOK_FIRST: the home bucket is read before the first compare-and-swap; it may hold the key, and
-  // tells the first free slot.  Without it a wavefront swaps as often as its slowest lane finds slots
-  // taken, which in a table that fills up to the half is five or six times.  Plans with few orders in
-  // a table (KEEP) have such tables: 128 x 8192 52.2 -> 48.6 us, 128 x 5000 31.1 -> 29.5, 1024 x 2048
-  // 45.8 -> 43.8, 4096 x 2048 with two references 153 -> 148.  In the emptier tables of the other plans
-  // the read costs up to 5 % (ROUGE-2 of 512 x 512 with three 9.4 -> 9.9).
-  template <bool LOOK_FIRST>
-  __device__ __forceinline__ uint32_t claim(uint32_t h, uint32_t id) const {
-    uint32_t s = (h >> home_shift) & bucket_mask;
+  // SEEN: the home bucket has been read (e).  It may hold the key, and tells the first free slot.
+  // Without it a wavefront swaps as often as its slowest lane finds slots taken.  Plans with many blocks
+  // a wavefront have tables that fill up to the half, where that is often (2041 x 1088 40.4 -> 38.7 us);
+  // in the emptier tables of the others the read costs more than it saves (ROUGE-2 of 512 x 512 with
+  // three references 9.6 -> 10.2, 1000 x 96 10.4 -> 10.5).
+  template <bool SEEN>
+  __device__ __forceinline__ uint32_t claim(uint32_t h, uint32_t id, const uint4& e) const {
+    uint32_t s = home(h);
     const uint32_t remainder = h << log2_buckets;
     uint32_t mine = remainder + id_limit;
     uint32_t x;
-    if (LOOK_FIRST) {
-      const uint4 e = bucket(s);
+    if (SEEN) {
       x = match(e, mine);
       if (x < id_limit) return x;
       s += first_free_slot(e.x, e.y, e.z);  // (a full one: its last slot, then the next bucket)
@@ -168,14 +181,16 @@ struct SymbolTable {
     return make_uint4(q.x, q.y, q.z, q.w);
   }
   // Id of the key, or a value of at least id_limit: one 16-byte request answers unless the bucket
-  // is full and does not hold the key.  dead: the sign bit for a lane without a key, else 0 (such
-  // lanes ask like the others, and their sequences must not be taken for one that was too long).
-  __device__ __forceinline__ uint32_t find(uint32_t h, uint32_t dead) const {
-    uint32_t s = (h >> home_shift) & bucket_mask;
+  // is full and does not hold the key.  known: it is `id` (the lane asks all the same, which is less
+  // than a branch, but not for a second bucket).  dead: the sign bit for a lane without a key, else 0
+  // (such lanes ask like the others, and their sequences must not be taken for one that was too long).
+  __device__ __forceinline__ uint32_t find(uint32_t h, uint32_t dead, bool known, uint32_t id) const {
+    uint32_t s = home(h);
     const uint32_t remainder = h << log2_buckets;
     uint32_t mine = remainder + id_limit;
     uint4 e = bucket(s);
     uint32_t x = match(e, mine);
+    x = known ? id : x;
     if (min(x, e.w) >= id_limit) {
       do {
         s = (s + step(remainder)) & bucket_mask;
@@ -185,7 +200,7 @@ struct SymbolTable {
       } while (min(x, e.w) >= id_limit);
       if (__builtin_expect((mine ^ dead) == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
     }
-    return x;
+    return x | dead;
   }
 };
 
@@ -195,51 +210,70 @@ struct SymbolTable {
 // SIMD need at most 80 scalar registers each on this hardware.)
 template <int BLOCKS, bool KEEP, bool WIDE, bool ROUGE>
 __global__ __launch_bounds__(1024, 8) __attribute__((amdgpu_num_sgpr(80)))
-void fused_kernel(FusedArgs by_value) {
-  // The arguments are read through the kernel-argument segment where they are used: loads of a
+void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
+                  const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
+                  uint32_t cand_shape, uint32_t ref_shape, FusedArgs by_value) {
+  // The struct is read through the kernel-argument segment where its fields are used: loads of a
   // by-value parameter all stand at the entry and would occupy scalar registers throughout.
   (void)by_value;
-  const FusedArgs& a = *(const FusedArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+  typedef const char __attribute__((address_space(4)))* Segment;
+  const FusedArgs& a =
+      *(const FusedArgs*)((Segment)__builtin_amdgcn_kernarg_segment_ptr() + kRegisterArgs);
   typedef std::conditional_t<WIDE, long long, int32_t> Token;
   typedef std::conditional_t<WIDE, unsigned long long, uint32_t> UToken;
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-  const Problem& pb = a.pb;
-  const int nt = blockDim.x, tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int cs = cand_shape & 0xFFFFu, R = (cand_shape >> 16) & 0xFFu, log2_waves = cand_shape >> 24;
+  const int rs = ref_shape & 0xFFFFu, N = ref_shape >> 16;
+  const int nwaves = 1 << log2_waves, nt = kWave << log2_waves;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int g = blockIdx.x, R = pb.R, N = pb.N;
-  // (in scalar registers: a select between two argument fields would otherwise become a vector
-  // load from a selected address)
-  const int cs = __builtin_amdgcn_readfirstlane(a.cand_stride);
-  const int rs = __builtin_amdgcn_readfirstlane(a.ref_stride);
-  const int log2_waves = a.log2_waves, nwaves = 1 << log2_waves;
-  const int lg = a.log2_slots, id_bits = a.id_bits;
-  const uint32_t sym_at = a.off_sym;
-  // per order and wavefront (16 words an order): clipped sum (low 16) | distinct count (high 16)
-  const uint32_t part_at = a.off_sums;
-  const uint32_t lost_at = part_at + 8 * 16 * 4;  // non-zero: a probe sequence was too long to be counted
-  const uint32_t overlap_at = lost_at + 4;        // ROUGE: overlap with each reference
-  const bool prio = a.progress_priority;
-
+  const int g = blockIdx.x;
   TB_FSTAMP(0);
-  if (prio) __builtin_amdgcn_s_setprio(3);
 
   // lane j of every wavefront: length of sequence j (0 for a reference not in use), where its row
   // is, and the prefix of the sequences' block counts
-  const RefRows rr = ref_rows(pb, g, tid == 0);
-  const int used = rr.used;
-  const int raw_cand = uniform_load(pb.cand_len, g);
+  const int raw_cand = uniform_load(cand_lens, g);
+  // (no branch: with neither counts nor lists a length is read, and not used)
+  const int32_t* const rows = ref_offsets ? ref_offsets : ref_count ? ref_count : cand_lens;
+  const int rows0 = uniform_load(rows, g), rows1 = uniform_load(rows, g + (ref_offsets ? 1 : 0));
+  int64_t row0 = int64_t(g) * R;
   int raw_ref = 0;
-  if (lane >= 1 && lane <= used) raw_ref = pb.ref_len[rr.row0 + lane - 1];
-  const Token* const cand_row = static_cast<const Token*>(pb.cand) + uint64_t(g) * uint32_t(cs);
-  const Token* const ref_row =
-      static_cast<const Token*>(pb.refs) + uint64_t(rr.row0) * uint32_t(rs);
+  if (!ref_offsets && lane >= 1 && lane <= R) raw_ref = ref_lens[row0 + lane - 1];
+  // (in one request while the lengths are on their way)
+  int table_and_counters = a.table_and_counters, vocab_size = a.vocab;
+  uint32_t sym_at = a.off_sym;
+  // per order and wavefront (16 words an order): clipped sum (low 16) | distinct count (high 16)
+  uint32_t part_at = a.off_sums;
+  int progress = a.progress_priority, lg = a.log2_slots, id_bits = a.id_bits;
+  asm volatile("" : "+s"(table_and_counters), "+s"(vocab_size), "+s"(sym_at), "+s"(part_at),
+               "+s"(progress), "+s"(lg), "+s"(id_bits));
+  int used = R;
+  bool odd = false;  // counts or lists that had to be clamped
+  if (ref_offsets) {  // uniform
+    const RefRows rr = listed_rows(rows0, rows1, a.ref_rows, R, &odd);
+    row0 = rr.row0;
+    used = rr.used;
+    if (lane >= 1 && lane <= used) raw_ref = ref_lens[row0 + lane - 1];
+  } else if (ref_count) {
+    used = min(max(rows0, 1), R);
+    odd = rows0 != used;
+    raw_ref = lane <= used ? raw_ref : 0;
+  }
+  const bool prio = progress != 0;
+  const uint32_t lost_at = part_at + 8 * 16 * 4;  // non-zero: a probe sequence was too long to be counted
+  const uint32_t overlap_at = lost_at + 4;        // ROUGE: overlap with each reference
+  if (prio) __builtin_amdgcn_s_setprio(3);
+
+  const Token* const cand_row = static_cast<const Token*>(cand) + uint64_t(g) * uint32_t(cs);
+  const Token* const ref_row = static_cast<const Token*>(refs) + uint64_t(row0) * uint32_t(rs);
   uint64_t row_at = reinterpret_cast<uint64_t>(ref_row) +
                     uint64_t(uint32_t(lane - 1) * uint32_t(rs)) * sizeof(Token);
   row_at = lane == 0 ? reinterpret_cast<uint64_t>(cand_row) : row_at;
   const int raw_len = lane == 0 ? raw_cand : raw_ref;
   const int my_len = min(max(raw_len, 0), lane == 0 ? cs : rs);
-  if (__builtin_amdgcn_ballot_w64(my_len != raw_len)) {  // uniform
-    if (wave == 0 && my_len != raw_len && pb.status) atomicOr(pb.status, TB_DEV_LENGTH_RANGE);
+  if (__builtin_amdgcn_ballot_w64(my_len != raw_len || odd)) {  // uniform
+    if (wave == 0 && (my_len != raw_len || odd) && a.status)
+      atomicOr(a.status, TB_DEV_LENGTH_RANGE);
   }
   const int cand_len = lane_value(my_len, 0);
   const int my_seq_blocks = (my_len + kWave - 1) >> 6;
@@ -276,14 +310,14 @@ void fused_kernel(FusedArgs by_value) {
       }
     }
     // meanwhile: table slots free, counters zero, symbols behind the sequences absent
-    for (uint32_t q = tid; q < uint32_t(a.table_and_counters); q += nt)
+    for (uint32_t q = tid; q < uint32_t(table_and_counters); q += nt)
       *lds<Quad>(16u * q) = Quad(0u);
     if (wave == 0 && lane <= R)
       *lds<Quad>(sym_at + uint32_t(2 * kWave) * block_ends + uint32_t(2 * kPadSymbols) * lane) =
           Quad(~0u);
     if (tid == 0) *lds<uint32_t>(lost_at) = 0u;
     if (ROUGE && tid < kMaxSeqs) *lds<uint32_t>(overlap_at + 4 * tid) = 0u;
-    const UToken vocab = UToken(uint32_t(pb.vocab));
+    const UToken vocab = UToken(uint32_t(vocab_size));
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < BLOCKS; ++i) {
@@ -294,7 +328,7 @@ void fused_kernel(FusedArgs by_value) {
       val[i] = here ? (outside ? 0 : int32_t(raw[i])) : -1;
     }
     if (__builtin_amdgcn_ballot_w64(bad)) {  // uniform
-      if (bad && pb.status) atomicOr(pb.status, TB_DEV_TOKEN_RANGE);
+      if (bad && a.status) atomicOr(a.status, TB_DEV_TOKEN_RANGE);
     }
   }
   __syncthreads();
@@ -303,6 +337,7 @@ void fused_kernel(FusedArgs by_value) {
   // The blocks at hand are val[0], ..., finished ones rotate to the end (a register array cannot be
   // indexed by a loop counter).  A rotation moves all of them, so they are taken in groups of up to
   // four, as far as full ones go: 128 x 8192 48.5 -> 46.7 us, 128 x 5000 29.5 -> 28.7.
+  constexpr bool LOOK = KEEP || BLOCKS > 6;  // (see claim)
   constexpr int GROUP = !KEEP ? 1 : BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
   auto rotate = [&](auto by) {
     constexpr int n = decltype(by)::value;
@@ -360,7 +395,10 @@ void fused_kernel(FusedArgs by_value) {
     each_block(i, my_cand_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       int32_t got = -1;
       if (v >= 0) {
-        got = int32_t(table.claim<KEEP>(uint32_t(v) * table.multiplier, id));
+        const uint32_t h = uint32_t(v) * table.multiplier;
+        uint4 e = make_uint4(0u, 0u, 0u, 0u);
+        if (LOOK) e = table.bucket(table.home(h));
+        got = int32_t(table.claim<LOOK>(h, id, e));
         if (!ROUGE || N == 1) lds_add(cnt_at + __umul24(uint32_t(got), W4), 1u);
       }
       *lds<int16_t>(s) = int16_t(got);
@@ -373,9 +411,7 @@ void fused_kernel(FusedArgs by_value) {
     TB_FSTAMP(2);
     each_block(i, my_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       const int f = sequence_of(b);
-      // (a lane without a token asks like the others; its sign bit then hides the answer)
-      const uint32_t dead = uint32_t(v) & 0x80000000u;
-      const uint32_t x = table.find(uint32_t(v) * table.multiplier, dead) | dead;
+      const uint32_t x = table.find(uint32_t(v) * table.multiplier, uint32_t(v) & 0x80000000u, false, 0u);
       const bool hit = x < id_limit;
       const int32_t got = hit ? int32_t(x) : -1;
       if (hit && (!ROUGE || N == 1))
@@ -457,7 +493,7 @@ void fused_kernel(FusedArgs by_value) {
       }
       __syncthreads();
       if (hi == N) break;
-      for (uint32_t q = tid; q < uint32_t(a.table_and_counters); q += nt)
+      for (uint32_t q = tid; q < uint32_t(table_and_counters); q += nt)
         *lds<Quad>(16u * q) = Quad(0u);
       __syncthreads();
       swept = hi;
@@ -486,26 +522,25 @@ void fused_kernel(FusedArgs by_value) {
     uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
     auto enter_block = [&](int32_t& v) __attribute__((always_inline)) {
       int32_t cur = KEEP ? v : int32_t(*lds<int16_t>(s));
-      uint32_t tag = first_tag, count = first_count, next = s + 2u * uint32_t(lo - 1);
-      int n = lo;
-      auto enter = [&](int offset) {
-        // (an absent symbol makes the key negative: no n-gram here)
-        const int32_t key =
-            int32_t(uint32_t(cur) << id_bits) | int32_t(*lds<int16_t>(next + uint32_t(offset)));
-        cur = -1;
-        if (key >= 0) {
-          cur = int32_t(table.claim<KEEP>(uint32_t(key) * table.multiplier + tag, id));
+      uint32_t tag = first_tag, count = first_count, ahead = 2u * uint32_t(lo - 1);
+      int32_t last = *lds<int16_t>(s + ahead);
+#pragma unroll 1
+      for (int n = lo;; ++n) {
+        // (the next order's last symbol is requested with this order's entry)
+        const int32_t after = *lds<int16_t>(s + ahead + 2u);
+        const int32_t implied = *lds<int16_t>(sym_at + ahead + 2u * uint32_t(cur));
+        if (last >= 0) {  // (an absent symbol: no n-gram here)
+          const uint32_t h = ((uint32_t(cur) << id_bits) | uint32_t(last)) * table.multiplier + tag;
+          uint4 e = make_uint4(0u, 0u, 0u, 0u);
+          if (LOOK) e = table.bucket(table.home(h));
+          if (last != implied) cur = int32_t(table.claim<LOOK>(h, id, e));
           if (!ROUGE || n == N) lds_add(count + __umul24(uint32_t(cur), W4), 1u);
         }
+        if (n >= hi) break;  // uniform
+        last = after;
         tag += tag_unit;
         if (!ROUGE) count += set_bytes;
-        ++n;
-      };
-      enter(0);
-#pragma unroll 1
-      while (n <= hi) {
-        enter(2);
-        next += 2u;
+        ahead += 2u;
       }
       if (KEEP) v = cur;
       id += nt;
@@ -517,22 +552,28 @@ void fused_kernel(FusedArgs by_value) {
       const uint32_t addend = (f & 1) ? 0x10000u : 1u;
       const uint32_t own = s + uint32_t(2 * kPadSymbols) * f;
       int32_t cur = KEEP ? v : int32_t(*lds<int16_t>(own));
-      uint32_t next = own + 2u * uint32_t(lo - 1);
+      uint32_t ahead = 2u * uint32_t(lo - 1);
       uint32_t tag = first_tag, count = first_count + 4u * uint32_t(f >> 1);
+      int32_t last = *lds<int16_t>(own + ahead);
 #pragma unroll 1
       for (int n = lo;; ++n) {
-        const int32_t key = int32_t(uint32_t(cur) << id_bits) | int32_t(*lds<int16_t>(next));
-        cur = -1;
-        if (!__builtin_amdgcn_ballot_w64(key >= 0)) break;  // uniform: nothing to extend
-        const uint32_t dead = uint32_t(key) & 0x80000000u;
-        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag, dead) | dead;
+        const int32_t key = int32_t(uint32_t(cur) << id_bits) | last;
+        if (!__builtin_amdgcn_ballot_w64(key >= 0)) {  // uniform: nothing to extend
+          cur = -1;
+          break;
+        }
+        const int32_t after = *lds<int16_t>(own + ahead + 2u);
+        const int32_t implied = *lds<int16_t>(sym_at + ahead + 2u * uint32_t(cur));
+        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag, uint32_t(key) & 0x80000000u,
+                                      last == implied, uint32_t(cur));
+        last = after;
         const bool hit = x < id_limit;
         cur = hit ? int32_t(x) : -1;
         if (hit && (!ROUGE || n == N)) lds_add(count + __umul24(x, W4), addend);
+        if (n >= hi) break;  // uniform
         tag += tag_unit;
         if (!ROUGE) count += set_bytes;
-        next += 2u;
-        if (n >= hi) break;  // uniform
+        ahead += 2u;
       }
       if (KEEP) v = cur;
       s += sym_stride;
@@ -564,9 +605,16 @@ void fused_kernel(FusedArgs by_value) {
     if (nt < 8 * 16 && tid < 64) *lds<uint32_t>(part_at + 4 * (tid + 64)) = 0u;
     if (ROUGE && tid < kMaxSeqs) *lds<uint32_t>(overlap_at + 4 * tid) = 0u;
     __syncthreads();
+    // (pointers from the argument segment again: they need no registers until here)
+    const Segment args = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
+    typedef const void* const __attribute__((address_space(4)))* Pointers;
+    const Pointers pointers = (Pointers)args;
+    const Token* const cand_row = static_cast<const Token*>(pointers[0]) + uint64_t(g) * uint32_t(cs);
+    const Token* const ref_row = static_cast<const Token*>(pointers[2]) + uint64_t(row0) * uint32_t(rs);
+    const int32_t* const ref_lens = static_cast<const int32_t*>(pointers[3]);
     auto token = [&](const Token* row, int i) {
       const Token t = row[i];
-      return UToken(t) >= UToken(uint32_t(pb.vocab)) ? 0 : int32_t(t);
+      return UToken(t) >= UToken(uint32_t(a.vocab)) ? 0 : int32_t(t);
     };
 #pragma unroll 1
     for (int n = ROUGE ? N : 1; n <= N; ++n) {
@@ -589,7 +637,7 @@ void fused_kernel(FusedArgs by_value) {
         int mx = 0;
 #pragma unroll 1
         for (int j = 0; j < used; ++j) {
-          const int len = min(max(pb.ref_len[rr.row0 + j], 0), rs);
+          const int len = min(max(ref_lens[row0 + j], 0), rs);
           const int c = occurrences(
               ref_row + int64_t(j) * rs, len, false);
           mx = max(mx, c);
@@ -684,24 +732,29 @@ int log2_ceil(int64_t v) {
 }
 
 template <int BLOCKS, bool KEEP, bool WIDE, bool ROUGE>
-hipError_t launch_shape(const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
+hipError_t launch_shape(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
   const auto kernel = fused_kernel<BLOCKS, KEEP, WIDE, ROUGE>;
   hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), plan.lds_bytes);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(kernel, dim3(uint32_t(a.pb.B)), dim3(plan.threads), plan.lds_bytes, s, a);
+  const uint32_t cand_shape = uint32_t(pb.cand_stride) | uint32_t(pb.R) << 16 |
+                              uint32_t(log2_ceil(plan.threads / kWave)) << 24;
+  const uint32_t ref_shape = uint32_t(pb.ref_stride) | uint32_t(pb.N) << 16;
+  hipLaunchKernelGGL(kernel, dim3(uint32_t(pb.B)), dim3(plan.threads), plan.lds_bytes, s, pb.cand,
+                     pb.cand_len, pb.refs, pb.ref_len, pb.ref_count, pb.ref_offsets, cand_shape,
+                     ref_shape, a);
   return hipGetLastError();
 }
 template <int BLOCKS, bool KEEP>
-hipError_t launch_keep(const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  if (a.pb.tok64)
-    return a.rouge_prf ? launch_shape<BLOCKS, KEEP, true, true>(a, plan, s)
-                       : launch_shape<BLOCKS, KEEP, true, false>(a, plan, s);
-  return a.rouge_prf ? launch_shape<BLOCKS, KEEP, false, true>(a, plan, s)
-                     : launch_shape<BLOCKS, KEEP, false, false>(a, plan, s);
+hipError_t launch_keep(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
+  if (pb.tok64)
+    return a.rouge_prf ? launch_shape<BLOCKS, KEEP, true, true>(pb, a, plan, s)
+                       : launch_shape<BLOCKS, KEEP, true, false>(pb, a, plan, s);
+  return a.rouge_prf ? launch_shape<BLOCKS, KEEP, false, true>(pb, a, plan, s)
+                     : launch_shape<BLOCKS, KEEP, false, false>(pb, a, plan, s);
 }
 template <int BLOCKS>
-hipError_t launch_blocks(const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  return plan.keep ? launch_keep<BLOCKS, true>(a, plan, s) : launch_keep<BLOCKS, false>(a, plan, s);
+hipError_t launch_blocks(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
+  return plan.keep ? launch_keep<BLOCKS, true>(pb, a, plan, s) : launch_keep<BLOCKS, false>(pb, a, plan, s);
 }
 
 constexpr size_t kLdsUnit = 1280;  // LDS is handed out in units of this size
@@ -816,7 +869,7 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           // 234 with two 20.4 -> 18.7; 150 shapes 0.85 to 1.03x).
           if (passes == 1 && (R == 3 || r > 8) && r >= 8 && r <= 10 && N > 2 && N <= 4) continue;
           if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2)) continue;
-          const int64_t entries = orders * cand_stride;
+          const int64_t entries = cand_stride;
           const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
           int lg_min = 6;
           while ((int64_t(kTwelfths[level]) << lg_min) < 12 * entries) ++lg_min;
@@ -828,7 +881,7 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           // would be by 1e-19.
           while (32 - widest + lg_min - 2 - p.id_bits < (level < 2 ? 4 : 6)) ++lg_min;
           int lg = lg_min;  // (a larger table than this costs more to clear than it saves)
-          while ((int64_t(1) << lg) < (r == 1 ? 6 : 4) * entries) ++lg;
+          while ((int64_t(1) << lg) < (r == 1 ? 12 : 8) * entries) ++lg;
           for (; lg >= lg_min; --lg) {
             const size_t front = (size_t(4) << lg) + size_t(rouge ? 1 : orders) * p.set_words * 4;
             p.lds_bytes = front + sym_bytes + kSumsBytes;
@@ -850,7 +903,9 @@ hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs
                         const ScoreParams& sp, void* out_bleu_or_null, hipStream_t s,
                         const RougeOut* rouge) {
   FusedArgs a;
-  a.pb = pb;
+  a.status = pb.status;
+  a.vocab = pb.vocab;
+  a.ref_rows = pb.ref_rows;
   a.st = st;
   a.sp = sp;
   a.out = out_bleu_or_null;
@@ -870,23 +925,20 @@ hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs
   a.table_and_counters = plan.table_and_counters;
   a.off_sym = plan.off_sym;
   a.off_sums = plan.off_sums;
-  a.cand_stride = int(pb.cand_stride);
-  a.ref_stride = int(pb.ref_stride);
-  a.log2_waves = log2_ceil(plan.threads / kWave);
   const int by_threads = 2048 / plan.threads;
   const int by_lds = int(size_t(kLdsBudget) / plan.lds_bytes);
   const int resident = 256 * (by_threads < by_lds ? by_threads : (by_lds < 1 ? 1 : by_lds));
   a.progress_priority = pb.B <= 2 * resident ? 1 : 0;
-  if (plan.blocks <= 1) return launch_blocks<1>(a, plan, s);
-  if (plan.blocks <= 2) return launch_blocks<2>(a, plan, s);
-  if (plan.blocks <= 3) return launch_blocks<3>(a, plan, s);
-  if (plan.blocks <= 4) return launch_blocks<4>(a, plan, s);
-  if (plan.blocks <= 5) return launch_blocks<5>(a, plan, s);
-  if (plan.blocks <= 6) return launch_blocks<6>(a, plan, s);
-  if (plan.blocks <= 8) return launch_blocks<8>(a, plan, s);
-  if (plan.blocks <= 12) return launch_blocks<12>(a, plan, s);
-  if (plan.blocks <= 16) return launch_blocks<16>(a, plan, s);
-  return launch_blocks<kMaxBlocks>(a, plan, s);
+  if (plan.blocks <= 1) return launch_blocks<1>(pb, a, plan, s);
+  if (plan.blocks <= 2) return launch_blocks<2>(pb, a, plan, s);
+  if (plan.blocks <= 3) return launch_blocks<3>(pb, a, plan, s);
+  if (plan.blocks <= 4) return launch_blocks<4>(pb, a, plan, s);
+  if (plan.blocks <= 5) return launch_blocks<5>(pb, a, plan, s);
+  if (plan.blocks <= 6) return launch_blocks<6>(pb, a, plan, s);
+  if (plan.blocks <= 8) return launch_blocks<8>(pb, a, plan, s);
+  if (plan.blocks <= 12) return launch_blocks<12>(pb, a, plan, s);
+  if (plan.blocks <= 16) return launch_blocks<16>(pb, a, plan, s);
+  return launch_blocks<kMaxBlocks>(pb, a, plan, s);
 }
 
 }  // namespace tb

@@ -2,6 +2,7 @@
 import ctypes
 import itertools
 import os
+import random
 import subprocess
 
 import numpy as np
@@ -34,17 +35,6 @@ def plans(tmp_path_factory):
     lib.first_free_slot.restype = ctypes.c_uint32
     lib.first_free_slot.argtypes = [ctypes.c_uint32] * 3
     return lib
-
-
-def orders_in_a_pass(N, pass_ends):
-    """The largest number of orders that share a table (see FusedArgs::pass_ends)."""
-    most = swept = 0
-    end = 1 if pass_ends & 1 else pass_ends >> 4 & 15 if N > 1 else 1
-    while True:
-        most, swept = max(most, end - swept), end
-        if swept >= N:
-            return most
-        end = pass_ends >> 4 * end & 15
 
 
 def test_sorted_runs_leave_their_tables_room(plans):
@@ -81,10 +71,47 @@ def fused_table(plans, *shape):
     out = (ctypes.c_int64 * 5)()
     if not plans.fused_plan(*shape, out):
         return None
-    lg, id_bits, key_bits, pass_ends, lds = out
+    lg, id_bits, key_bits, _, lds = out
     assert lds <= LDS, shape
-    load = orders_in_a_pass(shape[4], pass_ends) * shape[1] / 2 ** lg
+    # (however many orders share the table: test_a_table_holds_no_more_than_the_candidate)
+    load = shape[1] / 2 ** lg
     return load, min(32 - key_bits + lg - 2, 32) - id_bits
+
+
+def entries(tokens, first, last, rng):
+    """Entries that the orders first..last of a candidate make in the fused kernel's table, and the ids
+    of the last order's n-grams: an n-gram that goes on as the candidate does at its prefix's id needs
+    none, the others are entered once, by whichever position comes first."""
+    made, ids = 0, list(range(len(tokens)))
+    for n in range(1, last + 1):
+        table, new = {}, {}
+        where = list(range(len(tokens) - n + 1))
+        rng.shuffle(where)
+        for i in where:
+            key = (ids[i] if n > 1 else -1, tokens[i + n - 1])
+            at = ids[i] + n - 1
+            if n > 1 and at < len(tokens) and tokens[at] == tokens[i + n - 1]:
+                new[i] = ids[i]
+            else:
+                new[i] = table.setdefault(key, i)
+        ids = [new[i] for i in range(len(tokens) - n + 1)]
+        made += len(table) if first <= n else 0
+    return made, ids
+
+
+def test_a_table_holds_no_more_than_the_candidate():
+    # Order n makes at most d(n) - d(n - 1) + 1 entries, d(n) being the number of distinct n-grams: every
+    # (n-1)-gram but perhaps the last window's has one continuation that needs none.  d(N) is at most
+    # len - N + 1, so orders first..last make at most len - first + 1 together.
+    rng = random.Random(17)
+    for length, vocab in itertools.product((1, 2, 3, 7, 8, 9, 60, 300), (1, 2, 3, 20, 1000)):
+        for _ in range(4):
+            tokens = [rng.randrange(vocab) for _ in range(length)]
+            for first, last in ((1, 1), (1, 2), (1, 4), (2, 4), (3, 4), (1, 8), (4, 4), (7, 8)):
+                made, ids = entries(tokens, first, last, rng)
+                assert made <= max(length - first + 1, 0)
+                grams = [tuple(tokens[i:i + last]) for i in range(length - last + 1)]
+                assert len(set(ids)) == len(set(grams)) == len(set(zip(ids, grams)))
 
 
 def test_fused_tables_count_far_enough(plans):
