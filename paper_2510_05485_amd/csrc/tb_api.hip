@@ -369,8 +369,10 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
   FusedPlan plan;
   const bool fused = takes_fused(c, cfg, stats, false, &plan);
   if (!fused && c.plans.layout.path == TB_PATH_FUSED) return TB_ERR_UNSUPPORTED;
+  const bool group_distinct = stats && stats->group_distinct;
   if (fused) {
-    rc = hip_rc(launch_fused(c.pb, plan, c.st, c.sp, corpus ? nullptr : out_bleu, c.stream));
+    rc = hip_rc(launch_fused(c.pb, plan, c.st, c.sp, corpus ? nullptr : out_bleu, group_distinct,
+                             c.stream));
     if (rc != TB_OK) return rc;
     if (corpus || c.want_corpus_stats) {
       // per-sentence work is done by the fused kernel; only the batch sums remain
@@ -381,7 +383,6 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
     }
     return TB_OK;
   }
-  const bool group_distinct = stats && stats->group_distinct;
   RunsPlan runs;
   if (takes_runs(c, cfg, false, group_distinct, &runs)) {
     rc = hip_rc(launch_runs(c.pb, runs, runs_buffers(c.pb, c.ws, c.plans.part), c.st,
@@ -466,7 +467,7 @@ int tensorrouge_n(const void* cand, int64_t cand_stride, const int32_t* cand_len
   c.st.distinct = reinterpret_cast<int32_t*>(w + L.distinct_off);
   FusedPlan plan;
   if (takes_fused(c, cfg, nullptr, true, &plan))
-    return hip_rc(launch_fused(c.pb, plan, c.st, c.sp, nullptr, c.stream, &ro));
+    return hip_rc(launch_fused(c.pb, plan, c.st, c.sp, nullptr, false, c.stream, &ro));
   if (L.path == TB_PATH_FUSED) return TB_ERR_UNSUPPORTED;
   // GLOBAL: pack and dictionary as for BLEU (the keys of order n build on the ids of the orders
   // below), then the count pass for order n alone, which also sums the per-reference overlaps

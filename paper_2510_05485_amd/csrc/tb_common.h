@@ -67,6 +67,18 @@ __device__ __forceinline__ int wave_inclusive_scan(int v) {
   return x;
 }
 
+// Smallest value of the wavefront, returned in every lane (wave-uniform).  All 64 lanes must be active.
+__device__ __forceinline__ int wave_min(int v) {
+  auto step = [](int x, int y) { return y < x ? y : x; };
+  v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));  // row_shr:1
+  v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));  // row_shr:2
+  v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));  // row_shr:4
+  v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));  // row_shr:8
+  v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));  // row_bcast:15
+  v = step(v, __builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));  // row_bcast:31
+  return __builtin_amdgcn_readlane(v, kWave - 1);
+}
+
 // Sum over the wavefront, returned in every lane (wave-uniform).  All 64 lanes must be active.
 __device__ __forceinline__ int wave_sum(int v) {
   return __builtin_amdgcn_readlane(wave_inclusive_scan(v), kWave - 1);
@@ -131,7 +143,8 @@ __device__ __forceinline__ int block_sum(int v, int* scratch) {
 // free one hold other keys; the slot itself, whatever it has become since, is tried with a
 // compare-and-swap, and so is every one behind it.
 __host__ __device__ __forceinline__ uint32_t first_free_slot(uint32_t x, uint32_t y, uint32_t z) {
-  return !x ? 0u : !y ? 4u : !z ? 8u : 12u;
+  const uint32_t a = x < 1u ? x : 1u, b = y < a ? y : a, c = z < b ? z : b;  // all up to here taken?
+  return 4u * (a + b + c);
 }
 
 // Problem description handed to every kernel (device pointers + shapes).

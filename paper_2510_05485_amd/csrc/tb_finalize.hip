@@ -132,7 +132,8 @@ __global__ __launch_bounds__(1024) void corpus_kernel(FinalArgs a, int write_sco
       long long tn = 0;  // lane n < N: the total of order n + 1
 #pragma unroll
       for (int n = 0; n < 8; ++n) tn = lane == n ? sum_of(8 + n) : tn;
-      const float score = bleu_from_stats_wave<long long>(tot, tn, c, r, a.sp);
+      const float brevity = expf(1.0f - float(r) / float(c));
+      const float score = bleu_from_stats_wave<long long>(tot, tn, c, r, brevity, lane_weight(a.sp), a.sp);
       if (lane == 0)
         store_score(a.out, 0, s_spoilt ? __int_as_float(0x7FC00000) : score, a.sp.out_bf16);
     }

@@ -38,10 +38,11 @@
 //     its own.  How many orders that are is the plan's choice: all of them (fewest barriers), or
 //     fewer where LDS is short (table and counters are then swept and cleared in between).
 //
-// Counters: one 16-bit field per sequence and candidate id (the offset of Section 3.3 step 1 keeps
-// sequences apart the same way); the sweep takes the maximum over the reference fields and the
-// minimum with the candidate's (step 3).  Wavefront 0 forms brevity penalty, smoothing and geometric
-// mean (Section 3.4), one order per lane.  With ROUGE = true the kernel scores ROUGE-N for n = N.
+// Counters: 16-bit fields per candidate id and reference (the offset of Section 3.3 step 1 keeps
+// sequences apart the same way).  With one reference, and for ROUGE-N, a look-up sees by the counter it
+// decreases whether the candidate has the n-gram once more (step 3's minimum); with more, a pass over
+// the counters takes the maximum over the references.  Wavefront 0 forms brevity penalty, smoothing and
+// geometric mean (Section 3.4), one order per lane.  Mode kRouge scores ROUGE-N for n = N.
 //
 // Measured on gfx950 (us of GPU time, 4 orders; in brackets the kernel that had one barrier per
 // insertion and look-up of each order, 64-bit-wide slots and a list of live positions in LDS):
@@ -93,8 +94,8 @@ struct FusedArgs {
   int first_payload, first_key_bits;  // payload bits and key bits (order within the pass | payload)
                                       // of the table that order 1 is in
   int later_payload, later_key_bits;  // ... of the passes behind it
-  int words;               // 32-bit counter words per id; field 0: candidate, field 1 + j: reference j
-  int set_words;           // counter words of one order
+  int array_bytes;         // of one array of counter words, a word per id
+  int want_distinct;
   float beta2;             // ROUGE-N: beta squared
   StatPtrs st;
   ScoreParams sp;
@@ -118,8 +119,8 @@ __device__ __forceinline__ uint32_t lds_cas(uint32_t at, uint32_t desired) {  //
                                        __HIP_MEMORY_SCOPE_WORKGROUP);
   return expected;
 }
-__device__ __forceinline__ void lds_add(uint32_t at, uint32_t v) {
-  __hip_atomic_fetch_add((uint32_t*)lds<uint32_t>(at), v, __ATOMIC_RELAXED,
+__device__ __forceinline__ uint32_t lds_add(uint32_t at, uint32_t v) {  // returns what was there
+  return __hip_atomic_fetch_add((uint32_t*)lds<uint32_t>(at), v, __ATOMIC_RELAXED,
                          __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
@@ -139,39 +140,6 @@ struct SymbolTable {
   __device__ __forceinline__ uint32_t step(uint32_t remainder) const {
     return ((remainder >> 16) & ~31u) | 16u;
   }
-  // Id of the key with product h, entered as `id` where it is not there: tries the slots of its
-  // buckets one after the other.  Ends: the odd step visits every bucket, the plan keeps the table
-  // at most 3/4 full, and only this workgroup writes it.
-  // SEEN: the home bucket has been read (e).  It may hold the key, and tells the first free slot.
-  // Without it a wavefront swaps as often as its slowest lane finds slots taken.  Plans with many blocks
-  // a wavefront have tables that fill up to the half, where that is often (2041 x 1088 40.4 -> 38.7 us);
-  // in the emptier tables of the others the read costs more than it saves (ROUGE-2 of 512 x 512 with
-  // three references 9.6 -> 10.2, 1000 x 96 10.4 -> 10.5).
-  template <bool SEEN>
-  __device__ __forceinline__ uint32_t claim(uint32_t h, uint32_t id, const uint4& e) const {
-    uint32_t s = home(h);
-    const uint32_t remainder = h << log2_buckets;
-    uint32_t mine = remainder + id_limit;
-    uint32_t x;
-    if (SEEN) {
-      x = match(e, mine);
-      if (x < id_limit) return x;
-      s += first_free_slot(e.x, e.y, e.z);  // (a full one: its last slot, then the next bucket)
-    }
-    uint32_t old = lds_cas(s, mine + id);
-    x = old ^ mine;
-    while (min(old, x) >= id_limit) {  // neither free nor the key
-      s += 4u;
-      const bool leaves = (s & 15u) == 0u;  // (selects, no branch)
-      const uint32_t jump = (s - 16u + step(remainder)) & bucket_mask;
-      s = leaves ? jump : s;
-      mine = min(mine + (leaves ? id_limit : 0u), remainder + longest);
-      old = lds_cas(s, mine + id);
-      x = old ^ mine;
-    }
-    if (__builtin_expect(mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
-    return old == 0u ? id : x;
-  }
   __device__ __forceinline__ static uint32_t match(const uint4& e, uint32_t mine) {
     return min(min(min(e.x ^ mine, e.y ^ mine), e.z ^ mine), e.w ^ mine);
   }
@@ -180,35 +148,88 @@ struct SymbolTable {
     const Quad q = *lds<Quad>(at);
     return make_uint4(q.x, q.y, q.z, q.w);
   }
-  // Id of the key, or a value of at least id_limit: one 16-byte request answers unless the bucket
-  // is full and does not hold the key.  known: it is `id` (the lane asks all the same, which is less
-  // than a branch, but not for a second bucket).  dead: the sign bit for a lane without a key, else 0
-  // (such lanes ask like the others, and their sequences must not be taken for one that was too long).
-  __device__ __forceinline__ uint32_t find(uint32_t h, uint32_t dead, bool known, uint32_t id) const {
-    uint32_t s = home(h);
-    const uint32_t remainder = h << log2_buckets;
-    uint32_t mine = remainder + id_limit;
-    uint4 e = bucket(s);
-    uint32_t x = match(e, mine);
-    x = known ? id : x;
-    if (min(x, e.w) >= id_limit) {
+  struct Probe {
+    uint32_t x;     // the key's id if it was found, else at least id_limit
+    uint32_t s;     // the bucket that was read last, and what it held
+    uint4 e;
+    uint32_t mine;  // the key's entry there, without an id
+  };
+  // Reads buckets until one holds the key or is not full; ends, because the odd step visits every
+  // bucket and the plan keeps the table at most 3/4 full.  known(): the answer is `id` (the lane asks
+  // all the same, which is less than a branch, but not for a second bucket).
+  template <typename Known>
+  __device__ __forceinline__ Probe probe(uint32_t h, Known known, uint32_t id) const {
+    Probe p;
+    p.s = home(h);
+    p.e = bucket(p.s);
+    __builtin_amdgcn_sched_barrier(0);  // (whatever known() waits for is on its way with the bucket)
+    p.mine = (h << log2_buckets) + id_limit;
+    p.x = known() ? id : match(p.e, p.mine);
+    if (min(p.x, p.e.w) >= id_limit) {
+      const uint32_t remainder = h << log2_buckets;
       do {
-        s = (s + step(remainder)) & bucket_mask;
-        mine = min(mine + id_limit, remainder + longest);
-        e = bucket(s);
-        x = match(e, mine);
-      } while (min(x, e.w) >= id_limit);
-      if (__builtin_expect((mine ^ dead) == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
+        p.s = (p.s + step(remainder)) & bucket_mask;
+        p.mine = min(p.mine + id_limit, remainder + longest);
+        p.e = bucket(p.s);
+        p.x = match(p.e, p.mine);
+      } while (min(p.x, p.e.w) >= id_limit);
+      if (__builtin_expect(p.mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
     }
-    return x | dead;
+    return p;
+  }
+  template <typename Known>
+  __device__ __forceinline__ uint32_t find(uint32_t h, Known known, uint32_t id) const {
+    return probe(h, known, id).x;
+  }
+  // Id of the key, entered as `id` where it is not there.  LOOK: buckets are read before anything is
+  // swapped.  A wavefront that swaps from slot to slot does so as often as its slowest lane finds one
+  // taken, six times in a table that fills up to the half.  A swap that fails (lanes of this or another
+  // wavefront entered something there) goes on with the next slot.
+  template <bool LOOK>
+  __device__ __forceinline__ uint32_t claim(uint32_t h, uint32_t id) const {
+    uint32_t s = home(h), mine = (h << log2_buckets) + id_limit;
+    if (LOOK) {
+      const Probe p = probe(h, [] { return false; }, 0u);
+      if (p.x < id_limit) return p.x;
+      s = p.s + first_free_slot(p.e.x, p.e.y, p.e.z);
+      mine = p.mine;
+    }
+    uint32_t old = lds_cas(s, mine + id);
+    uint32_t x = old ^ mine;
+    if (min(old, x) >= id_limit) {  // neither free nor the key
+      const uint32_t remainder = h << log2_buckets;
+      do {
+        const bool leaves = (s & 12u) == 12u;  // (selects, no branch)
+        s = (s + (leaves ? step(remainder) - 12u : 4u)) & (bucket_mask | 12u);
+        mine = min(mine + (leaves ? id_limit : 0u), remainder + longest);
+        old = lds_cas(s, mine + id);
+        x = old ^ mine;
+      } while (min(old, x) >= id_limit);
+      if (__builtin_expect(mine == remainder + longest, 0)) *lds<uint32_t>(lost_at) = 1u;
+    }
+    return old == 0u ? id : x;
   }
 };
 
+// What a kernel is for.  With one or two references lengths, rows and counters of a block are known
+// without a look at other lanes, and no register holds what depends on the number of references.
+enum Mode { kOneReference, kTwoReferences, kReferences, kRouge };
+
+// The value of sequence f.  (Arguments by value: a choice between variables that closures refer to is
+// made between their addresses, which keeps all of them in memory.)
+template <bool THREE, typename T>
+__device__ __forceinline__ T pick(int f, T cand, T ref, T ref1) {
+  T v = cand;
+  if (f >= 1) v = ref;
+  if (THREE && f >= 2) v = ref1;
+  return v;
+}
+
 // BLOCKS: blocks of 64 positions per wavefront.  KEEP: a pass starts above order 2, with the ids of
-// the order below.  WIDE: int64 token ids.
+// the order below.
 // (The scalar-register cap keeps two 1024-thread workgroups on a compute unit: eight wavefronts per
 // SIMD need at most 80 scalar registers each on this hardware.)
-template <int BLOCKS, bool KEEP, bool WIDE, bool ROUGE>
+template <int BLOCKS, bool KEEP, Mode MODE>
 __global__ __launch_bounds__(1024, 8) __attribute__((amdgpu_num_sgpr(80)))
 void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
                   const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
@@ -219,30 +240,39 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   typedef const char __attribute__((address_space(4)))* Segment;
   const FusedArgs& a =
       *(const FusedArgs*)((Segment)__builtin_amdgcn_kernarg_segment_ptr() + kRegisterArgs);
-  typedef std::conditional_t<WIDE, long long, int32_t> Token;
-  typedef std::conditional_t<WIDE, unsigned long long, uint32_t> UToken;
+  constexpr bool ROUGE = MODE == kRouge, ONE = MODE == kOneReference, TWO = MODE == kTwoReferences;
+  constexpr bool FEW = ONE || TWO;
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
-  const int cs = cand_shape & 0xFFFFu, R = (cand_shape >> 16) & 0xFFu, log2_waves = cand_shape >> 24;
-  const int rs = ref_shape & 0xFFFFu, N = ref_shape >> 16;
+  const int cs = cand_shape & 0xFFFFu, R = ONE ? 1 : TWO ? 2 : (cand_shape >> 16) & 0xFFu;
+  const int log2_waves = cand_shape >> 24;
+  const int rs = ref_shape & 0xFFFFu, N = (ref_shape >> 16) & 0xFFu;
+  const bool wide = ref_shape >> 24;  // int64 token ids
   const int nwaves = 1 << log2_waves, nt = kWave << log2_waves;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
   const int g = blockIdx.x;
   TB_FSTAMP(0);
 
-  // lane j of every wavefront: length of sequence j (0 for a reference not in use), where its row
-  // is, and the prefix of the sequences' block counts
+  // Lengths (0 for a reference not in use) and rows of the sequences; with several references lane j of
+  // every wavefront holds those of sequence j, and the prefix of the sequences' block counts
   const int raw_cand = uniform_load(cand_lens, g);
   // (no branch: with neither counts nor lists a length is read, and not used)
   const int32_t* const rows = ref_offsets ? ref_offsets : ref_count ? ref_count : cand_lens;
   const int rows0 = uniform_load(rows, g), rows1 = uniform_load(rows, g + (ref_offsets ? 1 : 0));
   int64_t row0 = int64_t(g) * R;
-  int raw_ref = 0;
-  if (!ref_offsets && lane >= 1 && lane <= R) raw_ref = ref_lens[row0 + lane - 1];
+  int raw_ref = 0, raw_ref1 = 0;
+  if (FEW) {
+    if (!ref_offsets) {
+      raw_ref = uniform_load(ref_lens, row0);
+      if (TWO) raw_ref1 = uniform_load(ref_lens, row0 + 1);
+    }
+  } else {
+    if (!ref_offsets && lane >= 1 && lane <= R) raw_ref = ref_lens[row0 + lane - 1];
+  }
   // (in one request while the lengths are on their way)
   int table_and_counters = a.table_and_counters, vocab_size = a.vocab;
   uint32_t sym_at = a.off_sym;
-  // per order and wavefront (16 words an order): clipped sum (low 16) | distinct count (high 16)
+  // per order: sums (8 words), distinct n-grams (8 words)
   uint32_t part_at = a.off_sums;
   int progress = a.progress_priority, lg = a.log2_slots, id_bits = a.id_bits;
   asm volatile("" : "+s"(table_and_counters), "+s"(vocab_size), "+s"(sym_at), "+s"(part_at),
@@ -253,43 +283,88 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     const RefRows rr = listed_rows(rows0, rows1, a.ref_rows, R, &odd);
     row0 = rr.row0;
     used = rr.used;
-    if (lane >= 1 && lane <= used) raw_ref = ref_lens[row0 + lane - 1];
+    if (FEW) {
+      if (used > 0) raw_ref = uniform_load(ref_lens, row0);
+      if (TWO && used > 1) raw_ref1 = uniform_load(ref_lens, row0 + 1);
+    } else if (lane >= 1 && lane <= used) {
+      raw_ref = ref_lens[row0 + lane - 1];
+    }
   } else if (ref_count) {
     used = min(max(rows0, 1), R);
     odd = rows0 != used;
-    raw_ref = lane <= used ? raw_ref : 0;
+    if (TWO) raw_ref1 = used > 1 ? raw_ref1 : 0;
+    if (!FEW) raw_ref = lane <= used ? raw_ref : 0;
   }
   const bool prio = progress != 0;
-  const uint32_t lost_at = part_at + 8 * 16 * 4;  // non-zero: a probe sequence was too long to be counted
+  const uint32_t lost_at = part_at + 64;  // non-zero: a probe sequence was too long to be counted
   const uint32_t overlap_at = lost_at + 4;        // ROUGE: overlap with each reference
   if (prio) __builtin_amdgcn_s_setprio(3);
 
-  const Token* const cand_row = static_cast<const Token*>(cand) + uint64_t(g) * uint32_t(cs);
-  const Token* const ref_row = static_cast<const Token*>(refs) + uint64_t(row0) * uint32_t(rs);
-  uint64_t row_at = reinterpret_cast<uint64_t>(ref_row) +
-                    uint64_t(uint32_t(lane - 1) * uint32_t(rs)) * sizeof(Token);
-  row_at = lane == 0 ? reinterpret_cast<uint64_t>(cand_row) : row_at;
-  const int raw_len = lane == 0 ? raw_cand : raw_ref;
-  const int my_len = min(max(raw_len, 0), lane == 0 ? cs : rs);
-  if (__builtin_amdgcn_ballot_w64(my_len != raw_len || odd)) {  // uniform
-    if (wave == 0 && (my_len != raw_len || odd) && a.status)
-      atomicOr(a.status, TB_DEV_LENGTH_RANGE);
+  const uint32_t token_bytes = wide ? 8u : 4u;
+  const uint64_t cand_row = reinterpret_cast<uint64_t>(cand) + uint64_t(uint32_t(g)) * (uint32_t(cs) * token_bytes);
+  const uint64_t ref_row = reinterpret_cast<uint64_t>(refs) + uint64_t(row0) * (uint32_t(rs) * token_bytes);
+  const int cand_len = min(max(raw_cand, 0), cs);
+  const int ref_len = min(max(raw_ref, 0), rs), ref_len1 = min(max(raw_ref1, 0), rs);
+  const int my_len = pick<false>(FEW || lane > 0 ? 1 : 0, cand_len, ref_len, 0);
+  const bool clamped = cand_len != raw_cand || ref_len != raw_ref || ref_len1 != raw_ref1 || odd;
+  if (__builtin_amdgcn_ballot_w64(clamped)) {  // uniform
+    if (wave == 0 && clamped && a.status) atomicOr(a.status, TB_DEV_LENGTH_RANGE);
   }
-  const int cand_len = lane_value(my_len, 0);
-  const int my_seq_blocks = (my_len + kWave - 1) >> 6;
-  const int block_ends = wave_inclusive_scan(my_seq_blocks);
-  const int block_begins = block_ends - my_seq_blocks;
-  const int ends = lane <= R ? block_ends : 0x7FFFFFFF;
-  const int blocks = min(lane_value(block_ends, kWave - 1), BLOCKS << log2_waves);
-  const int cand_blocks = lane_value(block_ends, 0);
-  auto sequence_of = [&](int b) {  // of block b < blocks
+  const int cand_blocks = (cand_len + kWave - 1) >> 6;
+  int block_ends, block_begins = 0, ends = 0;
+  const int begin1 = cand_blocks + ((ref_len + kWave - 1) >> 6);  // (FEW: of the second reference)
+  uint64_t row_at = 0;
+  if (FEW) {
+    block_ends = begin1 + ((ref_len1 + kWave - 1) >> 6);
+  } else {
+    const int my_seq_blocks = (my_len + kWave - 1) >> 6;
+    block_ends = wave_inclusive_scan(my_seq_blocks);
+    block_begins = block_ends - my_seq_blocks;
+    ends = lane <= R ? block_ends : 0x7FFFFFFF;
+    row_at = lane == 0 ? cand_row : ref_row + uint64_t(uint32_t(lane - 1) * uint32_t(rs)) * token_bytes;
+  }
+  const int blocks =
+      min(FEW ? block_ends : lane_value(block_ends, kWave - 1), BLOCKS << log2_waves);
+  auto sequence_of = [&](int b) __attribute__((always_inline)) {  // of block b < blocks
+    if (FEW) return (b >= cand_blocks ? 1 : 0) + (TWO && b >= begin1 ? 1 : 0);
     return int(__popcll(__builtin_amdgcn_ballot_w64(ends <= b)));
+  };
+  // position of block b of sequence f in its row
+  auto first_of = [&](int b, int f) __attribute__((always_inline)) {
+    if (FEW) return (b - pick<TWO>(f, 0, cand_blocks, begin1)) << 6;
+    return (b - __builtin_amdgcn_readlane(block_begins, f)) << 6;
+  };
+  auto length_of = [&](int f) __attribute__((always_inline)) {
+    if (FEW) return pick<TWO>(f, cand_len, ref_len, ref_len1);
+    return int(__builtin_amdgcn_readlane(my_len, f));
+  };
+  auto row_of = [&](int f) __attribute__((always_inline)) {
+    if (FEW) return pick<TWO>(f, cand_row, ref_row, ref_row + uint32_t(rs) * token_bytes);
+    return uint64_t(uint32_t(__builtin_amdgcn_readlane(int(row_at >> 32), f))) << 32 |
+           uint32_t(__builtin_amdgcn_readlane(int(uint32_t(row_at)), f));
+  };
+  // Closest reference length, the shorter one on ties (no reference at all: 0).
+  auto closest_length = [&]() __attribute__((always_inline)) {
+    if (FEW) {
+      const int d0 = abs(ref_len - cand_len), d1 = abs(ref_len1 - cand_len);
+      const bool other = TWO && used > 1 && (d1 < d0 || (d1 == d0 && ref_len1 < ref_len));
+      return pick<TWO>(other ? 2 : 1, 0, ref_len, ref_len1);
+    }
+    const bool is_ref = lane >= 1 && lane <= used;
+    const int key = is_ref ? abs(my_len - cand_len) << 15 | my_len : 0x7FFFFFFF;
+    return used > 0 ? wave_min(key) & 0x7FFF : 0;
   };
 
   // This wavefront's blocks are wave, wave + nwaves, ... (the candidate's come first).  val[i]: the
   // token, then the symbol, of the lane's position (KEEP: then the id of the last finished order).
   int32_t val[BLOCKS];
-  {
+  int best = 0;
+  float brevity = 0.0f;
+  // Tokens are requested; while they are on their way, the lengths' part of the score is formed, table
+  // slots become free, counters zero, symbols behind the sequences absent.
+  auto stage = [&](auto token_type) __attribute__((always_inline)) {
+    typedef decltype(token_type) Token;
+    typedef std::make_unsigned_t<Token> UToken;
     Token raw[BLOCKS];
     int left[BLOCKS];  // positions of the block inside the sequence
 #pragma unroll
@@ -299,23 +374,24 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
       left[i] = 0;
       if (b < blocks) {  // uniform
         const int f = sequence_of(b);
-        const int first = (b - __builtin_amdgcn_readlane(block_begins, f)) << 6;
-        left[i] = __builtin_amdgcn_readlane(my_len, f) - first;
-        const uint64_t row =
-            (uint64_t(uint32_t(__builtin_amdgcn_readlane(int(row_at >> 32), f))) << 32) |
-            uint32_t(__builtin_amdgcn_readlane(int(uint32_t(row_at)), f));
+        const int first = first_of(b, f);
+        left[i] = length_of(f) - first;
         typedef const Token __attribute__((address_space(1)))* GlobalToken;
-        GlobalToken p = reinterpret_cast<GlobalToken>(row) + uint32_t(first);
+        GlobalToken p = reinterpret_cast<GlobalToken>(row_of(f)) + uint32_t(first);
         raw[i] = p[uint32_t(min(lane, left[i] - 1))];
       }
     }
-    // meanwhile: table slots free, counters zero, symbols behind the sequences absent
+    if (!ROUGE && wave == 0) {
+      best = closest_length();
+      brevity = expf(1.0f - float(best) / float(cand_len));
+    }
     for (uint32_t q = tid; q < uint32_t(table_and_counters); q += nt)
       *lds<Quad>(16u * q) = Quad(0u);
-    if (wave == 0 && lane <= R)
-      *lds<Quad>(sym_at + uint32_t(2 * kWave) * block_ends + uint32_t(2 * kPadSymbols) * lane) =
-          Quad(~0u);
-    if (tid == 0) *lds<uint32_t>(lost_at) = 0u;
+    if (wave == 0 && lane <= R) {
+      const int behind = FEW ? pick<TWO>(lane, cand_blocks, begin1, block_ends) : block_ends;
+      *lds<Quad>(sym_at + uint32_t(2 * kWave) * behind + uint32_t(2 * kPadSymbols) * lane) = Quad(~0u);
+    }
+    if (tid < 17) *lds<uint32_t>(part_at + 4 * tid) = 0u;  // (lost_at, too)
     if (ROUGE && tid < kMaxSeqs) *lds<uint32_t>(overlap_at + 4 * tid) = 0u;
     const UToken vocab = UToken(uint32_t(vocab_size));
     bool bad = false;
@@ -330,6 +406,11 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     if (__builtin_amdgcn_ballot_w64(bad)) {  // uniform
       if (bad && a.status) atomicOr(a.status, TB_DEV_TOKEN_RANGE);
     }
+  };
+  if (wide) {
+    stage(int64_t(0));
+  } else {
+    stage(int32_t(0));
   }
   __syncthreads();
   TB_FSTAMP(1);
@@ -339,7 +420,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   // four, as far as full ones go: 128 x 8192 48.5 -> 46.7 us, 128 x 5000 29.5 -> 28.7.
   constexpr bool LOOK = KEEP || BLOCKS > 6;  // (see claim)
   constexpr int GROUP = !KEEP ? 1 : BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
-  auto rotate = [&](auto by) {
+  auto rotate = [&](auto by) __attribute__((always_inline)) {
     constexpr int n = decltype(by)::value;
     int32_t first[n];
 #pragma unroll
@@ -373,13 +454,55 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   table.id_limit = 1u << id_bits;
   table.lost_at = lost_at;
   const uint32_t id_limit = table.id_limit;
-  auto set_key_bits = [&](int key_bits) {
+  auto set_key_bits = [&](int key_bits) __attribute__((always_inline)) {
     const int count_bits = min(32 - key_bits + lg - 2 - id_bits, 32 - id_bits);
     table.multiplier = 0x9E3779B1u << (32 - key_bits);
     table.longest = ((1u << count_bits) - 1u) << id_bits;
   };
   const uint32_t cnt_at = 4u << lg;
-  const uint32_t W4 = 4u * uint32_t(a.words), set_bytes = 4u * uint32_t(a.set_words);
+  // Counters: 16-bit fields, two a word, the words of all ids in one array per pair of fields.
+  //   * One reference, and ROUGE-N: a field is the n-gram's count in the candidate less what the
+  //     reference has had of it so far (a negative lower half borrows from the upper one).  A reference's
+  //     n-gram that finds it positive is a match, and matches are all that is asked for: no pass over
+  //     the counters, which cost a lone workgroup of 16 x 256 tokens 1600 of 15000 cycles, and one with
+  //     eight references of 464 tokens (ROUGE-1) 7 of 11 us.
+  //   * Two references: count less the reference's count, one field each; the smaller one is what the
+  //     candidate has beyond both.
+  //   * More: the count in the candidate, then the counts in the references.
+  const uint32_t array_bytes = uint32_t(a.array_bytes);
+  constexpr bool matching = ONE || ROUGE;
+  constexpr bool differences = MODE != kReferences;
+  const int order_fields = differences ? R : R + 1;
+  const uint32_t ref_unit = differences ? ~0u : 1u;
+  const int first_ref = differences ? -1 : 0;  // field of reference 0, which does not exist
+  auto array_of = [&](int field) __attribute__((always_inline)) { return cnt_at + uint32_t(field >> 1) * array_bytes; };
+  auto count_candidate = [&](int order, uint32_t id) __attribute__((always_inline)) {
+    if (ROUGE) {
+      uint32_t at = cnt_at + 4u * id;
+#pragma unroll 1
+      for (int j = R; j > 0; j -= 2, at += array_bytes) lds_add(at, j > 1 ? 0x10001u : 1u);
+    } else {
+      const int field = order * order_fields;
+      lds_add(array_of(field) + 4u * id, (TWO ? 0x10001u : 1u) << (16 * (field & 1)));
+    }
+  };
+  // the counter's word before reference f's n-gram was counted, if it is wanted
+  auto count_reference = [&](int order, int f, uint32_t id) __attribute__((always_inline)) {
+    const int field = (ROUGE ? 0 : order * order_fields) + first_ref + f;
+    const uint32_t at = array_of(field) + 4u * id, unit = ref_unit << (16 * (field & 1));
+    if (matching) return lds_add(at, unit);
+    lds_add(at, unit);
+    return 0u;
+  };
+  // whether the field was positive (low + 65536 * high, each within 32767)
+  auto is_match = [&](int order, int f, uint32_t word) __attribute__((always_inline)) {
+    const int odd = ((ROUGE ? 0 : order * order_fields) + first_ref + f) & 1;
+    return int32_t(word << (odd ? 0 : 16)) > (odd ? 0x7FFF : 0);
+  };
+  int matches1 = 0, matches[3] = {0, 0, 0};  // of this lane: order 1, orders lo.. of the pass
+  int overlap = 0;                           // ROUGE: lane f: matches with reference f
+  const bool want_distinct = a.want_distinct;
+  int distinct = 0;  // lane n - 1: this wavefront's positions whose n-gram has their id
   const int my_cand_blocks = (max(cand_blocks - wave, 0) + nwaves - 1) >> log2_waves;
   const int my_blocks = (max(blocks - wave, 0) + nwaves - 1) >> log2_waves;
   // byte offset of the symbol of this lane's position in the wavefront's first block, and from
@@ -395,11 +518,12 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     each_block(i, my_cand_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       int32_t got = -1;
       if (v >= 0) {
-        const uint32_t h = uint32_t(v) * table.multiplier;
-        uint4 e = make_uint4(0u, 0u, 0u, 0u);
-        if (LOOK) e = table.bucket(table.home(h));
-        got = int32_t(table.claim<LOOK>(h, id, e));
-        if (!ROUGE || N == 1) lds_add(cnt_at + __umul24(uint32_t(got), W4), 1u);
+        got = int32_t(table.claim<LOOK>(uint32_t(v) * table.multiplier, id));
+        if (!ROUGE || N == 1) count_candidate(0, uint32_t(got));
+      }
+      if (!ROUGE && want_distinct) {
+        const int own = __popcll(__builtin_amdgcn_ballot_w64(got == int32_t(id)));
+        distinct += lane == 0 ? own : 0;
       }
       *lds<int16_t>(s) = int16_t(got);
       v = got;
@@ -411,12 +535,24 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     TB_FSTAMP(2);
     each_block(i, my_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       const int f = sequence_of(b);
-      const uint32_t x = table.find(uint32_t(v) * table.multiplier, uint32_t(v) & 0x80000000u, false, 0u);
-      const bool hit = x < id_limit;
-      const int32_t got = hit ? int32_t(x) : -1;
-      if (hit && (!ROUGE || N == 1))
-        lds_add(cnt_at + 4u * uint32_t(f >> 1) + __umul24(x, W4), (f & 1) ? 0x10000u : 1u);
+      int32_t got = -1;
+      bool match = false;
+      if (v >= 0) {
+        const uint32_t x = table.find(uint32_t(v) * table.multiplier, [] { return false; }, 0u);
+        if (x < id_limit) {
+          got = int32_t(x);
+          if (!ROUGE || N == 1) {
+            const uint32_t word = count_reference(0, f, x);
+            if (matching) match = is_match(0, f, word);
+          }
+        }
+      }
       *lds<int16_t>(s + uint32_t(2 * kPadSymbols) * f) = int16_t(got);
+      if (!ROUGE) matches1 += match ? 1 : 0;
+      if (ROUGE && N == 1) {
+        const int of_block = __popcll(__builtin_amdgcn_ballot_w64(match));
+        overlap += lane == f ? of_block : 0;
+      }
       v = got;
       s += sym_stride;
       b += nwaves;
@@ -434,62 +570,87 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   while (true) {
     if (pass_ends) {
       if (hi == N && prio) __builtin_amdgcn_s_setprio(0);
-      __syncthreads();
-      // ---- counters of the pass's orders: maximum over the references, minimum with the
-      // candidate, sum
-      uint32_t at = cnt_at;
-      int n = ROUGE ? N : swept + 1;
-      if (!ROUGE && !KEEP) {  // two orders at once: each is a chain of dependent steps
-#pragma unroll 1
-        for (; n < hi; n += 2, at += 2 * set_bytes) {
-          uint32_t part0 = 0, part1 = 0;
-          uint32_t e = at + __umul24(uint32_t(tid), W4);
-#pragma unroll 1
-          for (int k = tid; k < cand_len; k += nt, e += __umul24(uint32_t(nt), W4)) {
-            const uint32_t first0 = *lds<uint32_t>(e), first1 = *lds<uint32_t>(e + set_bytes);
-            const uint32_t cc0 = first0 & 0xFFFFu, cc1 = first1 & 0xFFFFu;
-            uint32_t mx0 = first0 >> 16, mx1 = first1 >> 16;
-            for (uint32_t w = 4; w < W4; w += 4) {
-              const uint32_t v0 = *lds<uint32_t>(e + w), v1 = *lds<uint32_t>(e + set_bytes + w);
-              mx0 = max(mx0, max(v0 & 0xFFFFu, v0 >> 16));
-              mx1 = max(mx1, max(v1 & 0xFFFFu, v1 >> 16));
-            }
-            part0 += min(cc0, mx0) + (cc0 ? 0x10000u : 0u);
-            part1 += min(cc1, mx1) + (cc1 ? 0x10000u : 0u);
+      // ---- sums of the pass's orders, two in the halves of a word (neither exceeds the positions), in
+      // LDS, where the tail's lanes find theirs: matches, or what the candidate has of its n-grams
+      // beyond every reference (the rest of them is min(count, largest reference count))
+      auto add_up = [&](int n, uint32_t part) __attribute__((always_inline)) {
+        part = uint32_t(row_inclusive_scan(int(part)));
+        if ((lane & 15) == 15) lds_add(part_at + 4u * uint32_t(n - 1), part);
+      };
+      if (ROUGE) {
+        if (hi == N && lane >= 1 && lane <= R) lds_add(overlap_at + 4u * uint32_t(lane - 1), uint32_t(overlap));
+      } else if (matching) {
+        if (my_cand_blocks < my_blocks) {  // (uniform)
+          if (swept == 0) {
+            add_up(1, uint32_t(matches1 | matches[0] << 16));
+            if (hi > 2) add_up(3, uint32_t(matches[1] | matches[2] << 16));
+          } else {
+            add_up(swept + 1, uint32_t(matches[0] | matches[1] << 16));
+            if (hi > swept + 2) add_up(swept + 3, uint32_t(matches[2]));
           }
-          part0 = uint32_t(wave_inclusive_scan(int(part0)));
-          part1 = uint32_t(wave_inclusive_scan(int(part1)));
-          if (lane == kWave - 1) {
-            *lds<uint32_t>(part_at + 64u * uint32_t(n - 1) + 4u * wave) = part0;
-            *lds<uint32_t>(part_at + 64u * uint32_t(n) + 4u * wave) = part1;
+          matches[0] = matches[1] = matches[2] = 0;
+        }
+      } else {
+        __syncthreads();
+        if (TWO) {
+          const uint32_t at = cnt_at + 4u * uint32_t(tid);
+#pragma unroll 1
+          for (int n = swept + 1; n <= hi; n += 2) {
+            uint32_t part = 0;
+            uint32_t e = at + uint32_t(n - 1 - swept) * array_bytes;
+            const uint32_t second = n < hi ? array_bytes : 0u;
+#pragma unroll 1
+            for (int k = tid; k < cand_len; k += nt, e += 4u * uint32_t(nt)) {
+              const int32_t v0 = *lds<int32_t>(e), v1 = *lds<int32_t>(e + second);
+              const int32_t low0 = int16_t(v0), low1 = int16_t(v1);
+              part += uint32_t(max(min(low0, (v0 - low0) >> 16), 0)) |
+                      uint32_t(max(min(low1, (v1 - low1) >> 16), 0)) << 16;
+            }
+            if (n == hi) part &= 0xFFFFu;
+            add_up(n, part);
+          }
+        } else {
+          typedef uint16_t Halves __attribute__((ext_vector_type(2)));
+          auto max_halves = [](uint32_t a, uint32_t b) __attribute__((always_inline)) {
+            return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(
+                __builtin_bit_cast(Halves, a), __builtin_bit_cast(Halves, b)));
+          };
+          // Two orders have order_fields words: the first order's count and first reference in word 0,
+          // the second order's count in word `middle`, in the upper half if the last reference of the
+          // first order has the lower one.
+          const int middle = order_fields >> 1;
+          const bool shared = order_fields & 1;
+#pragma unroll 1
+          for (int n = swept + 1; n <= hi; n += 2) {
+            const bool two = n < hi;
+            uint32_t part = 0;
+            uint32_t e = array_of((n - 1 - swept) * order_fields) + 4u * uint32_t(tid);
+            const uint32_t to_middle = two || shared ? uint32_t(middle) * array_bytes : 0u;
+#pragma unroll 1
+            for (int k = tid; k < cand_len; k += nt, e += 4u * uint32_t(nt)) {
+              auto most_of = [&](uint32_t& most, int w, int end) __attribute__((always_inline)) {  // words w..end - 1
+                uint32_t at = e + uint32_t(w) * array_bytes;
+#pragma unroll 1
+                for (; w + 1 < end; w += 2, at += 2u * array_bytes)
+                  most = max_halves(most, max_halves(*lds<uint32_t>(at), *lds<uint32_t>(at + array_bytes)));
+                if (w < end) most = max_halves(most, *lds<uint32_t>(at));
+              };
+              auto above = [](uint32_t count, uint32_t most) __attribute__((always_inline)) {
+                return uint32_t(max(int32_t(count) - int32_t(max(most & 0xFFFFu, most >> 16)), 0));
+              };
+              const uint32_t head = *lds<uint32_t>(e), second = *lds<uint32_t>(e + to_middle);
+              uint32_t most0 = head >> 16, most1 = shared ? 0u : second >> 16;
+              if (shared) most0 = max_halves(most0, second & 0xFFFFu);
+              most_of(most0, 1, middle);
+              part += above(head & 0xFFFFu, most0);
+              if (two) {
+                most_of(most1, middle + 1, order_fields);
+                part += above(shared ? second >> 16 : second & 0xFFFFu, most1) << 16;
+              }
+            }
+            add_up(n, part);
           }
         }
-      }
-#pragma unroll 1
-      for (; n <= hi; ++n) {
-        uint32_t part = 0;
-        uint32_t e = at + __umul24(uint32_t(tid), W4);
-#pragma unroll 1
-        for (int k = tid; k < cand_len; k += nt, e += __umul24(uint32_t(nt), W4)) {
-          const uint32_t first = *lds<uint32_t>(e);
-          const uint32_t cc = first & 0xFFFFu;
-          uint32_t mx = first >> 16;
-          for (uint32_t w = 4; w < W4; w += 4) {
-            const uint32_t v = *lds<uint32_t>(e + w);
-            mx = max(mx, max(v & 0xFFFFu, v >> 16));
-          }
-          part += min(cc, mx) + (cc ? 0x10000u : 0u);
-          if (ROUGE && cc) {
-            for (int j = 1; j <= R; ++j) {
-              const uint32_t v = *lds<uint32_t>(e + 4u * uint32_t(j >> 1));
-              const uint32_t both = min(cc, (j & 1) ? v >> 16 : v & 0xFFFFu);
-              if (both) lds_add(overlap_at + 4u * uint32_t(j - 1), both);
-            }
-          }
-        }
-        part = uint32_t(wave_inclusive_scan(int(part)));
-        if (lane == kWave - 1) *lds<uint32_t>(part_at + 64u * uint32_t(n - 1) + 4u * wave) = part;
-        at += set_bytes;
       }
       __syncthreads();
       if (hi == N) break;
@@ -516,66 +677,79 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     const int payload = swept == 0 ? __builtin_amdgcn_readfirstlane(a.first_payload)
                                    : __builtin_amdgcn_readfirstlane(a.later_payload);
     const uint32_t tag_unit = table.multiplier << payload;
-    const uint32_t first_tag = uint32_t(lo - 1 - swept) * tag_unit;
-    const uint32_t first_count = cnt_at + (ROUGE ? 0u : uint32_t(lo - 1 - swept) * set_bytes);
     int i = 0, b = wave;
     uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
+    // At most three orders, side by side: their symbols are requested together, distances are immediate
+    // offsets, and what an order has of its own is worked out where it is needed.
+    const uint32_t ahead = KEEP ? 2u * uint32_t(lo - 1) : 2u;
     auto enter_block = [&](int32_t& v) __attribute__((always_inline)) {
       int32_t cur = KEEP ? v : int32_t(*lds<int16_t>(s));
-      uint32_t tag = first_tag, count = first_count, ahead = 2u * uint32_t(lo - 1);
-      int32_t last = *lds<int16_t>(s + ahead);
-#pragma unroll 1
-      for (int n = lo;; ++n) {
-        // (the next order's last symbol is requested with this order's entry)
-        const int32_t after = *lds<int16_t>(s + ahead + 2u);
-        const int32_t implied = *lds<int16_t>(sym_at + ahead + 2u * uint32_t(cur));
+      const uint32_t own = s + ahead, other = sym_at + ahead;
+      int32_t lasts[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) lasts[d] = *lds<int16_t>(own + 2u * d);
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        if (lo + d > hi) break;  // uniform
+        const int order = lo + d - 1 - swept;
+        const int32_t last = lasts[d];
         if (last >= 0) {  // (an absent symbol: no n-gram here)
-          const uint32_t h = ((uint32_t(cur) << id_bits) | uint32_t(last)) * table.multiplier + tag;
-          uint4 e = make_uint4(0u, 0u, 0u, 0u);
-          if (LOOK) e = table.bucket(table.home(h));
-          if (last != implied) cur = int32_t(table.claim<LOOK>(h, id, e));
-          if (!ROUGE || n == N) lds_add(count + __umul24(uint32_t(cur), W4), 1u);
+          const int32_t implied = *lds<int16_t>(other + 2u * uint32_t(cur) + 2u * d);
+          if (last != implied) {
+            const uint32_t h = ((uint32_t(cur) << id_bits) | uint32_t(last)) * table.multiplier +
+                               uint32_t(order) * tag_unit;
+            cur = int32_t(table.claim<LOOK>(h, id));
+          }
+          if (!ROUGE || lo + d == N) count_candidate(order, uint32_t(cur));
         }
-        if (n >= hi) break;  // uniform
-        last = after;
-        tag += tag_unit;
-        if (!ROUGE) count += set_bytes;
-        ahead += 2u;
+        if (!ROUGE && want_distinct) {
+          const int own_ids = __popcll(__builtin_amdgcn_ballot_w64(last >= 0 && cur == int32_t(id)));
+          distinct += lane == lo + d - 1 ? own_ids : 0;
+        }
       }
       if (KEEP) v = cur;
       id += nt;
       s += sym_stride;
       b += nwaves;
     };
+    // Lanes drop out where an n-gram is not the candidate's, and stay out for the orders behind it.
     auto look_up_block = [&](int32_t& v) __attribute__((always_inline)) {
       const int f = sequence_of(b);
-      const uint32_t addend = (f & 1) ? 0x10000u : 1u;
-      const uint32_t own = s + uint32_t(2 * kPadSymbols) * f;
-      int32_t cur = KEEP ? v : int32_t(*lds<int16_t>(own));
-      uint32_t ahead = 2u * uint32_t(lo - 1);
-      uint32_t tag = first_tag, count = first_count + 4u * uint32_t(f >> 1);
-      int32_t last = *lds<int16_t>(own + ahead);
-#pragma unroll 1
-      for (int n = lo;; ++n) {
-        const int32_t key = int32_t(uint32_t(cur) << id_bits) | last;
-        if (!__builtin_amdgcn_ballot_w64(key >= 0)) {  // uniform: nothing to extend
-          cur = -1;
-          break;
+      const uint32_t first = s + uint32_t(2 * kPadSymbols) * f;
+      const uint32_t own = first + ahead, other = sym_at + ahead;
+      int32_t lasts[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) lasts[d] = *lds<int16_t>(own + 2u * d);
+      int32_t left = -1;  // the id after these orders
+      bool match = false;
+      auto look_up = [&](auto depth, int32_t prefix, auto&& again) __attribute__((always_inline)) {
+        constexpr int d = decltype(depth)::value;
+        const int32_t key = int32_t(uint32_t(prefix) << id_bits) | lasts[d];
+        if (key < 0) return;
+        const int order = lo + d - 1 - swept;
+        const int32_t implied = *lds<int16_t>(other + 2u * uint32_t(prefix) + 2u * d);
+        const uint32_t x = table.find(uint32_t(key) * table.multiplier + uint32_t(order) * tag_unit,
+                                      [&] { return implied == lasts[d]; }, uint32_t(prefix));
+        if (x >= id_limit) return;
+        const bool counts = !ROUGE || lo + d == N;  // (uniform)
+        uint32_t word = 0;
+        if (counts) word = count_reference(order, f, x);
+        if (d == 2 || lo + d == hi) {  // (uniform)
+          left = int32_t(x);
+        } else {
+          if constexpr (d < 2) again(std::integral_constant<int, d + 1>{}, int32_t(x), again);
         }
-        const int32_t after = *lds<int16_t>(own + ahead + 2u);
-        const int32_t implied = *lds<int16_t>(sym_at + ahead + 2u * uint32_t(cur));
-        const uint32_t x = table.find(uint32_t(key) * table.multiplier + tag, uint32_t(key) & 0x80000000u,
-                                      last == implied, uint32_t(cur));
-        last = after;
-        const bool hit = x < id_limit;
-        cur = hit ? int32_t(x) : -1;
-        if (hit && (!ROUGE || n == N)) lds_add(count + __umul24(x, W4), addend);
-        if (n >= hi) break;  // uniform
-        tag += tag_unit;
-        if (!ROUGE) count += set_bytes;
-        ahead += 2u;
+        if (counts && matching) {
+          if (ROUGE) match = is_match(order, f, word);
+          else matches[d] += is_match(order, f, word) ? 1 : 0;
+        }
+      };
+      look_up(std::integral_constant<int, 0>{}, KEEP ? v : int32_t(*lds<int16_t>(first)), look_up);
+      if (ROUGE && hi == N) {
+        const int of_block = __popcll(__builtin_amdgcn_ballot_w64(match));
+        overlap += lane == f ? of_block : 0;
       }
-      if (KEEP) v = cur;
+      if (KEEP) v = left;
       s += sym_stride;
       b += nwaves;
     };
@@ -597,24 +771,29 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     }
     TB_FSTAMP(2 * lo + 1);
   }
+  if (!ROUGE && want_distinct) {
+    if (lane < N) lds_add(part_at + 32 + 4 * lane, uint32_t(distinct));
+    __syncthreads();
+  }
   TB_FSTAMP(20);
-  if (*lds<uint32_t>(lost_at)) {
+  const bool lost = *lds<uint32_t>(lost_at);
+  if (lost) {
     // Token ids chosen to collide: count by comparing n-grams, without a table.
     __syncthreads();
-    if (tid < 8 * 16) *lds<uint32_t>(part_at + 4 * tid) = 0u;
-    if (nt < 8 * 16 && tid < 64) *lds<uint32_t>(part_at + 4 * (tid + 64)) = 0u;
+    if (tid < 16) *lds<uint32_t>(part_at + 4 * tid) = 0u;
     if (ROUGE && tid < kMaxSeqs) *lds<uint32_t>(overlap_at + 4 * tid) = 0u;
     __syncthreads();
     // (pointers from the argument segment again: they need no registers until here)
     const Segment args = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
     typedef const void* const __attribute__((address_space(4)))* Pointers;
     const Pointers pointers = (Pointers)args;
-    const Token* const cand_row = static_cast<const Token*>(pointers[0]) + uint64_t(g) * uint32_t(cs);
-    const Token* const ref_row = static_cast<const Token*>(pointers[2]) + uint64_t(row0) * uint32_t(rs);
+    const char* const cand_row = static_cast<const char*>(pointers[0]) + uint64_t(uint32_t(g)) * (uint32_t(cs) * token_bytes);
+    const char* const ref_row = static_cast<const char*>(pointers[2]) + uint64_t(row0) * (uint32_t(rs) * token_bytes);
     const int32_t* const ref_lens = static_cast<const int32_t*>(pointers[3]);
-    auto token = [&](const Token* row, int i) {
-      const Token t = row[i];
-      return UToken(t) >= UToken(uint32_t(a.vocab)) ? 0 : int32_t(t);
+    auto token = [&](const char* row, int i) __attribute__((always_inline)) {
+      const uint64_t t = wide ? *reinterpret_cast<const uint64_t*>(row + 8 * int64_t(i))
+                              : *reinterpret_cast<const uint32_t*>(row + 4 * int64_t(i));
+      return t >= uint64_t(a.vocab) ? 0 : int32_t(t);
     };
 #pragma unroll 1
     for (int n = ROUGE ? N : 1; n <= N; ++n) {
@@ -622,7 +801,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
       for (int k = tid; k + n <= cand_len; k += nt) {
         // occurrences in row[0 .. len - 1] of the n-gram at candidate position k (at most one is
         // wanted with `once`)
-        auto occurrences = [&](const Token* row, int len, bool once) {
+        auto occurrences = [&](const char* row, int len, bool once) __attribute__((always_inline)) {
           int found = 0;
 #pragma unroll 1
           for (int i = 0; i + n <= len && !(once && found); ++i) {
@@ -639,11 +818,12 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
         for (int j = 0; j < used; ++j) {
           const int len = min(max(ref_lens[row0 + j], 0), rs);
           const int c = occurrences(
-              ref_row + int64_t(j) * rs, len, false);
+              ref_row + int64_t(j) * rs * token_bytes, len, false);
           mx = max(mx, c);
-          if (ROUGE && c) lds_add(overlap_at + 4u * j, uint32_t(min(cc, c)));
+          if (ROUGE) lds_add(overlap_at + 4u * j, uint32_t(min(cc, c)));
         }
-        lds_add(part_at + 64u * (n - 1), uint32_t(min(cc, mx) + 0x10000));
+        lds_add(part_at + 4u * uint32_t(n - 1), uint32_t(max(cc - mx, 0)));
+        lds_add(part_at + 32u + 4u * uint32_t(n - 1), 1u);
       }
     }
     __syncthreads();
@@ -652,46 +832,32 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   // wavefront 0: lane n < N owns order n + 1 (statistics out, one logarithm each)
   if (wave == 0) {
     const int c = cand_len;
-    // the wavefronts' sums of four orders in one request (16 lanes an order), added up across lanes:
-    // a loop over the wavefronts waited for LDS once each (16 x 256 7.0 -> 6.8 us with the pairs of
-    // orders in the sweep, 256 x 1088 9.9 -> 9.4, 1000 x 96 with up to eight references 11.3 -> 10.5)
-    auto four_orders = [&](uint32_t at) {
-      const uint32_t v = *lds<uint32_t>(at + 4u * uint32_t(lane));
-      const int mine = (lane & 15) < nwaves ? int(v) : 0;
-      return row_inclusive_scan(mine);  // lane 16 o + 15: order o
-    };
-    const int low = four_orders(part_at);
-    int sum = 0;
-#pragma unroll
-    for (int o = 0; o < 4; ++o) sum = lane == o ? lane_value(low, 16 * o + 15) : sum;
-    if (N > 4) {  // uniform
-      const int high = four_orders(part_at + 256u);
-#pragma unroll
-      for (int o = 0; o < 4; ++o) sum = lane == 4 + o ? lane_value(high, 16 * o + 15) : sum;
-    }
-    sum = lane < N ? sum : 0;
-    const int cn = sum & 0xFFFF;
-    const int tn = max(c - lane, 0);
     if (!ROUGE) {
-      if (lane < N) {
-        a.st.clipped[int64_t(g) * N + lane] = cn;
-        a.st.total[int64_t(g) * N + lane] = tn;
-        a.st.distinct[int64_t(g) * N + lane] = int(uint32_t(sum) >> 16);
-      }
-      // closest reference length, the shorter one on ties (lane j holds the length of sequence j;
-      // no reference at all: 0)
-      int best = lane_value(my_len, 1), bd = abs(best - c);
-      for (int j = 2; j <= used; ++j) {
-        const int l = lane_value(my_len, j), d = abs(l - c);
-        if (d < bd || (d == bd && l < best)) {
-          best = l;
-          bd = d;
-        }
-      }
-      const float score = bleu_from_stats_wave<int>(cn, tn, c, best, a.sp);
+      // (what the tail reads of the arguments: one request, with the sums)
+      // (a word holds the sum of the order in the lower half and, in the upper one, of the next order)
+      const uint32_t at = part_at + 4u * uint32_t(lane & 7);
+      const uint32_t here = *lds<uint32_t>(at), before = *lds<uint32_t>(lane & 7 ? at - 4u : lost_at);
+      const int sum = int((here & 0xFFFFu) + (before >> 16));
+      int32_t *clipped = a.st.clipped, *total = a.st.total, *closest = a.st.closest;
+      void* out = a.out;
+      ScoreParams sp;
+      sp.N = N;
+      sp.smoothing = a.sp.smoothing;
+      sp.param = a.sp.param;
+      sp.out_bf16 = a.sp.out_bf16;
+      asm volatile("" : "+s"(clipped), "+s"(total), "+s"(closest), "+s"(out), "+s"(sp.smoothing),
+                   "+s"(sp.param), "+s"(sp.out_bf16));
+      const float w = lane_weight(a.sp);
+      const int tn = max(c - lane, 0), cn = matching && !lost ? sum : tn - sum;
+      const float score = bleu_from_stats_wave<int>(cn, tn, c, best, brevity, w, sp);
       if (lane == 0) {
-        a.st.closest[g] = best;
-        if (a.out) store_score(a.out, g, score, a.sp.out_bf16);
+        if (out) store_score(out, g, score, sp.out_bf16);
+        closest[g] = best;
+      }
+      if (lane < N) {
+        clipped[int64_t(g) * N + lane] = cn;
+        total[int64_t(g) * N + lane] = tn;
+        if (want_distinct) a.st.distinct[int64_t(g) * N + lane] = int(*lds<uint32_t>(part_at + 32u + 4u * uint32_t(lane)));
       }
     } else {
       // lane j = 1..used: reference j - 1.  F is proportional to overlap / (cand + beta^2 ref)
@@ -731,14 +897,15 @@ int log2_ceil(int64_t v) {
   return b;
 }
 
-template <int BLOCKS, bool KEEP, bool WIDE, bool ROUGE>
+template <int BLOCKS, bool KEEP, Mode MODE>
 hipError_t launch_shape(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  const auto kernel = fused_kernel<BLOCKS, KEEP, WIDE, ROUGE>;
+  const auto kernel = fused_kernel<BLOCKS, KEEP, MODE>;
   hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), plan.lds_bytes);
   if (e != hipSuccess) return e;
   const uint32_t cand_shape = uint32_t(pb.cand_stride) | uint32_t(pb.R) << 16 |
                               uint32_t(log2_ceil(plan.threads / kWave)) << 24;
-  const uint32_t ref_shape = uint32_t(pb.ref_stride) | uint32_t(pb.N) << 16;
+  const uint32_t ref_shape = uint32_t(pb.ref_stride) | uint32_t(pb.N) << 16 |
+                             uint32_t(pb.tok64 ? 1 : 0) << 24;
   hipLaunchKernelGGL(kernel, dim3(uint32_t(pb.B)), dim3(plan.threads), plan.lds_bytes, s, pb.cand,
                      pb.cand_len, pb.refs, pb.ref_len, pb.ref_count, pb.ref_offsets, cand_shape,
                      ref_shape, a);
@@ -746,19 +913,19 @@ hipError_t launch_shape(const Problem& pb, const FusedArgs& a, const FusedPlan& 
 }
 template <int BLOCKS, bool KEEP>
 hipError_t launch_keep(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  if (pb.tok64)
-    return a.rouge_prf ? launch_shape<BLOCKS, KEEP, true, true>(pb, a, plan, s)
-                       : launch_shape<BLOCKS, KEEP, true, false>(pb, a, plan, s);
-  return a.rouge_prf ? launch_shape<BLOCKS, KEEP, false, true>(pb, a, plan, s)
-                     : launch_shape<BLOCKS, KEEP, false, false>(pb, a, plan, s);
+  if (a.rouge_prf) return launch_shape<BLOCKS, KEEP, kRouge>(pb, a, plan, s);
+  return pb.R == 1   ? launch_shape<BLOCKS, KEEP, kOneReference>(pb, a, plan, s)
+         : pb.R == 2 ? launch_shape<BLOCKS, KEEP, kTwoReferences>(pb, a, plan, s)
+                     : launch_shape<BLOCKS, KEEP, kReferences>(pb, a, plan, s);
 }
 template <int BLOCKS>
 hipError_t launch_blocks(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  return plan.keep ? launch_keep<BLOCKS, true>(pb, a, plan, s) : launch_keep<BLOCKS, false>(pb, a, plan, s);
+  return plan.keep ? launch_keep<BLOCKS, true>(pb, a, plan, s)
+                   : launch_keep<BLOCKS, false>(pb, a, plan, s);
 }
 
 constexpr size_t kLdsUnit = 1280;  // LDS is handed out in units of this size
-constexpr size_t kSumsBytes = 8 * 16 * 4 + 16 + kMaxSeqs * 4;
+constexpr size_t kSumsBytes = 64 + 16 + kMaxSeqs * 4;
 
 }  // namespace
 
@@ -779,18 +946,19 @@ bool fused_path_takes(int64_t cand_stride, int64_t ref_stride, int R, int bits) 
 
 namespace {
 
-// Passes of a plan: 0: all orders share a table; 1: order 1 on its own, then the others; 2: pairs;
-// 3: every order on its own.  Fills in pass_ends and the key widths; false: the key is too wide.
+// Passes of a plan: 0: orders 1 to 4 share a table; 1: order 1 on its own, then the others; 2: pairs;
+// 3: every order on its own.  (No pass has more than three orders above the first.)  Fills in pass_ends
+// and the key widths; false: the key is too wide.
 bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pass) {
   FusedPlan& p = *plan;
-  static const uint32_t kEnds[4] = {0u, 1u << 1, 0x154u, ~0u};  // bit n: a pass ends with order n
+  static const uint32_t kEnds[4] = {0x90u, 0x92u, 0x154u, ~0u};  // bit n: a pass ends with order n
   p.pass_ends = (N == 1 || (kEnds[passes] & 2u)) ? 1u : 0u;
   for (int n = 2; n <= N; ++n) {
     int end = n;
     while (end < N && !((kEnds[passes] >> end) & 1u)) ++end;
     p.pass_ends |= uint32_t(end) << (4 * (n - 1));
   }
-  static const int kOrders[4] = {8, 7, 2, 1};
+  static const int kOrders[4] = {4, 3, 2, 1};
   const int most = passes == 1 && N > 1 ? N - 1 : N;
   *orders_per_pass = kOrders[passes] < most ? kOrders[passes] : most;
   const int tag_bits = log2_ceil(*orders_per_pass);
@@ -801,7 +969,7 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
     p.first_payload = bits > p.later_payload ? bits : p.later_payload;
     p.first_key_bits = p.first_payload + tag_bits;
   }
-  p.keep = passes >= 2 && N > 2;
+  p.keep = N > 4 || (passes >= 2 && N > 2);  // (more than one pass above order 1)
   return p.first_key_bits <= 32 && p.later_key_bits <= 32;
 }
 
@@ -823,8 +991,8 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
   if (blocks > kMaxBlocks * 16) return false;
   FusedPlan& p = *plan;
   p.id_bits = cand_stride > 1 ? log2_ceil(cand_stride) : 1;
-  p.words = (R + 2) / 2;
-  p.set_words = (int(cand_stride) * p.words + 3) & ~3;
+  p.array_bytes = (int(cand_stride) * 4 + 15) & ~15;
+  const int order_fields = rouge || R <= 2 ? R : R + 1;
   const size_t sym_bytes = (size_t(blocks * kWave + (R + 1) * kPadSymbols) * 2 + 15) & ~size_t(15);
 
   // workgroups a compute unit gets, and with it its share of LDS and wavefronts
@@ -883,7 +1051,7 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
           int lg = lg_min;  // (a larger table than this costs more to clear than it saves)
           while ((int64_t(1) << lg) < (r == 1 ? 12 : 8) * entries) ++lg;
           for (; lg >= lg_min; --lg) {
-            const size_t front = (size_t(4) << lg) + size_t(rouge ? 1 : orders) * p.set_words * 4;
+            const size_t front = (size_t(4) << lg) + size_t(((rouge ? 1 : orders) * order_fields + 1) / 2) * p.array_bytes;
             p.lds_bytes = front + sym_bytes + kSumsBytes;
             if (p.lds_bytes > share) continue;
             p.log2_slots = lg;
@@ -900,8 +1068,8 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
 }
 
 hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs& st,
-                        const ScoreParams& sp, void* out_bleu_or_null, hipStream_t s,
-                        const RougeOut* rouge) {
+                        const ScoreParams& sp, void* out_bleu_or_null, bool want_distinct,
+                        hipStream_t s, const RougeOut* rouge) {
   FusedArgs a;
   a.status = pb.status;
   a.vocab = pb.vocab;
@@ -920,8 +1088,8 @@ hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs
   a.first_key_bits = plan.first_key_bits;
   a.later_payload = plan.later_payload;
   a.later_key_bits = plan.later_key_bits;
-  a.words = plan.words;
-  a.set_words = plan.set_words;
+  a.array_bytes = plan.array_bytes;
+  a.want_distinct = want_distinct ? 1 : 0;
   a.table_and_counters = plan.table_and_counters;
   a.off_sym = plan.off_sym;
   a.off_sums = plan.off_sums;

@@ -574,7 +574,8 @@ __global__ __launch_bounds__(1024) void hier_count_kernel(HierCountArgs a) {
         const int tn_read = __hip_atomic_load(&a.st.total[stat], __ATOMIC_RELAXED,
                                               __HIP_MEMORY_SCOPE_AGENT);
         const int cn_all = lane < N ? cn_read : 0, tn_all = lane < N ? tn_read : 0;
-        const float score = bleu_from_stats_wave(cn_all, tn_all, c, best, a.sp);
+        const float brevity = expf(1.0f - float(best) / float(c));
+        const float score = bleu_from_stats_wave(cn_all, tn_all, c, best, brevity, lane_weight(a.sp), a.sp);
         if (lane == 0) {
           a.st.closest[g] = best;
           store_score(a.score_out, g, score, a.sp.out_bf16);

@@ -63,7 +63,7 @@ struct FusedPlan {
   uint32_t pass_ends;      // see FusedArgs
   int log2_slots, id_bits;
   int first_payload, first_key_bits, later_payload, later_key_bits;
-  int words, set_words;
+  int array_bytes;
   int table_and_counters;  // 16-byte units
   uint32_t off_sym, off_sums;
   size_t lds_bytes;
@@ -206,9 +206,10 @@ struct RougeOut {
   int32_t* best;     // [B] or null
   float beta2;
 };
-// rouge == null: BLEU (statistics and, if out_bleu_or_null, per-sentence scores).
+// rouge == null: BLEU (statistics, st.distinct among them if want_distinct, and, if
+// out_bleu_or_null, per-sentence scores).
 hipError_t launch_fused(const Problem& pb, const FusedPlan& plan, const StatPtrs& st,
-                        const ScoreParams& sp, void* out_bleu_or_null, hipStream_t s,
-                        const RougeOut* rouge = nullptr);
+                        const ScoreParams& sp, void* out_bleu_or_null, bool want_distinct,
+                        hipStream_t s, const RougeOut* rouge = nullptr);
 
 }  // namespace tb

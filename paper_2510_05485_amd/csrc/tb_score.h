@@ -72,33 +72,49 @@ __device__ __forceinline__ float bleu_from_stats(const IntT* clipped, const IntT
   return bp * expf(logsum);
 }
 
+// Lane n's weight.  (Each goes through a register that the compiler cannot look into: a select between
+// fields in memory becomes a vector load from a selected address, 200 ns of a tail of 1000.)
+__device__ __forceinline__ float lane_weight(const ScoreParams& sp) {
+  const int lane = threadIdx.x & (kWave - 1);
+  float w = 0.0f;
+#pragma unroll
+  for (int n = 0; n < 8; ++n) {
+    float x = sp.w[n];
+    asm volatile("" : "+v"(x));
+    w = lane == n ? x : w;
+  }
+  return w;
+}
+
 // The same score, bit for bit, computed by one wavefront: lane n < N holds the statistics of
-// order n + 1, the four logarithms run side by side and so do the two exponentials.  All 64
-// lanes must be active; c and r are the same in every lane; the result is valid in every lane.
+// order n + 1, the logarithms run side by side.  All 64 lanes must be active; c, r and
+// brevity = expf(1 - r / c) are the same in every lane, w is lane_weight(); the result is valid in
+// every lane.
 template <typename IntT>
 __device__ __forceinline__ float bleu_from_stats_wave(IntT cn, IntT tn, IntT c, IntT r,
+                                                      float brevity, float w,
                                                       const ScoreParams& sp) {
   const int lane = threadIdx.x & (kWave - 1);
   const bool order_lane = lane < sp.N;
   const unsigned long long zero_mask = __builtin_amdgcn_ballot_w64(order_lane && cn == 0);
   const int zeros_seen = __popcll(zero_mask & ((2ull << lane) - 1ull));  // orders 1..lane+1
-  float w = sp.w[0];
-#pragma unroll
-  for (int n = 1; n < 8; ++n) w = (lane == n) ? sp.w[n] : w;
   bool dead = false;
   float t = 0.0f;
   if (order_lane) t = order_log_term<IntT>(lane + 1, cn, tn, zeros_seen, sp, w, &dead);
   const bool any_dead = __builtin_amdgcn_ballot_w64(dead) != 0ull;
   float logsum = 0.0f;
-#pragma unroll
-  for (int n = 0; n < 8; ++n)
+  auto add = [&](int n) {
     logsum = __fadd_rn(logsum, __int_as_float(lane_value(__float_as_int(t), n)));
-  const float x = lane == 0 ? logsum : 1.0f - float(r) / float(c);
-  const float y = expf(x);
-  const float e0 = __int_as_float(lane_value(__float_as_int(y), 0));
-  const float e1 = __int_as_float(lane_value(__float_as_int(y), 1));
+  };
+#pragma unroll
+  for (int n = 0; n < 4; ++n) add(n);
+  if (sp.N > 4) {  // uniform
+#pragma unroll
+    for (int n = 4; n < 8; ++n) add(n);
+  }
+  const float e0 = expf(logsum);
   if (c == 0 || (zero_mask & 1ull) || any_dead) return 0.0f;
-  return ((c > r) ? 1.0f : e1) * e0;
+  return ((c > r) ? 1.0f : brevity) * e0;
 }
 
 // Store score v as element i of `out`: fp32, or bfloat16 = the upper half of the fp32 pattern

@@ -100,3 +100,29 @@ def test_tokens_chosen_to_collide(N):
     w = syn.random_small(631, B=6, R=2, vocab=len(ids), max_len=400, min_len=300)
     w.cand, w.refs, w.vocab = ids[w.cand], ids[w.refs], vocab
     check(w, N)
+
+
+@pytest.mark.parametrize("N", [1, 2, 3, 5, 8])
+@pytest.mark.parametrize("R", [1, 2, 3, 4, 7])
+def test_counters(R, N):
+    # Counters of one, two and more references, an odd and an even number of orders in a pass, several
+    # passes: short cycles of tokens, so that counts are large and either side has more of an n-gram
+    # (differences below zero), with fewer references in use than there are rows.
+    w = syn.random_small(661 + R, B=40, R=R, vocab=3, max_len=200, min_len=1)
+    rng = np.random.default_rng(661 + 10 * R + N)
+    for i in range(0, w.B, 2):
+        n = int(rng.integers(1, 4))
+        w.cand[i] = np.arange(w.cand.shape[1]) % n
+        w.refs[i] = (np.arange(w.refs.shape[2]) // int(rng.integers(1, 5)) + i) % 3
+    used = rng.integers(1, R + 1, w.B).astype(np.int32)
+    ref = oracle.bleu(w.cand, w.cand_len, w.refs, w.ref_len, max_n=N, smoothing="exp", threads=8,
+                      ref_count=used)
+    stats = tb.Stats.allocate(w.B, N, DEV)
+    cfg = tb.make_config(max_n=N, smoothing="exp", vocab_size=w.vocab, ref_count=dev(used))
+    out = tb.tensorbleu_sentence(dev(w.cand), dev(w.cand_len), dev(w.refs), dev(w.ref_len), cfg, stats=stats)
+    np.testing.assert_array_equal(stats.clipped.cpu().numpy(), ref.clipped)
+    np.testing.assert_array_equal(stats.total.cpu().numpy(), ref.total)
+    np.testing.assert_array_equal(stats.closest_ref_len.cpu().numpy(), ref.closest_ref_len)
+    np.testing.assert_array_equal(stats.group_distinct.cpu().numpy(), ref.cand_distinct)
+    assert np.abs(out.cpu().numpy().astype(np.float64) - ref.bleu).max() <= TOL
+    check(w, N)
