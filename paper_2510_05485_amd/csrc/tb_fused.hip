@@ -298,6 +298,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   const bool prio = progress != 0;
   const uint32_t lost_at = part_at + 64;  // non-zero: a probe sequence was too long to be counted
   const uint32_t overlap_at = lost_at + 4;        // ROUGE: overlap with each reference
+  const uint32_t closest_at = lost_at + 4;        // BLEU: closest reference length, brevity penalty
   if (prio) __builtin_amdgcn_s_setprio(3);
 
   const uint32_t token_bytes = wide ? 8u : 4u;
@@ -358,10 +359,8 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   // This wavefront's blocks are wave, wave + nwaves, ... (the candidate's come first).  val[i]: the
   // token, then the symbol, of the lane's position (KEEP: then the id of the last finished order).
   int32_t val[BLOCKS];
-  int best = 0;
-  float brevity = 0.0f;
-  // Tokens are requested; while they are on their way, the lengths' part of the score is formed, table
-  // slots become free, counters zero, symbols behind the sequences absent.
+  // Tokens are requested; while they are on their way, table slots become free, counters zero, symbols
+  // behind the sequences absent.
   auto stage = [&](auto token_type) __attribute__((always_inline)) {
     typedef decltype(token_type) Token;
     typedef std::make_unsigned_t<Token> UToken;
@@ -380,10 +379,6 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
         GlobalToken p = reinterpret_cast<GlobalToken>(row_of(f)) + uint32_t(first);
         raw[i] = p[uint32_t(min(lane, left[i] - 1))];
       }
-    }
-    if (!ROUGE && wave == 0) {
-      best = closest_length();
-      brevity = expf(1.0f - float(best) / float(cand_len));
     }
     for (uint32_t q = tid; q < uint32_t(table_and_counters); q += nt)
       *lds<Quad>(16u * q) = Quad(0u);
@@ -531,6 +526,12 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
       s += sym_stride;
       b += nwaves;
     });
+    if (!ROUGE && wave == nwaves - 1) {
+      // the lengths' part of the score, for the tail: by the wavefront that has the fewest blocks
+      const int best = closest_length();
+      *lds<int32_t>(closest_at) = best;
+      *lds<float>(closest_at + 4) = expf(1.0f - float(best) / float(cand_len));
+    }
     __syncthreads();
     TB_FSTAMP(2);
     each_block(i, my_blocks, [&](int32_t& v) __attribute__((always_inline)) {
@@ -838,6 +839,8 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
       const uint32_t at = part_at + 4u * uint32_t(lane & 7);
       const uint32_t here = *lds<uint32_t>(at), before = *lds<uint32_t>(lane & 7 ? at - 4u : lost_at);
       const int sum = int((here & 0xFFFFu) + (before >> 16));
+      const int best = __builtin_amdgcn_readfirstlane(*lds<int32_t>(closest_at));
+      const float brevity = *lds<float>(closest_at + 4);
       int32_t *clipped = a.st.clipped, *total = a.st.total, *closest = a.st.closest;
       void* out = a.out;
       ScoreParams sp;
@@ -975,14 +978,21 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
 
 }  // namespace
 
-// What the choice weighs (times of kernels over some hundred plans and forty shapes):
+// What the choice weighs (all plans of 113 shapes timed, 8 to 4096 groups of 24 to 4096 tokens with one
+// to eight references, one to four orders; on average the choice is 1.4 % behind the best plan of a
+// shape, more than a tenth behind in five of them):
+//   * A pass costs its barriers, its sums, clearing the table and the block loop again, but has the
+//     counters of its orders only.  Up to four workgroups on a unit, all at once, want their exact share
+//     of LDS, whatever passes that takes (1024 x 2048: pairs, four a unit, 34.5 us; orders 1 to 4
+//     together, three a unit, 41).  Where there are more, fewer passes win with down to half as many of
+//     them side by side (4096 x 512 with two references: pairs, sixteen a unit, 44.9; orders 1 to 4 together, eight,
+//     37.9; 2493 x 711 with two 42.7 and 35.3).  Every order on its own only where nothing else fits.
 //   * A table that is nearly full costs more than anything else: probe sequences of the wavefront's
-//     slowest lane grow from 1 to 4 requests between a quarter and three quarters (twice the time).
-//   * A pass costs its barriers and the block loop again, but takes table and counters of its orders
-//     only: with few large workgroups on a unit fewer passes win, with many small ones (whose
-//     barriers the others fill) and short block loops (few references) more passes in less LDS do.
-//   * 32 wavefronts a unit hide latency; a workgroup with fewer blocks than wavefronts idles, and
-//     with two blocks or less per wavefront its prologue outweighs them.
+//     slowest lane grow from 1 to 4 requests between a quarter and three quarters.  More than twelve
+//     slots an entry cost more to clear than they save.
+//   * 32 wavefronts a unit hide latency (16 take 512 x 1024 with four references from 18.8 to 21.5 us);
+//     a workgroup with fewer blocks than wavefronts idles, and with two blocks or less per wavefront its
+//     prologue outweighs them.
 bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
                 bool rouge, FusedPlan* plan) {
   if (R + 1 > kMaxSeqs || cand_stride > 12288 || ref_stride > 65535 || bits > 31) return false;
@@ -994,75 +1004,62 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
   p.array_bytes = (int(cand_stride) * 4 + 15) & ~15;
   const int order_fields = rouge || R <= 2 ? R : R + 1;
   const size_t sym_bytes = (size_t(blocks * kWave + (R + 1) * kPadSymbols) * 2 + 15) & ~size_t(15);
+  const int resident = int(B > 256 * 32 ? 32 : (B + 255) / 256);  // workgroups a unit gets, if they fit
 
-  // workgroups a compute unit gets, and with it its share of LDS and wavefronts
-  int resident = 1;
-  while (resident < 32 && B > 256 * resident) resident *= 2;
-  // Nine or ten a unit: LDS for as many, not for sixteen, makes the tables emptier (2300 groups, us:
-  // one reference of 200 tokens 16.9 -> 14.5, of 500 27.2 -> 23.1; two of 256 25.6 -> 19.0; three of 200
-  // 23.9 -> 19.9).  It leaves a workgroup two wavefronts, where eight a unit have four: with more than
-  // eight blocks for each that costs more (two references of 500, 24 blocks: 32.0 -> 35.8), and so it does
-  // where counters of many references take the room (six of 97: 17.5 -> 18.5, four of 200 25.1 -> 28.2).
-  // Beyond 2560 groups ten a unit are two rounds (2700, two references of 200: 22.0 -> 26.3).
-  if (resident == 16 && B <= 2560 && R <= 3 && blocks <= 16) resident = B <= 2304 ? 9 : 10;
-  // share of the slots that may be taken if every row is full, in twelfths; the last resort comes
-  // after all numbers of workgroups have been tried with the others
-  static const int kTwelfths[3] = {5, 6, 9};
-  for (int last_resort = 0; last_resort < 2; ++last_resort) {
-    for (int r = resident; r >= 1; r = r == 9 || r == 10 ? 8 : r / 2) {
-      const size_t share = size_t(kLdsBudget) / r / kLdsUnit * kLdsUnit;
-      int waves = 1;
-      if (resident == 1) {  // the chip is not full: a wavefront for (nearly) each block
-        while (waves < 16 && 4 * waves < 3 * blocks) waves *= 2;
-      } else {
-        while (waves < 16 && 2 * waves <= 32 / r && blocks > waves * (waves < 4 ? 1 : waves < 8 ? 2 : 4))
-          waves *= 2;
-      }
-      while (waves < 16 && blocks > int64_t(kMaxBlocks) * waves) waves *= 2;
-      p.blocks = int((blocks + waves - 1) / waves);
-      p.threads = waves * kWave;
-      for (int level = last_resort ? 2 : 0; level < (last_resort ? 3 : 2); ++level) {
-        if (level == 1 && r >= 4 && R > 2) continue;  // (fewer workgroups first)
-        for (int passes = 0; passes < 4; ++passes) {
-          int orders;
-          if (!set_passes(passes, N, bits, plan, &orders)) continue;
-          // Three references, eight a unit: pairs instead of orders 2 to 4 in one table, which full rows
-          // fill to a third or more (us: 1561 groups of 283 tokens 20.1 -> 17.7, 1887 of 236 19.8 -> 18.2,
-          // 3435 of 276 31.9 -> 27.8).  Ragged rows fill it less, and the plan does not see lengths: over
-          // 140 shapes full or nearly full rows take 0.966 of the time (0.84 to 1.05), lengths down to a
-          // tenth 1.03 (0.88 to 1.11).  Not with more orders, whose pairs are more passes (1368 of 158, six
-          // orders, 15.9 -> 17.0).  One and two references gain on full rows (1561 of 283 with two 17.9 ->
-          // 15.8) what they lose on others, four and five do not differ, eight lose (1561 of 128 15.7 ->
-          // 16.7).  Nine or ten a unit: for one and two references, too (2264 of 276 17.3 -> 14.8, 2130 of
-          // 234 with two 20.4 -> 18.7; 150 shapes 0.85 to 1.03x).
-          if (passes == 1 && (R == 3 || r > 8) && r >= 8 && r <= 10 && N > 2 && N <= 4) continue;
-          if (level == 0 && passes == 3 && N > 2 && (r < 4 || R > 2)) continue;
-          const int64_t entries = cand_stride;
-          const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
-          int lg_min = 6;
-          while ((int64_t(kTwelfths[level]) << lg_min) < 12 * entries) ++lg_min;
-          // bits for the probe count.  A sequence that reaches the largest count sends the whole
-          // workgroup to the loop without a table, so ordinary tokens must not get there.  Every bucket
-          // further is reached by an eighth of the sequences at half load, by 0.43 of them at three
-          // quarters (look-ups and insertions of 128 x 8192 and 64 x 6144 Zipf-distributed tokens counted
-          // on the CPU): fifteen buckets were reached by 1e-9 of the groups and by one in twenty, sixty-three
-          // would be by 1e-19.
-          while (32 - widest + lg_min - 2 - p.id_bits < (level < 2 ? 4 : 6)) ++lg_min;
-          int lg = lg_min;  // (a larger table than this costs more to clear than it saves)
-          while ((int64_t(1) << lg) < (r == 1 ? 12 : 8) * entries) ++lg;
-          for (; lg >= lg_min; --lg) {
-            const size_t front = (size_t(4) << lg) + size_t(((rouge ? 1 : orders) * order_fields + 1) / 2) * p.array_bytes;
-            p.lds_bytes = front + sym_bytes + kSumsBytes;
-            if (p.lds_bytes > share) continue;
-            p.log2_slots = lg;
-            p.table_and_counters = int(front / 16);
-            p.off_sym = uint32_t(front);
-            p.off_sums = uint32_t(front + sym_bytes);
-            return true;
-          }
-        }
-      }
+  // r workgroups on a unit; the table may be half full if no n-gram repeats (three quarters: full)
+  auto fits = [&](int passes, int r, bool full) {
+    int orders;
+    if (!set_passes(passes, N, bits, plan, &orders)) return false;
+    int waves = 1;
+    if (resident <= 1) {  // the chip is not full: a wavefront for (nearly) each block
+      while (waves < 16 && 4 * waves < 3 * blocks) waves *= 2;
+    } else {
+      while (waves < 16 && 2 * waves <= 32 / r && blocks > waves * (waves < 4 ? 2 : waves < 8 ? 3 : 4))
+        waves *= 2;
     }
+    while (waves < 16 && blocks > int64_t(kMaxBlocks) * waves) waves *= 2;
+    // All orders of a pass together enter at most as many n-grams as the candidate has positions.
+    const int64_t entries = cand_stride;
+    const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
+    int lg_min = 6;
+    while ((int64_t(full ? 3 : 2) << lg_min) < 4 * entries) ++lg_min;
+    // bits for the probe count.  A sequence that reaches the largest count sends the whole
+    // workgroup to the loop without a table, so ordinary tokens must not get there.  Every bucket
+    // further is reached by an eighth of the sequences at half load, by 0.43 of them at three
+    // quarters (look-ups and insertions of 128 x 8192 and 64 x 6144 Zipf-distributed tokens counted
+    // on the CPU): fifteen buckets were reached by 1e-9 of the groups and by one in twenty, sixty-three
+    // would be by 1e-19.
+    while (32 - widest + lg_min - 2 - p.id_bits < (full ? 6 : 4)) ++lg_min;
+    int lg = lg_min;
+    while ((int64_t(1) << lg) < 12 * entries) ++lg;
+    const size_t share = size_t(kLdsBudget) / r / kLdsUnit * kLdsUnit;
+    const size_t counters = size_t(((rouge ? 1 : orders) * order_fields + 1) / 2) * p.array_bytes;
+    for (; lg >= lg_min; --lg) {
+      const size_t front = (size_t(4) << lg) + counters;
+      p.lds_bytes = front + sym_bytes + kSumsBytes;
+      if (p.lds_bytes > share) continue;
+      p.threads = waves * kWave;
+      p.blocks = int((blocks + waves - 1) / waves);
+      p.log2_slots = lg;
+      p.table_and_counters = int(front / 16);
+      p.off_sym = uint32_t(front);
+      p.off_sums = uint32_t(front + sym_bytes);
+      return true;
+    }
+    return false;
+  };
+  for (int full = 0; full < 2; ++full) {
+    int r = resident < 1 ? 1 : resident;
+    if (r > 4) {
+      const int shares[3] = {r, r * 7 / 10, r / 2};
+      for (int passes = 0; passes < 3; ++passes)
+        for (int share : shares)
+          if (fits(passes, share, full)) return true;
+      r = r / 2 - 1;
+    }
+    for (; r >= 1; --r)
+      for (int passes = 0; passes < (r > 1 ? 3 : 4); ++passes)
+        if (fits(passes, r, full)) return true;
   }
   return false;
 }
