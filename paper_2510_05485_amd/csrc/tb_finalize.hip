@@ -1,5 +1,7 @@
 // Score assembly from the integer statistics (paper Section 3.4): per-sentence scores, and the
 // corpus variant that sums numerators, denominators and lengths over the batch first.
+#include <type_traits>
+
 #include "tb_kernels.h"
 #include "tb_score.h"
 
@@ -34,14 +36,6 @@ __global__ __launch_bounds__(256) void sentence_score_kernel(FinalArgs a) {
               a.sp.out_bf16);
 }
 
-// Sum over the wavefront of a value in [0, 2^49) (its upper part then is below 2^25, 64 of these below
-// 2^31): two 32-bit DPP scans, no LDS round trips.
-__device__ __forceinline__ long long wave_sum64(long long v) {
-  const int lo = wave_sum(int(v & 0xFFFFFF));
-  const int hi = wave_sum(int(v >> 24));
-  return ((long long)(hi) << 24) + lo;
-}
-
 // A single workgroup strides over the batch and reduces the 2N+2 integer sums; wavefront 0 forms
 // the corpus score, one order per lane.
 //
@@ -50,22 +44,27 @@ __device__ __forceinline__ long long wave_sum64(long long v) {
 // round trip per 4096 sentences), the totals are recomputed from the lengths instead of read, and
 // KNOWN_CLOSEST (the per-sentence pass has stored the closest reference lengths, as the fused
 // kernel does) reads them instead of walking the references again.  Measured at B = 4096, N = 4,
-// R = 2: the call with corpus sums 74.4 us before (25 us of it this kernel), 54.4 us now.
-// FOUR_ORDERS: N = 4, one 16-byte request per sentence.
-template <bool KNOWN_CLOSEST, bool FOUR_ORDERS>
+// R = 2: 25 us with a round trip per field and sentence.
+// FOUR_ORDERS: N = 4, one 16-byte request per sentence.  Sum: int32_t where the host knows that no sum
+// leaves it (B times the longer stride), else int64_t, added up across lanes 20 bits at a time.  With sums
+// of 64 bits everywhere and a loop over the wavefronts' parts in LDS, which waited for each, the kernel
+// took 5.4 us instead of 3.5 (2000 x 64 corpus BLEU 12.4 -> 10.5, 1024 x 2048 35.0 -> 33.0).
+template <bool KNOWN_CLOSEST, bool FOUR_ORDERS, typename Sum>
 __global__ __launch_bounds__(1024) void corpus_kernel(FinalArgs a, int write_score) {
   constexpr int kUnroll = 4, kOrders = FOUR_ORDERS ? 4 : 8;
   struct __attribute__((packed, aligned(4))) Quad {  // the caller's array may be 4-byte aligned
     int32_t v[4];
   };
-  __shared__ long long part[18][16];
+  constexpr int kRows = 2 * kOrders + 4;  // sums, four (16 lanes each) to a register of wavefront 0
+  __shared__ int32_t part[kRows][16];
   __shared__ int s_spoilt;
   const Problem& pb = a.pb;
   const int tid = threadIdx.x, nt = blockDim.x, N = pb.N;
   if (tid == 0) s_spoilt = 0;
-  long long acc[18];  // clipped_1..8, total_1..8, candidate lengths, closest reference lengths
+  // clipped, total, candidate lengths, closest reference lengths
+  Sum acc[2 * kOrders + 2];
 #pragma unroll
-  for (int k = 0; k < 18; ++k) acc[k] = 0;
+  for (int k = 0; k < 2 * kOrders + 2; ++k) acc[k] = 0;
   bool spoilt = false;  // some group's dictionary overflowed
   for (int base = 0; base < pb.B; base += kUnroll * nt) {
     int c[kUnroll], r[kUnroll], cl[kUnroll][kOrders];
@@ -98,42 +97,69 @@ __global__ __launch_bounds__(1024) void corpus_kernel(FinalArgs a, int write_sco
 #pragma unroll
       for (int n = 0; n < kOrders; ++n) {
         acc[n] += cl[u][n];
-        acc[8 + n] += max(c[u] - n, 0);
+        acc[kOrders + n] += max(c[u] - n, 0);
       }
-      acc[16] += c[u];
-      acc[17] += r[u];
+      acc[2 * kOrders] += c[u];
+      acc[2 * kOrders + 1] += r[u];
     }
   }
   const int lane = tid & (kWave - 1), wave = tid / kWave;
-  __syncthreads();  // s_spoilt is cleared
-  if (spoilt) s_spoilt = 1;
-#pragma unroll
-  for (int k = 0; k < 18; ++k) {
-    if ((k & 7) >= N && k < 16) continue;  // uniform
-    const long long s = wave_sum64(acc[k]);
-    if (lane == 0) part[k][wave] = s;
+  if (!KNOWN_CLOSEST) {
+    __syncthreads();  // s_spoilt is cleared
+    if (spoilt) s_spoilt = 1;
   }
-  __syncthreads();
-  if (wave == 0) {
-    // lane k < 18: the batch's sum k
-    long long tot = 0;
-    const int k = min(lane, 17), nwaves = nt / kWave;
-    for (int w = 0; w < nwaves; ++w) tot += part[k][w];
-    auto sum_of = [&](int src) {  // (src is the same in every lane)
-      const uint32_t lo = uint32_t(lane_value(int(uint32_t(uint64_t(tot))), src));
-      const uint32_t hi = uint32_t(lane_value(int(uint32_t(uint64_t(tot) >> 32)), src));
-      return (long long)((uint64_t(hi) << 32) | lo);
-    };
-    if (lane < 8 && lane < N) a.st.corpus[lane] = tot;
-    if (lane >= 8 && lane < 8 + N) a.st.corpus[N + lane - 8] = tot;
-    if (lane == 16 || lane == 17) a.st.corpus[2 * N + lane - 16] = tot;
-    if (write_score) {
-      const long long c = sum_of(16), r = sum_of(17);
-      long long tn = 0;  // lane n < N: the total of order n + 1
+  Sum tot[kRows / 4] = {};  // lane 16 q + 15: sum 4 k + q
+  constexpr int kStep = sizeof(Sum) == 4 ? 32 : 20;
+#pragma unroll 1
+  for (int shift = 0; shift < int(8 * sizeof(Sum)); shift += kStep) {
+    if (shift) __syncthreads();  // the parts before have been read
 #pragma unroll
-      for (int n = 0; n < 8; ++n) tn = lane == n ? sum_of(8 + n) : tn;
+    for (int k = 0; k < 2 * kOrders + 2; ++k) {
+      const int v = wave_inclusive_scan(
+          sizeof(Sum) == 4 ? int(acc[k]) : int((int64_t(acc[k]) >> shift) & 0xFFFFF));
+      if (lane == kWave - 1) part[k][wave] = v;
+    }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+      for (int k = 0; k < kRows / 4; ++k) {
+        const int v = row_inclusive_scan(part[min(4 * k + lane / 16, 2 * kOrders + 1)][lane & 15]);
+        tot[k] += Sum(sizeof(Sum) == 4 ? int64_t(v) : int64_t(uint32_t(v)) << shift);
+      }
+    }
+  }
+  if (wave == 0) {
+    const int row = lane / 16;
+    if ((lane & 15) == 15) {
+#pragma unroll
+      for (int k = 0; k < kOrders / 4; ++k) {
+        const int n = 4 * k + row;
+        if (n < N) {
+          a.st.corpus[n] = tot[k];
+          a.st.corpus[N + n] = tot[kOrders / 4 + k];
+        }
+      }
+      if (row < 2) a.st.corpus[2 * N + row] = tot[kRows / 4 - 1];
+    }
+    if (write_score) {
+      // the value that lane `from` holds, in every lane (a lane may ask for another one)
+      auto value_of = [&](Sum v, int from) {
+        const uint64_t w = uint64_t(int64_t(v));
+        const uint32_t lo = uint32_t(__builtin_amdgcn_ds_bpermute(4 * from, int(uint32_t(w))));
+        if (sizeof(Sum) == 4) return Sum(int32_t(lo));
+        const uint32_t hi = uint32_t(__builtin_amdgcn_ds_bpermute(4 * from, int(uint32_t(w >> 32))));
+        return Sum(uint64_t(hi) << 32 | lo);
+      };
+      const int from = 16 * (lane & 3) + 15;  // lane n: order n + 1
+      Sum cn = value_of(tot[0], from), tn = value_of(tot[kOrders / 4], from);
+      if (!FOUR_ORDERS) {
+        const Sum cn1 = value_of(tot[1], from), tn1 = value_of(tot[kOrders / 4 + 1], from);
+        cn = lane & 4 ? cn1 : cn;
+        tn = lane & 4 ? tn1 : tn;
+      }
+      const Sum c = value_of(tot[kRows / 4 - 1], 15), r = value_of(tot[kRows / 4 - 1], 31);
       const float brevity = expf(1.0f - float(r) / float(c));
-      const float score = bleu_from_stats_wave<long long>(tot, tn, c, r, brevity, lane_weight(a.sp), a.sp);
+      const float score = bleu_from_stats_wave<Sum>(cn, tn, c, r, brevity, lane_weight(a.sp), a.sp);
       if (lane == 0)
         store_score(a.out, 0, s_spoilt ? __int_as_float(0x7FC00000) : score, a.sp.out_bf16);
     }
@@ -224,11 +250,19 @@ hipError_t launch_finalize(const Problem& pb, const StatPtrs& st, const ScorePar
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, s, a, score);
     };
-    const bool four = pb.N == 4;
+    const bool narrow =
+        pb.B * (pb.cand_stride > pb.ref_stride ? pb.cand_stride : pb.ref_stride) < (int64_t(1) << 31);
+    auto choose = [&](auto known, auto four) {
+      constexpr bool k = decltype(known)::value, f = decltype(four)::value;
+      narrow ? launch(corpus_kernel<k, f, int32_t>) : launch(corpus_kernel<k, f, int64_t>);
+    };
+    auto choose_orders = [&](auto known) {
+      pb.N == 4 ? choose(known, std::true_type{}) : choose(known, std::false_type{});
+    };
     if (known_closest || sentence_scores)
-      four ? launch(corpus_kernel<true, true>) : launch(corpus_kernel<true, false>);
+      choose_orders(std::true_type{});
     else
-      four ? launch(corpus_kernel<false, true>) : launch(corpus_kernel<false, false>);
+      choose_orders(std::false_type{});
     return hipGetLastError();
   }
   return hipSuccess;

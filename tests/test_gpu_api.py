@@ -260,3 +260,22 @@ def test_two_streams_with_their_own_workspaces_run_side_by_side():
     sa.check(); sb.check()
     ref = oracle.bleu(wb.cand, wb.cand_len, wb.refs, wb.ref_len, smoothing="exp")
     assert np.abs(serial_b.cpu().numpy() - ref.bleu).max() <= 1e-5
+
+
+def test_corpus_sums_beyond_32_bits():
+    # B times the longer stride is above 2^31, and so is the sum of the reference lengths: every token
+    # is 0, so a candidate matches all its n-grams
+    B, cs, rs, N = 200_000, 64, 11_000, 4
+    rng = np.random.default_rng(71)
+    cl = rng.integers(1, cs + 1, B).astype(np.int32)
+    rl = rng.integers(rs - 50, rs + 1, (B, 1)).astype(np.int32)
+    cand = torch.zeros((B, cs), dtype=torch.int32, device=DEV)
+    refs = torch.zeros((B, 1, rs), dtype=torch.int32, device=DEV)
+    scorer = tb.BleuScorer(B, 1, cs, rs, vocab_size=10, max_n=N, smoothing="exp", device=DEV, want_stats=True)
+    score = scorer.corpus(cand, torch.from_numpy(cl).to(DEV), refs, torch.from_numpy(rl).to(DEV))
+    totals = [int(np.maximum(cl.astype(np.int64) - n, 0).sum()) for n in range(N)]
+    c, r = int(cl.sum(dtype=np.int64)), int(rl.sum(dtype=np.int64))
+    assert r > 2**31
+    assert scorer.stats.corpus_stats.cpu().tolist() == totals + totals + [c, r]
+    want = oracle.bleu_from_stats(totals, totals, c, r, [1.0 / N] * N, smoothing="exp")
+    assert abs(float(score) - want) <= 1e-5
