@@ -133,6 +133,8 @@ struct SymbolTable {
   int log2_buckets;
   uint32_t multiplier;   // odd << (32 - key bits)
   uint32_t id_limit;     // 1 << id_bits
+  uint32_t limit;        // the same in a vector register: with the shift count one instruction may not
+                         // read two scalar registers
   uint32_t longest;      // largest probe count an entry can hold, << id_bits
   uint32_t lost_at;      // LDS word set to 1 when a probe sequence reaches that count
 
@@ -163,7 +165,7 @@ struct SymbolTable {
     p.s = home(h);
     p.e = bucket(p.s);
     __builtin_amdgcn_sched_barrier(0);  // (whatever known() waits for is on its way with the bucket)
-    p.mine = (h << log2_buckets) + id_limit;
+    p.mine = (h << log2_buckets) + limit;
     p.x = known() ? id : match(p.e, p.mine);
     if (min(p.x, p.e.w) >= id_limit) {
       const uint32_t remainder = h << log2_buckets;
@@ -187,7 +189,7 @@ struct SymbolTable {
   // wavefront entered something there) goes on with the next slot.
   template <bool LOOK>
   __device__ __forceinline__ uint32_t claim(uint32_t h, uint32_t id) const {
-    uint32_t s = home(h), mine = (h << log2_buckets) + id_limit;
+    uint32_t s = home(h), mine = (h << log2_buckets) + limit;
     if (LOOK) {
       const Probe p = probe(h, [] { return false; }, 0u);
       if (p.x < id_limit) return p.x;
@@ -330,6 +332,14 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     if (FEW) return (b >= cand_blocks ? 1 : 0) + (TWO && b >= begin1 ? 1 : 0);
     return int(__popcll(__builtin_amdgcn_ballot_w64(ends <= b)));
   };
+  auto reference_of = [&](int b) __attribute__((always_inline)) {  // the same, of a block behind the candidate's
+    if (FEW) {
+      int f = 1;
+      if (TWO && b >= begin1) f = 2;
+      return f;
+    }
+    return sequence_of(b);
+  };
   // position of block b of sequence f in its row
   auto first_of = [&](int b, int f) __attribute__((always_inline)) {
     if (FEW) return (b - pick<TWO>(f, 0, cand_blocks, begin1)) << 6;
@@ -371,14 +381,16 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
       const int b = wave + (i << log2_waves);
       raw[i] = 0;
       left[i] = 0;
-      if (b < blocks) {  // uniform
-        const int f = sequence_of(b);
-        const int first = first_of(b, f);
-        left[i] = length_of(f) - first;
-        typedef const Token __attribute__((address_space(1)))* GlobalToken;
-        GlobalToken p = reinterpret_cast<GlobalToken>(row_of(f)) + uint32_t(first);
-        raw[i] = p[uint32_t(min(lane, left[i] - 1))];
-      }
+      // (uniform; blocks that are not there are not touched any more.  With more references the other
+      // form is the better one: the values set above need no registers)
+      if (FEW && b >= blocks) break;
+      if (b >= blocks) continue;
+      const int f = sequence_of(b);
+      const int first = first_of(b, f);
+      left[i] = length_of(f) - first;
+      typedef const Token __attribute__((address_space(1)))* GlobalToken;
+      GlobalToken p = reinterpret_cast<GlobalToken>(row_of(f)) + uint32_t(first);
+      raw[i] = p[uint32_t(min(lane, left[i] - 1))];
     }
     for (uint32_t q = tid; q < uint32_t(table_and_counters); q += nt)
       *lds<Quad>(16u * q) = Quad(0u);
@@ -392,6 +404,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < BLOCKS; ++i) {
+      if (FEW && wave + (i << log2_waves) >= blocks) break;  // uniform
       // a token outside the vocabulary is reported and taken as 0
       const bool outside = UToken(raw[i]) >= vocab;
       const bool here = lane < left[i];
@@ -412,9 +425,11 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
 
   // The blocks at hand are val[0], ..., finished ones rotate to the end (a register array cannot be
   // indexed by a loop counter).  A rotation moves all of them, so they are taken in groups of up to
-  // four, as far as full ones go: 128 x 8192 48.5 -> 46.7 us, 128 x 5000 29.5 -> 28.7.
+  // four, as far as full ones go (128 x 8192 48.5 -> 46.7 us, 128 x 5000 29.5 -> 28.7); where only order 1
+  // keeps them in registers, in twos (4096 x 2048 with two references 109.0 -> 106.5; four are no better, and
+  // with more references, whose kernels are short of registers, twos cost a tenth).
   constexpr bool LOOK = KEEP || BLOCKS > 6;  // (see claim)
-  constexpr int GROUP = !KEEP ? 1 : BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
+  constexpr int GROUP = !KEEP ? (FEW && BLOCKS >= 8 ? 2 : 1) : BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
   auto rotate = [&](auto by) __attribute__((always_inline)) {
     constexpr int n = decltype(by)::value;
     int32_t first[n];
@@ -447,6 +462,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   table.home_shift = 30 - lg;
   table.log2_buckets = lg - 2;
   table.id_limit = 1u << id_bits;
+  asm("v_mov_b32 %0, %1" : "=v"(table.limit) : "s"(table.id_limit));
   table.lost_at = lost_at;
   const uint32_t id_limit = table.id_limit;
   auto set_key_bits = [&](int key_bits) __attribute__((always_inline)) {
@@ -535,7 +551,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     __syncthreads();
     TB_FSTAMP(2);
     each_block(i, my_blocks, [&](int32_t& v) __attribute__((always_inline)) {
-      const int f = sequence_of(b);
+      const int f = reference_of(b);
       int32_t got = -1;
       bool match = false;
       if (v >= 0) {
@@ -715,7 +731,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     };
     // Lanes drop out where an n-gram is not the candidate's, and stay out for the orders behind it.
     auto look_up_block = [&](int32_t& v) __attribute__((always_inline)) {
-      const int f = sequence_of(b);
+      const int f = reference_of(b);
       const uint32_t first = s + uint32_t(2 * kPadSymbols) * f;
       const uint32_t own = first + ahead, other = sym_at + ahead;
       int32_t lasts[3];
