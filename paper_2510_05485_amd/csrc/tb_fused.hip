@@ -366,6 +366,31 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     return used > 0 ? wave_min(key) & 0x7FFF : 0;
   };
 
+  SymbolTable table;
+  auto set_key_bits = [&](int key_bits) __attribute__((always_inline)) {
+    const int count_bits = min(32 - key_bits + lg - 2 - id_bits, 32 - id_bits);
+    table.multiplier = 0x9E3779B1u << (32 - key_bits);
+    table.longest = ((1u << count_bits) - 1u) << id_bits;
+  };
+  const uint32_t cnt_at = 4u << lg;
+  uint32_t array_bytes = 0;
+  int want = 0;
+  // (pinned, so that nothing of this is left for after the barrier)
+  auto set_up = [&]() __attribute__((always_inline)) {
+    table.bucket_mask = (((1u << lg) - 1u) << 2) & ~15u;
+    table.home_shift = 30 - lg;
+    table.log2_buckets = lg - 2;
+    table.id_limit = 1u << id_bits;
+    table.lost_at = lost_at;
+    set_key_bits(a.first_key_bits);
+    array_bytes = uint32_t(a.array_bytes);
+    want = a.want_distinct;
+    asm volatile("v_mov_b32 %0, %1" : "=v"(table.limit) : "s"(table.id_limit));
+    asm volatile("" : "+s"(table.bucket_mask), "+s"(table.home_shift), "+s"(table.log2_buckets),
+                 "+s"(table.id_limit), "+s"(table.multiplier), "+s"(table.longest), "+s"(array_bytes),
+                 "+s"(want));
+  };
+
   // This wavefront's blocks are wave, wave + nwaves, ... (the candidate's come first).  val[i]: the
   // token, then the symbol, of the lane's position (KEEP: then the id of the last finished order).
   int32_t val[BLOCKS];
@@ -392,6 +417,7 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
       GlobalToken p = reinterpret_cast<GlobalToken>(row_of(f)) + uint32_t(first);
       raw[i] = p[uint32_t(min(lane, left[i] - 1))];
     }
+    set_up();
     for (uint32_t q = tid; q < uint32_t(table_and_counters); q += nt)
       *lds<Quad>(16u * q) = Quad(0u);
     if (wave == 0 && lane <= R) {
@@ -457,20 +483,6 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
     }
   };
 
-  SymbolTable table;
-  table.bucket_mask = (((1u << lg) - 1u) << 2) & ~15u;
-  table.home_shift = 30 - lg;
-  table.log2_buckets = lg - 2;
-  table.id_limit = 1u << id_bits;
-  asm("v_mov_b32 %0, %1" : "=v"(table.limit) : "s"(table.id_limit));
-  table.lost_at = lost_at;
-  const uint32_t id_limit = table.id_limit;
-  auto set_key_bits = [&](int key_bits) __attribute__((always_inline)) {
-    const int count_bits = min(32 - key_bits + lg - 2 - id_bits, 32 - id_bits);
-    table.multiplier = 0x9E3779B1u << (32 - key_bits);
-    table.longest = ((1u << count_bits) - 1u) << id_bits;
-  };
-  const uint32_t cnt_at = 4u << lg;
   // Counters: 16-bit fields, two a word, the words of all ids in one array per pair of fields.
   //   * One reference, and ROUGE-N: a field is the n-gram's count in the candidate less what the
   //     reference has had of it so far (a negative lower half borrows from the upper one).  A reference's
@@ -480,7 +492,6 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   //   * Two references: count less the reference's count, one field each; the smaller one is what the
   //     candidate has beyond both.
   //   * More: the count in the candidate, then the counts in the references.
-  const uint32_t array_bytes = uint32_t(a.array_bytes);
   constexpr bool matching = ONE || ROUGE;
   constexpr bool differences = MODE != kReferences;
   const int order_fields = differences ? R : R + 1;
@@ -512,7 +523,6 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   };
   int matches1 = 0, matches[3] = {0, 0, 0};  // of this lane: order 1, orders lo.. of the pass
   int overlap = 0;                           // ROUGE: lane f: matches with reference f
-  const bool want_distinct = a.want_distinct;
   int distinct = 0;  // lane n - 1: this wavefront's positions whose n-gram has their id
   const int my_cand_blocks = (max(cand_blocks - wave, 0) + nwaves - 1) >> log2_waves;
   const int my_blocks = (max(blocks - wave, 0) + nwaves - 1) >> log2_waves;
@@ -521,8 +531,10 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   const uint32_t first_sym = sym_at + 2u * uint32_t(kWave * wave + lane);
   const uint32_t sym_stride = 2u * uint32_t(nt);
 
+  const uint32_t id_limit = table.id_limit;
+  const bool want_distinct = want;
+
   // ---- order 1: tokens become symbols
-  set_key_bits(a.first_key_bits);
   {
     int i = 0, b = wave;
     uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
