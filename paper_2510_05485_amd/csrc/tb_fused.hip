@@ -229,16 +229,13 @@ __device__ __forceinline__ T pick(int f, T cand, T ref, T ref1) {
 
 // BLOCKS: blocks of 64 positions per wavefront.  KEEP: a pass starts above order 2, with the ids of
 // the order below.
-// (The scalar-register cap keeps two 1024-thread workgroups on a compute unit: eight wavefronts per
-// SIMD need at most 80 scalar registers each on this hardware.)
 template <int BLOCKS, bool KEEP, Mode MODE>
-__global__ __launch_bounds__(1024, 8) __attribute__((amdgpu_num_sgpr(80)))
-void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
+__device__ __forceinline__
+void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
                   const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
-                  uint32_t cand_shape, uint32_t ref_shape, FusedArgs by_value) {
-  // The struct is read through the kernel-argument segment where its fields are used: loads of a
+                  uint32_t cand_shape, uint32_t ref_shape) {
+  // The struct behind the plain arguments is read through the kernel-argument segment where its fields are used: loads of a
   // by-value parameter all stand at the entry and would occupy scalar registers throughout.
-  (void)by_value;
   typedef const char __attribute__((address_space(4)))* Segment;
   const FusedArgs& a =
       *(const FusedArgs*)((Segment)__builtin_amdgcn_kernarg_segment_ptr() + kRegisterArgs);
@@ -922,15 +919,43 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   TB_FSTAMP(21);
 }
 
+// (The scalar-register cap keeps two 1024-thread workgroups on a compute unit: eight wavefronts per
+// SIMD need at most 80 scalar registers each on this hardware.)
+template <int BLOCKS, bool KEEP, Mode MODE>
+__global__ __launch_bounds__(1024, 8) __attribute__((amdgpu_num_sgpr(80)))
+void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
+                  const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
+                  uint32_t cand_shape, uint32_t ref_shape, FusedArgs by_value) {
+  fused_group<BLOCKS, KEEP, MODE>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
+                                  ref_shape);
+}
+// The same where a compute unit has one workgroup at most, which waits for each of its instructions: with
+// as many scalar registers as it likes (25 to 50 of them move to lanes of a vector register and back
+// otherwise).  us: 3 x 124 with three references 9.84 -> 9.41, 142 x 93 with eight 10.5 -> 10.3, 16 x 256
+// 6.03 -> 5.98.
+template <int BLOCKS, bool KEEP, Mode MODE>
+__global__ __launch_bounds__(1024, 4)
+void fused_kernel_alone(const void* cand, const int32_t* cand_lens, const void* refs,
+                        const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
+                        uint32_t cand_shape, uint32_t ref_shape, FusedArgs by_value) {
+  fused_group<BLOCKS, KEEP, MODE>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
+                                  ref_shape);
+}
+
 int log2_ceil(int64_t v) {
   int b = 0;
   while ((int64_t(1) << b) < v) ++b;
   return b;
 }
 
-template <int BLOCKS, bool KEEP, Mode MODE>
+template <int BLOCKS, bool KEEP, Mode MODE, bool ALONE>
 hipError_t launch_shape(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  const auto kernel = fused_kernel<BLOCKS, KEEP, MODE>;
+  const auto kernel = [] {  // (the other one is not to be instantiated)
+    if constexpr (ALONE)
+      return fused_kernel_alone<BLOCKS, KEEP, MODE>;
+    else
+      return fused_kernel<BLOCKS, KEEP, MODE>;
+  }();
   hipError_t e = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), plan.lds_bytes);
   if (e != hipSuccess) return e;
   const uint32_t cand_shape = uint32_t(pb.cand_stride) | uint32_t(pb.R) << 16 |
@@ -942,12 +967,20 @@ hipError_t launch_shape(const Problem& pb, const FusedArgs& a, const FusedPlan& 
                      ref_shape, a);
   return hipGetLastError();
 }
+template <int BLOCKS, bool KEEP, bool ALONE>
+hipError_t launch_mode(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
+  if (a.rouge_prf) return launch_shape<BLOCKS, KEEP, kRouge, ALONE>(pb, a, plan, s);
+  return pb.R == 1   ? launch_shape<BLOCKS, KEEP, kOneReference, ALONE>(pb, a, plan, s)
+         : pb.R == 2 ? launch_shape<BLOCKS, KEEP, kTwoReferences, ALONE>(pb, a, plan, s)
+                     : launch_shape<BLOCKS, KEEP, kReferences, ALONE>(pb, a, plan, s);
+}
 template <int BLOCKS, bool KEEP>
 hipError_t launch_keep(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  if (a.rouge_prf) return launch_shape<BLOCKS, KEEP, kRouge>(pb, a, plan, s);
-  return pb.R == 1   ? launch_shape<BLOCKS, KEEP, kOneReference>(pb, a, plan, s)
-         : pb.R == 2 ? launch_shape<BLOCKS, KEEP, kTwoReferences>(pb, a, plan, s)
-                     : launch_shape<BLOCKS, KEEP, kReferences>(pb, a, plan, s);
+  // (the larger plans spend their time in loops, where the registers suffice: 0.6 to 1 % to gain)
+  if constexpr (!KEEP && BLOCKS <= 6) {
+    if (pb.B <= 256) return launch_mode<BLOCKS, KEEP, true>(pb, a, plan, s);
+  }
+  return launch_mode<BLOCKS, KEEP, false>(pb, a, plan, s);
 }
 template <int BLOCKS>
 hipError_t launch_blocks(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
