@@ -96,6 +96,19 @@ def test_rouge_n_beyond_the_fused_plans(seed, B, R, V, L, parts):
     check(w, 2, beta=0.5, ref_count=syn.ref_counts(seed, w.B, w.R) if R > 1 else None)
 
 
+@pytest.mark.parametrize("seed,B,R,V,L,n", [
+    (541, 38, 1, 50257, 8192, 2),     # the last group count on the sorted runs,
+    (542, 39, 1, 50257, 8192, 2),     # the first one with a workgroup a group
+    (543, 1, 3, 300, 5000, 1),        # a single group, one workgroup
+    (544, 1, 62, 3000, 250, 4),
+    (545, 8, 24, 300, 900, 3),
+])
+def test_rouge_n_on_both_sides_of_the_sorted_runs_line(seed, B, R, V, L, n):
+    w = syn.random_small(seed, B=B, R=R, vocab=V, max_len=L, min_len=0 if R > 1 else L // 2)
+    check(w, n)
+    check(w, n, ref_count=syn.ref_counts(seed, w.B, w.R) if R > 1 else None, int64=True)
+
+
 def test_rouge_n_closed_forms_and_unsupported_shapes():
     L = 64
     ref = np.arange(100, 100 + L, dtype=np.int32)
