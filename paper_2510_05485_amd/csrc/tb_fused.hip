@@ -929,10 +929,13 @@ void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
   fused_group<BLOCKS, KEEP, MODE>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
                                   ref_shape);
 }
-// The same where a compute unit has one workgroup at most, which waits for each of its instructions: with
-// as many scalar registers as it likes (25 to 50 of them move to lanes of a vector register and back
-// otherwise).  us: 3 x 124 with three references 9.84 -> 9.41, 142 x 93 with eight 10.5 -> 10.3, 16 x 256
-// 6.03 -> 5.98.
+// The same where a compute unit has one workgroup at a time: its wavefronts, four per SIMD, may have all
+// scalar registers (25 to 50 of them move to lanes of a vector register and back otherwise) and 128
+// vector registers (with 64, the values of 24 blocks and the sweep's do not fit).  us, plans of few
+// blocks: 3 x 124 with three references 9.84 -> 9.41, 142 x 93 with eight 10.5 -> 10.3, 16 x 256 6.03 -> 5.98;
+// of 8 to 16: 1 to 3 % (128 x 8192 34.2 -> 33.8, 128 x 2500 with four references 24.1 -> 23.4); of 24, with three
+// references or more, a fifth (128 x 5000 with three 53.8 -> 45.1, 700 of them 155 -> 128, 800 x 2400 with eight
+// 176 -> 149).
 template <int BLOCKS, bool KEEP, Mode MODE>
 __global__ __launch_bounds__(1024, 4)
 void fused_kernel_alone(const void* cand, const int32_t* cand_lens, const void* refs,
@@ -976,10 +979,9 @@ hipError_t launch_mode(const Problem& pb, const FusedArgs& a, const FusedPlan& p
 }
 template <int BLOCKS, bool KEEP>
 hipError_t launch_keep(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  // (the larger plans spend their time in loops, where the registers suffice: 0.6 to 1 % to gain)
-  if constexpr (!KEEP && BLOCKS <= 6) {
-    if (pb.B <= 256) return launch_mode<BLOCKS, KEEP, true>(pb, a, plan, s);
-  }
+  // One workgroup a unit: no more of them than units, or LDS for one only.
+  if (pb.B <= 256 || plan.lds_bytes > kLdsBudget / 2)
+    return launch_mode<BLOCKS, KEEP, true>(pb, a, plan, s);
   return launch_mode<BLOCKS, KEEP, false>(pb, a, plan, s);
 }
 template <int BLOCKS>
