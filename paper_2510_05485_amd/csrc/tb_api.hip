@@ -331,14 +331,14 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
 // time does not depend on the number of groups until each unit has one; it grows mostly with the
 // candidate's tokens, while the sorted runs' grows with all tokens of the batch.  Both grow with the
 // number of orders, except that ROUGE-N needs the sorted runs of one order only.  Measured (us, sorted
-// runs / fused): one reference of 8192 tokens, 40 groups 43 / 34, 56 56 / 33; of 6200 32 30 / 28; two of
-// 4200 16 26 / 28, 32 36 / 28; four of 3500 24 32 / 41, 40 47 / 41; eight of 1500 8 29 / 26; 16 of 1400
-// 8 36 / 45, 24 56 / 45; 62 of 250 8 59 / 33.  ROUGE-1, 2 and 4: one reference of 8192 64 18 / 13, 23 /
-// 21, 24 / 33; three of 5000 16 20 / 16, 22 / 23, 48 31 / 23 (ROUGE-2), 31 / 39 (ROUGE-4); 24 of 900 16
-// 41 / 19, 8 45 / 25, 16 43 / 36.  The lines are linear fits to 5500 (ROUGE 3500) such pairs, shapes of
+// runs / fused): one reference of 8192 tokens, 40 groups 43 / 33, 56 55 / 33; of 6200 32 30 / 28; two of
+// 4200 16 26 / 28, 32 36 / 28; four of 3500 24 32 / 36, 40 47 / 36; eight of 1500 8 28 / 25; 16 of 1400
+// 8 36 / 40, 24 56 / 40; 62 of 250 8 59 / 32.  ROUGE-1, 2 and 4: one reference of 8192 64 18 / 13, 23 /
+// 21, 24 / 33; three of 5000 16 20 / 16, 22 / 23, 48 31 / 23 (ROUGE-2), 31 / 38 (ROUGE-4); 24 of 900 16
+// 41 / 19, 8 45 / 25, 16 43 / 35.  The lines are linear fits to 5500 (ROUGE 3500) such pairs, shapes of
 // 12 400 to 24 500 positions with 1 to 62 references and 4 to 130 groups, one to six orders: on average
-// 0.5 % (ROUGE 0.1 %) behind the better kernel, more than a tenth behind in 2.1 % (0.4 %) of them.  (The
-// lines fitted before the kernel found n-grams without looking them up: 0.8 % and 18 %.)
+// 0.5 % (ROUGE 0.2 %) behind the better kernel, more than a tenth behind in 2.3 % (0.5 %) of them.  (The
+// lines fitted before the kernel found n-grams without looking them up: 1.0 % and 17 %.)
 // Against the partitioned kernels, which take what the sorted runs do not: 32.
 bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
                  FusedPlan* plan) {
@@ -351,7 +351,7 @@ bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats,
     if (takes_runs(c, cfg, rouge, false, &runs)) {
       const int64_t refs = pb.R * pb.ref_stride;
       few = rouge ? pb.N * pb.cand_stride / 260 + pb.N * refs / 1400 - 5 * pb.R / 2 - 33
-                  : pb.cand_stride / 200 + refs / 650 - pb.R / 2 + 6 * pb.N - 37;
+                  : pb.cand_stride / 200 + refs / 700 - pb.R / 2 + 5 * pb.N - 33;
     }
     if (c.plans.use_part && pb.B < few) return false;
   }
