@@ -71,6 +71,18 @@ def test_plans(B, R, L, vocab, N):
     check(syn.random_small(B + L, B=B, R=R, vocab=vocab, max_len=L, min_len=L // 3), N)
 
 
+@pytest.mark.parametrize("B", [256, 257])   # a unit for each workgroup, and one shared
+@pytest.mark.parametrize("R,L,vocab,N", [
+    (1, 100, 40, 4),
+    (2, 6200, 3000, 3),         # 24 blocks a wavefront, all of LDS: alone on the unit either way
+    (3, 5000, 3000, 4),
+    (62, 300, 50, 4),           # 24 blocks, less than half of LDS
+])
+def test_alone_on_a_unit(B, R, L, vocab, N):
+    w = syn.random_small(680 + R, B=B, R=R, vocab=vocab, max_len=L, min_len=L // 2)
+    check(w, N, rouge=R != 2)
+
+
 @pytest.mark.parametrize("B,R,L,Lr,vocab,N", [
     (30, 16, 2984, 895, 1 << 23, 4),   # a table of 4096 slots 0.73 full, six bits for the probe count
     (12, 62, 1059, 105, 2000, 4),      # of 2048 slots 0.52 full
