@@ -59,7 +59,7 @@ def kernel_names(fn, torch):
             torch.cuda.synchronize()
         names = []
         for e in p.events():
-            m = re.match(r"(?:void )?(tb::.*)\(tb::.*\)$", e.name.replace("(anonymous namespace)::", ""))
+            m = re.match(r"(?:void )?(tb::\w+(?:<.*?>)?)\(", e.name.replace("(anonymous namespace)::", ""))
             if m and m.group(1) not in names:
                 names.append(m.group(1))
         return names
