@@ -3,10 +3,10 @@
 // Tokens are read from HBM once; dictionary and counters never leave LDS; one score (plus optional
 // integer statistics) goes out.  What bounds it: instruction issue.  A lone small group pays seven or
 // eight cycles per instruction of its longest wavefront.  A full chip issues, per cycle and compute unit,
-// 0.70 vector and 0.51 scalar instructions (512 x 1024 with four references), 0.84 and 0.45 (1024 x 2048),
-// 0.79 and 0.51 (4096 x 512 with two): 71 to 76 % of the 1.7 that a mix of both kinds reaches at most
+// 0.71 vector and 0.49 scalar instructions (512 x 1024 with four references), 0.81 and 0.53 (1024 x 2048),
+// 0.56 and 0.56 (4096 x 512 with two): 66 to 79 % of the 1.7 that a mix of both kinds reaches at most
 // (counters of rocprofv3; 1.5 of vector instructions alone, 1.0 of scalar ones), the scalar ones from
-// loops, masks and bookkeeping.  LDS is not the limit (0.05 to 0.07 instructions; a random 16-byte read
+// loops, masks and bookkeeping.  LDS is not the limit (0.06 to 0.09 instructions; a random 16-byte read
 // takes 12.5 cycles per wavefront, a 4-byte one 6.5, a compare-and-swap 12).  So:
 //   * Symbols.  Order 1 turns every token into the candidate position that holds its first
 //     occurrence there (its "symbol"), or into "absent" (-1).  An n-gram of order n >= 2 is then
@@ -44,12 +44,13 @@
 // the counters takes the maximum over the references.  Wavefront 0 forms brevity penalty, smoothing and
 // geometric mean (Section 3.4), one order per lane.  Mode kRouge scores ROUGE-N for n = N.
 //
-// Measured on gfx950 (us of GPU time, 4 orders; in brackets the kernel that had one barrier per
-// insertion and look-up of each order, 64-bit-wide slots and a list of live positions in LDS):
-// 16 x 256 tokens with one reference 6.7 (9.5), 256 x 1088 9.4 (12.8), 512 x 1024 with four
-// references 19.6 (22.8), 4096 x 512 with two and the batch's sums 47.5 (50.5), 4096 x 2048 with two 143
-// (171), 1000 x 96 with up to eight 10.6 (13.7), ROUGE-2 of 512 x 512 with three 9.6 (12.5); 128 x 5000
-// with one 28.5 (55, on three staged kernels), 128 x 8192 46.7 (98, on the partitioned ones).
+// Measured on gfx950 (us of GPU time, 4 orders; in brackets the kernel that entered every n-gram and
+// swept its counters, and the one before that, with a barrier per insertion and look-up of each order):
+// 16 x 256 tokens with one reference 6.0 (6.7, 9.5), 256 x 1088 8.3 (9.4, 12.8), 512 x 1024 with four
+// references 17.8 (19.8, 22.8), 4096 x 512 with two and the batch's sums 34.7 (47.7, 50.5), 4096 x 2048 with
+// two 106 (145, 171), 1000 x 96 with up to eight 10.4 (10.5, 13.7), ROUGE-2 of 512 x 512 with three 7.1
+// (9.6, 12.5); 128 x 5000 with one 22.7 (28.5; 55 on three staged kernels), 128 x 8192 32.7 (46.6; 98 on the
+// partitioned ones).
 #include <type_traits>
 
 #include "tb_kernels.h"
