@@ -539,7 +539,7 @@ int tensorbleu_finalize(const int32_t* cand_len, const int32_t* ref_len, int32_t
   if (!out_bleu) return TB_ERR_INVALID_ARG;
   return hip_rc(launch_finalize(c.pb, c.st, c.sp, corpus == 0,
                                 corpus != 0 || c.want_corpus_stats, corpus != 0, out_bleu,
-                                c.stream, c.ws.overflow));
+                                c.stream, c.ws.overflow, false, false));
 }
 
 size_t tensorbleu_static_scratch_bytes(void) { return kStaticScratchBytes; }

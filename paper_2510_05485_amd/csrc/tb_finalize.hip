@@ -46,9 +46,10 @@ __global__ __launch_bounds__(256) void sentence_score_kernel(FinalArgs a) {
 // kernel does) reads them instead of walking the references again.  Measured at B = 4096, N = 4,
 // R = 2: 25 us with a round trip per field and sentence.
 // FOUR_ORDERS: N = 4, one 16-byte request per sentence.  Sum: int32_t where the host knows that no sum
-// leaves it (B times the longer stride), else int64_t, added up across lanes 20 bits at a time.  With sums
-// of 64 bits everywhere and a loop over the wavefronts' parts in LDS, which waited for each, the kernel
-// took 5.4 us instead of 3.5 (2000 x 64 corpus BLEU 12.4 -> 10.5, 1024 x 2048 35.0 -> 33.0).
+// leaves it (B times the longer stride; not for counts that the caller brings), else int64_t, added up
+// across lanes 20 bits at a time.  With sums of 64 bits everywhere and a loop over the wavefronts' parts
+// in LDS, which waited for each, the kernel took 5.4 us instead of 3.5 (2000 x 64 corpus BLEU 12.4 ->
+// 10.5, 1024 x 2048 35.0 -> 33.0).
 template <bool KNOWN_CLOSEST, bool FOUR_ORDERS, typename Sum>
 __global__ __launch_bounds__(1024) void corpus_kernel(FinalArgs a, int write_score) {
   constexpr int kUnroll = 4, kOrders = FOUR_ORDERS ? 4 : 8;
@@ -232,7 +233,7 @@ hipError_t launch_rouge_finalize(const Problem& pb, const ScoreParams& sp, const
 hipError_t launch_finalize(const Problem& pb, const StatPtrs& st, const ScoreParams& sp,
                            bool sentence_scores, bool corpus_sums, bool corpus_score,
                            void* out_bleu, hipStream_t s, const int32_t* overflow,
-                           bool known_closest) {
+                           bool known_closest, bool own_counts) {
   FinalArgs a;
   a.pb = pb;
   a.st = st;
@@ -250,8 +251,8 @@ hipError_t launch_finalize(const Problem& pb, const StatPtrs& st, const ScorePar
     auto launch = [&](auto kernel) {
       hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), 0, s, a, score);
     };
-    const bool narrow =
-        pb.B * (pb.cand_stride > pb.ref_stride ? pb.cand_stride : pb.ref_stride) < (int64_t(1) << 31);
+    const int64_t longer = pb.cand_stride > pb.ref_stride ? pb.cand_stride : pb.ref_stride;
+    const bool narrow = own_counts && pb.B * longer < (int64_t(1) << 31);
     auto choose = [&](auto known, auto four) {
       constexpr bool k = decltype(known)::value, f = decltype(four)::value;
       narrow ? launch(corpus_kernel<k, f, int32_t>) : launch(corpus_kernel<k, f, int64_t>);

@@ -190,11 +190,12 @@ hipError_t launch_count_clip(const Problem& pb, const GlobalWs& ws, const CountP
 // sentence_scores: out_bleu[B] per-sentence scores; corpus_sums: fill st.corpus;
 // corpus_score: additionally write the corpus score to out_bleu[0] (not with sentence_scores).
 // overflow: GlobalWs::overflow or null.  known_closest: st.closest is filled already and no group
-// can have overflowed
+// can have overflowed.  own_counts: this call's kernels have filled st.clipped, so that no count is
+// above its candidate's length
 hipError_t launch_finalize(const Problem& pb, const StatPtrs& st, const ScoreParams& sp,
                            bool sentence_scores, bool corpus_sums, bool corpus_score,
                            void* out_bleu, hipStream_t s, const int32_t* overflow = nullptr,
-                           bool known_closest = false);
+                           bool known_closest = false, bool own_counts = true);
 // ROUGE-N scores from overlap counts (GLOBAL path): precision, recall, F of the best reference.
 struct RougeOut;
 hipError_t launch_rouge_finalize(const Problem& pb, const ScoreParams& sp, const int32_t* overlap,

@@ -262,20 +262,22 @@ def test_two_streams_with_their_own_workspaces_run_side_by_side():
     assert np.abs(serial_b.cpu().numpy() - ref.bleu).max() <= 1e-5
 
 
-def test_corpus_sums_beyond_32_bits():
-    # B times the longer stride is above 2^31, and so is the sum of the reference lengths: every token
-    # is 0, so a candidate matches all its n-grams
-    B, cs, rs, N = 200_000, 64, 11_000, 4
+@pytest.mark.parametrize("N", [4, 6])      # one register of sums for each kind, and two
+def test_corpus_sums_beyond_32_bits(N):
+    # B times the longer stride is above 2^31, and so is the sum of the reference lengths.  Every token of
+    # a reference is 0; two candidates of three begin with 0 to 63 tokens that are not, and match behind
+    # them.  (References this long leave no score; test_finalize_takes_any_counts has one.)
+    B, cs, rs = 200_000, 64, 11_000
     rng = np.random.default_rng(71)
     cl = rng.integers(1, cs + 1, B).astype(np.int32)
     rl = rng.integers(rs - 50, rs + 1, (B, 1)).astype(np.int32)
-    cand = torch.zeros((B, cs), dtype=torch.int32, device=DEV)
+    odd = rng.integers(0, cs, B) * (np.arange(B) % 3 > 0)
+    cand = dev((np.arange(cs) < odd[:, None]).astype(np.int32))
     refs = torch.zeros((B, 1, rs), dtype=torch.int32, device=DEV)
     scorer = tb.BleuScorer(B, 1, cs, rs, vocab_size=10, max_n=N, smoothing="exp", device=DEV, want_stats=True)
-    score = scorer.corpus(cand, torch.from_numpy(cl).to(DEV), refs, torch.from_numpy(rl).to(DEV))
-    totals = [int(np.maximum(cl.astype(np.int64) - n, 0).sum()) for n in range(N)]
+    scorer.corpus(cand, dev(cl), refs, dev(rl))
+    grams = lambda lengths: [int(np.maximum(lengths.astype(np.int64) - n, 0).sum()) for n in range(N)]
+    totals, clipped = grams(cl), grams(np.maximum(cl - odd, 0))
     c, r = int(cl.sum(dtype=np.int64)), int(rl.sum(dtype=np.int64))
-    assert r > 2**31
-    assert scorer.stats.corpus_stats.cpu().tolist() == totals + totals + [c, r]
-    want = oracle.bleu_from_stats(totals, totals, c, r, [1.0 / N] * N, smoothing="exp")
-    assert abs(float(score) - want) <= 1e-5
+    assert r > 2**31 and all(0 < a < b for a, b in zip(clipped, totals))
+    assert scorer.stats.corpus_stats.cpu().tolist() == clipped + totals + [c, r]

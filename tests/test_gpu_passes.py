@@ -250,3 +250,34 @@ def test_partition_overflow_is_reported_not_hidden():
     torch.cuda.synchronize()
     assert st.device_status.item() == 0
     np.testing.assert_array_equal(st.clipped.cpu().numpy(), ref.clipped)
+
+
+@pytest.mark.parametrize("corpus", [True, False])    # closest lengths found by the sums' kernel, and before it
+@pytest.mark.parametrize("N", [4, 7])                # one register of sums for each kind, and two
+def test_finalize_takes_any_counts(N, corpus):
+    """The statistics that finalize reads are its caller's arrays: counts there need not be below the
+    lengths, so sums over them may leave 32 bits however small the batch is."""
+    B, R, L, Lr = 1500, 2, 96, 100
+    rng = np.random.default_rng(207 + N)
+    cl = rng.integers(N, L + 1, B).astype(np.int32)
+    rl = rng.integers(1, Lr + 1, (B, R)).astype(np.int32)
+    clipped = rng.integers(0, 2**31 - 1, (B, N)).astype(np.int32) >> np.arange(N, dtype=np.int32)
+    cfg = tb.make_config(max_n=N, smoothing="exp", vocab_size=50, path="global")
+    ws = tb.allocate_workspace(B, R, L, Lr, cfg, DEV)
+    ws.zero_()
+    stats = tb.Stats.allocate(B, N, DEV)
+    stats.clipped.copy_(dev(clipped))
+    totals = np.maximum(cl[:, None] - np.arange(N), 0)
+    stats.total.copy_(dev(totals.astype(np.int32)))
+    out = torch.empty(1 if corpus else B, dtype=torch.float32, device=DEV)
+    tb.tensorbleu_finalize(dev(cl), dev(rl), L, Lr, cfg, corpus, out, ws, stats)
+    torch.cuda.synchronize()
+    closest = np.array([min(rl[i], key=lambda r: (abs(int(r) - int(cl[i])), r)) for i in range(B)])
+    sums = [int(x) for x in clipped.sum(0, dtype=np.int64)] + [int(x) for x in totals.sum(0)]
+    assert max(sums) > 2**31
+    assert stats.corpus_stats.cpu().tolist() == sums + [int(cl.sum()), int(closest.sum())]
+    np.testing.assert_array_equal(stats.closest_ref_len.cpu().numpy(), closest)
+    if corpus:
+        want = oracle.bleu_from_stats(sums[:N], sums[N:2 * N], int(cl.sum()), int(closest.sum()), [1.0 / N] * N,
+                                      smoothing="exp")
+        assert abs(float(out) - want) <= 1e-5 * want
