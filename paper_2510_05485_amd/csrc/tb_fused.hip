@@ -255,10 +255,10 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
 
   // Lengths (0 for a reference not in use) and rows of the sequences; with several references lane j of
   // every wavefront holds those of sequence j, and the prefix of the sequences' block counts
-  const int raw_cand = uniform_load(cand_lens, g);
+  int raw_cand = uniform_load(cand_lens, g);
   // (no branch: with neither counts nor lists a length is read, and not used)
   const int32_t* const rows = ref_offsets ? ref_offsets : ref_count ? ref_count : cand_lens;
-  const int rows0 = uniform_load(rows, g), rows1 = uniform_load(rows, g + (ref_offsets ? 1 : 0));
+  int rows0 = uniform_load(rows, g), rows1 = uniform_load(rows, g + (ref_offsets ? 1 : 0));
   int64_t row0 = int64_t(g) * R;
   int raw_ref = 0, raw_ref1 = 0;
   if (FEW) {
@@ -276,7 +276,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   uint32_t part_at = a.off_sums;
   int progress = a.progress_priority, lg = a.log2_slots, id_bits = a.id_bits;
   asm volatile("" : "+s"(table_and_counters), "+s"(vocab_size), "+s"(sym_at), "+s"(part_at),
-               "+s"(progress), "+s"(lg), "+s"(id_bits));
+               "+s"(progress), "+s"(lg), "+s"(id_bits), "+s"(raw_cand), "+s"(rows0), "+s"(rows1));
   int used = R;
   bool odd = false;  // counts or lists that had to be clamped
   if (ref_offsets) {  // uniform
@@ -347,10 +347,13 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     if (FEW) return pick<TWO>(f, cand_len, ref_len, ref_len1);
     return int(__builtin_amdgcn_readlane(my_len, f));
   };
+  auto lane_value64 = [](uint64_t v, int from) __attribute__((always_inline)) {
+    return uint64_t(uint32_t(__builtin_amdgcn_readlane(int(v >> 32), from))) << 32 |
+           uint32_t(__builtin_amdgcn_readlane(int(uint32_t(v)), from));
+  };
   auto row_of = [&](int f) __attribute__((always_inline)) {
     if (FEW) return pick<TWO>(f, cand_row, ref_row, ref_row + uint32_t(rs) * token_bytes);
-    return uint64_t(uint32_t(__builtin_amdgcn_readlane(int(row_at >> 32), f))) << 32 |
-           uint32_t(__builtin_amdgcn_readlane(int(uint32_t(row_at)), f));
+    return lane_value64(row_at, f);
   };
   // Closest reference length, the shorter one on ties (no reference at all: 0).
   auto closest_length = [&]() __attribute__((always_inline)) {
@@ -392,6 +395,19 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   // This wavefront's blocks are wave, wave + nwaves, ... (the candidate's come first).  val[i]: the
   // token, then the symbol, of the lane's position (KEEP: then the id of the last finished order).
   int32_t val[BLOCKS];
+  // Lane i: positions that the wavefront's block i has, and where its tokens are.  Chosen block by block
+  // from two or three sequences these are scalar instructions (33 a block with two references), of which a
+  // unit issues one a cycle for all its wavefronts: us of the call with the choice per block and like this,
+  // one order with two references 825 x 643 9.5 -> 8.2, 101 x 1194 7.3 -> 6.5, four orders 11.1 -> 10.3;
+  // 256 x 1088 with one 8.4 -> 8.1.  One or two blocks have too few.
+  constexpr bool ALL_AT_ONCE = FEW && BLOCKS >= 3;
+  int block_left = 0;
+  uint64_t block_at = 0;
+  if (ALL_AT_ONCE) {
+    const int b = wave + (lane << log2_waves), f = sequence_of(b), first = first_of(b, f);
+    block_left = length_of(f) - first;
+    block_at = row_of(f) + uint32_t(first) * token_bytes;
+  }
   // Tokens are requested; while they are on their way, table slots become free, counters zero, symbols
   // behind the sequences absent.
   auto stage = [&](auto token_type) __attribute__((always_inline)) {
@@ -408,12 +424,17 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       // form is the better one: the values set above need no registers)
       if (FEW && b >= blocks) break;
       if (b >= blocks) continue;
-      const int f = sequence_of(b);
-      const int first = first_of(b, f);
-      left[i] = length_of(f) - first;
+      uint64_t at;
+      if (ALL_AT_ONCE) {
+        left[i] = __builtin_amdgcn_readlane(block_left, i);
+        at = lane_value64(block_at, i);
+      } else {
+        const int f = sequence_of(b), first = first_of(b, f);
+        left[i] = length_of(f) - first;
+        at = row_of(f) + uint32_t(first) * token_bytes;
+      }
       typedef const Token __attribute__((address_space(1)))* GlobalToken;
-      GlobalToken p = reinterpret_cast<GlobalToken>(row_of(f)) + uint32_t(first);
-      raw[i] = p[uint32_t(min(lane, left[i] - 1))];
+      raw[i] = reinterpret_cast<GlobalToken>(at)[uint32_t(min(lane, left[i] - 1))];
     }
     set_up();
     for (uint32_t q = tid; q < uint32_t(table_and_counters); q += nt)
