@@ -90,8 +90,9 @@ struct FusedArgs {
   int log2_slots;
   int id_bits;             // ids (candidate positions) are below 2^id_bits
   int64_t ref_rows;        // CSR lists: number of reference rows
-  uint32_t pass_ends;      // bits 4(n - 1)..: last order of the pass that starts with order n >= 2;
-                           // bits 0..3: 1 if order 1 is a pass of its own, else 0
+  uint32_t pass_ends;      // bits 4(n - 1)..: last order of the stretch that starts with order n >= 2;
+                           // bit 0: order 1 is a pass of its own; bit 1: the others are one pass, not one
+                           // for each stretch
   int first_payload, first_key_bits;  // payload bits and key bits (order within the pass | payload)
                                       // of the table that order 1 is in
   int later_payload, later_key_bits;  // ... of the passes behind it
@@ -612,33 +613,40 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   }
   TB_FSTAMP(3);
 
-  int swept = 0, hi = 1;
+  // A stretch is up to three orders that a block takes in one go, a pass one stretch or several with
+  // one table (from order 5 on): the next stretch's insertions go beside the look-ups before them as
+  // those of order 2 go beside the look-ups of order 1.  (A pass for each stretch, with its sums, its
+  // clearing and three barriers more: eight orders of 457 x 10 with three references 10.9 us instead of
+  // 9.8, of 3946 x 21 17.0 instead of 15.5; 517 drawn shapes of five to eight orders 1.09 of its speed.)
+  int swept = 0, counted = 0, hi = 1;
   bool pass_ends = a.pass_ends & 1u;
 #pragma unroll 1
   while (true) {
+    // ---- sums of the orders, two in the halves of a word (neither exceeds the positions), in LDS, where
+    // the tail's lanes find theirs: matches of a stretch, or for a whole pass what the candidate has of
+    // its n-grams beyond every reference (the rest of them is min(count, largest reference count))
+    auto add_up = [&](int n, uint32_t part) __attribute__((always_inline)) {
+      part = uint32_t(row_inclusive_scan(int(part)));
+      if ((lane & 15) == 15) lds_add(part_at + 4u * uint32_t(n - 1), part);
+    };
+    if (!ROUGE && matching && (pass_ends || (KEEP && hi > 1))) {
+      if (my_cand_blocks < my_blocks) {  // (uniform)
+        if (counted == 0) {
+          add_up(1, uint32_t(matches1 | matches[0] << 16));
+          if (hi > 2) add_up(3, uint32_t(matches[1] | matches[2] << 16));
+        } else {
+          add_up(counted + 1, uint32_t(matches[0] | matches[1] << 16));
+          if (hi > counted + 2) add_up(counted + 3, uint32_t(matches[2]));
+        }
+        matches[0] = matches[1] = matches[2] = 0;
+      }
+      counted = hi;
+    }
     if (pass_ends) {
       if (hi == N && prio) __builtin_amdgcn_s_setprio(0);
-      // ---- sums of the pass's orders, two in the halves of a word (neither exceeds the positions), in
-      // LDS, where the tail's lanes find theirs: matches, or what the candidate has of its n-grams
-      // beyond every reference (the rest of them is min(count, largest reference count))
-      auto add_up = [&](int n, uint32_t part) __attribute__((always_inline)) {
-        part = uint32_t(row_inclusive_scan(int(part)));
-        if ((lane & 15) == 15) lds_add(part_at + 4u * uint32_t(n - 1), part);
-      };
       if (ROUGE) {
         if (hi == N && lane >= 1 && lane <= R) lds_add(overlap_at + 4u * uint32_t(lane - 1), uint32_t(overlap));
-      } else if (matching) {
-        if (my_cand_blocks < my_blocks) {  // (uniform)
-          if (swept == 0) {
-            add_up(1, uint32_t(matches1 | matches[0] << 16));
-            if (hi > 2) add_up(3, uint32_t(matches[1] | matches[2] << 16));
-          } else {
-            add_up(swept + 1, uint32_t(matches[0] | matches[1] << 16));
-            if (hi > swept + 2) add_up(swept + 3, uint32_t(matches[2]));
-          }
-          matches[0] = matches[1] = matches[2] = 0;
-        }
-      } else {
+      } else if (!matching) {
         __syncthreads();
         if (TWO) {
           const uint32_t at = cnt_at + 4u * uint32_t(tid);
@@ -711,7 +719,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     // ---- orders lo..hi
     const int lo = hi + 1;
     hi = int((a.pass_ends >> (4 * hi)) & 15u);
-    pass_ends = true;
+    pass_ends = hi == N || !(a.pass_ends & 2u);
     // Two workgroups share a compute unit and its arbiter serves the older wavefronts first: left
     // alone, the one dispatched first finishes early and its mate runs alone on a half-empty unit.
     // The workgroup that is behind therefore gets the higher priority.
@@ -1034,20 +1042,27 @@ bool fused_path_takes(int64_t cand_stride, int64_t ref_stride, int R, int bits) 
 
 namespace {
 
-// Passes of a plan: 0: orders 1 to 4 share a table; 1: order 1 on its own, then the others; 2: pairs;
-// 3: every order on its own.  (No pass has more than three orders above the first.)  Fills in pass_ends
-// and the key widths; false: the key is too wide.
+// Passes of a plan.  Fills in pass_ends and the key widths; false: the key is too wide.
+enum Passes {
+  kTogether,         // all orders share a table
+  kFirstApart,       // order 1 on its own, then all others
+  kStretches,        // orders 1 to 4, 5 to 7, 8: a table for each stretch
+  kFirstStretches,   // order 1 on its own, then 2 to 4, 5 to 7, 8
+  kPairs,
+  kSingle,           // every order on its own
+};
 bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pass) {
   FusedPlan& p = *plan;
-  static const uint32_t kEnds[4] = {0x90u, 0x92u, 0x154u, ~0u};  // bit n: a pass ends with order n
+  static const uint32_t kEnds[6] = {0x90u, 0x92u, 0x90u, 0x92u, 0x154u, ~0u};  // bit n: a stretch ends with order n
   p.pass_ends = (N == 1 || (kEnds[passes] & 2u)) ? 1u : 0u;
+  if (passes <= kFirstApart) p.pass_ends |= 2u;
   for (int n = 2; n <= N; ++n) {
     int end = n;
     while (end < N && !((kEnds[passes] >> end) & 1u)) ++end;
     p.pass_ends |= uint32_t(end) << (4 * (n - 1));
   }
-  static const int kOrders[4] = {4, 3, 2, 1};
-  const int most = passes == 1 && N > 1 ? N - 1 : N;
+  static const int kOrders[6] = {8, 7, 4, 3, 2, 1};
+  const int most = (passes == kFirstApart || passes == kFirstStretches) && N > 1 ? N - 1 : N;
   *orders_per_pass = kOrders[passes] < most ? kOrders[passes] : most;
   const int tag_bits = log2_ceil(*orders_per_pass);
   p.later_payload = 2 * p.id_bits;
@@ -1057,7 +1072,7 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
     p.first_payload = bits > p.later_payload ? bits : p.later_payload;
     p.first_key_bits = p.first_payload + tag_bits;
   }
-  p.keep = N > 4 || (passes >= 2 && N > 2);  // (more than one pass above order 1)
+  p.keep = N > 4 || (passes >= kPairs && N > 2);  // (more than one stretch above order 1)
   return p.first_key_bits <= 32 && p.later_key_bits <= 32;
 }
 
@@ -1134,17 +1149,20 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
     return false;
   };
   for (int full = 0; full < 2; ++full) {
+    auto some_fits = [&](int passes, int r) {  // (up to order 4 there is one stretch)
+      return (N > 4 || passes < kStretches || passes > kFirstStretches) && fits(passes, r, full);
+    };
     int r = resident < 1 ? 1 : resident;
     if (r > 4) {
       const int shares[3] = {r, r * 7 / 10, r / 2};
-      for (int passes = 0; passes < 3; ++passes)
+      for (int passes = kTogether; passes <= kPairs; ++passes)
         for (int share : shares)
-          if (fits(passes, share, full)) return true;
+          if (some_fits(passes, share)) return true;
       r = r / 2 - 1;
     }
     for (; r >= 1; --r)
-      for (int passes = 0; passes < (r > 1 ? 3 : 4); ++passes)
-        if (fits(passes, r, full)) return true;
+      for (int passes = kTogether; passes <= (r > 1 ? kPairs : kSingle); ++passes)
+        if (some_fits(passes, r)) return true;
   }
   return false;
 }

@@ -18,7 +18,7 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
 
 
-def check(w, N, int64=False, rouge=True):
+def check(w, N, int64=False, rouge=True, rouge_n=2):
     cand, refs = dev(w.cand), dev(w.refs)
     if int64:
         cand, refs = cand.long(), refs.long()
@@ -35,7 +35,7 @@ def check(w, N, int64=False, rouge=True):
     np.testing.assert_array_equal(stats.closest_ref_len.cpu().numpy(), ref.closest_ref_len)
     assert np.abs(out.cpu().numpy().astype(np.float64) - ref.bleu).max() <= TOL
     if rouge:
-        n = min(N, 2)
+        n = min(N, rouge_n)
         want = oracle.rouge_n(w.cand, w.cand_len, w.refs, w.ref_len, n=n)
         prf, overlap, best = tb.tensorrouge_n(cand, cl, refs, rl, n=n, vocab_size=w.vocab,
                                               want_overlap=True, want_best=True)
@@ -112,6 +112,19 @@ def test_tokens_chosen_to_collide(N):
     w = syn.random_small(631, B=6, R=2, vocab=len(ids), max_len=400, min_len=300)
     w.cand, w.refs, w.vocab = ids[w.cand], ids[w.refs], vocab
     check(w, N)
+
+
+@pytest.mark.parametrize("N", [5, 6, 7, 8])
+@pytest.mark.parametrize("B,R", [(20, 1), (300, 1), (20, 2), (300, 2), (300, 3), (20, 4), (300, 6)])
+def test_orders_beyond_four(B, R, N):
+    # several stretches of orders with one table and one set of counters, workgroups alone on a unit and
+    # not; short cycles, so that the upper orders have matches
+    w = syn.random_small(671 + R, B=B, R=R, vocab=4, max_len=150, min_len=3)
+    for i in range(0, w.B, 2):
+        w.cand[i] = np.arange(w.cand.shape[1]) % (2 + i % 11)
+        w.refs[i] = np.arange(w.refs.shape[2]) % (2 + i % 13)
+    w.vocab = 16
+    check(w, N, int64=N == 7, rouge_n=N)
 
 
 @pytest.mark.parametrize("N", [1, 2, 3, 5, 8])
