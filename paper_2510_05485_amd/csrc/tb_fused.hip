@@ -673,34 +673,45 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
           };
           // Two orders have order_fields words: the first order's count and first reference in word 0,
           // the second order's count in word `middle`, in the upper half if the last reference of the
-          // first order has the lower one.
+          // first order has the lower one.  Words of both are read side by side: one after the other
+          // they are two chains of dependent steps.
           const int middle = order_fields >> 1;
           const bool shared = order_fields & 1;
+          auto above = [](uint32_t count, uint32_t most) __attribute__((always_inline)) {
+            return uint32_t(max(int32_t(count) - int32_t(max(most & 0xFFFFu, most >> 16)), 0));
+          };
 #pragma unroll 1
           for (int n = swept + 1; n <= hi; n += 2) {
             const bool two = n < hi;
             uint32_t part = 0;
             uint32_t e = array_of((n - 1 - swept) * order_fields) + 4u * uint32_t(tid);
             const uint32_t to_middle = two || shared ? uint32_t(middle) * array_bytes : 0u;
+            const uint32_t to_other = two ? to_middle : 0u;
 #pragma unroll 1
             for (int k = tid; k < cand_len; k += nt, e += 4u * uint32_t(nt)) {
-              auto most_of = [&](uint32_t& most, int w, int end) __attribute__((always_inline)) {  // words w..end - 1
-                uint32_t at = e + uint32_t(w) * array_bytes;
-#pragma unroll 1
-                for (; w + 1 < end; w += 2, at += 2u * array_bytes)
-                  most = max_halves(most, max_halves(*lds<uint32_t>(at), *lds<uint32_t>(at + array_bytes)));
-                if (w < end) most = max_halves(most, *lds<uint32_t>(at));
-              };
-              auto above = [](uint32_t count, uint32_t most) __attribute__((always_inline)) {
-                return uint32_t(max(int32_t(count) - int32_t(max(most & 0xFFFFu, most >> 16)), 0));
-              };
               const uint32_t head = *lds<uint32_t>(e), second = *lds<uint32_t>(e + to_middle);
               uint32_t most0 = head >> 16, most1 = shared ? 0u : second >> 16;
               if (shared) most0 = max_halves(most0, second & 0xFFFFu);
-              most_of(most0, 1, middle);
+              uint32_t at = e;
+              int w = 1;
+#pragma unroll 1
+              for (; w + 1 < middle; w += 2) {
+                at += array_bytes;
+                const uint32_t v0 = *lds<uint32_t>(at), v1 = *lds<uint32_t>(at + to_other);
+                at += array_bytes;
+                const uint32_t u0 = *lds<uint32_t>(at), u1 = *lds<uint32_t>(at + to_other);
+                most0 = max_halves(most0, max_halves(v0, u0));
+                most1 = max_halves(most1, max_halves(v1, u1));
+              }
+              if (w < middle) {
+                at += array_bytes;
+                const uint32_t v0 = *lds<uint32_t>(at), v1 = *lds<uint32_t>(at + to_other);
+                most0 = max_halves(most0, v0);
+                most1 = max_halves(most1, v1);
+              }
               part += above(head & 0xFFFFu, most0);
               if (two) {
-                most_of(most1, middle + 1, order_fields);
+                if (shared) most1 = max_halves(most1, *lds<uint32_t>(at + array_bytes + to_middle));
                 part += above(shared ? second >> 16 : second & 0xFFFFu, most1) << 16;
               }
             }
