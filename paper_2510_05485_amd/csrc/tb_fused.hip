@@ -1020,10 +1020,10 @@ hipError_t launch_mode(const Problem& pb, const FusedArgs& a, const FusedPlan& p
 }
 template <int BLOCKS, bool KEEP>
 hipError_t launch_keep(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  // One workgroup a unit: no more of them than units, or LDS for one only.
-  if (pb.B <= 256 || plan.lds_bytes > kLdsBudget / 2)
-    return launch_mode<BLOCKS, KEEP, true>(pb, a, plan, s);
-  return launch_mode<BLOCKS, KEEP, false>(pb, a, plan, s);
+  if (fused_alone(pb.B, plan)) return launch_mode<BLOCKS, KEEP, true>(pb, a, plan, s);
+  // (plans for shared units have two blocks or more)
+  if constexpr (BLOCKS > 1) return launch_mode<BLOCKS, KEEP, false>(pb, a, plan, s);
+  return hipErrorInvalidValue;
 }
 template <int BLOCKS>
 hipError_t launch_blocks(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
@@ -1035,6 +1035,11 @@ constexpr size_t kLdsUnit = 1280;  // LDS is handed out in units of this size
 constexpr size_t kSumsBytes = 64 + 16 + kMaxSeqs * 4;
 
 }  // namespace
+
+// One workgroup a unit: no more of them than units, or LDS for one only.
+bool fused_alone(int64_t B, const FusedPlan& plan) {
+  return B <= 256 || plan.lds_bytes > kLdsBudget / 2;
+}
 
 bool fused_path_takes(int64_t cand_stride, int64_t ref_stride, int R, int bits) {
   if (R + 1 > kMaxSeqs) return false;
@@ -1104,6 +1109,13 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
 //   * 32 wavefronts a unit hide latency (16 take 512 x 1024 with four references from 18.8 to 21.5 us);
 //     a workgroup with fewer blocks than wavefronts idles, and with two blocks or less per wavefront its
 //     prologue outweighs them.
+//   * More than 12 to 16 blocks a wavefront are short of registers where workgroups share a unit (of 24, 28 to
+//     54 vector registers go to scratch): these get more wavefronts, and the LDS of as many workgroups as then
+//     fit (5340 x 242 with six references, 17 blocks, 76.8 us; 9 blocks of four wavefronts 51.0; 13 blocks and
+//     more in 300 drawn shapes: 1.09 of the speed).  Two wavefronts, and four with more than one order, gain from 13
+//     blocks on (1.13 and 1.07), four with one order, one and eight from 17 on (13 to 16: 0.9 to 1.0 with twice
+//     the wavefronts).  Two workgroups of 16 wavefronts keep up to 24 blocks: they are faster with
+//     scratch than one a unit without it (90 shapes: 1.23).
 bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
                 bool rouge, FusedPlan* plan) {
   if (R + 1 > kMaxSeqs || cand_stride > 12288 || ref_stride > 65535 || bits > 31) return false;
@@ -1128,7 +1140,10 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
       while (waves < 16 && 2 * waves <= 32 / r && blocks > waves * (waves < 4 ? 2 : waves < 8 ? 3 : 4))
         waves *= 2;
     }
-    while (waves < 16 && blocks > int64_t(kMaxBlocks) * waves) waves *= 2;
+    // blocks a wavefront takes at most (see above), and workgroups that the wavefronts then leave room for
+    const int most = r < 2 ? kMaxBlocks : waves == 2 || (waves == 4 && N > 1) ? 12 : 16;
+    while (waves < 16 && blocks > int64_t(most) * waves) waves *= 2;
+    if (r > 32 / waves) r = 32 / waves;
     // All orders of a pass together enter at most as many n-grams as the candidate has positions.
     const int64_t entries = cand_stride;
     const int widest = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;

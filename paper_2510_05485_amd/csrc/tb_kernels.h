@@ -181,6 +181,8 @@ bool plan_count(int64_t group_cap, int64_t cand_stride, int64_t ref_stride, int 
 bool fused_path_takes(int64_t cand_stride, int64_t ref_stride, int R, int bits);
 bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
                 bool rouge, FusedPlan* plan);
+// Whether the plan's workgroups have a compute unit each, and with it the kernel that has more registers.
+bool fused_alone(int64_t B, const FusedPlan& plan);
 
 hipError_t launch_pack(const Problem& pb, const GlobalWs& ws, hipStream_t s);
 hipError_t launch_dictionary(const Problem& pb, const GlobalWs& ws, const DictPlan& plan,

@@ -17,7 +17,8 @@ bool runs_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   return true;
 }
 
-// log2 of the slots; bits of an id and of the widest key; pass_ends; LDS bytes; false: no such plan
+// log2 of the slots; bits of an id and of the widest key; pass_ends; LDS bytes; wavefronts; blocks of one
+// of them; whether ids are kept between passes; whether a workgroup has its unit to itself; false: no such plan
 bool fused_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits, bool rouge,
                 int64_t* out) {
   tb::FusedPlan p;
@@ -27,6 +28,10 @@ bool fused_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
   out[2] = p.first_key_bits > p.later_key_bits ? p.first_key_bits : p.later_key_bits;
   out[3] = p.pass_ends;
   out[4] = int64_t(p.lds_bytes);
+  out[5] = p.threads / 64;
+  out[6] = p.blocks;
+  out[7] = p.keep;
+  out[8] = tb::fused_alone(B, p);
   return true;
 }
 

@@ -68,14 +68,31 @@ def test_sorted_runs_leave_their_tables_room(plans):
 def fused_table(plans, *shape):
     """Share of the table's slots that are taken if no n-gram repeats, and bits of an entry's probe
     count (what the remainder of the key and the id leave of 32); None: no such plan."""
-    out = (ctypes.c_int64 * 5)()
+    out = (ctypes.c_int64 * 9)()
     if not plans.fused_plan(*shape, out):
         return None
-    lg, id_bits, key_bits, _, lds = out
+    lg, id_bits, key_bits, _, lds = out[:5]
     assert lds <= LDS, shape
     # (however many orders share the table: test_a_table_holds_no_more_than_the_candidate)
     load = shape[1] / 2 ** lg
     return load, min(32 - key_bits + lg - 2, 32) - id_bits
+
+
+def test_shared_units_keep_their_registers(plans):
+    # more than 16 blocks a wavefront need scratch where workgroups share a unit, and are for workgroups
+    # of 16 wavefronts only; no kernel of one block is built for these units
+    out = (ctypes.c_int64 * 9)()
+    rng, seen = random.Random(29), {}
+    for _ in range(40000):
+        R, N, rouge = rng.choice((1, 2, 3, 5, 8, 16, 40, 62)), rng.randint(1, 8), rng.random() < 0.3
+        cs = int(8192 ** rng.random())
+        rs = int(max(24000 - cs, R) / R * rng.random()) + 1
+        if not plans.fused_plan(int(257 * 40 ** rng.random()), cs, rs, R, N, 16, rouge, out) or out[8]:
+            continue
+        waves, blocks = out[5:7]
+        assert blocks >= 2 and (blocks <= 16 or waves == 16), (cs, rs, R, N, rouge, list(out))
+        seen[waves] = max(seen.get(waves, 0), blocks)
+    assert seen[16] > 16 and min(seen[w] for w in (1, 2, 4, 8)) > 8, seen
 
 
 def entries(tokens, first, last, rng):
