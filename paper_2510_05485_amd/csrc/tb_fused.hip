@@ -475,6 +475,9 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   // keeps them in registers, in twos (4096 x 2048 with two references 109.0 -> 106.5; four are no better, and
   // with more references, whose kernels are short of registers, twos cost a tenth).
   constexpr bool LOOK = KEEP || BLOCKS > 6;  // (see claim)
+  // (Order 1 of a table that is for more orders, or for one order only, enters few of its slots' worth: with
+  // three references or more 1 % faster without the look, with fewer 4 % slower where many tokens are the same.)
+  constexpr bool LOOK_FIRST = KEEP || (LOOK && MODE != kReferences);
   constexpr int GROUP = !KEEP ? (FEW && BLOCKS >= 8 ? 2 : 1) : BLOCKS >= 8 ? 4 : BLOCKS >= 4 ? 2 : 1;
   auto rotate = [&](auto by) __attribute__((always_inline)) {
     constexpr int n = decltype(by)::value;
@@ -561,7 +564,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     each_block(i, my_cand_blocks, [&](int32_t& v) __attribute__((always_inline)) {
       int32_t got = -1;
       if (v >= 0) {
-        got = int32_t(table.claim<LOOK>(uint32_t(v) * table.multiplier, id));
+        got = int32_t(table.claim<LOOK_FIRST>(uint32_t(v) * table.multiplier, id));
         if (!ROUGE || N == 1) count_candidate(0, uint32_t(got));
       }
       if (!ROUGE && want_distinct) {
@@ -1105,7 +1108,8 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
 //     37.9; 2493 x 711 with two 42.7 and 35.3).  Every order on its own only where nothing else fits.
 //   * A table that is nearly full costs more than anything else: probe sequences of the wavefront's
 //     slowest lane grow from 1 to 4 requests between a quarter and three quarters.  More than twelve
-//     slots an entry cost more to clear than they save.
+//     slots a position, six for one order, cost more to clear than they save (38 x 1425 with three
+//     references, one order: 7.2 -> 6.8 us).
 //   * 32 wavefronts a unit hide latency (16 take 512 x 1024 with four references from 18.8 to 21.5 us);
 //     a workgroup with fewer blocks than wavefronts idles, and with two blocks or less per wavefront its
 //     prologue outweighs them.
@@ -1157,7 +1161,7 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
     // would be by 1e-19.
     while (32 - widest + lg_min - 2 - p.id_bits < (full ? 6 : 4)) ++lg_min;
     int lg = lg_min;
-    while ((int64_t(1) << lg) < 12 * entries) ++lg;
+    while ((int64_t(1) << lg) < (N == 1 ? 6 : 12) * entries) ++lg;
     const size_t share = size_t(kLdsBudget) / r / kLdsUnit * kLdsUnit;
     const size_t counters = size_t(((rouge ? 1 : orders) * order_fields + 1) / 2) * p.array_bytes;
     for (; lg >= lg_min; --lg) {
