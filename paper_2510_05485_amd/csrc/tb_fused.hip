@@ -1109,7 +1109,7 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
 //   * A table that is nearly full costs more than anything else: probe sequences of the wavefront's
 //     slowest lane grow from 1 to 4 requests between a quarter and three quarters.  More than twelve
 //     slots a position, six for one order, cost more to clear than they save (38 x 1425 with three
-//     references, one order: 7.2 -> 6.8 us).
+//     references, one order: 7.2 -> 6.9 us).
 //   * 32 wavefronts a unit hide latency (16 take 512 x 1024 with four references from 18.8 to 21.5 us);
 //     a workgroup with fewer blocks than wavefronts idles, and with two blocks or less per wavefront its
 //     prologue outweighs them.
@@ -1186,8 +1186,12 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
     if (r > 4) {
       const int shares[3] = {r, r * 7 / 10, r / 2};
       for (int passes = kTogether; passes <= kPairs; ++passes)
-        for (int share : shares)
+        for (int share : shares) {
+          // (Counters of five orders and more with three references or more take so much LDS that a table
+          // for each stretch is better than fewer workgroups: 3615 x 26 with 16, eight orders, 39.4 -> 30.5 us.)
+          if (N > 4 && R > 2 && passes <= kFirstApart && share < r) break;
           if (some_fits(passes, share)) return true;
+        }
       r = r / 2 - 1;
     }
     for (; r >= 1; --r)

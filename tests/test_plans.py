@@ -95,6 +95,17 @@ def test_shared_units_keep_their_registers(plans):
     assert seen[16] > 16 and min(seen[w] for w in (1, 2, 4, 8)) > 8, seen
 
 
+def test_many_counters_get_a_table_for_each_stretch(plans):
+    # five orders and more with three references or more: no single table (bit 1 of pass_ends) where fewer
+    # workgroups would be on a unit for it
+    out = (ctypes.c_int64 * 9)()
+    for B, R, cs, rs, N, bits in ((3615, 16, 26, 16, 8, 7), (3711, 16, 42, 50, 5, 16), (2636, 3, 319, 330, 8, 9),
+                                  (5013, 3, 84, 85, 8, 10), (1184, 16, 280, 91, 5, 7)):
+        assert plans.fused_plan(B, cs, rs, R, N, bits, False, out)
+        workgroups = min((B + 255) // 256, 32 // out[5])
+        assert not out[3] & 2 or out[4] * workgroups <= LDS, (B, R, N)
+
+
 def entries(tokens, first, last, rng):
     """Entries that the orders first..last of a candidate make in the fused kernel's table, and the ids
     of the last order's n-grams: an n-gram that goes on as the candidate does at its prefix's id needs
