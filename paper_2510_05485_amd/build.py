@@ -23,11 +23,12 @@ HOST_SRC = os.path.join(CSRC, "tb_host.cpp")
 HOST_LIB = os.path.join(PKG, "_host.so")
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+PRELOADED_WORDS = 14  # of a kernel's plain arguments
 FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     # the first 56 bytes of a kernel's plain arguments come in scalar registers
-    "-mllvm", "-amdgpu-kernarg-preload-count=14",
+    "-mllvm", f"-amdgpu-kernarg-preload-count={PRELOADED_WORDS}", f"-DTB_PRELOADED_WORDS={PRELOADED_WORDS}",
     "-Wall", "-Wno-unused-function",
 ]
 

@@ -75,7 +75,21 @@ namespace {
 constexpr int kMaxSeqs = kWave;     // candidate + references, one lane each
 constexpr int kPadSymbols = 8;      // absent symbols behind every sequence: orders up to 8
 constexpr int kMaxBlocks = 24;      // per wavefront
-constexpr int kRegisterArgs = 56;   // bytes of the arguments before the struct
+
+// A kernel's plain arguments as they lie at the start of its argument segment.
+struct PlainArgs {
+  const void* cand;
+  const int32_t* cand_lens;
+  const void* refs;
+  const int32_t* ref_lens;
+  const int32_t* ref_count;
+  const int32_t* ref_offsets;
+  uint32_t cand_shape, ref_shape;
+};
+constexpr int kRegisterArgs = sizeof(PlainArgs);
+#ifdef TB_PRELOADED_WORDS
+static_assert(4 * TB_PRELOADED_WORDS == kRegisterArgs, "the build asks for other arguments in registers");
+#endif
 
 // The eight plain arguments before it come in scalar registers (the build asks for 56 bytes), so that
 // the lengths are requested at once; what else is read before the tokens arrive stands first here and
@@ -396,6 +410,9 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   // This wavefront's blocks are wave, wave + nwaves, ... (the candidate's come first).  val[i]: the
   // token, then the symbol, of the lane's position (KEEP: then the id of the last finished order).
   int32_t val[BLOCKS];
+#pragma unroll
+  for (int i = 0; i < BLOCKS; ++i)  // (blocks that are not there hold any value: nothing reads it)
+    val[i] = __builtin_nondeterministic_value(0);
   // Lane i: positions that the wavefront's block i has, and where its tokens are.  Chosen block by block
   // from two or three sequences these are scalar instructions (33 a block with two references), of which a
   // unit issues one a cycle for all its wavefronts: us of the call with the choice per block and like this,
@@ -855,11 +872,10 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     __syncthreads();
     // (pointers from the argument segment again: they need no registers until here)
     const Segment args = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
-    typedef const void* const __attribute__((address_space(4)))* Pointers;
-    const Pointers pointers = (Pointers)args;
-    const char* const cand_row = static_cast<const char*>(pointers[0]) + uint64_t(uint32_t(g)) * (uint32_t(cs) * token_bytes);
-    const char* const ref_row = static_cast<const char*>(pointers[2]) + uint64_t(row0) * (uint32_t(rs) * token_bytes);
-    const int32_t* const ref_lens = static_cast<const int32_t*>(pointers[3]);
+    const PlainArgs& plain = *(const PlainArgs*)args;
+    const char* const cand_row = static_cast<const char*>(plain.cand) + uint64_t(uint32_t(g)) * (uint32_t(cs) * token_bytes);
+    const char* const ref_row = static_cast<const char*>(plain.refs) + uint64_t(row0) * (uint32_t(rs) * token_bytes);
+    const int32_t* const ref_lens = plain.ref_lens;
     auto token = [&](const char* row, int i) __attribute__((always_inline)) {
       const uint64_t t = wide ? *reinterpret_cast<const uint64_t*>(row + 8 * int64_t(i))
                               : *reinterpret_cast<const uint32_t*>(row + 4 * int64_t(i));
@@ -988,6 +1004,17 @@ void fused_kernel_alone(const void* cand, const int32_t* cand_lens, const void* 
   fused_group<BLOCKS, KEEP, MODE>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
                                   ref_shape);
 }
+
+// The kernels read the struct behind the plain arguments, and some of these again, from the argument
+// segment, where arguments lie like the members of a struct.
+template <typename... Args>
+constexpr size_t last_argument_at(void (*)(Args...)) {
+  size_t end = 0, at = 0;
+  ((at = (end + alignof(Args) - 1) / alignof(Args) * alignof(Args), end = at + sizeof(Args)), ...);
+  return at;
+}
+static_assert(last_argument_at(decltype(&fused_kernel<2, false, kRouge>){}) == kRegisterArgs);
+static_assert(last_argument_at(decltype(&fused_kernel_alone<2, false, kRouge>){}) == kRegisterArgs);
 
 int log2_ceil(int64_t v) {
   int b = 0;
