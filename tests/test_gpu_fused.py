@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+import fused_rows
 import oracle
 import paper_2510_05485_amd as tb
 import synth_inputs as syn
@@ -57,12 +58,12 @@ def test_block_edges(N, L, Lr):
 
 @pytest.mark.parametrize("B,R,L,vocab,N", [
     (300, 1, 90, 40, 4),        # two workgroups on a unit
-    (1300, 1, 1000, 300, 4),    # every order on its own
-    (1300, 4, 300, 50, 4),      # pairs
-    (2300, 2, 200, 500, 4),     # ten workgroups on a unit
-    (1600, 3, 280, 3000, 4),    # pairs, eight on a unit
+    (1300, 1, 1000, 300, 4),    # six
+    (1300, 4, 300, 50, 4),
+    (2300, 2, 200, 500, 4),     # nine
+    (1600, 3, 280, 3000, 4),    # seven
     (9000, 1, 40, 30, 4),       # as many workgroups as a unit takes
-    (40, 2, 2700, 50257, 4),    # order 1 apart from the others
+    (40, 2, 2700, 50257, 4),    # a unit for each, nine blocks a wavefront
     (600, 1, 4096, 2, 3),       # long runs: counters near their limit
     (70, 1, 7000, 50257, 4),    # longer than the path's own shapes
     (33, 1, 8192, 3, 8),
@@ -74,9 +75,12 @@ def test_plans(B, R, L, vocab, N):
 @pytest.mark.parametrize("B", [256, 257])   # a unit for each workgroup, and one shared
 @pytest.mark.parametrize("R,L,vocab,N", [
     (1, 100, 40, 4),
+    (2, 4000, 3000, 2),
+    (3, 2500, 300, 2),
+    (62, 190, 50, 2),
     (2, 6200, 3000, 3),         # 24 blocks a wavefront, all of LDS: alone on the unit either way
     (3, 5000, 3000, 4),
-    (62, 300, 50, 4),           # 24 blocks, less than half of LDS
+    (62, 300, 50, 4),
 ])
 def test_alone_on_a_unit(B, R, L, vocab, N):
     w = syn.random_small(680 + R, B=B, R=R, vocab=vocab, max_len=L, min_len=L // 2)
@@ -102,16 +106,60 @@ def test_full_tables(B, R, L, Lr, vocab, N):
 
 
 @pytest.mark.parametrize("N", [1, 4])
-def test_tokens_chosen_to_collide(N):
-    # 150 token ids whose products with the table's multiplier are the smallest there are: all of
-    # them walk the same sequence of buckets, further than an entry can count
-    vocab = (1 << 31) - 1
-    inverse = pow(0x9E3779B1, -1, 1 << 31)
-    ids = np.array([(k * inverse) % (1 << 31) for k in range(150)], dtype=np.int64)
-    ids = ids[ids < vocab].astype(np.int32)
-    w = syn.random_small(631, B=6, R=2, vocab=len(ids), max_len=400, min_len=300)
+@pytest.mark.parametrize("R", [1, 2, 3])
+def test_tokens_chosen_to_collide(R, N):
+    # tokens that walk the same sequence of buckets, further than an entry can count (test_plans.py):
+    # the loop that needs no table, for each way of counting matches
+    ids, vocab = fused_rows.colliding_ids()
+    w = syn.random_small(631, B=6, R=R, vocab=len(ids), max_len=400, min_len=300)
     w.cand, w.refs, w.vocab = ids[w.cand], ids[w.refs], vocab
     check(w, N)
+
+
+def drawn(seed, B, R, cs, rs):
+    """Every eighth row full, the others up to an eighth of it; between 3 and 100 different tokens a group,
+    references that share three quarters of them with the candidate."""
+    rng = np.random.default_rng(seed)
+    full = (np.arange(B) % 8 == seed % 8) | (np.arange(B) < 2)
+    cl = np.where(full, cs, rng.integers(0, cs // 8 + 2, B)).astype(np.int32)
+    rl = np.where(full[:, None], rs, rng.integers(0, rs // 8 + 2, (B, R))).astype(np.int32)
+    cl, rl = np.minimum(cl, cs), np.minimum(rl, rs)
+    kinds = rng.choice([3, 20, 100], B).astype(np.int32)
+    base = rng.integers(0, 1 << 30, (B, max(cs, rs)), dtype=np.int32) % kinds[:, None]
+
+    def varied(rows, length):
+        other = rng.integers(0, 100, rows.shape, dtype=np.int32)
+        rows = np.where(rng.random(rows.shape, dtype=np.float32) < 0.25, other, rows)
+        return np.where(np.arange(rows.shape[-1]) < length[..., None], rows, 0).astype(np.int32)
+
+    cand = varied(base[:, :cs], cl)
+    refs = varied(np.broadcast_to(base[:, None, :rs], (B, R, rs)), rl)
+    return syn.Workload("drawn", 100, cand, cl, refs, rl)
+
+
+def check_row(seed, mode, shape):
+    B, R, cs, rs, N = shape
+    w = drawn(seed, B, R, cs, rs)
+    print(mode, shape, flush=True)
+    if mode != "rouge":
+        check(w, N, int64=seed % 2 == 1, rouge=False)
+        return
+    want = oracle.rouge_n(w.cand, w.cand_len, w.refs, w.ref_len, n=N)
+    prf, overlap, best = tb.tensorrouge_n(dev(w.cand), dev(w.cand_len), dev(w.refs), dev(w.ref_len), n=N,
+                                          vocab_size=w.vocab, want_overlap=True, want_best=True)
+    check_rouge(want, overlap.cpu().numpy(), best.cpu().numpy(), prf.cpu().numpy(), TOL)
+
+
+@pytest.mark.parametrize("kernel", list(fused_rows.KERNELS), ids=str)
+def test_every_kernel(kernel):
+    for blocks, shape in fused_rows.KERNELS[kernel].items():
+        check_row(690 + blocks, kernel[2], shape)
+
+
+@pytest.mark.parametrize("way", list(fused_rows.PASSES))
+def test_every_way_to_divide_the_orders(way):
+    for i, (alone, mode, shape) in enumerate(fused_rows.PASSES[way]):
+        check_row(720 + i, mode, shape)
 
 
 @pytest.mark.parametrize("N", [5, 6, 7, 8])

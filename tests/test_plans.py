@@ -9,6 +9,7 @@ import numpy as np
 import pytest
 from scipy import stats
 
+import fused_rows
 import paper_2510_05485_amd as tb
 from paper_2510_05485_amd import build
 
@@ -104,6 +105,53 @@ def test_many_counters_get_a_table_for_each_stretch(plans):
         assert plans.fused_plan(B, cs, rs, R, N, bits, False, out)
         workgroups = min((B + 255) // 256, 32 // out[5])
         assert not out[3] & 2 or out[4] * workgroups <= LDS, (B, R, N)
+
+
+def way_of(pass_ends, orders):
+    ends = [pass_ends >> 4 * n & 15 for n in range(1, orders)]  # of the stretches that begin with 2, 3, ...
+    if ends[0] == 2 and orders > 2:
+        return "single" if ends[1] == 3 else "pairs"
+    return ("together" if pass_ends & 2 else "stretches") + (" apart" if pass_ends & 1 else "")
+
+
+def test_the_rows_reach_what_they_name(plans):
+    out = (ctypes.c_int64 * 9)()
+    kernels = (1, 2, 3, 4, 5, 6, 8, 12, 16, 24)
+
+    def planned(mode, B, R, cs, rs, N):
+        assert R in {"one": (1,), "two": (2,), "more": range(3, 63), "rouge": range(1, 63)}[mode]
+        assert plans.fused_plan(B, cs, rs, R, N, fused_rows.BITS, mode == "rouge", out)
+        # (longer shapes than the path's own go there from some tens of groups on)
+        assert B >= 100 or plans.fused_path(cs, rs, R, fused_rows.BITS)
+        return out
+
+    for (alone, keep, mode), rows in fused_rows.KERNELS.items():
+        assert sorted(rows) == list(kernels[0 if alone else 1:])
+        for blocks, shape in rows.items():
+            plan = planned(mode, *shape)
+            assert (plan[8], plan[7]) == (alone, keep), (shape, list(plan))
+            assert blocks == min(k for k in kernels if k >= plan[6]), (shape, list(plan))
+    for way, rows in fused_rows.PASSES.items():
+        for alone, mode, shape in rows:
+            plan = planned(mode, *shape)
+            assert (plan[8], way_of(plan[3], shape[4])) == (alone, way), (shape, list(plan))
+    assert len(fused_rows.KERNELS) == 16
+
+
+def test_colliding_ids_walk_further_than_an_entry_counts(plans):
+    # order 1 of the batch of test_gpu_fused.py: so many of the ids have the same bucket and the same step that
+    # they fill more buckets than an entry can count
+    out = (ctypes.c_int64 * 9)()
+    ids = fused_rows.colliding_ids()[0].astype(np.uint64)
+    word = np.uint64(0xFFFFFFFF)
+    for R, N, rouge in itertools.product((1, 2, 3), (1, 2, 4), (False, True)):
+        assert plans.fused_plan(6, 400, 400, R, N, 31, rouge, out)
+        lg, id_bits, key_bits = out[:3]
+        h = ids * np.uint64(0x9E3779B1 << 32 - key_bits) & word
+        remainder = h << np.uint64(lg - 2) & word
+        walks = list(zip(h >> np.uint64(34 - lg), remainder >> np.uint64(21)))
+        longest = 2 ** (min(32 - key_bits + lg - 2, 32) - id_bits) - 1
+        assert max(walks.count(walk) for walk in set(walks)) > 4 * longest, (R, N, rouge, list(out))
 
 
 def entries(tokens, first, last, rng):
