@@ -3,10 +3,10 @@
 // Tokens are read from HBM once; dictionary and counters never leave LDS; one score (plus optional
 // integer statistics) goes out.  What bounds it: instruction issue.  A lone small group pays seven or
 // eight cycles per instruction of its longest wavefront.  A full chip issues, per cycle and compute unit,
-// 0.71 vector and 0.49 scalar instructions (512 x 1024 with four references), 0.81 and 0.53 (1024 x 2048),
-// 0.56 and 0.56 (4096 x 512 with two): 66 to 79 % of the 1.7 that a mix of both kinds reaches at most
+// 0.71 vector and 0.48 scalar instructions (512 x 1024 with four references), 0.85 and 0.49 (1024 x 2048),
+// 0.66 and 0.53 (4096 x 512 with two): 70 to 79 % of the 1.7 that a mix of both kinds reaches at most
 // (counters of rocprofv3; 1.5 of vector instructions alone, 1.0 of scalar ones), the scalar ones from
-// loops, masks and bookkeeping.  LDS is not the limit (0.06 to 0.09 instructions; a random 16-byte read
+// loops, masks and bookkeeping.  LDS is not the limit (0.07 to 0.09 instructions; a random 16-byte read
 // takes 12.5 cycles per wavefront, a 4-byte one 6.5, a compare-and-swap 12).  So:
 //   * Symbols.  Order 1 turns every token into the candidate position that holds its first
 //     occurrence there (its "symbol"), or into "absent" (-1).  An n-gram of order n >= 2 is then
@@ -47,9 +47,9 @@
 // Measured on gfx950 (us of GPU time, 4 orders; in brackets the kernel that entered every n-gram and
 // swept its counters, and the one before that, with a barrier per insertion and look-up of each order):
 // 16 x 256 tokens with one reference 6.0 (6.7, 9.5), 256 x 1088 8.3 (9.4, 12.8), 512 x 1024 with four
-// references 17.8 (19.8, 22.8), 4096 x 512 with two and the batch's sums 34.7 (47.7, 50.5), 4096 x 2048 with
-// two 106 (145, 171), 1000 x 96 with up to eight 10.4 (10.5, 13.7), ROUGE-2 of 512 x 512 with three 7.1
-// (9.6, 12.5); 128 x 5000 with one 22.7 (28.5; 55 on three staged kernels), 128 x 8192 32.7 (46.6; 98 on the
+// references 17.5 (19.8, 22.8), 4096 x 512 with two and the batch's sums 31.7 (47.7, 50.5), 4096 x 2048 with
+// two 102 (145, 171), 1000 x 96 with up to eight 10.2 (10.5, 13.7), ROUGE-2 of 512 x 512 with three 7.1
+// (9.6, 12.5); 128 x 5000 with one 21.7 (28.5; 55 on three staged kernels), 128 x 8192 31.1 (46.6; 98 on the
 // partitioned ones).
 #include <type_traits>
 
@@ -1129,15 +1129,16 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
 // shape, more than a tenth behind in five of them):
 //   * A pass costs its barriers, its sums, clearing the table and the block loop again, but has the
 //     counters of its orders only.  Up to four workgroups on a unit, all at once, want their exact share
-//     of LDS, whatever passes that takes (1024 x 2048: pairs, four a unit, 34.5 us; orders 1 to 4
-//     together, three a unit, 41).  Where there are more, fewer passes win with down to half as many of
-//     them side by side (4096 x 512 with two references: pairs, sixteen a unit, 44.9; orders 1 to 4 together, eight,
-//     37.9; 2493 x 711 with two 42.7 and 35.3).  Every order on its own only where nothing else fits.
+//     of LDS, whatever passes that takes (1024 x 2048: pairs, four a unit, 25.4 us; orders 1 to 4
+//     together, three a unit, 33.3).  Where there are more, fewer passes win with down to half as many of
+//     them side by side (4096 x 512 with two references: pairs, sixteen a unit, 32.0; orders 1 to 4 together, eight,
+//     28.0; 2493 x 711 with two, ten and seven a unit, 34.3 and 30.4).  Every order on its own only where nothing
+//     else fits.
 //   * A table that is nearly full costs more than anything else: probe sequences of the wavefront's
 //     slowest lane grow from 1 to 4 requests between a quarter and three quarters.  More than twelve
 //     slots a position, six for one order, cost more to clear than they save (38 x 1425 with three
 //     references, one order: 7.2 -> 6.9 us).
-//   * 32 wavefronts a unit hide latency (16 take 512 x 1024 with four references from 18.8 to 21.5 us);
+//   * 32 wavefronts a unit hide latency (16 take 512 x 1024 with four references from 17.8 to 19.6 us);
 //     a workgroup with fewer blocks than wavefronts idles, and with two blocks or less per wavefront its
 //     prologue outweighs them.
 //   * More than 12 to 16 blocks a wavefront are short of registers where workgroups share a unit (of 24, 28 to
