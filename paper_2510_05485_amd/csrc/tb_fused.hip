@@ -244,8 +244,8 @@ __device__ __forceinline__ T pick(int f, T cand, T ref, T ref1) {
 }
 
 // BLOCKS: blocks of 64 positions per wavefront.  KEEP: a pass starts above order 2, with the ids of
-// the order below.
-template <int BLOCKS, bool KEEP, Mode MODE>
+// the order below.  ALONE: the kernel that has more registers.
+template <int BLOCKS, bool KEEP, Mode MODE, bool ALONE>
 __device__ __forceinline__
 void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
                   const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
@@ -694,7 +694,10 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
           // Two orders have order_fields words: the first order's count and first reference in word 0,
           // the second order's count in word `middle`, in the upper half if the last reference of the
           // first order has the lower one.  Words of both are read side by side: one after the other
-          // they are two chains of dependent steps.
+          // they are two chains of dependent steps, which is better only where registers are so short that
+          // what is read side by side goes through scratch (24 blocks, shared units: 860 x 343 with 16 references
+          // of 1184, eight orders, 150 -> 115 us; 170 shapes 1.024, the slowest 0.975).
+          constexpr bool BOTH = BLOCKS <= 16 || ALONE;
           const int middle = order_fields >> 1;
           const bool shared = order_fields & 1;
           auto above = [](uint32_t count, uint32_t most) __attribute__((always_inline)) {
@@ -712,6 +715,20 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
               const uint32_t head = *lds<uint32_t>(e), second = *lds<uint32_t>(e + to_middle);
               uint32_t most0 = head >> 16, most1 = shared ? 0u : second >> 16;
               if (shared) most0 = max_halves(most0, second & 0xFFFFu);
+              if (!BOTH) {
+                auto most_of = [&](uint32_t& most, int w, int end) __attribute__((always_inline)) {  // words w..end - 1
+                  uint32_t at = e + uint32_t(w) * array_bytes;
+#pragma unroll 1
+                  for (; w < end; ++w, at += array_bytes) most = max_halves(most, *lds<uint32_t>(at));
+                };
+                most_of(most0, 1, middle);
+                part += above(head & 0xFFFFu, most0);
+                if (two) {
+                  most_of(most1, middle + 1, order_fields);
+                  part += above(shared ? second >> 16 : second & 0xFFFFu, most1) << 16;
+                }
+                continue;
+              }
               uint32_t at = e;
               int w = 1;
 #pragma unroll 1
@@ -986,7 +1003,7 @@ __global__ __launch_bounds__(1024, 8) __attribute__((amdgpu_num_sgpr(80)))
 void fused_kernel(const void* cand, const int32_t* cand_lens, const void* refs,
                   const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
                   uint32_t cand_shape, uint32_t ref_shape, FusedArgs by_value) {
-  fused_group<BLOCKS, KEEP, MODE>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
+  fused_group<BLOCKS, KEEP, MODE, false>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
                                   ref_shape);
 }
 // The same where a compute unit has one workgroup at a time: its wavefronts, four per SIMD, may have all
@@ -1001,7 +1018,7 @@ __global__ __launch_bounds__(1024, 4)
 void fused_kernel_alone(const void* cand, const int32_t* cand_lens, const void* refs,
                         const int32_t* ref_lens, const int32_t* ref_count, const int32_t* ref_offsets,
                         uint32_t cand_shape, uint32_t ref_shape, FusedArgs by_value) {
-  fused_group<BLOCKS, KEEP, MODE>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
+  fused_group<BLOCKS, KEEP, MODE, true>(cand, cand_lens, refs, ref_lens, ref_count, ref_offsets, cand_shape,
                                   ref_shape);
 }
 
