@@ -1162,9 +1162,9 @@ bool set_passes(int passes, int N, int bits, FusedPlan* plan, int* orders_per_pa
 //     54 vector registers go to scratch): these get more wavefronts, and the LDS of as many workgroups as then
 //     fit (5340 x 242 with six references, 17 blocks, 76.8 us; 9 blocks of four wavefronts 51.0; 13 blocks and
 //     more in 300 drawn shapes: 1.09 of the speed).  Two wavefronts, and four with more than one order, gain from 13
-//     blocks on (1.13 and 1.07), four with one order, one and eight from 17 on (13 to 16: 0.9 to 1.0 with twice
-//     the wavefronts).  Two workgroups of 16 wavefronts keep up to 24 blocks: they are faster with
-//     scratch than one a unit without it (90 shapes: 1.23).
+//     blocks on (1.13 and 1.07); four with one order, one, and eight with more than two orders from 17 on (13 to
+//     16: 0.9 to 1.0 with twice the wavefronts); eight with one or two orders never do (0.97).  Two workgroups of
+//     16 wavefronts keep up to 24 blocks: they are faster with scratch than one a unit without it (90 shapes: 1.23).
 bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits,
                 bool rouge, FusedPlan* plan) {
   if (R + 1 > kMaxSeqs || cand_stride > 12288 || ref_stride > 65535 || bits > 31) return false;
@@ -1190,8 +1190,11 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
         waves *= 2;
     }
     // blocks a wavefront takes at most (see above), and workgroups that the wavefronts then leave room for
-    const int most = r < 2 ? kMaxBlocks : waves == 2 || (waves == 4 && N > 1) ? 12 : 16;
-    while (waves < 16 && blocks > int64_t(most) * waves) waves *= 2;
+    auto most = [&]() -> int64_t {
+      if (r < 2 || (waves == 8 && N <= 2)) return kMaxBlocks;
+      return waves == 2 || (waves == 4 && N > 1) ? 12 : 16;
+    };
+    while (waves < 16 && blocks > most() * waves) waves *= 2;
     if (r > 32 / waves) r = 32 / waves;
     // All orders of a pass together enter at most as many n-grams as the candidate has positions.
     const int64_t entries = cand_stride;

@@ -80,8 +80,8 @@ def fused_table(plans, *shape):
 
 
 def test_shared_units_keep_their_registers(plans):
-    # more than 16 blocks a wavefront need scratch where workgroups share a unit, and are for workgroups
-    # of 16 wavefronts only; no kernel of one block is built for these units
+    # more than 16 blocks a wavefront need scratch where workgroups share a unit, and are for workgroups of 16
+    # wavefronts and, up to order 2, of 8 only; no kernel of one block is built for these units
     out = (ctypes.c_int64 * 9)()
     rng, seen = random.Random(29), {}
     for _ in range(40000):
@@ -91,7 +91,7 @@ def test_shared_units_keep_their_registers(plans):
         if not plans.fused_plan(int(257 * 40 ** rng.random()), cs, rs, R, N, 16, rouge, out) or out[8]:
             continue
         waves, blocks = out[5:7]
-        assert blocks >= 2 and (blocks <= 16 or waves == 16), (cs, rs, R, N, rouge, list(out))
+        assert blocks >= 2 and (blocks <= 16 or waves == 16 or (waves == 8 and N <= 2)), (cs, rs, R, N, rouge, list(out))
         seen[waves] = max(seen.get(waves, 0), blocks)
     assert seen[16] > 16 and min(seen[w] for w in (1, 2, 4, 8)) > 8, seen
 
