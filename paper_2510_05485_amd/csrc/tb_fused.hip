@@ -4,7 +4,7 @@
 // integer statistics) goes out.  What bounds it: instruction issue.  A lone small group pays seven or
 // eight cycles per instruction of its longest wavefront.  A full chip issues, per cycle and compute unit,
 // 0.71 vector and 0.48 scalar instructions (512 x 1024 with four references), 0.85 and 0.49 (1024 x 2048),
-// 0.66 and 0.53 (4096 x 512 with two): 70 to 79 % of the 1.7 that a mix of both kinds reaches at most
+// 0.67 and 0.53 (4096 x 512 with two): 70 to 79 % of the 1.7 that a mix of both kinds reaches at most
 // (counters of rocprofv3; 1.5 of vector instructions alone, 1.0 of scalar ones), the scalar ones from
 // loops, masks and bookkeeping.  LDS is not the limit (0.07 to 0.09 instructions; a random 16-byte read
 // takes 12.5 cycles per wavefront, a 4-byte one 6.5, a compare-and-swap 12).  So:
