@@ -75,6 +75,8 @@ namespace {
 constexpr int kMaxSeqs = kWave;     // candidate + references, one lane each
 constexpr int kPadSymbols = 8;      // absent symbols behind every sequence: orders up to 8
 constexpr int kMaxBlocks = 24;      // per wavefront
+constexpr int kApartBlocks = 3;     // up to here what is left of a wavefront's blocks is not put together
+constexpr size_t sums_bytes(bool rouge) { return 64 + 16 + (rouge ? kMaxSeqs * 4 : 0); }
 
 // A kernel's plain arguments as they lie at the start of its argument segment.
 struct PlainArgs {
@@ -314,6 +316,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   const uint32_t lost_at = part_at + 64;  // non-zero: a probe sequence was too long to be counted
   const uint32_t overlap_at = lost_at + 4;        // ROUGE: overlap with each reference
   const uint32_t closest_at = lost_at + 4;        // BLEU: closest reference length, brevity penalty
+  const uint32_t sequence_at = part_at + uint32_t(sums_bytes(ROUGE));  // a byte for each block: its reference (see LISTED)
   if (prio) __builtin_amdgcn_s_setprio(3);
 
   const uint32_t token_bytes = wide ? 8u : 4u;
@@ -523,15 +526,17 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     }
   };
 
-  // Counters: 16-bit fields, two a word, the words of all ids in one array per pair of fields.
-  //   * One reference, and ROUGE-N: a field is the n-gram's count in the candidate less what the
-  //     reference has had of it so far (a negative lower half borrows from the upper one).  A reference's
-  //     n-gram that finds it positive is a match, and matches are all that is asked for: no pass over
-  //     the counters, which cost a lone workgroup of 16 x 256 tokens 1600 of 15000 cycles, and one with
-  //     eight references of 464 tokens (ROUGE-1) 7 of 11 us.
-  //   * Two references: count less the reference's count, one field each; the smaller one is what the
-  //     candidate has beyond both.
-  //   * More: the count in the candidate, then the counts in the references.
+  // Counters: 16-bit fields, two a word, the words of all ids in one array per pair of fields.  A position
+  // whose n-gram has the position's own id (its first occurrence) is not counted: no reference asks for
+  // other ids, so a field that nothing was added to stands for one occurrence in the candidate.
+  //   * One reference, and ROUGE-N: a field is one less than the n-gram's count in the candidate, less
+  //     what the reference has had of it so far (a negative lower half borrows from the upper one).  A
+  //     reference's n-gram that does not find it negative is a match, and matches are all that is asked
+  //     for: no pass over the counters, which cost a lone workgroup of 16 x 256 tokens 1600 of 15000
+  //     cycles, and one with eight references of 464 tokens (ROUGE-1) 7 of 11 us.
+  //   * Two references: the same less the reference's count, one field each; the smaller one is (one less
+  //     than) what the candidate has beyond both.
+  //   * More: one less than the count in the candidate, then the counts in the references.
   constexpr bool matching = ONE || ROUGE;
   constexpr bool differences = MODE != kReferences;
   const int order_fields = differences ? R : R + 1;
@@ -556,14 +561,17 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     lds_add(at, unit);
     return 0u;
   };
-  // whether the field was positive (low + 65536 * high, each within 32767)
+  // whether the field was not negative (low + 65536 * high, each within 32767)
   auto is_match = [&](int order, int f, uint32_t word) __attribute__((always_inline)) {
     const int odd = ((ROUGE ? 0 : order * order_fields) + first_ref + f) & 1;
-    return int32_t(word << (odd ? 0 : 16)) > (odd ? 0x7FFF : 0);
+    return int32_t(word << (odd ? 0 : 16)) >= (odd ? -0x8000 : 0);
   };
-  int matches1 = 0, matches[3] = {0, 0, 0};  // of this lane: order 1, orders lo.. of the pass
+  // Of this lane, orders 1, 2 and the ones behind them that a stretch has: the reference's matches, and
+  // the candidate's positions whose n-gram has another position's id.
+  // (Two orders in the halves of a word, the second one in the upper half.)
+  uint32_t match12 = 0, matches[2] = {0, 0};
+  uint32_t repeat12 = 0, repeats[2] = {0, 0};
   int overlap = 0;                           // ROUGE: lane f: matches with reference f
-  int distinct = 0;  // lane n - 1: this wavefront's positions whose n-gram has their id
   const int my_cand_blocks = (max(cand_blocks - wave, 0) + nwaves - 1) >> log2_waves;
   const int my_blocks = (max(blocks - wave, 0) + nwaves - 1) >> log2_waves;
   // byte offset of the symbol of this lane's position in the wavefront's first block, and from
@@ -574,6 +582,10 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   const uint32_t id_limit = table.id_limit;
   const bool want_distinct = want;
 
+  // What is left of blocks is put together to full ones (COMPACT; not where a wavefront has few).
+  constexpr bool COMPACT = BLOCKS > kApartBlocks;
+  constexpr bool LISTED = COMPACT && !FEW;  // the references of positions are looked up
+
   // ---- order 1: tokens become symbols
   {
     int i = 0, b = wave;
@@ -582,14 +594,12 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       int32_t got = -1;
       if (v >= 0) {
         got = int32_t(table.claim<LOOK_FIRST>(uint32_t(v) * table.multiplier, id));
-        if (!ROUGE || N == 1) count_candidate(0, uint32_t(got));
-      }
-      if (!ROUGE && want_distinct) {
-        const int own = __popcll(__builtin_amdgcn_ballot_w64(got == int32_t(id)));
-        distinct += lane == 0 ? own : 0;
+        if (got != int32_t(id)) {
+          if (!ROUGE || N == 1) count_candidate(0, uint32_t(got));
+          if (!ROUGE) ++repeat12;
+        }
       }
       *lds<int16_t>(s) = int16_t(got);
-      v = got;
       id += nt;
       s += sym_stride;
       b += nwaves;
@@ -617,19 +627,15 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
         }
       }
       *lds<int16_t>(s + uint32_t(2 * kPadSymbols) * f) = int16_t(got);
-      if (!ROUGE) matches1 += match ? 1 : 0;
+      if (LISTED && N > 2) *lds<uint8_t>(sequence_at + uint32_t(b)) = uint8_t(f);
+      if (!ROUGE) match12 += match ? 1u : 0u;
       if (ROUGE && N == 1) {
         const int of_block = __popcll(__builtin_amdgcn_ballot_w64(match));
         overlap += lane == f ? of_block : 0;
       }
-      v = got;
       s += sym_stride;
       b += nwaves;
     });
-    if (KEEP) {
-#pragma unroll 1
-      for (; i < BLOCKS; ++i) rotate(std::integral_constant<int, 1>{});
-    }
   }
   TB_FSTAMP(3);
 
@@ -638,27 +644,38 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   // those of order 2 go beside the look-ups of order 1.  (A pass for each stretch, with its sums, its
   // clearing and three barriers more: eight orders of 457 x 10 with three references 10.9 us instead of
   // 9.8, of 3946 x 21 17.0 instead of 15.5; 517 drawn shapes of five to eight orders 1.09 of its speed.)
+  constexpr int DEPTH = KEEP ? 3 : 2;  // orders of a stretch behind order 2 (without KEEP there are four at most)
+  // KEEP: blocks of val that hold what is left of the candidate's and of the references' positions (from
+  // my_cand_blocks on)
+  int kept_cand = 0, kept = my_cand_blocks;
   int swept = 0, counted = 0, hi = 1;
   bool pass_ends = a.pass_ends & 1u;
 #pragma unroll 1
   while (true) {
     // ---- sums of the orders, two in the halves of a word (neither exceeds the positions), in LDS, where
-    // the tail's lanes find theirs: matches of a stretch, or for a whole pass what the candidate has of
-    // its n-grams beyond every reference (the rest of them is min(count, largest reference count))
-    auto add_up = [&](int n, uint32_t part) __attribute__((always_inline)) {
+    // the tail's lanes find theirs: matches of a stretch, or for a whole pass min(count, largest reference
+    // count) of the candidate's n-grams; with two references what the candidate has of them beyond both
+    // (the rest of them is that minimum)
+    auto add_up = [&](uint32_t at, int n, uint32_t part) __attribute__((always_inline)) {
       part = uint32_t(row_inclusive_scan(int(part)));
-      if ((lane & 15) == 15) lds_add(part_at + 4u * uint32_t(n - 1), part);
+      if ((lane & 15) == 15) lds_add(at + 4u * uint32_t(n - 1), part);
     };
-    if (!ROUGE && matching && (pass_ends || (KEEP && hi > 1))) {
-      if (my_cand_blocks < my_blocks) {  // (uniform)
-        if (counted == 0) {
-          add_up(1, uint32_t(matches1 | matches[0] << 16));
-          if (hi > 2) add_up(3, uint32_t(matches[1] | matches[2] << 16));
-        } else {
-          add_up(counted + 1, uint32_t(matches[0] | matches[1] << 16));
-          if (hi > counted + 2) add_up(counted + 3, uint32_t(matches[2]));
-        }
-        matches[0] = matches[1] = matches[2] = 0;
+    auto add_orders = [&](uint32_t at, uint32_t first, const uint32_t (&more)[2]) __attribute__((always_inline)) {
+      if (counted < 2) add_up(at, 1, first);
+      if (hi > 2) {
+        const int n = KEEP ? max(counted, 2) + 1 : 3;
+        add_up(at, n, more[0]);
+        if (KEEP && hi > n + 1) add_up(at, n + 2, more[1]);
+      }
+    };
+    if (!ROUGE && (pass_ends || (KEEP && hi > 1))) {
+      if (matching && my_cand_blocks < my_blocks) {  // (uniform)
+        add_orders(part_at, match12, matches);
+        match12 = matches[0] = matches[1] = 0;
+      }
+      if ((TWO || want_distinct) && my_cand_blocks > 0) {
+        add_orders(part_at + 32, repeat12, repeats);
+        repeat12 = repeats[0] = repeats[1] = 0;
       }
       counted = hi;
     }
@@ -679,11 +696,11 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
             for (int k = tid; k < cand_len; k += nt, e += 4u * uint32_t(nt)) {
               const int32_t v0 = *lds<int32_t>(e), v1 = *lds<int32_t>(e + second);
               const int32_t low0 = int16_t(v0), low1 = int16_t(v1);
-              part += uint32_t(max(min(low0, (v0 - low0) >> 16), 0)) |
-                      uint32_t(max(min(low1, (v1 - low1) >> 16), 0)) << 16;
+              part += uint32_t(max(min(low0, (v0 - low0) >> 16) + 1, 0)) |
+                      uint32_t(max(min(low1, (v1 - low1) >> 16) + 1, 0)) << 16;
             }
             if (n == hi) part &= 0xFFFFu;
-            add_up(n, part);
+            add_up(part_at, n, part);
           }
         } else {
           typedef uint16_t Halves __attribute__((ext_vector_type(2)));
@@ -700,8 +717,9 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
           constexpr bool BOTH = BLOCKS <= 16 || ALONE;
           const int middle = order_fields >> 1;
           const bool shared = order_fields & 1;
-          auto above = [](uint32_t count, uint32_t most) __attribute__((always_inline)) {
-            return uint32_t(max(int32_t(count) - int32_t(max(most & 0xFFFFu, most >> 16)), 0));
+          // (where nothing has been added to a position's fields, no reference has)
+          auto least = [](uint32_t count, uint32_t most) __attribute__((always_inline)) {
+            return min(count + 1u, max(most & 0xFFFFu, most >> 16));
           };
 #pragma unroll 1
           for (int n = swept + 1; n <= hi; n += 2) {
@@ -722,10 +740,10 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
                   for (; w < end; ++w, at += array_bytes) most = max_halves(most, *lds<uint32_t>(at));
                 };
                 most_of(most0, 1, middle);
-                part += above(head & 0xFFFFu, most0);
+                part += least(head & 0xFFFFu, most0);
                 if (two) {
                   most_of(most1, middle + 1, order_fields);
-                  part += above(shared ? second >> 16 : second & 0xFFFFu, most1) << 16;
+                  part += least(shared ? second >> 16 : second & 0xFFFFu, most1) << 16;
                 }
                 continue;
               }
@@ -746,13 +764,13 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
                 most0 = max_halves(most0, v0);
                 most1 = max_halves(most1, v1);
               }
-              part += above(head & 0xFFFFu, most0);
+              part += least(head & 0xFFFFu, most0);
               if (two) {
                 if (shared) most1 = max_halves(most1, *lds<uint32_t>(at + array_bytes + to_middle));
-                part += above(shared ? second >> 16 : second & 0xFFFFu, most1) << 16;
+                part += least(shared ? second >> 16 : second & 0xFFFFu, most1) << 16;
               }
             }
-            add_up(n, part);
+            add_up(part_at, n, part);
           }
         }
       }
@@ -781,103 +799,210 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     const int payload = swept == 0 ? __builtin_amdgcn_readfirstlane(a.first_payload)
                                    : __builtin_amdgcn_readfirstlane(a.later_payload);
     const uint32_t tag_unit = table.multiplier << payload;
+    auto hash_of = [&](int n, uint32_t prefix, uint32_t last) __attribute__((always_inline)) {
+      return ((prefix << id_bits) | last) * table.multiplier + uint32_t(n - 1 - swept) * tag_unit;
+    };
+    // Order 2 is for all positions of a block, and what goes on from it is a word: the position as
+    // blocks number them (64 * block + lane) and, in the upper half, its id; -1: nothing.  Orders from
+    // `next` on take such words.
+    const bool dense = !KEEP || lo == 2;
+    const int next = dense ? 3 : lo;
+    const bool deeper = KEEP || hi > 2;
+    const uint32_t ahead = 2u * uint32_t(next - 1), other = sym_at + ahead;
+    auto word_of = [](uint32_t position, uint32_t id) __attribute__((always_inline)) { return int32_t(position | id << 16); };
+
+    // The candidate's n-gram at `position`; repeated(id): its id is that of another position.  (The n-gram
+    // that goes on like the candidate does at the prefix's id has that id.)  A position that has its own id
+    // is through: all longer n-grams at it have the same, they go on like it does, and none is counted.
+    auto enter = [&](int n, uint32_t position, uint32_t prefix, int32_t last, int32_t implied,
+                     auto&& repeated) __attribute__((always_inline)) {
+      uint32_t id = prefix;
+      if (last != implied) id = table.claim<LOOK>(hash_of(n, prefix, uint32_t(last)), position);
+      if (id == position) return;
+      if (!ROUGE || n == N) count_candidate(n - 1 - swept, id);
+      repeated(id);
+    };
+    // Orders from `next` on, of lanes that have gone on so far; left: the word of those that go on from there.
+    auto enter_step = [&](auto depth, uint32_t position, uint32_t prefix, const int32_t (&lasts)[DEPTH],
+                          int32_t& left, auto&& again) __attribute__((always_inline)) {
+      constexpr int d = decltype(depth)::value;
+      if (lasts[d] < 0) return;  // (an absent symbol: no n-gram here)
+      const int32_t implied = *lds<int16_t>(other + 2u * prefix + 2u * d);
+      enter(next + d, position, prefix, lasts[d], implied, [&](uint32_t id) __attribute__((always_inline)) {
+        if (!ROUGE) repeats[d >> 1] += d & 1 ? 0x10000u : 1u;
+        if (d == DEPTH - 1 || next + d == hi) {  // (uniform)
+          left = word_of(position, id);
+        } else {
+          if constexpr (d + 1 < DEPTH) again(std::integral_constant<int, d + 1>{}, position, id, lasts, left, again);
+        }
+      });
+    };
+    auto enter_more = [&](int32_t word) __attribute__((always_inline)) {
+      int32_t left = -1;
+      const uint32_t position = uint32_t(word) & 0xFFFFu;
+      if (word >= 0) {
+        int32_t lasts[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) lasts[d] = *lds<int16_t>(other + 2u * position + 2u * d);
+        enter_step(std::integral_constant<int, 0>{}, position, uint32_t(word) >> 16, lasts, left, enter_step);
+      }
+      return left;
+    };
+    // The n-gram of reference f; found(id, what count_reference returned).  Lanes drop out where an n-gram is
+    // not the candidate's, and stay out for the orders behind it.
+    auto look_up = [&](int n, int f, uint32_t prefix, int32_t last, uint32_t implied_at, auto&& found) __attribute__((always_inline)) {
+      const int32_t implied = *lds<int16_t>(implied_at);
+      const uint32_t id = table.find(hash_of(n, prefix, uint32_t(last)), [&] { return implied == last; }, prefix);
+      if (id >= id_limit) return;
+      uint32_t word = 0;
+      if (!ROUGE || n == N) word = count_reference(n - 1 - swept, f, id);
+      found(id, word);
+    };
+    auto look_up_step = [&](auto depth, int f, uint32_t position, uint32_t prefix, const int32_t (&lasts)[DEPTH],
+                            int32_t& left, auto&& again) __attribute__((always_inline)) {
+      constexpr int d = decltype(depth)::value;
+      if (lasts[d] < 0) return;
+      look_up(next + d, f, prefix, lasts[d], other + 2u * prefix + 2u * d, [&](uint32_t id, uint32_t counter) __attribute__((always_inline)) {
+        if (d == DEPTH - 1 || next + d == hi) {  // (uniform)
+          left = word_of(position, id);
+        } else {
+          if constexpr (d + 1 < DEPTH) again(std::integral_constant<int, d + 1>{}, f, position, id, lasts, left, again);
+        }
+        if (ROUGE) {
+          if (next + d == N && is_match(0, f, counter)) lds_add(overlap_at + 4u * uint32_t(f - 1), 1u);
+        } else if (matching) {
+          matches[d >> 1] += is_match(next + d - 1 - swept, f, counter) ? (d & 1 ? 0x10000u : 1u) : 0u;
+        }
+      });
+    };
+    // block: of the wavefront's, where words are still in the place of their positions
+    auto look_up_more = [&](int32_t word, int block) __attribute__((always_inline)) {
+      int32_t left = -1;
+      const uint32_t position = uint32_t(word) & 0xFFFFu;
+      int f = 1;
+      if (!FEW && !LISTED) f = reference_of(wave + (block << log2_waves));  // (all lanes take part)
+      if (word >= 0) {
+        if (LISTED) f = *lds<uint8_t>(sequence_at + (position >> 6));
+        if (TWO) f = position >= uint32_t(begin1) * kWave ? 2 : 1;
+        const uint32_t own = other + 2u * position + uint32_t(2 * kPadSymbols) * f;
+        int32_t lasts[DEPTH];
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) lasts[d] = *lds<int16_t>(own + 2u * d);
+        look_up_step(std::integral_constant<int, 0>{}, f, position, uint32_t(word) >> 16, lasts, left, look_up_step);
+      }
+      return left;
+    };
+    // A block's order 2, and without COMPACT the orders behind it at once.
+    const bool at_once = !COMPACT && hi > 2;
     int i = 0, b = wave;
     uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
-    // At most three orders, side by side: their symbols are requested together, distances are immediate
-    // offsets, and what an order has of its own is worked out where it is needed.
-    const uint32_t ahead = KEEP ? 2u * uint32_t(lo - 1) : 2u;
-    auto enter_block = [&](int32_t& v) __attribute__((always_inline)) {
-      int32_t cur = KEEP ? v : int32_t(*lds<int16_t>(s));
-      const uint32_t own = s + ahead, other = sym_at + ahead;
-      int32_t lasts[3];
+    auto enter_block = [&]() __attribute__((always_inline)) {
+      int32_t left = -1;
+      const int32_t prefix = *lds<int16_t>(s), last = *lds<int16_t>(s + 2);
+      int32_t lasts[DEPTH];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) lasts[d] = *lds<int16_t>(own + 2u * d);
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        if (lo + d > hi) break;  // uniform
-        const int order = lo + d - 1 - swept;
-        const int32_t last = lasts[d];
-        if (last >= 0) {  // (an absent symbol: no n-gram here)
-          const int32_t implied = *lds<int16_t>(other + 2u * uint32_t(cur) + 2u * d);
-          if (last != implied) {
-            const uint32_t h = ((uint32_t(cur) << id_bits) | uint32_t(last)) * table.multiplier +
-                               uint32_t(order) * tag_unit;
-            cur = int32_t(table.claim<LOOK>(h, id));
-          }
-          if (!ROUGE || lo + d == N) count_candidate(order, uint32_t(cur));
-        }
-        if (!ROUGE && want_distinct) {
-          const int own_ids = __popcll(__builtin_amdgcn_ballot_w64(last >= 0 && cur == int32_t(id)));
-          distinct += lane == lo + d - 1 ? own_ids : 0;
-        }
+      for (int d = 0; !COMPACT && d < DEPTH; ++d) lasts[d] = *lds<int16_t>(s + 4 + 2u * d);
+      if (last >= 0 && prefix != int32_t(id)) {
+        const int32_t implied = *lds<int16_t>(sym_at + 2u * uint32_t(prefix) + 2u);
+        enter(2, id, uint32_t(prefix), last, implied, [&](uint32_t got) __attribute__((always_inline)) {
+          if (!ROUGE) repeat12 += 0x10000u;
+          if (at_once)
+            enter_step(std::integral_constant<int, 0>{}, id, got, lasts, left, enter_step);
+          else
+            left = word_of(id, got);
+        });
       }
-      if (KEEP) v = cur;
       id += nt;
       s += sym_stride;
       b += nwaves;
+      return left;
     };
-    // Lanes drop out where an n-gram is not the candidate's, and stay out for the orders behind it.
-    auto look_up_block = [&](int32_t& v) __attribute__((always_inline)) {
+    auto look_up_block = [&]() __attribute__((always_inline)) {
       const int f = reference_of(b);
-      const uint32_t first = s + uint32_t(2 * kPadSymbols) * f;
-      const uint32_t own = first + ahead, other = sym_at + ahead;
-      int32_t lasts[3];
+      const uint32_t own = s + uint32_t(2 * kPadSymbols) * f;
+      const int32_t prefix = *lds<int16_t>(own), last = *lds<int16_t>(own + 2);
+      int32_t lasts[DEPTH];
 #pragma unroll
-      for (int d = 0; d < 3; ++d) lasts[d] = *lds<int16_t>(own + 2u * d);
-      int32_t left = -1;  // the id after these orders
+      for (int d = 0; !COMPACT && d < DEPTH; ++d) lasts[d] = *lds<int16_t>(own + 4 + 2u * d);
+      int32_t left = -1;
       bool match = false;
-      auto look_up = [&](auto depth, int32_t prefix, auto&& again) __attribute__((always_inline)) {
-        constexpr int d = decltype(depth)::value;
-        const int32_t key = int32_t(uint32_t(prefix) << id_bits) | lasts[d];
-        if (key < 0) return;
-        const int order = lo + d - 1 - swept;
-        const int32_t implied = *lds<int16_t>(other + 2u * uint32_t(prefix) + 2u * d);
-        const uint32_t x = table.find(uint32_t(key) * table.multiplier + uint32_t(order) * tag_unit,
-                                      [&] { return implied == lasts[d]; }, uint32_t(prefix));
-        if (x >= id_limit) return;
-        const bool counts = !ROUGE || lo + d == N;  // (uniform)
-        uint32_t word = 0;
-        if (counts) word = count_reference(order, f, x);
-        if (d == 2 || lo + d == hi) {  // (uniform)
-          left = int32_t(x);
-        } else {
-          if constexpr (d < 2) again(std::integral_constant<int, d + 1>{}, int32_t(x), again);
-        }
-        if (counts && matching) {
-          if (ROUGE) match = is_match(order, f, word);
-          else matches[d] += is_match(order, f, word) ? 1 : 0;
-        }
-      };
-      look_up(std::integral_constant<int, 0>{}, KEEP ? v : int32_t(*lds<int16_t>(first)), look_up);
-      if (ROUGE && hi == N) {
+      if ((int32_t(uint32_t(prefix) << id_bits) | last) >= 0) {
+        look_up(2, f, uint32_t(prefix), last, sym_at + 2u * uint32_t(prefix) + 2u, [&](uint32_t got, uint32_t counter) __attribute__((always_inline)) {
+          if (at_once)
+            look_up_step(std::integral_constant<int, 0>{}, f, id, got, lasts, left, look_up_step);
+          else
+            left = word_of(id, got);
+          if (ROUGE) match = is_match(0, f, counter);
+          else if (matching) match12 += is_match(1 - swept, f, counter) ? 0x10000u : 0u;
+        });
+      }
+      if (ROUGE && N == 2) {
         const int of_block = __popcll(__builtin_amdgcn_ballot_w64(match));
         overlap += lane == f ? of_block : 0;
       }
-      if (KEEP) v = left;
+      id += nt;
       s += sym_stride;
       b += nwaves;
+      return left;
     };
-    if (KEEP) {
-      each_block(i, my_cand_blocks, enter_block);
-    } else {
+    // Blocks i..end - 1 of the candidate or of the references: order 2 of each (first), and the orders
+    // behind it (more) of what is left, where COMPACT puts that together to full blocks: of the candidate's
+    // positions a tenth to a quarter go on behind order 2, of the references' a quarter to a half, but hardly
+    // a block is without one.  KEEP: the orders behind it follow later.  `kept`: where the next block is kept.
+    auto all_blocks = [&](int end, int& kept, auto&& first, auto&& more) __attribute__((always_inline)) {
+      int32_t waiting = -1;  // lanes 0 .. pending - 1: words of blocks before
+      int pending = 0;
+      auto go_on = [&](int32_t word) __attribute__((always_inline)) {
+        if (KEEP) {
+          // (a branch: chosen without one, every register of val would be)
+          asm volatile("" : "+s"(kept));
+          val[kept++] = word;
+        } else {
+          more(word, 0);
+        }
+      };
 #pragma unroll 1
-      for (; i < my_cand_blocks; ++i) enter_block(val[0]);
-    }
+      for (; i < end; ++i) {
+        int32_t word = first();
+        if (!deeper || (!COMPACT && !KEEP)) continue;
+        const uint64_t going = __builtin_amdgcn_ballot_w64(word >= 0);
+        if (COMPACT) {
+          // Lanes that go on move behind those waiting, the others behind these (a permutation).
+          const int n = __popcll(going);
+          const int rank = int(__builtin_amdgcn_mbcnt_hi(uint32_t(going >> 32),
+                                                         __builtin_amdgcn_mbcnt_lo(uint32_t(going), 0u)));
+          const int place = word >= 0 ? rank : n + lane - rank;
+          const int32_t moved = __builtin_amdgcn_ds_permute((place + pending) << 2, word);
+          const bool behind = lane >= pending;
+          word = behind ? moved : waiting;
+          waiting = word;
+          pending += n;
+          if (pending < kWave) continue;
+          waiting = behind ? -1 : moved;
+          pending -= kWave;
+        }
+        go_on(word);
+      }
+      if (COMPACT && pending > 0) go_on(waiting);
+    };
+    // KEEP: the orders from `next` on of what is left
+    auto kept_blocks = [&](int k, int end, auto&& more) __attribute__((always_inline)) {
+      if (next > hi || (dense && !COMPACT)) return;
+#pragma unroll 1
+      for (; k < end; ++k)
+        if (__builtin_amdgcn_ballot_w64(val[k] >= 0)) val[k] = more(val[k], k);
+    };
+    const auto enter_words = [&](int32_t word, int) __attribute__((always_inline)) { return enter_more(word); };
+    if (dense) all_blocks(my_cand_blocks, kept_cand, enter_block, enter_words);
+    if (KEEP) kept_blocks(0, kept_cand, enter_words);
     __syncthreads();
     TB_FSTAMP(2 * lo);
-    if (KEEP) {
-      each_block(i, my_blocks, look_up_block);
-#pragma unroll 1
-      for (; i < BLOCKS; ++i) rotate(std::integral_constant<int, 1>{});
-    } else {
-#pragma unroll 1
-      for (; i < my_blocks; ++i) look_up_block(val[0]);
+    if (dense) {
+      i = my_cand_blocks;
+      all_blocks(my_blocks, kept, look_up_block, look_up_more);
     }
+    if (KEEP) kept_blocks(my_cand_blocks, kept, look_up_more);
     TB_FSTAMP(2 * lo + 1);
-  }
-  if (!ROUGE && want_distinct) {
-    if (lane < N) lds_add(part_at + 32 + 4 * lane, uint32_t(distinct));
-    __syncthreads();
   }
   TB_FSTAMP(20);
   const bool lost = *lds<uint32_t>(lost_at);
@@ -941,6 +1066,11 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       const uint32_t at = part_at + 4u * uint32_t(lane & 7);
       const uint32_t here = *lds<uint32_t>(at), before = *lds<uint32_t>(lane & 7 ? at - 4u : lost_at);
       const int sum = int((here & 0xFFFFu) + (before >> 16));
+      int repeated = 0;  // (lost: the distinct n-grams)
+      if (TWO || want_distinct) {
+        const uint32_t here = *lds<uint32_t>(at + 32u), before = *lds<uint32_t>(lane & 7 ? at + 28u : lost_at);
+        repeated = int((here & 0xFFFFu) + (before >> 16));
+      }
       const int best = __builtin_amdgcn_readfirstlane(*lds<int32_t>(closest_at));
       const float brevity = *lds<float>(closest_at + 4);
       int32_t *clipped = a.st.clipped, *total = a.st.total, *closest = a.st.closest;
@@ -953,7 +1083,9 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       asm volatile("" : "+s"(clipped), "+s"(total), "+s"(closest), "+s"(out), "+s"(sp.smoothing),
                    "+s"(sp.param), "+s"(sp.out_bf16));
       const float w = lane_weight(a.sp);
-      const int tn = max(c - lane, 0), cn = matching && !lost ? sum : tn - sum;
+      // (two references: among the sum is every position that is no id, for a counter that nothing was added
+      // to stands for one occurrence: those that repeat another's n-gram, and those behind the last one)
+      const int tn = max(c - lane, 0), cn = lost ? tn - sum : TWO ? c - (sum - repeated) : sum;
       const float score = bleu_from_stats_wave<int>(cn, tn, c, best, brevity, w, sp);
       if (lane == 0) {
         if (out) store_score(out, g, score, sp.out_bf16);
@@ -962,7 +1094,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       if (lane < N) {
         clipped[int64_t(g) * N + lane] = cn;
         total[int64_t(g) * N + lane] = tn;
-        if (want_distinct) a.st.distinct[int64_t(g) * N + lane] = int(*lds<uint32_t>(part_at + 32u + 4u * uint32_t(lane)));
+        if (want_distinct) a.st.distinct[int64_t(g) * N + lane] = lost ? repeated : tn - repeated;
       }
     } else {
       // lane j = 1..used: reference j - 1.  F is proportional to overlap / (cand + beta^2 ref)
@@ -1079,7 +1211,6 @@ hipError_t launch_blocks(const Problem& pb, const FusedArgs& a, const FusedPlan&
 }
 
 constexpr size_t kLdsUnit = 1280;  // LDS is handed out in units of this size
-constexpr size_t kSumsBytes = 64 + 16 + kMaxSeqs * 4;
 
 }  // namespace
 
@@ -1210,11 +1341,13 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
     while (32 - widest + lg_min - 2 - p.id_bits < (full ? 6 : 4)) ++lg_min;
     int lg = lg_min;
     while ((int64_t(1) << lg) < (N == 1 ? 6 : 12) * entries) ++lg;
+    const bool listed = N > 2 && blocks > kApartBlocks * waves && (rouge || R > 2);  // (see LISTED)
+    const size_t sums = sums_bytes(rouge) + (listed ? size_t(blocks + 15) & ~size_t(15) : 0);
     const size_t share = size_t(kLdsBudget) / r / kLdsUnit * kLdsUnit;
     const size_t counters = size_t(((rouge ? 1 : orders) * order_fields + 1) / 2) * p.array_bytes;
     for (; lg >= lg_min; --lg) {
       const size_t front = (size_t(4) << lg) + counters;
-      p.lds_bytes = front + sym_bytes + kSumsBytes;
+      p.lds_bytes = front + sym_bytes + sums;
       if (p.lds_bytes > share) continue;
       p.threads = waves * kWave;
       p.blocks = int((blocks + waves - 1) / waves);
