@@ -324,6 +324,18 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
                    plan);
 }
 
+// Whether a BLEU call that the sorted runs take, without dictionary sizes, goes to the kernels that deal every
+// position out once.  Of 590 drawn shapes of 12 000 to 2 000 000 positions with 1 to 16 references, one to four
+// orders, the ones that do take 0.84 of the sorted runs' time on average.  Below 98 304 positions in all both are a
+// chain of latencies, and the sorted runs' is the shorter one (three groups of two times 8000 17.8 us, 19.5 here;
+// three of two times 19 000 17.9 and 16.2); with three references or more whose counters need 32 bits, tables take
+// so much LDS that partitions become too small (two groups of 131 072 with three references 64.5, 88.7).
+bool takes_deal(const Problem& pb, DealPlan* plan) {
+  if (pb.B * pb.group_cap < 98304) return false;
+  if (pb.R > 2 && (pb.cand_stride > 65535 || pb.ref_stride > 65535)) return false;
+  return plan_deal(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.vocab, plan);
+}
+
 // Whether the call runs on the fused kernel: on its own path, and on AUTO also for longer shapes
 // that its plan covers.  (In a workspace that is larger than it needs.  The statistic group_distinct
 // is the size of the group's dictionary there, which only the kernels of the GLOBAL path build.)
@@ -339,6 +351,9 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
 // 12 400 to 24 500 positions with 1 to 62 references and 4 to 130 groups, one to six orders: on average
 // 0.5 % (ROUGE 0.2 %) behind the better kernel, more than a tenth behind in 2.3 % (0.5 %) of them.  (The
 // lines fitted before the kernel found n-grams without looking them up: 1.0 % and 17 %.)
+// Against the kernels that deal every position out once, BLEU's line is another: linear fit to 480 pairs of the
+// same shapes, 0.7 % behind the better kernel on average, more than a tenth behind in 2.5 % (the other line: 1.9
+// and 6.2); 6 groups of 6235 with three references of 5797 22 us there, 43.9 here; 35 of two times 7000 24.0, 23.2.
 // Against the partitioned kernels, which take what the sorted runs do not: 32.
 bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
                  FusedPlan* plan) {
@@ -347,11 +362,15 @@ bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats,
     if (cfg->force_path != TB_PATH_AUTO || cfg->workspace_tables) return false;
     if (stats && stats->group_distinct) return false;
     RunsPlan runs;
+    DealPlan deal;
     int64_t few = 32;
     if (takes_runs(c, cfg, rouge, false, &runs)) {
       const int64_t refs = pb.R * pb.ref_stride;
-      few = rouge ? pb.N * pb.cand_stride / 260 + pb.N * refs / 1400 - 5 * pb.R / 2 - 33
-                  : pb.cand_stride / 200 + refs / 700 - pb.R / 2 + 5 * pb.N - 33;
+      if (!rouge && takes_deal(pb, &deal))
+        few = pb.cand_stride / 600 + refs / 1000 - pb.R + 4 * pb.N - 18;
+      else
+        few = rouge ? pb.N * pb.cand_stride / 260 + pb.N * refs / 1400 - 5 * pb.R / 2 - 33
+                    : pb.cand_stride / 200 + refs / 700 - pb.R / 2 + 5 * pb.N - 33;
     }
     if (c.plans.use_part && pb.B < few) return false;
   }
@@ -386,8 +405,11 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
   }
   RunsPlan runs;
   if (takes_runs(c, cfg, false, group_distinct, &runs)) {
-    rc = hip_rc(launch_runs(c.pb, runs, runs_buffers(c.pb, c.ws, c.plans.part), c.st,
-                            group_distinct, nullptr, c.stream));
+    const RunsBuffers buffers = runs_buffers(c.pb, c.ws, c.plans.part);
+    DealPlan deal;
+    rc = hip_rc(!group_distinct && takes_deal(c.pb, &deal)
+                    ? launch_deal(c.pb, deal, buffers, c.st, c.stream)
+                    : launch_runs(c.pb, runs, buffers, c.st, group_distinct, nullptr, c.stream));
     if (rc != TB_OK) return rc;
     return hip_rc(launch_finalize(c.pb, c.st, c.sp, !corpus, corpus || c.want_corpus_stats, corpus,
                                   out_bleu, c.stream, c.ws.overflow));

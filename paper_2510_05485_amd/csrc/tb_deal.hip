@@ -1,0 +1,880 @@
+// Whole BLEU calls of up to four orders on groups beyond one LDS table, in two kernels:
+//
+//   deal_kernel   one workgroup per (group, chunk of 1024 or 2048 positions of one sequence): deals the
+//                 chunk's positions out to partitions three times, as three kinds of members: its tokens by a
+//                 hash of the token, its pairs by a hash of both, its 4-grams by a hash of the first three
+//                 tokens.  Equal ones are merged, what is left is written as one run per partition, with the
+//                 runs' places
+//   tally_kernel  one workgroup per (group, partition of a kind): gathers the partition's runs, enters the
+//                 candidate's members into an LDS table, looks the references' up, counts and clips; orders 3
+//                 and 4 in one go
+//
+// The sorted runs (tb_runs.hip) do the same for one order at a time: every position is dealt out four times
+// there, each time with six barriers, and four workgroups count a partition's share, each with its own trips to
+// memory.  Here the tokens are read once and the barriers are shared.  Orders 3 and 4 go together because an
+// n-gram that is new to the candidate at order 3 is new at order 4, too, and the 4-gram that goes on like the
+// first one does needs no entry (as in the fused kernel).  Order 2 stays apart: the most frequent pair of a
+// Zipf-distributed text is a fiftieth of it, and the partition that received all 4-grams that start with it took
+// five times as long as the others.  One workgroup for all kinds of a partition was tried, too: its tables left
+// room for shares of 640 positions only, and what a workgroup costs however little it has (places, clearing,
+// sums) ate the gain (50 groups of two times 20 000: 66.6 us a call, 61.5 like this).
+//
+// Equal ones are merged as in the sorted runs: of the positions whose keys hash to the same word one is kept
+// there, and those equal to it add themselves to its count; any other is passed on as it is.
+//
+// What bounds it.  Dealing: 7.7 us a workgroup, six barriers' worth of LDS and memory latency, two of them on a
+// unit, and the 19 bytes a position that it writes.  Tallying: issue, 560 vector and 450 scalar instructions of a
+// wavefront's 9 us (a third of them exec masks of the probing loops), and the longest workgroups.
+//
+// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 32.9 -> 27.9 (dealing 8,
+// tallying 15); 11 groups of two times 90 000 96.7 -> 62.8; 50 of two times 20 000 80.4 -> 61.5; 5 of 17 327 tokens
+// with three references 35.1 -> 29.2; two of 174 762 with two 65.1 -> 43.
+//
+// Keys are exact.  What the tables hold is bounded by the hashes whatever the tokens are, except for 4-grams:
+// where many different ones start with the same three tokens and ids run out, the partition counts orders 3 and
+// 4 again, each on its own and in as many rounds as leave each its share (see tally_kind).  A table that is full
+// then (which takes tokens chosen to collide) is reported through TB_DEV_TABLE_OVERFLOW and scored NaN.
+#include <cmath>
+#include <type_traits>
+
+#include "tb_kernels.h"
+
+namespace tb {
+
+namespace {
+
+constexpr int kThreads = 1024;
+constexpr int kKinds = 3;
+constexpr int kMaxParts = 2 * kThreads;  // of all kinds (a thread of the dealing kernel scans two counts)
+constexpr int kTallyThreads = 1024;
+constexpr int kMaxDealChunks = kTallyThreads;  // per group: one thread each reads a run's place
+constexpr int kTokenBits = 20;
+constexpr uint32_t kNoToken = (1u << kTokenBits) - 1u;  // behind the end of a sequence
+
+struct DealArgs {
+  Problem pb;
+  StatPtrs st;
+  uint64_t* pair;    // [B * group_cap]: tokens 0 and 1 | multiplicity - 1, from bit 40 on
+  uint64_t* rest;    // tokens 1 to 3 of a 4-gram
+  uint32_t* lead;    // its token 0 | multiplicity - 1, from bit 20 on
+  uint32_t* first;   // token | multiplicity - 1, from bit 20 on
+  uint32_t* run_at;  // [B][chunks][parts of all kinds]: first of the run within its chunk | size << 16
+  int32_t* overflow; // [B]
+  int kinds, all_parts;
+  int parts[kKinds], parts_before[kKinds];  // of each kind; of the kinds before it
+  int log2_chunk;
+  int cand_chunks, ref_chunks, chunks;  // of the candidate, of one reference, of a group
+  // tally_kernel
+  int words;         // per counter
+  int capacity;      // ids of order 3 and 4 n-grams
+  int window;        // members of a kind that the marks are for, a multiple of 64
+  int id_bits, log2_first, log2_pair, log2_item;
+  // LDS: table and counters at 0
+  uint32_t off_sums, off_owner;  // cleared, too
+  uint32_t off_places, off_tokens, off_lead, off_scratch;
+};
+
+struct DealChunk {
+  int seq, first;
+};
+__device__ __forceinline__ DealChunk deal_chunk(const DealArgs& a, int c) {
+  DealChunk k;
+  const int q = max(c - a.cand_chunks, 0);
+  const int j = a.pb.R > 1 ? q / a.ref_chunks : 0;
+  k.seq = c < a.cand_chunks ? 0 : 1 + j;
+  k.first = (c < a.cand_chunks ? c : q - j * a.ref_chunks) << a.log2_chunk;
+  return k;
+}
+// Where a chunk's n-grams lie among the group's slots.
+__device__ __forceinline__ int deal_base(const DealArgs& a, const DealChunk& k, int* seq) {
+  *seq = k.seq;
+  return (k.seq == 0 ? 0 : int(a.pb.cand_stride) + (k.seq - 1) * int(a.pb.ref_stride)) + k.first;
+}
+
+// Hashes of one, two, three and four tokens: top bits choose the partition.
+__device__ __forceinline__ uint32_t hash1(uint32_t t0) { return t0 * 0x9E3779B1u + 0x6A09E667u; }
+__device__ __forceinline__ uint32_t mix(uint32_t h) { return (h ^ (h >> 15)) * 0xC2B2AE3Du; }
+__device__ __forceinline__ uint32_t hash2(uint32_t t0, uint32_t t1) { return mix(t0 * 0x9E3779B1u + t1 * 0x85EBCA6Bu); }
+__device__ __forceinline__ uint32_t hash3(uint32_t t0, uint32_t t1, uint32_t t2) {
+  return mix(t0 * 0x9E3779B1u + t1 * 0x85EBCA6Bu + t2 * 0x27D4EB2Fu);
+}
+// (The partition is the high word of hash * parts: the low word's top bits choose the slot.)
+
+// A store that leaves the XCD's L2 at once.  (Ordinary ones wait there for the end of the kernel, which then takes
+// as long as it takes to write them all.)
+template <typename T>
+__device__ __forceinline__ void write_through(T* at, T v) {
+  __hip_atomic_store(at, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int ITEMS>
+__global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
+  constexpr int kChunk = ITEMS * kThreads;
+  constexpr int kLog2Chunk = ITEMS == 2 ? 11 : 10;
+  static_assert((1 << kLog2Chunk) == kChunk, "chunk");
+  struct Out {
+    uint64_t pair[kChunk], rest[kChunk];
+    uint32_t lead[kChunk], first[kChunk];
+  };
+  union Space {
+    uint32_t kept[kKinds][kChunk];  // by hash: position kept there | its duplicates << 12
+    Out out;
+  };
+  __shared__ Space space;
+  __shared__ uint32_t token[kChunk + 8];
+  __shared__ int in_part[2 * kThreads];
+  __shared__ int kind_base[kKinds + 1];
+  __shared__ int scan_scratch[17];
+  const Problem& pb = a.pb;
+  const int tid = threadIdx.x, kinds = a.kinds;
+  const int c = blockIdx.x, g = blockIdx.y;
+  const DealChunk me = deal_chunk(a, c);
+  const RefRows rr = ref_rows(pb, g);
+  int len = 0;
+  int64_t row;
+  const void* base;
+  if (me.seq == 0) {  // uniform
+    len = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, nullptr);
+    base = pb.cand;
+    row = int64_t(g) * pb.cand_stride;
+  } else {
+    const int64_t r = rr.row0 + me.seq - 1;
+    if (me.seq <= rr.used) len = clamped_len(uniform_load(pb.ref_len, r), pb.ref_stride, nullptr);
+    base = pb.refs;
+    row = r * pb.ref_stride;
+  }
+  row += me.first;
+  const int left = max(len - me.first, 0);
+  const int staged = min(left, kChunk + 3);
+
+  bool bad = false;
+  auto put = [&](int i, int32_t t) {
+    const bool outside = uint32_t(t) >= uint32_t(pb.vocab);  // reported and taken as 0
+    bad |= outside;
+    token[i] = outside ? 0u : uint32_t(t);
+  };
+  if (staged > 0) {  // uniform
+    int32_t t[ITEMS];
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u)
+      t[u] = load_token(base, row + min(u * kThreads + tid, staged - 1), pb.tok64);
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u)
+      if (u * kThreads + tid < staged) put(u * kThreads + tid, t[u]);
+    if (kChunk + tid < staged) put(kChunk + tid, load_token(base, row + kChunk + tid, pb.tok64));
+  }
+  reinterpret_cast<int2*>(in_part)[tid] = make_int2(0, 0);
+  if (c == 0) {  // what the partitions' workgroups add to
+    if (tid < pb.N) {
+      a.st.clipped[int64_t(g) * pb.N + tid] = 0;
+      a.st.distinct[int64_t(g) * pb.N + tid] = 0;
+    }
+    if (tid == 0) a.overflow[g] = 0;
+  }
+  if (bad && pb.status) atomicOr(pb.status, TB_DEV_TOKEN_RANGE);
+  __syncthreads();
+
+  uint32_t t[ITEMS][4], h[ITEMS][kKinds];
+  auto slot = [&](int u, int kind) { return h[u][kind] >> (32 - kLog2Chunk); };
+  // tokens from its position on that a member of the kind has, and one that others are merged into
+  auto is_member = [&](int u, int kind) { return left - (u * kThreads + tid) > kind; };
+  auto merges = [&](int u, int kind) { return left - (u * kThreads + tid) > (kind == 2 ? 3 : kind); };
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u) {
+    const int k = u * kThreads + tid;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) t[u][j] = token[k + j];
+    if (left - k <= 3) t[u][3] = kNoToken;
+    h[u][0] = hash1(t[u][0]);
+    h[u][1] = hash2(t[u][0], t[u][1]);
+    h[u][2] = hash3(t[u][0], t[u][1], t[u][2]);
+#pragma unroll
+    for (int kind = 0; kind < kKinds; ++kind)
+      if (kind < kinds && merges(u, kind)) space.kept[kind][slot(u, kind)] = uint32_t(k);
+  }
+  __syncthreads();
+  // (Reads of all kinds first, whether they count or not: with a branch around each, a wavefront waited for six
+  // chains of three LDS accesses one after the other.)
+  bool merged[ITEMS][kKinds];
+  int part[ITEMS][kKinds];
+  {
+    uint32_t w[ITEMS][kKinds];
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u)
+#pragma unroll
+      for (int kind = 0; kind < kKinds; ++kind)
+        w[u][kind] = space.kept[kind][slot(u, kind)] & uint32_t(kChunk - 1);
+    uint32_t differs[ITEMS][kKinds];
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u)
+#pragma unroll
+      for (int kind = 0; kind < kKinds; ++kind) {
+        differs[u][kind] = 0;
+#pragma unroll
+        for (int j = 0; j < (kind == 2 ? 4 : kind + 1); ++j) differs[u][kind] |= token[w[u][kind] + j] ^ t[u][j];
+      }
+#pragma unroll
+    for (int u = 0; u < ITEMS; ++u)
+#pragma unroll
+      for (int kind = 0; kind < kKinds; ++kind) {
+        merged[u][kind] = merges(u, kind) && w[u][kind] != uint32_t(u * kThreads + tid) && differs[u][kind] == 0u;
+        part[u][kind] = a.parts_before[kind] + int(__umulhi(h[u][kind], uint32_t(a.parts[kind])));
+      }
+  }
+  int rank[ITEMS][kKinds];
+  uint32_t member = 0;  // by bits: what is passed on
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u)
+#pragma unroll
+    for (int kind = 0; kind < kKinds; ++kind) {
+      rank[u][kind] = 0;
+      if (kind >= kinds) continue;  // uniform
+      if (merged[u][kind]) {
+        atomicAdd(&space.kept[kind][slot(u, kind)], 0x1000u);
+      } else if (is_member(u, kind)) {
+        rank[u][kind] = atomicAdd(&in_part[part[u][kind]], 1);
+        member |= 1u << (u * kKinds + kind);
+      }
+    }
+  __syncthreads();
+  uint32_t times[ITEMS][kKinds];
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u)
+#pragma unroll
+    for (int kind = 0; kind < kKinds; ++kind) {
+      const uint32_t word = space.kept[kind][slot(u, kind)];
+      times[u][kind] = merges(u, kind) && int(word & 0xFFFu) == u * kThreads + tid ? word >> 12 : 0u;
+    }
+  const int2 mine = reinterpret_cast<const int2*>(in_part)[tid];
+  int total;
+  const int before = block_exclusive_scan(mine.x + mine.y, scan_scratch, &total);
+#pragma unroll
+  for (int kind = 0; kind <= kKinds; ++kind) {
+    const int q = kind < kinds ? a.parts_before[kind] : a.all_parts;  // (its members begin where all before it end)
+    if (tid == q / 2) kind_base[kind] = before + (q & 1 ? mine.x : 0);
+    if (q == 2 * kThreads && tid == 0) kind_base[kind] = total;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < 2; ++j) {
+    const int q = 2 * tid + j, size = j ? mine.y : mine.x;
+    if (q >= a.all_parts) continue;
+    const int kind = kinds > 2 && q >= a.parts_before[2] ? 2 : kinds > 1 && q >= a.parts_before[1] ? 1 : 0;
+    const int first = before + (j ? mine.x : 0) - kind_base[kind];
+    in_part[q] = first;
+    write_through(a.run_at + (int64_t(g) * a.chunks + c) * a.all_parts + q, uint32_t(first) | uint32_t(size) << 16);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u)
+#pragma unroll
+    for (int kind = 0; kind < kKinds; ++kind)
+      if (kind < kinds) rank[u][kind] += in_part[part[u][kind]];
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u) {
+#pragma unroll
+    for (int kind = 0; kind < kKinds; ++kind) {
+      if (!(member >> (u * kKinds + kind) & 1u)) continue;
+      const int at = rank[u][kind];
+      if (kind == 0) space.out.first[at] = t[u][0] | times[u][0] << kTokenBits;
+      if (kind == 1)
+        space.out.pair[at] = uint64_t(t[u][0]) | uint64_t(t[u][1]) << kTokenBits |
+                             uint64_t(times[u][1]) << (2 * kTokenBits);
+      if (kind == 2) {
+        space.out.rest[at] = uint64_t(t[u][1]) | uint64_t(t[u][2]) << kTokenBits |
+                             uint64_t(t[u][3]) << (2 * kTokenBits);
+        space.out.lead[at] = t[u][0] | times[u][2] << kTokenBits;
+      }
+    }
+  }
+  __syncthreads();
+  int seq;
+  const int64_t out = int64_t(g) * pb.group_cap + deal_base(a, me, &seq);
+#pragma unroll
+  for (int u = 0; u < ITEMS; ++u) {
+    const int i = u * kThreads + tid;
+    if (i < kind_base[1]) write_through(a.first + out + i, space.out.first[i]);
+    if (kinds > 1 && i < kind_base[2] - kind_base[1]) write_through(a.pair + out + i, space.out.pair[i]);
+    if (kinds > 2 && i < kind_base[3] - kind_base[2]) {
+      write_through(a.rest + out + i, space.out.rest[i]);
+      write_through(a.lead + out + i, space.out.lead[i]);
+    }
+  }
+}
+
+__device__ __forceinline__ int wave_inclusive_max(int v) {  // of values >= 0
+  v = max(v, dpp_or_zero<0x111, 0xf, 0xf>(v));  // row_shr:1
+  v = max(v, dpp_or_zero<0x112, 0xf, 0xf>(v));  // row_shr:2
+  v = max(v, dpp_or_zero<0x114, 0xf, 0xf>(v));  // row_shr:4
+  v = max(v, dpp_or_zero<0x118, 0xf, 0xf>(v));  // row_shr:8
+  v = max(v, dpp_or_zero<0x142, 0xa, 0xf>(v));  // row_bcast:15 into rows 1 and 3
+  return max(v, dpp_or_zero<0x143, 0xc, 0xf>(v));  // row_bcast:31 into rows 2 and 3
+}
+
+template <typename T>
+__device__ __forceinline__ __attribute__((address_space(3))) T* lds(uint32_t offset) {
+  typedef __attribute__((address_space(3))) T* Ptr;
+  return (Ptr)(uintptr_t)(offset);
+}
+template <typename T>
+__device__ __forceinline__ T lds_cas(uint32_t at, T desired) {  // expects 0
+  T expected = 0;
+  __hip_atomic_compare_exchange_strong((T*)lds<T>(at), &expected, desired, __ATOMIC_RELAXED,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+  return expected;
+}
+__device__ __forceinline__ uint32_t lds_add(uint32_t at, uint32_t v) {
+  return __hip_atomic_fetch_add((uint32_t*)lds<uint32_t>(at), v, __ATOMIC_RELAXED,
+                                __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ void lds_add_only(uint32_t at, uint32_t v) {
+  __hip_atomic_fetch_add((uint32_t*)lds<uint32_t>(at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+typedef uint32_t Quad __attribute__((ext_vector_type(4)));
+
+// One reference: a counter is one less than the candidate's count, less what the reference has had of it; what
+// the reference finds is a match.  More: counters of the candidate (one less) and of each reference, two a word
+// where no sequence is longer than 65 535, and a pass over them in the end.
+enum Counters { kOneReference, kHalves, kWords };
+
+// One partition's members of one kind.
+template <int KIND, Counters COUNTERS>
+__device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
+  constexpr bool ONE = COUNTERS == kOneReference, HALVES = COUNTERS == kHalves;
+  const Problem& pb = a.pb;
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+  const int g = blockIdx.y;
+  const int N = pb.N;
+  const uint32_t parts = uint32_t(a.parts[KIND]);
+  // (LDS: the table at 0, its counters behind it, then what follows here)
+  const uint32_t lost_at = a.off_sums, ids_at = lost_at + 4u, again_at = lost_at + 8u;
+
+  uint32_t place = 0;
+  if (tid < a.chunks) place = a.run_at[(int64_t(g) * a.chunks + tid) * a.all_parts + a.parts_before[KIND] + p];
+  auto clear = [&](uint32_t from, uint32_t to) __attribute__((always_inline)) {
+    for (uint32_t q = from + 16u * uint32_t(tid); q < to; q += 16u * kTallyThreads) *lds<Quad>(q) = Quad(0u);
+  };
+  const uint32_t table_bytes = KIND == 0 ? 4u << a.log2_first : KIND == 1 ? 8u << a.log2_pair : 4u << a.log2_item;
+  const uint32_t slots_bytes = KIND == 0 ? 4u << a.log2_first : KIND == 1 ? 4u << a.log2_pair : 4u * uint32_t(a.capacity);
+  const uint32_t counters4 = table_bytes + slots_bytes * uint32_t(ONE ? 1 : a.words);  // KIND 2: order 4's
+  const uint32_t used_bytes = KIND < 2 ? counters4 : counters4 + slots_bytes * uint32_t(N < 4 ? 0 : ONE ? 1 : a.words);
+  clear(0, used_bytes);
+  clear(a.off_sums, a.off_places);
+  // Members: those of the candidate's chunks, then those of the references'.
+  auto scratch = [&](int i) __attribute__((always_inline)) { return lds<int>(a.off_scratch + 4u * uint32_t(i)); };
+  constexpr int kWaves = kTallyThreads / kWave;
+  const int run_size = int(place >> 16);
+  int before = wave_inclusive_scan(run_size);
+  if (lane == kWave - 1) *scratch(wave) = before;
+  __syncthreads();
+  const int of_waves = row_inclusive_scan(*scratch(lane & (kWaves - 1)));
+  const int members = lane_value(of_waves, kWaves - 1);
+  if (wave > 0) before += __builtin_amdgcn_readlane(of_waves, (wave - 1) & 15);
+  before -= run_size;
+  if (tid == a.cand_chunks) *scratch(16) = before;
+  // where a run's members are: x + member; and whose they are
+  if (tid < a.chunks) {
+    int seq;
+    const int base = deal_base(a, deal_chunk(a, tid), &seq);
+    *lds<int>(a.off_places + 4u * uint32_t(tid)) = base + int(place & 0xFFFFu) - before;
+    if (KIND == 2) *lds<int>(a.off_places + 4u * uint32_t(a.chunks + tid)) = before;
+    if (!ONE) *lds<int>(a.off_places + 4u * uint32_t(2 * a.chunks + tid)) = seq;
+  }
+  // Windows of a.window members, in blocks of 64 that the wavefronts take in turn.  A run marks its first member
+  // in the window and every member at a multiple of 64: the largest mark up to a lane is its run.
+  auto mark = [&](uint32_t marks, int begin, int size) __attribute__((always_inline)) {
+    const int lo = max(before - begin, 0), hi = min(before + run_size - begin, size);
+#pragma unroll 1
+    for (int i = lo; i < hi; i = (i | (kWave - 1)) + 1) *lds<uint16_t>(marks + 2u * uint32_t(i)) = uint16_t(tid + 1);
+  };
+  const uint32_t cand_marks = a.off_owner, ref_marks = a.off_owner + 2u * uint32_t(a.window);
+  __syncthreads();
+  const int cand_members = __builtin_amdgcn_readfirstlane(*scratch(16));
+  mark(cand_marks, 0, min(cand_members, a.window));
+  mark(ref_marks, cand_members, min(members - cand_members, a.window));
+  __syncthreads();
+
+  const int64_t slots = int64_t(g) * pb.group_cap;
+  struct Member {
+    uint64_t key;   // pair, or the rest of a 4-gram
+    uint32_t word;  // token, or the first one of a 4-gram
+    int f;
+  };
+  auto load = [&](int i, int run, bool cand) __attribute__((always_inline)) {
+    Member m;
+    const int64_t at = slots + i + *lds<int>(a.off_places + 4u * uint32_t(run));
+    m.f = cand ? 0 : ONE ? 1 : *lds<int>(a.off_places + 4u * uint32_t(2 * a.chunks + run));
+    m.key = 0;
+    m.word = 0;
+    if (KIND == 0) m.word = a.first[at];
+    if (KIND == 1) m.key = a.pair[at];
+    if (KIND == 2) m.key = a.rest[at], m.word = a.lead[at];
+    return m;
+  };
+  // block of a window of `size` > 64 * block members from `begin` on
+  auto fetch = [&](uint32_t marks, int begin, int size, int block, bool cand) __attribute__((always_inline)) {
+    const uint32_t mark = marks + 2u * uint32_t(block * kWave + lane);
+    const int run = wave_inclusive_max(*lds<uint16_t>(mark)) - 1;
+    *lds<uint16_t>(mark) = 0;  // (for the next window)
+    // (behind the last member: the last one again)
+    return load(begin + min(block * kWave + lane, size - 1), run, cand);
+  };
+
+  uint32_t matches = 0, matches4 = 0;  // (4-grams)
+  // Adds `times` occurrences in sequence f to the counter; `is_new`: the candidate's first.
+  auto count = [&](uint32_t at, uint32_t times, int f, bool is_new, uint32_t& matched) __attribute__((always_inline)) {
+    if (f == 0) {
+      lds_add_only(at, times - (is_new ? 1u : 0u));
+    } else if (ONE) {
+      const int had = int(lds_add(at, 0u - times)) + 1;
+      matched += uint32_t(min(max(had, 0), int(times)));
+    } else {
+      lds_add_only(at + uint32_t(HALVES ? f >> 1 : f) * slots_bytes, HALVES ? times << (16 * (f & 1)) : times);
+    }
+  };
+  // Tables of whole keys, probed slot by slot.
+  auto do_key = [&](auto key, uint32_t s, uint32_t times, int f) __attribute__((always_inline)) {
+    typedef decltype(key) Key;
+    constexpr uint32_t kSize = sizeof(Key);
+    Key old = *lds<Key>(s);
+    if (f > 0) {
+      for (uint32_t left = table_bytes; old != key && old != 0 && left; left -= kSize) {
+        s = (s + kSize) & (table_bytes - 1u);
+        old = *lds<Key>(s);
+      }
+      if (old != key) return;
+    } else {
+      uint32_t left = table_bytes;
+      while (true) {
+        if (old == 0) old = lds_cas<Key>(s, key);
+        if (old == 0 || old == key || left == 0) break;
+        s = (s + kSize) & (table_bytes - 1u);
+        old = *lds<Key>(s);
+        left -= kSize;
+      }
+      if (old != 0 && old != key) {  // (full)
+        *lds<uint32_t>(lost_at) = 1u;
+        return;
+      }
+    }
+    count(table_bytes + s / (kSize / 4u), times, f, old == 0, matches);
+  };
+  auto do_first = [&](uint32_t word, int f) __attribute__((always_inline)) {
+    const uint32_t t = word & kNoToken;
+    do_key(uint32_t(t + 1u), (hash1(t) * parts) >> (32 - a.log2_first) << 2, (word >> kTokenBits) + 1u, f);
+  };
+  auto do_pair = [&](uint64_t word, int f) __attribute__((always_inline)) {
+    const uint32_t h = hash2(uint32_t(word) & kNoToken, uint32_t(word >> kTokenBits) & kNoToken);
+    do_key(uint64_t((word & ((1ull << (2 * kTokenBits)) - 1ull)) | 1ull << 63), (h * parts) >> (32 - a.log2_pair) << 3,
+           uint32_t(word >> (2 * kTokenBits)) + 1u, f);
+  };
+
+  // ---- 4-grams: ids, and the tokens under them
+  const uint32_t id_limit = 1u << a.id_bits, capacity = uint32_t(a.capacity);
+  const uint32_t bucket_mask = ((4u << a.log2_item) - 1u) & ~15u;
+  struct Item {
+    uint32_t t0;
+    uint64_t rest;
+  };
+  auto load_item = [&](uint32_t id) __attribute__((always_inline)) {
+    return Item{*lds<uint32_t>(a.off_lead + 4u * id), *lds<uint64_t>(a.off_tokens + 8u * id)};
+  };
+  auto same = [](const Item& x, const Item& y, int n) __attribute__((always_inline)) {
+    const uint64_t mask = n == 3 ? (1ull << (2 * kTokenBits)) - 1ull : ~0ull;
+    return x.t0 == y.t0 && ((x.rest ^ y.rest) & mask) == 0ull;
+  };
+  auto last_of = [](const Item& x) __attribute__((always_inline)) { return uint32_t(x.rest >> (2 * kTokenBits)); };
+  // The id of the n-gram of order n (3 or 4) with hash h, and the item under it; it is entered if it is the
+  // candidate's and not there.  false: not there, or no id left for it.  Lanes that enter the n-gram that the first
+  // one of them does wait for its id, or each would use one up (a frequent beginning); `careful`: one n-gram is
+  // entered after the other.
+  auto resolve = [&](const Item& x, uint32_t h, int n, int f, uint32_t& id, Item& found, bool& is_new,
+                     auto careful) __attribute__((always_inline)) {
+    uint32_t s = ((h * parts) >> (30 - a.log2_item)) & bucket_mask;
+    const uint32_t mine = h << (a.id_bits + 1) | uint32_t(n - 2) << a.id_bits;
+    Quad e;
+    is_new = false;
+    // (buckets of four, filled front to back: a free slot ends the search)
+    while (true) {
+      e = *lds<Quad>(s);
+      id = min(min(e.x ^ mine, e.y ^ mine), min(e.z ^ mine, e.w ^ mine));
+      if (id < id_limit) {
+        found = load_item(id);
+        if (same(found, x, n)) return true;
+#pragma unroll 1
+        for (uint32_t k = 0; k < 16u; k += 4u) {  // another one with the same bits: each entry of its own
+          id = *lds<uint32_t>(s + k) ^ mine;
+          if (id >= id_limit) continue;
+          found = load_item(id);
+          if (same(found, x, n)) return true;
+        }
+      }
+      if (e.w == 0u) break;
+      s = (s + 16u) & bucket_mask;
+    }
+    if (f > 0) return false;
+    while (true) {
+      const uint64_t going = __builtin_amdgcn_ballot_w64(true);
+      const int leader = __ffsll((unsigned long long)going) - 1;
+      const Item first{uint32_t(__builtin_amdgcn_readlane(int(x.t0), leader)),
+                       uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x.rest >> 32), leader))) << 32 |
+                           uint32_t(__builtin_amdgcn_readlane(int(uint32_t(x.rest)), leader))};
+      const bool follows = lane != leader && same(first, x, n);
+      const bool waits = decltype(careful)::value && lane != leader;
+      id = ~0u;
+      if (!follows && !waits) {
+        const uint64_t entering = __builtin_amdgcn_ballot_w64(true);
+        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(entering >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo(uint32_t(entering), 0u));
+        uint32_t next = 0;
+        if (rank == 0) next = lds_add(ids_at, uint32_t(__popcll(entering)));
+        const uint32_t own = uint32_t(__builtin_amdgcn_readfirstlane(int(next))) + rank;
+        if (own < capacity) {
+          *lds<uint64_t>(a.off_tokens + 8u * own) = x.rest;
+          *lds<uint32_t>(a.off_lead + 4u * own) = x.t0;
+          asm volatile("" ::: "memory");  // (a wavefront's LDS accesses happen in their order)
+          s += first_free_slot(e.x, e.y, e.z);
+          while (true) {
+            const uint32_t old = lds_cas<uint32_t>(s, mine + own);
+            if (old == 0u) {
+              is_new = true;
+              id = own;
+              found = x;
+              break;
+            }
+            id = old ^ mine;
+            if (id < id_limit) {
+              found = load_item(id);
+              if (same(found, x, n)) break;
+            }
+            s = (s + 4u) & (bucket_mask | 12u);
+          }
+        } else {
+          *lds<uint32_t>(again_at) = 1u;
+        }
+      }
+      const uint32_t leaders = uint32_t(__builtin_amdgcn_readlane(int(id), leader));
+      if (follows) {
+        id = leaders;
+        if (id < id_limit) found = load_item(id);
+      }
+      // (the slots from the first one that was free on are looked at one by one, so that what has been entered
+      // since is seen)
+      if (!decltype(careful)::value || follows || !waits) break;
+    }
+    return id < id_limit;
+  };
+  auto item_hash = [](const Item& x) __attribute__((always_inline)) {
+    return hash3(x.t0, uint32_t(x.rest) & kNoToken, uint32_t(x.rest >> kTokenBits) & kNoToken);
+  };
+  auto longer_hash = [&](const Item& x, uint32_t h) __attribute__((always_inline)) { return mix(h + last_of(x) * 0x165667B1u); };
+  auto do_item = [&](uint64_t rest, uint32_t lead, int f) __attribute__((always_inline)) {
+    const uint32_t times = (lead >> kTokenBits) + 1u;
+    const Item x{lead & kNoToken, rest};
+    const uint32_t h = item_hash(x);
+    Item found;
+    uint32_t id;
+    bool is_new;
+    if (!resolve(x, h, 3, f, id, found, is_new, std::false_type{})) return;
+    // (one that is new at order 3 is new at order 4, too)
+    if (f == 0 && is_new && times == 1u) return;
+    count(table_bytes + 4u * id, times, f, is_new, matches);
+    // (behind the end there is no fourth token)
+    if (N < 4 || last_of(x) == kNoToken) return;
+    if (last_of(x) != last_of(found) && !resolve(x, longer_hash(x, h), 4, f, id, found, is_new, std::false_type{}))
+      return;
+    count(counters4 + 4u * id, times, f, is_new, matches4);
+  };
+
+  auto side = [&](bool cand, Member m) __attribute__((always_inline)) {
+    const uint32_t marks = cand ? cand_marks : ref_marks;
+    int begin = cand ? 0 : cand_members;
+    const int end = cand ? cand_members : members;
+#pragma unroll 1
+    while (true) {
+      const int size = min(end - begin, a.window);
+#pragma unroll 1
+      for (int block = wave; block * kWave < size; block += kWaves) {
+        const Member now = m;
+        if ((block + kWaves) * kWave < size) m = fetch(marks, begin, size, block + kWaves, cand);
+        const int f = cand ? 0 : ONE ? 1 : now.f;
+        if (block * kWave + lane < size) {
+          if (KIND == 2) do_item(now.key, now.word, f);
+          if (KIND == 1) do_pair(now.key, f);
+          if (KIND == 0) do_first(now.word, f);
+        }
+      }
+      begin += a.window;
+      if (begin >= end) break;
+      const int next = min(end - begin, a.window);
+      __syncthreads();
+      mark(marks, begin, next);
+      __syncthreads();
+      if (wave * kWave < next) m = fetch(marks, begin, next, wave, cand);
+    }
+  };
+  Member m{0, 0, 0}, later{0, 0, 0};
+  const int refs_size = min(members - cand_members, a.window);
+  if (wave * kWave < min(cand_members, a.window)) m = fetch(cand_marks, 0, min(cand_members, a.window), wave, true);
+  // (on their way while the candidate's are entered)
+  if (wave * kWave < refs_size) later = fetch(ref_marks, cand_members, refs_size, wave, false);
+  side(true, m);
+  __syncthreads();
+  side(false, later);
+  __syncthreads();
+  auto sweep = [&](uint32_t at) __attribute__((always_inline)) {
+    uint32_t part = 0;
+    for (uint32_t k = at + 4u * uint32_t(tid); k < at + slots_bytes; k += 4u * kTallyThreads) {
+      const uint32_t head = *lds<uint32_t>(k);
+      uint32_t most = HALVES ? head >> 16 : 0u;
+      for (int w = 1; w < a.words; ++w) {
+        const uint32_t word = *lds<uint32_t>(k + uint32_t(w) * slots_bytes);
+        most = max(most, HALVES ? max(word & 0xFFFFu, word >> 16) : word);
+      }
+      part += min((HALVES ? head & 0xFFFFu : head) + 1u, most);
+    }
+    return part;
+  };
+  auto add_up = [&](int n, uint32_t part) __attribute__((always_inline)) {
+    const int sum = wave_sum(int(part));
+    if (lane == 0 && sum) lds_add_only(lost_at + 12u + 4u * uint32_t(n), uint32_t(sum));
+  };
+  const bool again = KIND == 2 && *lds<uint32_t>(again_at);  // uniform
+  if (!again) {
+    add_up(KIND + 1, ONE ? matches : sweep(table_bytes));
+    if (KIND == 2 && N > 3) add_up(4, ONE ? matches4 : sweep(counters4));
+  } else {
+    // Orders 3 and 4, each on its own, in rounds of the n-grams whose hash falls into the round; more rounds where
+    // one has too many all the same.
+#pragma unroll 1
+    for (int n = 3; n <= N; ++n) {
+      uint32_t part = 0;
+      int rounds = 2 + 2 * cand_members / int(capacity);
+#pragma unroll 1
+      for (int round = 0; round < rounds; ++round) {
+        __syncthreads();
+        clear(0, counters4);
+        if (tid == 0) *lds<uint32_t>(ids_at) = 0u, *lds<uint32_t>(again_at) = 0u;
+        matches = 0;
+#pragma unroll 1
+        for (int i = tid, refs = 0; refs < 2; ++refs) {
+          __syncthreads();
+#pragma unroll 1
+          for (; i < (refs ? members : cand_members); i += kTallyThreads) {
+            int run = 0;
+#pragma unroll 1
+            for (int step = kMaxDealChunks / 2; step; step /= 2)
+              if (run + step < a.chunks && *lds<int>(a.off_places + 4u * uint32_t(a.chunks + run + step)) <= i) run += step;
+            const Member m = load(i, run, refs == 0);
+            const Item x{m.word & kNoToken, m.key};
+            uint32_t h = item_hash(x);
+            if (n == 4) {
+              if (last_of(x) == kNoToken) continue;
+              h = longer_hash(x, h);
+            }
+            if (int(__umulhi(h * 0x9E3779B1u, uint32_t(rounds))) != round) continue;
+            Item found;
+            uint32_t id;
+            bool is_new;
+            if (resolve(x, h, n, m.f, id, found, is_new, std::true_type{}))
+              count(table_bytes + 4u * id, (m.word >> kTokenBits) + 1u, m.f, is_new, matches);
+          }
+          if (refs == 0) i = cand_members + tid;
+        }
+        __syncthreads();
+        if (!*lds<uint32_t>(again_at)) {  // uniform
+          part += ONE ? matches : sweep(table_bytes);
+        } else if (rounds < 1 << 14) {
+          rounds *= 2;
+          part = 0;
+          round = -1;
+        } else {
+          if (tid == 0) *lds<uint32_t>(lost_at) = 1u;
+          round = rounds;
+        }
+      }
+      add_up(n, part);
+    }
+  }
+  __syncthreads();
+  if (tid == 0 && *lds<uint32_t>(lost_at)) {
+    if (pb.status) atomicOr(pb.status, TB_DEV_TABLE_OVERFLOW);
+    a.overflow[g] = 1;
+  }
+  const int n0 = KIND + tid;  // order n0 + 1
+  if (tid < (KIND == 2 ? 2 : 1) && n0 < N) {
+    const int64_t stat = int64_t(g) * N + n0;
+    const uint32_t sum = *lds<uint32_t>(lost_at + 16u + 4u * uint32_t(n0));
+    if (sum) atomicAdd(&a.st.clipped[stat], int(sum));
+    if (p == 0) {
+      const int len = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, nullptr);
+      a.st.total[stat] = max(len - n0, 0);
+    }
+  }
+}
+template <Counters COUNTERS>
+__global__ __launch_bounds__(kTallyThreads, 8) void tally_kernel(DealArgs a) {
+  int p = blockIdx.x;  // (the kind with the most work first)
+  if (a.kinds > 2) {
+    if (p < a.parts[2]) return tally_kind<2, COUNTERS>(a, p);
+    p -= a.parts[2];
+  }
+  if (a.kinds > 1) {
+    if (p < a.parts[1]) return tally_kind<1, COUNTERS>(a, p);
+    p -= a.parts[1];
+  }
+  tally_kind<0, COUNTERS>(a, p);
+}
+
+int log2_ceil(int64_t v) {
+  int b = 0;
+  while ((int64_t(1) << b) < v) ++b;
+  return b;
+}
+
+// Whether a table of `slots` holds what a hash sends to it of its binomial share (see has_room in tb_runs.hip:
+// less likely than exp(-40) not to).
+bool deal_has_room(int64_t share, int64_t slots) {
+  const double mean = double(share), k = double(slots);
+  return mean < k && k - mean - k * std::log(k / mean) <= -40.0;
+}
+
+template <int ITEMS>
+hipError_t launch_items(const DealArgs& a, const DealPlan& plan, hipStream_t s) {
+  hipLaunchKernelGGL(deal_kernel<ITEMS>, dim3(a.chunks, a.pb.B), dim3(kThreads), 0, s, a);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  auto tally = [&](auto kernel) {
+    e = grant_dynamic_lds(reinterpret_cast<const void*>(kernel), plan.lds_bytes);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(kernel, dim3(a.all_parts, a.pb.B), dim3(kTallyThreads), plan.lds_bytes, s, a);
+    return hipGetLastError();
+  };
+  return a.pb.R == 1 ? tally(tally_kernel<kOneReference>)
+         : plan.halves ? tally(tally_kernel<kHalves>) : tally(tally_kernel<kWords>);
+}
+
+}  // namespace
+
+// What the choice of the shares weighs (14 shapes of one to three references, all shares; us a call):
+//   * A workgroup's start (its runs' places, clearing, marks) costs as much as some 500 members, so shares are as
+//     large as the LDS of two workgroups a unit allows: one reference, 50 groups of two times 20 000, shares of
+//     320, 640 and 1280 4-grams 99.9, 71.5 and 61.5; 11 groups of 180 000 120.9, 71.3 and 62.8.
+//   * Where the chip is not full, smaller ones down to that: 16 groups of two times 8192 640 4-grams 21.3, 1280
+//     22.7; one text of 30 000 480 16.5, 1280 18.8, 160 20.
+//   * A share of the candidate brings one of each reference with it.  9 groups of 25 236 with three references of
+//     27 025: 480 4-grams 42.8, 1280 49.5, 320 50.0.
+//   * A 4-gram costs 1.6 times a pair, and a token, of which most are merged, half as much.
+bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, DealPlan* plan) {
+  DealPlan& p = *plan;
+  const int64_t cap = cand_stride + R * ref_stride;
+  if (N > 4 || R >= kWave || B > 65535 || vocab >= int32_t(kNoToken)) return false;
+  p.kinds = N < 3 ? N : 3;
+  p.halves = cand_stride <= 65535 && ref_stride <= 65535;
+  p.words = R == 1 ? 1 : p.halves ? (R + 2) / 2 : 1 + R;
+  p.items = B * cap < 256 * 2 * kThreads ? 1 : 2;  // (one workgroup for every compute unit)
+  auto split = [&] {
+    const int64_t chunk = p.items * kThreads;
+    p.cand_chunks = int((cand_stride + chunk - 1) / chunk);
+    p.ref_chunks = int((ref_stride + chunk - 1) / chunk);
+    return p.cand_chunks + int64_t(R) * p.ref_chunks;
+  };
+  if (cap > int64_t(2) * kThreads * kMaxDealChunks) return false;
+  if (split() > kMaxDealChunks) p.items = 2;
+  const int64_t chunks = split();
+  if (chunks > kMaxDealChunks) return false;
+  p.chunks = int(chunks);
+
+  // shares: candidate's positions that a partition of each kind may expect
+  auto fits = [&](int scale) {
+    int64_t share[kKinds] = {256 * scale, 128 * scale, 80 * scale};
+    int log2_slots[kKinds];
+    p.all_parts = 0;
+    for (int kind = 0; kind < kKinds; ++kind) {
+      int64_t parts = (cand_stride + share[kind] - 1) / share[kind];
+      if (parts < 2) parts = 2;
+      share[kind] = (cand_stride + parts - 1) / parts;
+      p.parts[kind] = int(kind < p.kinds ? parts : 1);
+      p.parts_before[kind] = kind < p.kinds ? p.all_parts : 0;
+      if (kind < p.kinds) p.all_parts += int(parts);
+      log2_slots[kind] = log2_ceil(share[kind] + share[kind] / 2);
+      while (!deal_has_room(share[kind], int64_t(1) << log2_slots[kind])) ++log2_slots[kind];
+    }
+    // ids: the most frequent three tokens of a Zipf-distributed text start one of 370 of its 4-grams
+    p.capacity = int((share[2] + share[2] / 4 + cand_stride / 512 + 128 + 7) & ~int64_t(7));
+    p.id_bits = log2_ceil(p.capacity);
+    p.log2_first = log2_slots[0];
+    p.log2_pair = log2_slots[1];
+    p.log2_item = log2_ceil(2 * share[2]);
+    while ((int64_t(3) << p.log2_item) < 4 * int64_t(p.capacity)) ++p.log2_item;
+    const uint32_t ids = N > 2 ? uint32_t(p.capacity) : 0u, counter = 4u * uint32_t(p.words);
+    uint32_t most = (4u + counter) << p.log2_first;
+    if (N > 1 && most < (8u + counter) << p.log2_pair) most = (8u + counter) << p.log2_pair;
+    // (4-grams: the tokens under the ids behind table and counters)
+    const uint32_t items = N > 2 ? (4u << p.log2_item) + counter * ids * uint32_t(N - 2) : 0u;
+    p.off_tokens = (items + 15u) & ~15u;
+    p.off_lead = p.off_tokens + 8u * ids;
+    if (most < p.off_lead + 4u * ids) most = p.off_lead + 4u * ids;
+    p.off_sums = (most + 15u) & ~15u;
+    p.off_owner = p.off_sums + 32;
+    const int64_t longest = share[1] > share[2] ? share[1] : share[2];
+    p.window = int(longest + longest / 4 + 127) & ~(kWave - 1);
+    p.off_places = p.off_owner + 2u * 2u * uint32_t(p.window);
+    p.off_scratch = p.off_places + 4u * uint32_t(3 * p.chunks);
+    p.lds_bytes = p.off_scratch + 4 * 17;
+    return p.all_parts <= kMaxParts && chunks * p.all_parts <= p.kinds * cap;
+  };
+  const int most = 32 / (1 + R) < 2 ? 2 : 32 / (1 + R), least = (12 + R) / (1 + R) < 2 ? 2 : (12 + R) / (1 + R);
+  int scale = 0;
+  for (int s = 1; s <= most; ++s) {
+    if (!fits(s)) continue;
+    if (p.lds_bytes > size_t(kLdsBudget) / 2 / 1280 * 1280) break;
+    scale = s;
+    if (s >= least && B * p.all_parts <= 512) break;
+  }
+  return scale > 0 && fits(scale);
+}
+
+hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffers& buffers, const StatPtrs& st,
+                       hipStream_t s) {
+  DealArgs a;
+  a.pb = pb;
+  a.st = st;
+  const size_t n = size_t(pb.B) * size_t(pb.group_cap);
+  uint64_t* at = buffers.keys;  // N * n of them
+  a.pair = at;
+  if (pb.N > 1) at += n;
+  a.rest = at;
+  if (pb.N > 2) at += n;
+  a.first = reinterpret_cast<uint32_t*>(at);
+  a.lead = a.first + n;
+  a.run_at = buffers.places;
+  a.overflow = buffers.overflow;
+  a.kinds = plan.kinds;
+  a.all_parts = plan.all_parts;
+  for (int kind = 0; kind < kKinds; ++kind) {
+    a.parts[kind] = kind < plan.kinds ? plan.parts[kind] : 1;
+    a.parts_before[kind] = kind < plan.kinds ? plan.parts_before[kind] : 0;
+  }
+  a.log2_chunk = plan.items == 2 ? 11 : 10;
+  a.cand_chunks = plan.cand_chunks;
+  a.ref_chunks = plan.ref_chunks;
+  a.chunks = plan.chunks;
+  a.words = plan.words;
+  a.capacity = plan.capacity;
+  a.window = plan.window;
+  a.id_bits = plan.id_bits;
+  a.log2_first = plan.log2_first;
+  a.log2_pair = plan.log2_pair;
+  a.log2_item = plan.log2_item;
+  a.off_sums = plan.off_sums;
+  a.off_owner = plan.off_owner;
+  a.off_places = plan.off_places;
+  a.off_tokens = plan.off_tokens;
+  a.off_lead = plan.off_lead;
+  a.off_scratch = plan.off_scratch;
+  return plan.items == 2 ? launch_items<2>(a, plan, s) : launch_items<1>(a, plan, s);
+}
+
+}  // namespace tb

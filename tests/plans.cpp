@@ -17,6 +17,25 @@ bool runs_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   return true;
 }
 
+// kinds; partitions, slots and candidate's positions of each; ids; slots of their table; members in a window;
+// partitions of all kinds; chunks; LDS bytes; false: no such plan
+bool deal_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, int64_t* out) {
+  tb::DealPlan p;
+  if (!tb::plan_deal(B, cand_stride, ref_stride, R, N, vocab, &p)) return false;
+  out[0] = p.kinds;
+  for (int kind = 0; kind < 3; ++kind) out[1 + kind] = p.parts[kind];
+  out[4] = int64_t(1) << p.log2_first;
+  out[5] = int64_t(1) << p.log2_pair;
+  out[6] = int64_t(1) << p.log2_item;
+  out[7] = p.capacity;
+  out[8] = int64_t(1) << p.id_bits;
+  out[9] = p.window;
+  out[10] = p.all_parts;
+  out[11] = p.chunks;
+  out[12] = int64_t(p.lds_bytes);
+  return true;
+}
+
 // log2 of the slots; bits of an id and of the widest key; pass_ends; LDS bytes; wavefronts; blocks of one
 // of them; whether ids are kept between passes; whether a workgroup has its unit to itself; false: no such plan
 bool fused_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits, bool rouge,

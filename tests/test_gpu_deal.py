@@ -1,0 +1,160 @@
+"""The kernels that deal every position of a long group out once, against the CPU oracle: edges of their chunks,
+short and empty rows, one to four orders, counters of 32 and 16 bits, several windows of members, reference
+lists, and 4-grams that need more ids than a partition has."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2510_05485_amd as tb
+import synth_inputs as syn
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+TOL = 1e-5     # scores; whole numbers are exact
+
+
+def dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a)).to(DEV)
+
+
+def check(w, N, int64=False, lists=None, counts=None):
+    # (the kernels are for 98 304 positions in all and more, and rows beyond the fused kernel's)
+    assert w.B * (w.cand.shape[1] + w.R * w.refs.shape[2]) >= 98304
+    cand, cl = dev(w.cand), dev(w.cand_len)
+    rows, lens = (w.refs, w.ref_len) if lists is None else lists[:2]
+    refs, rl = dev(rows), dev(lens)
+    if int64:
+        cand, refs = cand.long(), refs.long()
+    extra, host = {}, {}
+    if lists is not None:
+        extra, host = dict(ref_offsets=dev(lists[2]), max_refs=w.R), dict(ref_offsets=lists[2])
+    if counts is not None:
+        extra, host = dict(ref_count=dev(counts)), dict(ref_count=counts)
+    ref = oracle.bleu(w.cand, w.cand_len, rows, lens, max_n=N, smoothing="exp", threads=8, **host)
+    cfg = tb.make_config(max_n=N, smoothing="exp", vocab_size=w.vocab, **extra)
+    for fn in (tb.tensorbleu_sentence, tb.tensorbleu_corpus):
+        st = tb.Stats.allocate(w.B, N, DEV)
+        st.group_distinct = None
+        out = fn(cand, cl, refs, rl, cfg, stats=st).cpu().numpy().astype(np.float64)
+        assert st.device_status.item() == 0
+        np.testing.assert_array_equal(st.clipped.cpu().numpy(), ref.clipped)
+        np.testing.assert_array_equal(st.total.cpu().numpy(), ref.total)
+        np.testing.assert_array_equal(st.closest_ref_len.cpu().numpy(), ref.closest_ref_len)
+        np.testing.assert_array_equal(st.corpus_stats.cpu().numpy(), ref.corpus_stats)
+        if fn is tb.tensorbleu_corpus:
+            assert abs(out[0] - ref.corpus_bleu) <= TOL
+        else:
+            assert np.abs(out - ref.bleu).max() <= TOL
+
+
+@pytest.mark.parametrize("B,R,L,Lr,vocab,N", [
+    (3, 1, 20000, 20481, 50257, 4),          # 1024 positions a chunk
+    (20, 1, 15360, 15361, 50257, 4),         # 2048 a chunk; rows that end with one and one behind it
+    (20, 2, 10000, 10100, 3000, 4),          # counters of 16 bits, two words
+    (4, 15, 4097, 4100, 900, 4),             # eight words
+    (2, 2, 70000, 66000, 1000, 4),           # of 32 bits, three words
+    (2, 1, 70000, 66000, 2, 4),              # sixteen 4-grams: counts beyond 16 bits
+    (4, 1, 14000, 14000, (1 << 20) - 2, 4),  # the largest vocabulary
+    (5, 2, 9000, 9001, 300, 3),
+    (5, 3, 9000, 9001, 50257, 2),
+    (5, 1, 30000, 30000, 50257, 1),
+    (1, 1, 600, 120000, 500, 4),             # candidate much shorter than the reference
+    (1, 1, 120000, 600, 500, 4),
+])
+def test_shapes(B, R, L, Lr, vocab, N):
+    w = syn.random_small(911 + L, B=B, R=R, vocab=vocab, max_len=min(L, Lr), min_len=min(L, Lr) // 2,
+                         cand_stride=L, ref_stride=Lr)
+    if B > 1:                                # empty rows, and rows shorter than an n-gram
+        w.cand_len[0], w.ref_len[1, 0] = 2, 0
+    check(w, N, int64=B % 2 == 0)
+
+
+@pytest.mark.parametrize("length", [1023, 1024, 1026, 2047, 2048, 2050, 4096, 13000])
+def test_chunk_edges(length):
+    # the length ends a chunk, starts one, or leaves fewer positions than an n-gram has
+    for B in (4, 24):                        # 1024 and 2048 positions a chunk
+        w = syn.random_small(921, B=B, R=1, vocab=900, max_len=13000, min_len=13000)
+        for i in range(B):
+            w.cand_len[i], w.ref_len[i, 0] = length + i % 4, length + 3 - i % 4
+        w.cand_len, w.ref_len = np.minimum(w.cand_len, 13000), np.minimum(w.ref_len, 13000)
+        check(w, 4)
+
+
+def test_frequent_tokens():
+    w = syn.long_form(B=2, L=100000, vocab=50257)
+    check(w, 4)
+
+
+def test_repetition():
+    # one token, and a few of them: a partition receives whole chunks, merged
+    w = syn.random_small(931, B=4, R=1, vocab=50257, max_len=40000, min_len=39000)
+    w.cand[0], w.refs[0] = 7, 7
+    w.cand[1, 100:30000] = 9
+    w.refs[2, 0, 500:39000] = np.resize(np.arange(11), 38500)
+    w.cand[2, 1000:20000] = np.resize(np.arange(11), 19000)
+    check(w, 4)
+
+
+@pytest.mark.parametrize("R,N", [(1, 4), (2, 4), (1, 3), (3, 4)])
+def test_more_ids_than_a_partition_has(R, N):
+    # 4-grams of one beginning, a quarter of the text: counted in rounds
+    w = syn.random_small(941, B=2, R=R, vocab=50257, max_len=30000, min_len=29000)
+    rng = np.random.default_rng(941)
+    for i in range(2):
+        text = np.full(30000, 5, dtype=np.int32)
+        text[3::4] = rng.permutation(50000)[:7500] + 100
+        w.cand[i] = text
+        for j in range(R):
+            other = text.copy()
+            other[3 + 4 * j:20000:8] = 17
+            w.refs[i, j] = other
+    check(w, N)
+
+
+def test_members_beyond_a_window():
+    # pairs and 4-grams of few tokens: unmerged in part, far more of them in a partition than its share
+    w = syn.random_small(951, B=2, R=1, vocab=13, max_len=60000, min_len=60000)
+    check(w, 4)
+    w = syn.random_small(952, B=4, R=3, vocab=40, max_len=20000, min_len=18000)
+    check(w, 4)
+
+
+def test_lists_and_counts():
+    w = syn.random_small(961, B=10, R=6, vocab=5000, max_len=5000, min_len=4000)
+    counts = syn.ref_counts(961, w.B, w.R)
+    check(w, 4, counts=counts)
+    check(w, 4, lists=syn.pack_reference_lists(w.refs, w.ref_len, counts))
+
+
+def test_tokens_outside_the_vocabulary_are_reported():
+    w = syn.random_small(971, B=4, R=1, vocab=3000, max_len=20000, min_len=20000)
+    for bad, where in ((3000, 0), (-1, 19999), (1 << 33, 2048)):
+        cand, refs = dev(w.cand).long(), dev(w.refs).long()
+        cand[3, where] = bad
+        w.cand[3, where] = 0
+        st = tb.Stats.allocate(4, 4, DEV)
+        st.group_distinct = None
+        cfg = tb.make_config(vocab_size=3000, smoothing="exp")
+        tb.tensorbleu_sentence(cand, dev(w.cand_len), refs, dev(w.ref_len), cfg, stats=st)
+        assert st.device_status.item() == tb.TB_DEV_TOKEN_RANGE
+        ref = oracle.bleu(w.cand, w.cand_len, w.refs, w.ref_len, smoothing="exp", threads=4)
+        np.testing.assert_array_equal(st.clipped.cpu().numpy(), ref.clipped)
+
+
+def test_replays_of_a_captured_call():
+    ws = [syn.random_small(s, B=3, R=1, vocab=50257, max_len=20000, min_len=19000) for s in (981, 982)]
+    scorer = tb.BleuScorer(3, 1, 20000, 20000, vocab_size=50257, smoothing="exp", device=DEV)
+    held = [dev(a) for a in (ws[0].cand, ws[0].cand_len, ws[0].refs, ws[0].ref_len)]
+    scorer(*held)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = scorer(*held)
+    for w in (ws[0], ws[1], ws[0]):
+        for t, a in zip(held, (w.cand, w.cand_len, w.refs, w.ref_len)):
+            t.copy_(dev(a))
+        graph.replay()
+        torch.cuda.synchronize()
+        ref = oracle.bleu(w.cand, w.cand_len, w.refs, w.ref_len, smoothing="exp")
+        assert np.abs(out.cpu().numpy() - ref.bleu).max() <= TOL

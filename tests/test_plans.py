@@ -30,6 +30,8 @@ def plans(tmp_path_factory):
     i64, i32, flag = ctypes.c_int64, ctypes.c_int, ctypes.c_bool
     lib.runs_plan.restype = flag
     lib.runs_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, flag, ctypes.POINTER(i64)]
+    lib.deal_plan.restype = flag
+    lib.deal_plan.argtypes = [i64, i64, i64, i32, i32, i32, ctypes.POINTER(i64)]
     lib.fused_plan.restype = lib.fused_path.restype = flag
     lib.fused_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, ctypes.POINTER(i64)]
     lib.fused_path.argtypes = [i64, i64, i32, i32]
@@ -64,6 +66,36 @@ def test_sorted_runs_leave_their_tables_room(plans):
     chance = stats.binom.logsf(slots, entries, 1.0 / np.array(tables, dtype=np.float64))
     worst = int(np.argmax(chance))
     assert chance[worst] <= -40.0, (shapes[worst], tables[worst], slots[worst], chance[worst])
+
+
+def test_dealt_partitions_leave_their_tables_room(plans):
+    # tables of tokens and of pairs: as the sorted runs'; ids never fill their table (a search ends at a free
+    # slot); two workgroups on a unit; runs' places fit their part of the workspace
+    out = (ctypes.c_int64 * 13)()
+    rng, shapes, mean, tables, slots = random.Random(31), 0, [], [], []
+    for _ in range(60000):
+        R, N = rng.choice((1, 1, 2, 3, 5, 8, 16, 40, 61)), rng.randint(1, 4)
+        cs = int(2 ** (20.5 * rng.random()))
+        rs = max(1, min(int(2097152 / R), int(cs * 4 ** rng.uniform(-3, 1.5))))
+        B, vocab = int(2 ** (8 * rng.random())), rng.choice((2, 1000, 65536, (1 << 20) - 2))
+        cap = cs + R * rs
+        if not 12288 < cap <= 2097152 or not plans.deal_plan(B, cs, rs, R, N, vocab, out):
+            continue
+        shapes += 1
+        kinds = out[0]
+        assert kinds == min(N, 3) and out[10] == sum(out[1:1 + kinds]) <= 2048
+        assert out[12] <= LDS // 2 and out[11] <= 1024 and out[11] * out[10] <= kinds * cap
+        assert out[9] % 64 == 0 and 4 * out[7] <= 3 * out[6] and out[7] <= out[8] and out[7] % 8 == 0
+        assert out[8] <= 1 << 20             # (id, order and at least eleven bits of the hash in a word)
+        for kind in range(min(kinds, 2)):
+            mean.append(cs)
+            tables.append(out[1 + kind])
+            slots.append(out[4 + kind])
+    assert shapes > 10000
+    assert not plans.deal_plan(4, 20000, 20000, 1, 4, (1 << 20) - 1, out)
+    assert not plans.deal_plan(4, 20000, 20000, 1, 5, 1000, out)
+    chance = stats.binom.logsf(slots, mean, 1.0 / np.array(tables, dtype=np.float64))
+    assert chance.max() <= -40.0
 
 
 def fused_table(plans, *shape):
