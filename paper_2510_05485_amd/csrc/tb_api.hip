@@ -324,16 +324,24 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
                    plan);
 }
 
-// Whether a BLEU call that the sorted runs take, without dictionary sizes, goes to the kernels that deal every
-// position out once.  Of 590 drawn shapes of 12 000 to 2 000 000 positions with 1 to 16 references, one to four
-// orders, the ones that do take 0.84 of the sorted runs' time on average.  Below 98 304 positions in all both are a
-// chain of latencies, and the sorted runs' is the shorter one (three groups of two times 8000 17.8 us, 19.5 here;
-// three of two times 19 000 17.9 and 16.2); with three references or more whose counters need 32 bits, tables take
-// so much LDS that partitions become too small (two groups of 131 072 with three references 64.5, 88.7).
-bool takes_deal(const Problem& pb, DealPlan* plan) {
-  if (pb.B * pb.group_cap < 98304) return false;
+// Whether a call that the sorted runs take goes to the kernels that deal every position out once.  BLEU: of 590
+// drawn shapes of 12 000 to 2 000 000 positions with 1 to 16 references, one to four orders, the ones that do take
+// 0.84 of the sorted runs' time on average.  Below 98 304 positions in all both are a chain of latencies, and the
+// sorted runs' is the shorter one (three groups of two times 8000 17.8 us, 19.5 here; three of two times 19 000 17.9
+// and 16.2); with three references or more whose counters need 32 bits, tables take so much LDS that partitions
+// become too small (two groups of 131 072 with three references 64.5, 88.7).  With dictionary sizes, where the tables
+// hold the references' n-grams, too, 0.88 of 35 shapes of up to four references (30 groups of two times 21 000 81.9,
+// 64.1), 1.1 with eight (4 of 37 199 81.0, 100.7).  ROUGE-N has one kind of members, whose order the sorted runs deal
+// out by themselves as well, in longer chunks: with few positions a candidate, many of them with more than
+// 1 000 000 for ROUGE-2, or many references these are faster (two groups of two times 138 993 25.2, 19.1; 21 of two
+// times 40 393 29.7, 34.4; 84 of 7239 23.4, 30.9; 7 of 15 076 with 16 references 48.2, 59.8).
+bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* plan) {
+  const int64_t positions = pb.B * pb.group_cap;
+  if (positions < 98304) return false;
   if (pb.R > 2 && (pb.cand_stride > 65535 || pb.ref_stride > 65535)) return false;
-  return plan_deal(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.vocab, plan);
+  if (group_distinct && pb.R > 4) return false;
+  if (rouge && (pb.cand_stride < 12000 || pb.R > 8 || (pb.N > 1 && positions > 1000000))) return false;
+  return plan_deal(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.vocab, rouge, group_distinct, plan);
 }
 
 // Whether the call runs on the fused kernel: on its own path, and on AUTO also for longer shapes
@@ -366,7 +374,7 @@ bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats,
     int64_t few = 32;
     if (takes_runs(c, cfg, rouge, false, &runs)) {
       const int64_t refs = pb.R * pb.ref_stride;
-      if (!rouge && takes_deal(pb, &deal))
+      if (!rouge && takes_deal(pb, false, false, &deal))
         few = pb.cand_stride / 600 + refs / 1000 - pb.R + 4 * pb.N - 18;
       else
         few = rouge ? pb.N * pb.cand_stride / 260 + pb.N * refs / 1400 - 5 * pb.R / 2 - 33
@@ -407,8 +415,8 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
   if (takes_runs(c, cfg, false, group_distinct, &runs)) {
     const RunsBuffers buffers = runs_buffers(c.pb, c.ws, c.plans.part);
     DealPlan deal;
-    rc = hip_rc(!group_distinct && takes_deal(c.pb, &deal)
-                    ? launch_deal(c.pb, deal, buffers, c.st, c.stream)
+    rc = hip_rc(takes_deal(c.pb, false, group_distinct, &deal)
+                    ? launch_deal(c.pb, deal, buffers, c.st, nullptr, c.stream)
                     : launch_runs(c.pb, runs, buffers, c.st, group_distinct, nullptr, c.stream));
     if (rc != TB_OK) return rc;
     return hip_rc(launch_finalize(c.pb, c.st, c.sp, !corpus, corpus || c.want_corpus_stats, corpus,
@@ -500,8 +508,11 @@ int tensorrouge_n(const void* cand, int64_t cand_stride, const int32_t* cand_len
   int32_t* ov = reinterpret_cast<int32_t*>(w + L.overlap_off);
   RunsPlan runs;
   if (takes_runs(c, cfg, true, false, &runs)) {
-    rc = hip_rc(launch_runs(c.pb, runs, runs_buffers(c.pb, c.ws, c.plans.part), c.st, false, ov,
-                            c.stream));
+    const RunsBuffers buffers = runs_buffers(c.pb, c.ws, c.plans.part);
+    DealPlan deal;
+    rc = hip_rc(takes_deal(c.pb, true, false, &deal)
+                    ? launch_deal(c.pb, deal, buffers, c.st, ov, c.stream)
+                    : launch_runs(c.pb, runs, buffers, c.st, false, ov, c.stream));
     if (rc != TB_OK) return rc;
     return hip_rc(launch_rouge_finalize(c.pb, c.sp, ov, ro, c.stream));
   }

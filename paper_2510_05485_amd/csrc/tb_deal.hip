@@ -1,4 +1,4 @@
-// Whole BLEU calls of up to four orders on groups beyond one LDS table, in two kernels:
+// Whole calls on groups beyond one LDS table, BLEU of up to four orders and ROUGE-1 and -2, in two kernels:
 //
 //   deal_kernel   one workgroup per (group, chunk of 1024 or 2048 positions of one sequence): deals the
 //                 chunk's positions out to partitions three times, as three kinds of members: its tokens by a
@@ -60,18 +60,18 @@ struct DealArgs {
   uint32_t* first;   // token | multiplicity - 1, from bit 20 on
   uint32_t* run_at;  // [B][chunks][parts of all kinds]: first of the run within its chunk | size << 16
   int32_t* overflow; // [B]
-  int kinds, all_parts;
+  int32_t* rouge_overlap;  // [B, R] or null
+  int first_kind, kinds, all_parts;  // kinds first_kind .. kinds - 1
   int parts[kKinds], parts_before[kKinds];  // of each kind; of the kinds before it
   int log2_chunk;
   int cand_chunks, ref_chunks, chunks;  // of the candidate, of one reference, of a group
   // tally_kernel
   int words;         // per counter
   int capacity;      // ids of order 3 and 4 n-grams
-  int window;        // members of a kind that the marks are for, a multiple of 64
+  int window[kKinds];  // members of a kind that the marks are for, a multiple of 64
   int id_bits, log2_first, log2_pair, log2_item;
-  // LDS: table and counters at 0
-  uint32_t off_sums, off_owner;  // cleared, too
-  uint32_t off_places, off_tokens, off_lead, off_scratch;
+  // LDS: table and counters at 0, (4-grams: tokens under the ids,) marks, and for all kinds
+  uint32_t off_tokens, off_lead, off_sums, off_places, off_scratch;
 };
 
 struct DealChunk {
@@ -126,7 +126,7 @@ __global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
   __shared__ int kind_base[kKinds + 1];
   __shared__ int scan_scratch[17];
   const Problem& pb = a.pb;
-  const int tid = threadIdx.x, kinds = a.kinds;
+  const int tid = threadIdx.x, kinds = a.kinds, first_kind = a.first_kind;
   const int c = blockIdx.x, g = blockIdx.y;
   const DealChunk me = deal_chunk(a, c);
   const RefRows rr = ref_rows(pb, g);
@@ -170,6 +170,7 @@ __global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
       a.st.distinct[int64_t(g) * pb.N + tid] = 0;
     }
     if (tid == 0) a.overflow[g] = 0;
+    if (a.rouge_overlap && tid < pb.R) a.rouge_overlap[int64_t(g) * pb.R + tid] = 0;
   }
   if (bad && pb.status) atomicOr(pb.status, TB_DEV_TOKEN_RANGE);
   __syncthreads();
@@ -190,7 +191,7 @@ __global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
     h[u][2] = hash3(t[u][0], t[u][1], t[u][2]);
 #pragma unroll
     for (int kind = 0; kind < kKinds; ++kind)
-      if (kind < kinds && merges(u, kind)) space.kept[kind][slot(u, kind)] = uint32_t(k);
+      if (kind >= first_kind && kind < kinds && merges(u, kind)) space.kept[kind][slot(u, kind)] = uint32_t(k);
   }
   __syncthreads();
   // (Reads of all kinds first, whether they count or not: with a branch around each, a wavefront waited for six
@@ -228,7 +229,7 @@ __global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
 #pragma unroll
     for (int kind = 0; kind < kKinds; ++kind) {
       rank[u][kind] = 0;
-      if (kind >= kinds) continue;  // uniform
+      if (kind < first_kind || kind >= kinds) continue;  // uniform
       if (merged[u][kind]) {
         atomicAdd(&space.kept[kind][slot(u, kind)], 0x1000u);
       } else if (is_member(u, kind)) {
@@ -269,7 +270,7 @@ __global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
   for (int u = 0; u < ITEMS; ++u)
 #pragma unroll
     for (int kind = 0; kind < kKinds; ++kind)
-      if (kind < kinds) rank[u][kind] += in_part[part[u][kind]];
+      if (kind >= first_kind && kind < kinds) rank[u][kind] += in_part[part[u][kind]];
 #pragma unroll
   for (int u = 0; u < ITEMS; ++u) {
 #pragma unroll
@@ -335,12 +336,15 @@ typedef uint32_t Quad __attribute__((ext_vector_type(4)));
 // One reference: a counter is one less than the candidate's count, less what the reference has had of it; what
 // the reference finds is a match.  More: counters of the candidate (one less) and of each reference, two a word
 // where no sequence is longer than 65 535, and a pass over them in the end.
-enum Counters { kOneReference, kHalves, kWords };
+// With the sizes of the group's dictionaries (kAll...) the references' n-grams are entered, too, and every
+// occurrence is counted.
+enum Counters { kOneReference, kHalves, kWords, kAllHalves, kAllWords };
 
 // One partition's members of one kind.
 template <int KIND, Counters COUNTERS>
 __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
-  constexpr bool ONE = COUNTERS == kOneReference, HALVES = COUNTERS == kHalves;
+  constexpr bool ONE = COUNTERS == kOneReference, HALVES = COUNTERS == kHalves || COUNTERS == kAllHalves;
+  constexpr bool ALL = COUNTERS == kAllHalves || COUNTERS == kAllWords;
   const Problem& pb = a.pb;
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
@@ -359,7 +363,11 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
   const uint32_t slots_bytes = KIND == 0 ? 4u << a.log2_first : KIND == 1 ? 4u << a.log2_pair : 4u * uint32_t(a.capacity);
   const uint32_t counters4 = table_bytes + slots_bytes * uint32_t(ONE ? 1 : a.words);  // KIND 2: order 4's
   const uint32_t used_bytes = KIND < 2 ? counters4 : counters4 + slots_bytes * uint32_t(N < 4 ? 0 : ONE ? 1 : a.words);
+  const int window = a.window[KIND];
+  const uint32_t cand_marks = KIND < 2 ? used_bytes : (a.off_lead + 4u * uint32_t(a.capacity) + 15u) & ~15u;
+  const uint32_t ref_marks = cand_marks + 2u * uint32_t(window);
   clear(0, used_bytes);
+  clear(cand_marks, cand_marks + 4u * uint32_t(window));
   clear(a.off_sums, a.off_places);
   // Members: those of the candidate's chunks, then those of the references'.
   auto scratch = [&](int i) __attribute__((always_inline)) { return lds<int>(a.off_scratch + 4u * uint32_t(i)); };
@@ -381,18 +389,17 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     if (KIND == 2) *lds<int>(a.off_places + 4u * uint32_t(a.chunks + tid)) = before;
     if (!ONE) *lds<int>(a.off_places + 4u * uint32_t(2 * a.chunks + tid)) = seq;
   }
-  // Windows of a.window members, in blocks of 64 that the wavefronts take in turn.  A run marks its first member
+  // Windows of `window` members, in blocks of 64 that the wavefronts take in turn.  A run marks its first member
   // in the window and every member at a multiple of 64: the largest mark up to a lane is its run.
   auto mark = [&](uint32_t marks, int begin, int size) __attribute__((always_inline)) {
     const int lo = max(before - begin, 0), hi = min(before + run_size - begin, size);
 #pragma unroll 1
     for (int i = lo; i < hi; i = (i | (kWave - 1)) + 1) *lds<uint16_t>(marks + 2u * uint32_t(i)) = uint16_t(tid + 1);
   };
-  const uint32_t cand_marks = a.off_owner, ref_marks = a.off_owner + 2u * uint32_t(a.window);
   __syncthreads();
   const int cand_members = __builtin_amdgcn_readfirstlane(*scratch(16));
-  mark(cand_marks, 0, min(cand_members, a.window));
-  mark(ref_marks, cand_members, min(members - cand_members, a.window));
+  mark(cand_marks, 0, min(cand_members, window));
+  mark(ref_marks, cand_members, min(members - cand_members, window));
   __syncthreads();
 
   const int64_t slots = int64_t(g) * pb.group_cap;
@@ -422,10 +429,11 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
   };
 
   uint32_t matches = 0, matches4 = 0;  // (4-grams)
+  uint32_t created = 0, created4 = 0;
   // Adds `times` occurrences in sequence f to the counter; `is_new`: the candidate's first.
   auto count = [&](uint32_t at, uint32_t times, int f, bool is_new, uint32_t& matched) __attribute__((always_inline)) {
     if (f == 0) {
-      lds_add_only(at, times - (is_new ? 1u : 0u));
+      lds_add_only(at, times - (is_new && !ALL ? 1u : 0u));
     } else if (ONE) {
       const int had = int(lds_add(at, 0u - times)) + 1;
       matched += uint32_t(min(max(had, 0), int(times)));
@@ -438,7 +446,7 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     typedef decltype(key) Key;
     constexpr uint32_t kSize = sizeof(Key);
     Key old = *lds<Key>(s);
-    if (f > 0) {
+    if (f > 0 && !ALL) {
       for (uint32_t left = table_bytes; old != key && old != 0 && left; left -= kSize) {
         s = (s + kSize) & (table_bytes - 1u);
         old = *lds<Key>(s);
@@ -458,6 +466,7 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
         return;
       }
     }
+    if (ALL) created += old == 0 ? 1u : 0u;
     count(table_bytes + s / (kSize / 4u), times, f, old == 0, matches);
   };
   auto do_first = [&](uint32_t word, int f) __attribute__((always_inline)) {
@@ -513,7 +522,7 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
       if (e.w == 0u) break;
       s = (s + 16u) & bucket_mask;
     }
-    if (f > 0) return false;
+    if (f > 0 && !ALL) return false;
     while (true) {
       const uint64_t going = __builtin_amdgcn_ballot_w64(true);
       const int leader = __ffsll((unsigned long long)going) - 1;
@@ -578,12 +587,14 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     bool is_new;
     if (!resolve(x, h, 3, f, id, found, is_new, std::false_type{})) return;
     // (one that is new at order 3 is new at order 4, too)
-    if (f == 0 && is_new && times == 1u) return;
+    if (f == 0 && is_new && times == 1u && !ALL) return;
+    if (ALL) created += is_new ? 1u : 0u;
     count(table_bytes + 4u * id, times, f, is_new, matches);
     // (behind the end there is no fourth token)
     if (N < 4 || last_of(x) == kNoToken) return;
     if (last_of(x) != last_of(found) && !resolve(x, longer_hash(x, h), 4, f, id, found, is_new, std::false_type{}))
       return;
+    if (ALL) created4 += is_new ? 1u : 0u;
     count(counters4 + 4u * id, times, f, is_new, matches4);
   };
 
@@ -593,7 +604,7 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     const int end = cand ? cand_members : members;
 #pragma unroll 1
     while (true) {
-      const int size = min(end - begin, a.window);
+      const int size = min(end - begin, window);
 #pragma unroll 1
       for (int block = wave; block * kWave < size; block += kWaves) {
         const Member now = m;
@@ -605,9 +616,9 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
           if (KIND == 0) do_first(now.word, f);
         }
       }
-      begin += a.window;
+      begin += window;
       if (begin >= end) break;
-      const int next = min(end - begin, a.window);
+      const int next = min(end - begin, window);
       __syncthreads();
       mark(marks, begin, next);
       __syncthreads();
@@ -615,8 +626,8 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     }
   };
   Member m{0, 0, 0}, later{0, 0, 0};
-  const int refs_size = min(members - cand_members, a.window);
-  if (wave * kWave < min(cand_members, a.window)) m = fetch(cand_marks, 0, min(cand_members, a.window), wave, true);
+  const int refs_size = min(members - cand_members, window);
+  if (wave * kWave < min(cand_members, window)) m = fetch(cand_marks, 0, min(cand_members, window), wave, true);
   // (on their way while the candidate's are entered)
   if (wave * kWave < refs_size) later = fetch(ref_marks, cand_members, refs_size, wave, false);
   side(true, m);
@@ -627,30 +638,48 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     uint32_t part = 0;
     for (uint32_t k = at + 4u * uint32_t(tid); k < at + slots_bytes; k += 4u * kTallyThreads) {
       const uint32_t head = *lds<uint32_t>(k);
+      const uint32_t of_cand = (HALVES ? head & 0xFFFFu : head) + (ALL ? 0u : 1u);
       uint32_t most = HALVES ? head >> 16 : 0u;
       for (int w = 1; w < a.words; ++w) {
         const uint32_t word = *lds<uint32_t>(k + uint32_t(w) * slots_bytes);
         most = max(most, HALVES ? max(word & 0xFFFFu, word >> 16) : word);
       }
-      part += min((HALVES ? head & 0xFFFFu : head) + 1u, most);
+      part += min(of_cand, most);
     }
     return part;
   };
-  auto add_up = [&](int n, uint32_t part) __attribute__((always_inline)) {
+  auto add_to = [&](uint32_t at, uint32_t part) __attribute__((always_inline)) {
     const int sum = wave_sum(int(part));
-    if (lane == 0 && sum) lds_add_only(lost_at + 12u + 4u * uint32_t(n), uint32_t(sum));
+    if (lane == 0 && sum) lds_add_only(at, uint32_t(sum));
   };
+  auto add_up = [&](int n, uint32_t part, uint32_t sizes) __attribute__((always_inline)) {
+    add_to(lost_at + 12u + 4u * uint32_t(n), part);
+    if (ALL) add_to(lost_at + 28u + 4u * uint32_t(n), sizes);
+  };
+  const bool rouge = KIND < 2 && a.rouge_overlap;  // uniform
+  const uint32_t overlaps_at = lost_at + 64u;
+  if (rouge && !ONE) {  // the overlap with each reference
+    for (int f = 1; f <= pb.R; ++f) {
+      uint32_t part = 0;
+      for (uint32_t k = table_bytes + 4u * uint32_t(tid); k < table_bytes + slots_bytes; k += 4u * kTallyThreads) {
+        const uint32_t head = *lds<uint32_t>(k), word = *lds<uint32_t>(k + uint32_t(HALVES ? f >> 1 : f) * slots_bytes);
+        part += HALVES ? min((head & 0xFFFFu) + 1u, f & 1 ? word >> 16 : word & 0xFFFFu) : min(head + 1u, word);
+      }
+      add_to(overlaps_at + 4u * uint32_t(f), part);
+    }
+  }
   const bool again = KIND == 2 && *lds<uint32_t>(again_at);  // uniform
   if (!again) {
-    add_up(KIND + 1, ONE ? matches : sweep(table_bytes));
-    if (KIND == 2 && N > 3) add_up(4, ONE ? matches4 : sweep(counters4));
+    if (ONE || !rouge) add_up(KIND + 1, ONE ? matches : sweep(table_bytes), created);
+    if (KIND == 2 && N > 3) add_up(4, ONE ? matches4 : sweep(counters4), created4);
   } else {
     // Orders 3 and 4, each on its own, in rounds of the n-grams whose hash falls into the round; more rounds where
     // one has too many all the same.
 #pragma unroll 1
     for (int n = 3; n <= N; ++n) {
       uint32_t part = 0;
-      int rounds = 2 + 2 * cand_members / int(capacity);
+      int rounds = 2 + 2 * (ALL ? members : cand_members) / int(capacity);
+      created = 0;
 #pragma unroll 1
       for (int round = 0; round < rounds; ++round) {
         __syncthreads();
@@ -677,8 +706,9 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
             Item found;
             uint32_t id;
             bool is_new;
-            if (resolve(x, h, n, m.f, id, found, is_new, std::true_type{}))
-              count(table_bytes + 4u * id, (m.word >> kTokenBits) + 1u, m.f, is_new, matches);
+            if (!resolve(x, h, n, m.f, id, found, is_new, std::true_type{})) continue;
+            if (ALL) created += is_new ? 1u : 0u;
+            count(table_bytes + 4u * id, (m.word >> kTokenBits) + 1u, m.f, is_new, matches);
           }
           if (refs == 0) i = cand_members + tid;
         }
@@ -687,14 +717,14 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
           part += ONE ? matches : sweep(table_bytes);
         } else if (rounds < 1 << 14) {
           rounds *= 2;
-          part = 0;
+          part = created = 0;
           round = -1;
         } else {
           if (tid == 0) *lds<uint32_t>(lost_at) = 1u;
           round = rounds;
         }
       }
-      add_up(n, part);
+      add_up(n, part, created);
     }
   }
   __syncthreads();
@@ -703,10 +733,14 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     a.overflow[g] = 1;
   }
   const int n0 = KIND + tid;  // order n0 + 1
-  if (tid < (KIND == 2 ? 2 : 1) && n0 < N) {
+  if (rouge) {
+    const uint32_t at = ONE ? lost_at + 16u + 4u * uint32_t(KIND) : overlaps_at + 4u * uint32_t(tid + 1);
+    if (tid < pb.R && *lds<uint32_t>(at)) atomicAdd(&a.rouge_overlap[int64_t(g) * pb.R + tid], int(*lds<uint32_t>(at)));
+  } else if (tid < (KIND == 2 ? 2 : 1) && n0 < N) {
     const int64_t stat = int64_t(g) * N + n0;
     const uint32_t sum = *lds<uint32_t>(lost_at + 16u + 4u * uint32_t(n0));
     if (sum) atomicAdd(&a.st.clipped[stat], int(sum));
+    if (ALL) atomicAdd(&a.st.distinct[stat], int(*lds<uint32_t>(lost_at + 32u + 4u * uint32_t(n0))));
     if (p == 0) {
       const int len = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, nullptr);
       a.st.total[stat] = max(len - n0, 0);
@@ -751,6 +785,7 @@ hipError_t launch_items(const DealArgs& a, const DealPlan& plan, hipStream_t s) 
     hipLaunchKernelGGL(kernel, dim3(a.all_parts, a.pb.B), dim3(kTallyThreads), plan.lds_bytes, s, a);
     return hipGetLastError();
   };
+  if (plan.all) return plan.halves ? tally(tally_kernel<kAllHalves>) : tally(tally_kernel<kAllWords>);
   return a.pb.R == 1 ? tally(tally_kernel<kOneReference>)
          : plan.halves ? tally(tally_kernel<kHalves>) : tally(tally_kernel<kWords>);
 }
@@ -766,13 +801,20 @@ hipError_t launch_items(const DealArgs& a, const DealPlan& plan, hipStream_t s) 
 //   * A share of the candidate brings one of each reference with it.  9 groups of 25 236 with three references of
 //     27 025: 480 4-grams 42.8, 1280 49.5, 320 50.0.
 //   * A 4-gram costs 1.6 times a pair, and a token, of which most are merged, half as much.
-bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, DealPlan* plan) {
+//   * Tables of tokens and pairs at most half full: a wavefront probes as long as its unluckiest lane.  With up to
+//     two thirds, 22 groups of two times 17 000, two orders, 28.4 instead of 24.0, 4 of two times 50 000 29.3 instead
+//     of 26.9.
+bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, bool rouge,
+               bool group_distinct, DealPlan* plan) {
   DealPlan& p = *plan;
   const int64_t cap = cand_stride + R * ref_stride;
-  if (N > 4 || R >= kWave || B > 65535 || vocab >= int32_t(kNoToken)) return false;
+  if (N > (rouge ? 2 : 4) || R >= kWave || B > 65535 || vocab >= int32_t(kNoToken)) return false;
   p.kinds = N < 3 ? N : 3;
+  p.first_kind = rouge ? N - 1 : 0;
+  p.all = group_distinct;
   p.halves = cand_stride <= 65535 && ref_stride <= 65535;
-  p.words = R == 1 ? 1 : p.halves ? (R + 2) / 2 : 1 + R;
+  p.window[0] = p.window[1] = p.window[2] = kWave;
+  p.words = R == 1 && !p.all ? 1 : p.halves ? (R + 2) / 2 : 1 + R;
   p.items = B * cap < 256 * 2 * kThreads ? 1 : 2;  // (one workgroup for every compute unit)
   auto split = [&] {
     const int64_t chunk = p.items * kThreads;
@@ -786,44 +828,47 @@ bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   if (chunks > kMaxDealChunks) return false;
   p.chunks = int(chunks);
 
-  // shares: candidate's positions that a partition of each kind may expect
+  // shares: positions whose n-grams are entered, as a partition of each kind may expect them
+  const int64_t entries = p.all ? cap : cand_stride;
   auto fits = [&](int scale) {
     int64_t share[kKinds] = {256 * scale, 128 * scale, 80 * scale};
     int log2_slots[kKinds];
     p.all_parts = 0;
     for (int kind = 0; kind < kKinds; ++kind) {
-      int64_t parts = (cand_stride + share[kind] - 1) / share[kind];
+      int64_t parts = (entries + share[kind] - 1) / share[kind];
       if (parts < 2) parts = 2;
-      share[kind] = (cand_stride + parts - 1) / parts;
-      p.parts[kind] = int(kind < p.kinds ? parts : 1);
-      p.parts_before[kind] = kind < p.kinds ? p.all_parts : 0;
-      if (kind < p.kinds) p.all_parts += int(parts);
-      log2_slots[kind] = log2_ceil(share[kind] + share[kind] / 2);
+      share[kind] = (entries + parts - 1) / parts;
+      const bool used = kind >= p.first_kind && kind < p.kinds;
+      p.parts[kind] = int(used ? parts : 1);
+      p.parts_before[kind] = used ? p.all_parts : 0;
+      if (used) p.all_parts += int(parts);
+      log2_slots[kind] = log2_ceil(2 * share[kind]);
       while (!deal_has_room(share[kind], int64_t(1) << log2_slots[kind])) ++log2_slots[kind];
     }
     // ids: the most frequent three tokens of a Zipf-distributed text start one of 370 of its 4-grams
-    p.capacity = int((share[2] + share[2] / 4 + cand_stride / 512 + 128 + 7) & ~int64_t(7));
+    p.capacity = int((share[2] + share[2] / 4 + entries / 512 + 128 + 7) & ~int64_t(7));
     p.id_bits = log2_ceil(p.capacity);
     p.log2_first = log2_slots[0];
     p.log2_pair = log2_slots[1];
     p.log2_item = log2_ceil(2 * share[2]);
     while ((int64_t(3) << p.log2_item) < 4 * int64_t(p.capacity)) ++p.log2_item;
-    const uint32_t ids = N > 2 ? uint32_t(p.capacity) : 0u, counter = 4u * uint32_t(p.words);
-    uint32_t most = (4u + counter) << p.log2_first;
-    if (N > 1 && most < (8u + counter) << p.log2_pair) most = (8u + counter) << p.log2_pair;
-    // (4-grams: the tokens under the ids behind table and counters)
-    const uint32_t items = N > 2 ? (4u << p.log2_item) + counter * ids * uint32_t(N - 2) : 0u;
-    p.off_tokens = (items + 15u) & ~15u;
+    const uint32_t ids = uint32_t(p.capacity), counter = 4u * uint32_t(p.words);
+    p.off_tokens = ((4u << p.log2_item) + counter * ids * (N > 3 ? 2u : 1u) + 15u) & ~15u;
     p.off_lead = p.off_tokens + 8u * ids;
-    if (most < p.off_lead + 4u * ids) most = p.off_lead + 4u * ids;
-    p.off_sums = (most + 15u) & ~15u;
-    p.off_owner = p.off_sums + 32;
-    const int64_t longest = share[1] > share[2] ? share[1] : share[2];
-    p.window = int(longest + longest / 4 + 127) & ~(kWave - 1);
-    p.off_places = p.off_owner + 2u * 2u * uint32_t(p.window);
+    const uint32_t tables[kKinds] = {(4u + counter) << p.log2_first, (8u + counter) << p.log2_pair,
+                                     (p.off_lead + 4u * ids + 15u) & ~15u};
+    // marks: of pairs for a quarter more than the share, of 4-grams for as many (a partition may have a frequent
+    // beginning), of tokens, of which most are merged, for three quarters
+    p.off_sums = 0;
+    for (int kind = p.first_kind; kind < p.kinds; ++kind) {
+      p.window[kind] = int((kind ? 5 * share[1] : 3 * share[0]) / 4 + 127) & ~(kWave - 1);
+      const uint32_t end = tables[kind] + 4u * uint32_t(p.window[kind]);
+      if (p.off_sums < end) p.off_sums = end;
+    }
+    p.off_places = p.off_sums + 64 + (rouge ? 4 * kWave : 0);
     p.off_scratch = p.off_places + 4u * uint32_t(3 * p.chunks);
     p.lds_bytes = p.off_scratch + 4 * 17;
-    return p.all_parts <= kMaxParts && chunks * p.all_parts <= p.kinds * cap;
+    return p.all_parts <= kMaxParts && chunks * p.all_parts <= (p.kinds - p.first_kind) * cap;
   };
   const int most = 32 / (1 + R) < 2 ? 2 : 32 / (1 + R), least = (12 + R) / (1 + R) < 2 ? 2 : (12 + R) / (1 + R);
   int scale = 0;
@@ -837,7 +882,7 @@ bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
 }
 
 hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffers& buffers, const StatPtrs& st,
-                       hipStream_t s) {
+                       int32_t* rouge_overlap, hipStream_t s) {
   DealArgs a;
   a.pb = pb;
   a.st = st;
@@ -851,11 +896,14 @@ hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffer
   a.lead = a.first + n;
   a.run_at = buffers.places;
   a.overflow = buffers.overflow;
+  a.rouge_overlap = rouge_overlap;
+  a.first_kind = plan.first_kind;
   a.kinds = plan.kinds;
   a.all_parts = plan.all_parts;
   for (int kind = 0; kind < kKinds; ++kind) {
-    a.parts[kind] = kind < plan.kinds ? plan.parts[kind] : 1;
-    a.parts_before[kind] = kind < plan.kinds ? plan.parts_before[kind] : 0;
+    a.window[kind] = plan.window[kind];
+    a.parts[kind] = plan.parts[kind];
+    a.parts_before[kind] = plan.parts_before[kind];
   }
   a.log2_chunk = plan.items == 2 ? 11 : 10;
   a.cand_chunks = plan.cand_chunks;
@@ -863,16 +911,14 @@ hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffer
   a.chunks = plan.chunks;
   a.words = plan.words;
   a.capacity = plan.capacity;
-  a.window = plan.window;
   a.id_bits = plan.id_bits;
   a.log2_first = plan.log2_first;
   a.log2_pair = plan.log2_pair;
   a.log2_item = plan.log2_item;
-  a.off_sums = plan.off_sums;
-  a.off_owner = plan.off_owner;
-  a.off_places = plan.off_places;
   a.off_tokens = plan.off_tokens;
   a.off_lead = plan.off_lead;
+  a.off_sums = plan.off_sums;
+  a.off_places = plan.off_places;
   a.off_scratch = plan.off_scratch;
   return plan.items == 2 ? launch_items<2>(a, plan, s) : launch_items<1>(a, plan, s);
 }

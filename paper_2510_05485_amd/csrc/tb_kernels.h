@@ -163,20 +163,21 @@ hipError_t launch_runs(const Problem& pb, const RunsPlan& plan, const RunsBuffer
                        const StatPtrs& st, bool group_distinct, int32_t* rouge_overlap,
                        hipStream_t s);
 
-// Whole BLEU calls of up to four orders on the same groups, every position dealt out once (tb_deal.hip);
-// in the same share of the workspace.
+// Whole calls on the same groups, BLEU of up to four orders and ROUGE-1 and -2, every position dealt out once
+// (tb_deal.hip); in the same share of the workspace.
 struct DealPlan {
   int items;                                // positions per thread of the dealing kernel: 1 or 2
-  int kinds, all_parts, parts[3], parts_before[3];
+  int first_kind, kinds, all_parts, parts[3], parts_before[3];
+  int all;                                  // the references' n-grams are entered, too (group_distinct)
   int cand_chunks, ref_chunks, chunks;
-  int words, halves, capacity, window, id_bits, log2_first, log2_pair, log2_item;
-  uint32_t off_sums, off_owner, off_places, off_tokens, off_lead, off_scratch;
+  int words, halves, capacity, window[3], id_bits, log2_first, log2_pair, log2_item;
+  uint32_t off_tokens, off_lead, off_sums, off_places, off_scratch;
   size_t lds_bytes;
 };
-bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab,
-               DealPlan* plan);
+bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, bool rouge,
+               bool group_distinct, DealPlan* plan);
 hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffers& buffers,
-                       const StatPtrs& st, hipStream_t s);
+                       const StatPtrs& st, int32_t* rouge_overlap, hipStream_t s);
 
 bool plan_big(int64_t group_cap, int N, BigPlan* plan);
 hipError_t launch_big_dictionary(const Problem& pb, const GlobalWs& ws, const BigPlan& plan,

@@ -17,19 +17,21 @@ bool runs_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   return true;
 }
 
-// kinds; partitions, slots and candidate's positions of each; ids; slots of their table; members in a window;
-// partitions of all kinds; chunks; LDS bytes; false: no such plan
-bool deal_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, int64_t* out) {
+// kinds; partitions, slots and candidate's positions of each; ids; slots of their table; members in a window (of any kind);
+// partitions of all kinds; chunks; LDS bytes; first kind; false: no such plan
+bool deal_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, bool rouge,
+               bool group_distinct, int64_t* out) {
   tb::DealPlan p;
-  if (!tb::plan_deal(B, cand_stride, ref_stride, R, N, vocab, &p)) return false;
+  if (!tb::plan_deal(B, cand_stride, ref_stride, R, N, vocab, rouge, group_distinct, &p)) return false;
   out[0] = p.kinds;
+  out[13] = p.first_kind;
   for (int kind = 0; kind < 3; ++kind) out[1 + kind] = p.parts[kind];
   out[4] = int64_t(1) << p.log2_first;
   out[5] = int64_t(1) << p.log2_pair;
   out[6] = int64_t(1) << p.log2_item;
   out[7] = p.capacity;
   out[8] = int64_t(1) << p.id_bits;
-  out[9] = p.window;
+  out[9] = p.window[0] | p.window[1] | p.window[2];
   out[10] = p.all_parts;
   out[11] = p.chunks;
   out[12] = int64_t(p.lds_bytes);

@@ -1,6 +1,6 @@
 """The kernels that deal every position of a long group out once, against the CPU oracle: edges of their chunks,
 short and empty rows, one to four orders, counters of 32 and 16 bits, several windows of members, reference
-lists, and 4-grams that need more ids than a partition has."""
+lists, 4-grams that need more ids than a partition has; with and without dictionary sizes, and ROUGE-1 and -2."""
 import numpy as np
 import pytest
 import torch
@@ -8,6 +8,7 @@ import torch
 import oracle
 import paper_2510_05485_amd as tb
 import synth_inputs as syn
+from rouge_validity import check_rouge
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -33,19 +34,27 @@ def check(w, N, int64=False, lists=None, counts=None):
         extra, host = dict(ref_count=dev(counts)), dict(ref_count=counts)
     ref = oracle.bleu(w.cand, w.cand_len, rows, lens, max_n=N, smoothing="exp", threads=8, **host)
     cfg = tb.make_config(max_n=N, smoothing="exp", vocab_size=w.vocab, **extra)
-    for fn in (tb.tensorbleu_sentence, tb.tensorbleu_corpus):
+    for fn, sizes in ((tb.tensorbleu_sentence, False), (tb.tensorbleu_sentence, True), (tb.tensorbleu_corpus, False)):
         st = tb.Stats.allocate(w.B, N, DEV)
-        st.group_distinct = None
+        if not sizes:
+            st.group_distinct = None
         out = fn(cand, cl, refs, rl, cfg, stats=st).cpu().numpy().astype(np.float64)
         assert st.device_status.item() == 0
         np.testing.assert_array_equal(st.clipped.cpu().numpy(), ref.clipped)
         np.testing.assert_array_equal(st.total.cpu().numpy(), ref.total)
         np.testing.assert_array_equal(st.closest_ref_len.cpu().numpy(), ref.closest_ref_len)
         np.testing.assert_array_equal(st.corpus_stats.cpu().numpy(), ref.corpus_stats)
+        if sizes:
+            np.testing.assert_array_equal(st.group_distinct.cpu().numpy(), ref.group_distinct)
         if fn is tb.tensorbleu_corpus:
             assert abs(out[0] - ref.corpus_bleu) <= TOL
         else:
             assert np.abs(out - ref.bleu).max() <= TOL
+    for n in (1, 2):
+        want = oracle.rouge_n(w.cand, w.cand_len, rows, lens, n=n, **host)
+        prf, overlap, best = tb.tensorrouge_n(cand, cl, refs, rl, n=n, vocab_size=w.vocab,
+                                              want_overlap=True, want_best=True, **extra)
+        check_rouge(want, overlap.cpu().numpy(), best.cpu().numpy(), prf.cpu().numpy(), TOL)
 
 
 @pytest.mark.parametrize("B,R,L,Lr,vocab,N", [
@@ -53,6 +62,7 @@ def check(w, N, int64=False, lists=None, counts=None):
     (20, 1, 15360, 15361, 50257, 4),         # 2048 a chunk; rows that end with one and one behind it
     (20, 2, 10000, 10100, 3000, 4),          # counters of 16 bits, two words
     (4, 15, 4097, 4100, 900, 4),             # eight words
+    (4, 4, 12100, 9000, 900, 4),             # three, also with dictionary sizes and for ROUGE
     (2, 2, 70000, 66000, 1000, 4),           # of 32 bits, three words
     (2, 1, 70000, 66000, 2, 4),              # sixteen 4-grams: counts beyond 16 bits
     (4, 1, 14000, 14000, (1 << 20) - 2, 4),  # the largest vocabulary
@@ -121,10 +131,12 @@ def test_members_beyond_a_window():
 
 
 def test_lists_and_counts():
-    w = syn.random_small(961, B=10, R=6, vocab=5000, max_len=5000, min_len=4000)
-    counts = syn.ref_counts(961, w.B, w.R)
-    check(w, 4, counts=counts)
-    check(w, 4, lists=syn.pack_reference_lists(w.refs, w.ref_len, counts))
+    for R, L in ((6, 5000), (3, 12500)):
+        w = syn.random_small(961, B=10, R=R, vocab=5000, max_len=L, min_len=L - 1000)
+        counts = syn.ref_counts(961, w.B, w.R)
+        counts[0], counts[1] = R, 1
+        check(w, 4, counts=counts)
+        check(w, 4, lists=syn.pack_reference_lists(w.refs, w.ref_len, counts))
 
 
 def test_tokens_outside_the_vocabulary_are_reported():

@@ -31,7 +31,7 @@ def plans(tmp_path_factory):
     lib.runs_plan.restype = flag
     lib.runs_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, flag, ctypes.POINTER(i64)]
     lib.deal_plan.restype = flag
-    lib.deal_plan.argtypes = [i64, i64, i64, i32, i32, i32, ctypes.POINTER(i64)]
+    lib.deal_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, flag, ctypes.POINTER(i64)]
     lib.fused_plan.restype = lib.fused_path.restype = flag
     lib.fused_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, ctypes.POINTER(i64)]
     lib.fused_path.argtypes = [i64, i64, i32, i32]
@@ -71,29 +71,31 @@ def test_sorted_runs_leave_their_tables_room(plans):
 def test_dealt_partitions_leave_their_tables_room(plans):
     # tables of tokens and of pairs: as the sorted runs'; ids never fill their table (a search ends at a free
     # slot); two workgroups on a unit; runs' places fit their part of the workspace
-    out = (ctypes.c_int64 * 13)()
+    out = (ctypes.c_int64 * 14)()
     rng, shapes, mean, tables, slots = random.Random(31), 0, [], [], []
     for _ in range(60000):
         R, N = rng.choice((1, 1, 2, 3, 5, 8, 16, 40, 61)), rng.randint(1, 4)
+        rouge, sizes = rng.choice(((False, False), (False, True), (True, False)))
         cs = int(2 ** (20.5 * rng.random()))
         rs = max(1, min(int(2097152 / R), int(cs * 4 ** rng.uniform(-3, 1.5))))
         B, vocab = int(2 ** (8 * rng.random())), rng.choice((2, 1000, 65536, (1 << 20) - 2))
         cap = cs + R * rs
-        if not 12288 < cap <= 2097152 or not plans.deal_plan(B, cs, rs, R, N, vocab, out):
+        if not 12288 < cap <= 2097152 or not plans.deal_plan(B, cs, rs, R, N, vocab, rouge, sizes, out):
             continue
         shapes += 1
-        kinds = out[0]
-        assert kinds == min(N, 3) and out[10] == sum(out[1:1 + kinds]) <= 2048
-        assert out[12] <= LDS // 2 and out[11] <= 1024 and out[11] * out[10] <= kinds * cap
+        first, kinds = out[13], out[0]
+        assert kinds == min(N, 3) and first == (N - 1 if rouge else 0) and (not rouge or N <= 2)
+        assert out[10] == sum(out[1 + first:1 + kinds]) <= 2048
+        assert out[12] <= LDS // 2 and out[11] <= 1024 and out[11] * out[10] <= (kinds - first) * cap
         assert out[9] % 64 == 0 and 4 * out[7] <= 3 * out[6] and out[7] <= out[8] and out[7] % 8 == 0
         assert out[8] <= 1 << 20             # (id, order and at least eleven bits of the hash in a word)
-        for kind in range(min(kinds, 2)):
-            mean.append(cs)
+        for kind in range(first, min(kinds, 2)):
+            mean.append(cap if sizes else cs)
             tables.append(out[1 + kind])
             slots.append(out[4 + kind])
     assert shapes > 10000
-    assert not plans.deal_plan(4, 20000, 20000, 1, 4, (1 << 20) - 1, out)
-    assert not plans.deal_plan(4, 20000, 20000, 1, 5, 1000, out)
+    assert not plans.deal_plan(4, 20000, 20000, 1, 4, (1 << 20) - 1, False, False, out)
+    assert not plans.deal_plan(4, 20000, 20000, 1, 5, 1000, False, False, out)
     chance = stats.binom.logsf(slots, mean, 1.0 / np.array(tables, dtype=np.float64))
     assert chance.max() <= -40.0
 
