@@ -415,12 +415,12 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
   if (takes_runs(c, cfg, false, group_distinct, &runs)) {
     const RunsBuffers buffers = runs_buffers(c.pb, c.ws, c.plans.part);
     DealPlan deal;
-    rc = hip_rc(takes_deal(c.pb, false, group_distinct, &deal)
-                    ? launch_deal(c.pb, deal, buffers, c.st, nullptr, c.stream)
-                    : launch_runs(c.pb, runs, buffers, c.st, group_distinct, nullptr, c.stream));
-    if (rc != TB_OK) return rc;
-    return hip_rc(launch_finalize(c.pb, c.st, c.sp, !corpus, corpus || c.want_corpus_stats, corpus,
-                                  out_bleu, c.stream, c.ws.overflow));
+    const bool dealt = takes_deal(c.pb, false, group_distinct, &deal);  // (scores the sentences, too)
+    rc = hip_rc(dealt ? launch_deal(c.pb, deal, buffers, c.st, c.sp, corpus ? nullptr : out_bleu, nullptr, c.stream)
+                      : launch_runs(c.pb, runs, buffers, c.st, group_distinct, nullptr, c.stream));
+    if (rc != TB_OK || (dealt && !corpus && !c.want_corpus_stats)) return rc;
+    return hip_rc(launch_finalize(c.pb, c.st, c.sp, !corpus && !dealt, corpus || c.want_corpus_stats, corpus,
+                                  out_bleu, c.stream, c.ws.overflow, dealt && !corpus));
   }
   if (!c.plans.use_part && (rc = hip_rc(launch_pack(c.pb, c.ws, c.stream))) != TB_OK) return rc;
   if ((rc = hip_rc(run_dictionary(c, true, true))) != TB_OK) return rc;
@@ -511,7 +511,7 @@ int tensorrouge_n(const void* cand, int64_t cand_stride, const int32_t* cand_len
     const RunsBuffers buffers = runs_buffers(c.pb, c.ws, c.plans.part);
     DealPlan deal;
     rc = hip_rc(takes_deal(c.pb, true, false, &deal)
-                    ? launch_deal(c.pb, deal, buffers, c.st, ov, c.stream)
+                    ? launch_deal(c.pb, deal, buffers, c.st, c.sp, nullptr, ov, c.stream)
                     : launch_runs(c.pb, runs, buffers, c.st, false, ov, c.stream));
     if (rc != TB_OK) return rc;
     return hip_rc(launch_rouge_finalize(c.pb, c.sp, ov, ro, c.stream));

@@ -26,9 +26,10 @@
 // unit, and the 19 bytes a position that it writes.  Tallying: issue, 560 vector and 450 scalar instructions of a
 // wavefront's 9 us (a third of them exec masks of the probing loops), and the longest workgroups.
 //
-// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 32.9 -> 27.9 (dealing 8,
-// tallying 15); 11 groups of two times 90 000 96.7 -> 62.8; 50 of two times 20 000 80.4 -> 61.5; 5 of 17 327 tokens
-// with three references 35.1 -> 29.2; two of 174 762 with two 65.1 -> 43.
+// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 33 -> 25; 11 groups of two
+// times 90 000 96.7 -> 59; 50 of two times 20 000 80.4 -> 57; 16 of two times 12 500 32 -> 22.6; two of 174 762
+// with two references 65 -> 40.  Of these the scores inside the counting kernel, instead of in one of their own, and
+// arguments read where they are used (113 scalar registers were moved to lanes and back, now 33) 2 to 4 us each.
 //
 // Keys are exact.  What the tables hold is bounded by the hashes whatever the tokens are, except for 4-grams:
 // where many different ones start with the same three tokens and ids run out, the partition counts orders 3 and
@@ -38,6 +39,7 @@
 #include <type_traits>
 
 #include "tb_kernels.h"
+#include "tb_score.h"
 
 namespace tb {
 
@@ -61,6 +63,10 @@ struct DealArgs {
   uint32_t* run_at;  // [B][chunks][parts of all kinds]: first of the run within its chunk | size << 16
   int32_t* overflow; // [B]
   int32_t* rouge_overlap;  // [B, R] or null
+  unsigned long long* arrived;  // [B, N]: sum of the partitions' matches | partitions << 40 | spoilt ones << 52
+  int32_t* complete;  // [B]: orders all of whose partitions have arrived
+  ScoreParams sp;
+  void* out;          // per-sentence scores, or null
   int first_kind, kinds, all_parts;  // kinds first_kind .. kinds - 1
   int parts[kKinds], parts_before[kKinds];  // of each kind; of the kinds before it
   int log2_chunk;
@@ -169,7 +175,8 @@ __global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
       a.st.clipped[int64_t(g) * pb.N + tid] = 0;
       a.st.distinct[int64_t(g) * pb.N + tid] = 0;
     }
-    if (tid == 0) a.overflow[g] = 0;
+    if (tid == 0) a.overflow[g] = a.complete[g] = 0;
+    if (tid < pb.N) a.arrived[int64_t(g) * pb.N + tid] = 0;
     if (a.rouge_overlap && tid < pb.R) a.rouge_overlap[int64_t(g) * pb.R + tid] = 0;
   }
   if (bad && pb.status) atomicOr(pb.status, TB_DEV_TOKEN_RANGE);
@@ -728,27 +735,55 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     }
   }
   __syncthreads();
-  if (tid == 0 && *lds<uint32_t>(lost_at)) {
+  const uint32_t lost = *lds<uint32_t>(lost_at);  // uniform
+  if (tid == 0 && lost) {
     if (pb.status) atomicOr(pb.status, TB_DEV_TABLE_OVERFLOW);
     a.overflow[g] = 1;
   }
-  const int n0 = KIND + tid;  // order n0 + 1
   if (rouge) {
     const uint32_t at = ONE ? lost_at + 16u + 4u * uint32_t(KIND) : overlaps_at + 4u * uint32_t(tid + 1);
     if (tid < pb.R && *lds<uint32_t>(at)) atomicAdd(&a.rouge_overlap[int64_t(g) * pb.R + tid], int(*lds<uint32_t>(at)));
-  } else if (tid < (KIND == 2 ? 2 : 1) && n0 < N) {
-    const int64_t stat = int64_t(g) * N + n0;
-    const uint32_t sum = *lds<uint32_t>(lost_at + 16u + 4u * uint32_t(n0));
-    if (sum) atomicAdd(&a.st.clipped[stat], int(sum));
+    return;
+  }
+  if (wave != 0) return;
+  // The last partition of an order to arrive writes the order's statistics, and the last of these scores the
+  // sentence: one round trip to memory for a workgroup, three for the last one, where a kernel of its own took
+  // 3.5 us.  Everything that passes between workgroups goes through atomics whose answers are awaited.
+  const int n0 = KIND + lane;  // order n0 + 1
+  const int64_t stat = int64_t(g) * N + n0;
+  bool last = false;
+  if (lane < (KIND == 2 ? 2 : 1) && n0 < N) {
     if (ALL) atomicAdd(&a.st.distinct[stat], int(*lds<uint32_t>(lost_at + 32u + 4u * uint32_t(n0))));
-    if (p == 0) {
+    const unsigned long long add = *lds<uint32_t>(lost_at + 16u + 4u * uint32_t(n0)) | 1ull << 40 | (lost ? 1ull << 52 : 0ull);
+    const unsigned long long all = add + __hip_atomic_fetch_add(&a.arrived[stat], add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((all >> 40 & 0xFFFu) == parts) {
       const int len = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, nullptr);
+      a.st.clipped[stat] = int32_t(all & 0xFFFFFFFFull);
       a.st.total[stat] = max(len - n0, 0);
+      if (a.out)
+        last = __hip_atomic_fetch_add(&a.complete[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == N - 1;
     }
+  }
+  if (!__builtin_amdgcn_ballot_w64(last)) return;  // uniform
+  unsigned long long all = 0;
+  if (lane < N) all = __hip_atomic_load(&a.arrived[int64_t(g) * N + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const int c = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, pb.status);
+  const RefRows rows = ref_rows(pb, g, true);
+  const int r = closest_ref_len(c, pb.ref_len + rows.row0, rows.used, pb.ref_stride, pb.status);
+  const float brevity = expf(1.0f - float(r) / float(c));
+  const float score = bleu_from_stats_wave<int>(int(all & 0xFFFFFFFFull), max(c - lane, 0), c, r, brevity, lane_weight(a.sp), a.sp);
+  const bool spoilt = __builtin_amdgcn_ballot_w64(all >> 52 != 0) != 0;
+  if (lane == 0) {
+    a.st.closest[g] = r;
+    store_score(a.out, g, spoilt ? __int_as_float(0x7FC00000) : score, a.sp.out_bf16);
   }
 }
 template <Counters COUNTERS>
-__global__ __launch_bounds__(kTallyThreads, 8) void tally_kernel(DealArgs a) {
+__global__ __launch_bounds__(kTallyThreads, 8) void tally_kernel(DealArgs by_value) {
+  // (read through the argument segment where its fields are used: loads of a by-value parameter all stand at the
+  // entry and occupy scalar registers throughout)
+  typedef const char __attribute__((address_space(4)))* Segment;
+  const DealArgs& a = *(const DealArgs*)(Segment)__builtin_amdgcn_kernarg_segment_ptr();
   int p = blockIdx.x;  // (the kind with the most work first)
   if (a.kinds > 2) {
     if (p < a.parts[2]) return tally_kind<2, COUNTERS>(a, p);
@@ -882,7 +917,7 @@ bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
 }
 
 hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffers& buffers, const StatPtrs& st,
-                       int32_t* rouge_overlap, hipStream_t s) {
+                       const ScoreParams& sp, void* out_bleu_or_null, int32_t* rouge_overlap, hipStream_t s) {
   DealArgs a;
   a.pb = pb;
   a.st = st;
@@ -897,6 +932,10 @@ hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffer
   a.run_at = buffers.places;
   a.overflow = buffers.overflow;
   a.rouge_overlap = rouge_overlap;
+  a.arrived = reinterpret_cast<unsigned long long*>(buffers.times);  // (N * n words there)
+  a.complete = reinterpret_cast<int32_t*>(a.arrived + size_t(pb.B) * pb.N);
+  a.sp = sp;
+  a.out = out_bleu_or_null;
   a.first_kind = plan.first_kind;
   a.kinds = plan.kinds;
   a.all_parts = plan.all_parts;

@@ -177,7 +177,8 @@ struct DealPlan {
 bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, bool rouge,
                bool group_distinct, DealPlan* plan);
 hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffers& buffers,
-                       const StatPtrs& st, int32_t* rouge_overlap, hipStream_t s);
+                       const StatPtrs& st, const ScoreParams& sp, void* out_bleu_or_null,
+                       int32_t* rouge_overlap, hipStream_t s);
 
 bool plan_big(int64_t group_cap, int N, BigPlan* plan);
 hipError_t launch_big_dictionary(const Problem& pb, const GlobalWs& ws, const BigPlan& plan,
