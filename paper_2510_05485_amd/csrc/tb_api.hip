@@ -324,23 +324,28 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
                    plan);
 }
 
-// Whether a call that the sorted runs take goes to the kernels that deal every position out once.  BLEU: of 590
-// drawn shapes of 12 000 to 2 000 000 positions with 1 to 16 references, one to four orders, the ones that do take
-// 0.84 of the sorted runs' time on average.  Below 98 304 positions in all both are a chain of latencies, and the
-// sorted runs' is the shorter one (three groups of two times 8000 17.8 us, 19.5 here; three of two times 19 000 17.9
-// and 16.2); with three references or more whose counters need 32 bits, tables take so much LDS that partitions
-// become too small (two groups of 131 072 with three references 64.5, 88.7).  With dictionary sizes, where the tables
-// hold the references' n-grams, too, 0.88 of 35 shapes of up to four references (30 groups of two times 21 000 81.9,
-// 64.1), 1.1 with eight (4 of 37 199 81.0, 100.7).  ROUGE-N has one kind of members, whose order the sorted runs deal
-// out by themselves as well, in longer chunks: with few positions a candidate, many of them with more than
-// 1 000 000 for ROUGE-2, or many references these are faster (two groups of two times 138 993 25.2, 19.1; 21 of two
-// times 40 393 29.7, 34.4; 84 of 7239 23.4, 30.9; 7 of 15 076 with 16 references 48.2, 59.8).
+// Whether a call that the sorted runs take goes to the kernels that deal every position out once.  Lines by 600 drawn
+// shapes of 12 000 to 2 000 000 positions with 1 to 16 references, one to four orders.  BLEU: 0.82 of the sorted runs'
+// time on average of the shapes drawn with one to three references.  Below 65 536 positions in all both are a chain of
+// latencies, and the sorted runs' is the shorter one (one text of 13 121 and 10 863 tokens 15.3 us, 21.1 here; two of
+// two times 20 000 20.6, 19.2); a partition has all references of its share of the candidate, so that more than
+// four need more positions, and more than eight leave the partitions too few (three groups of 5700 with eight of 5123
+// 23.7, 31.5; one of 4728 with 16 23.3, 36.9; one of 51 059 with eight 34.1, 29.2); with three references or more
+// whose counters need 32 bits, tables take too much LDS (two groups of 131 072 with three 58.2, 124.6).  Two orders
+// have no third that goes along with a fourth: with more than one reference and 1 000 000 positions the sorted runs
+// are faster (19 groups of 20 809 with two of 21 000 34.9, 37.3; 13 of two times 63 000 with one 48.1, 41.7).  With
+// dictionary sizes, where the tables hold the references' n-grams, too, 0.88 of 35 shapes of up to four references (30
+// groups of two times 21 000 81.9, 64.1), 1.1 with eight (4 of 37 199 81.0, 100.7).  ROUGE-N has one kind of members,
+// whose order the sorted runs deal out by themselves as well, in longer chunks: with few positions a candidate, many
+// of them with more than 1 000 000 for ROUGE-2, or many references these are faster (two groups of two times 138 993
+// 25.2, 19.1; 21 of two times 40 393 29.7, 34.4; 84 of 7239 23.4, 30.9).
 bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* plan) {
   const int64_t positions = pb.B * pb.group_cap;
-  if (positions < 98304) return false;
+  if (pb.R > 8 || positions < (pb.R <= 4 ? 65536 : 262144)) return false;
+  if (pb.N <= 2 && pb.R > 1 && positions > 1000000) return false;
   if (pb.R > 2 && (pb.cand_stride > 65535 || pb.ref_stride > 65535)) return false;
-  if (group_distinct && pb.R > 4) return false;
-  if (rouge && (pb.cand_stride < 12000 || pb.R > 8 || (pb.N > 1 && positions > 1000000))) return false;
+  if (group_distinct && (pb.R > 4 || positions < 98304)) return false;
+  if (rouge && (pb.cand_stride < 12000 || positions < 98304 || (pb.N > 1 && positions > 1000000))) return false;
   return plan_deal(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.vocab, rouge, group_distinct, plan);
 }
 
@@ -359,9 +364,9 @@ bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* pl
 // 12 400 to 24 500 positions with 1 to 62 references and 4 to 130 groups, one to six orders: on average
 // 0.5 % (ROUGE 0.2 %) behind the better kernel, more than a tenth behind in 2.3 % (0.5 %) of them.  (The
 // lines fitted before the kernel found n-grams without looking them up: 1.0 % and 17 %.)
-// Against the kernels that deal every position out once, BLEU's line is another: linear fit to 480 pairs of the
-// same shapes, 0.7 % behind the better kernel on average, more than a tenth behind in 2.5 % (the other line: 1.9
-// and 6.2); 6 groups of 6235 with three references of 5797 22 us there, 43.9 here; 35 of two times 7000 24.0, 23.2.
+// Against the kernels that deal every position out once, BLEU's line is another: linear fit to 275 pairs of the
+// same shapes, 0.5 % behind the better kernel on average, more than a tenth behind in 1.5 %; 6 groups of 6235 with
+// three references of 5797 20 us there, 43.9 here; 60 of two times 8192 38, 27.
 // Against the partitioned kernels, which take what the sorted runs do not: 32.
 bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
                  FusedPlan* plan) {
@@ -375,7 +380,7 @@ bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats,
     if (takes_runs(c, cfg, rouge, false, &runs)) {
       const int64_t refs = pb.R * pb.ref_stride;
       if (!rouge && takes_deal(pb, false, false, &deal))
-        few = pb.cand_stride / 600 + refs / 1000 - pb.R + 4 * pb.N - 18;
+        few = pb.cand_stride / 300 + refs / 700 + 6 * pb.N - 36;
       else
         few = rouge ? pb.N * pb.cand_stride / 260 + pb.N * refs / 1400 - 5 * pb.R / 2 - 33
                     : pb.cand_stride / 200 + refs / 700 - pb.R / 2 + 5 * pb.N - 33;

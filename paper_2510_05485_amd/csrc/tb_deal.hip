@@ -835,7 +835,10 @@ hipError_t launch_items(const DealArgs& a, const DealPlan& plan, hipStream_t s) 
 //     22.7; one text of 30 000 480 16.5, 1280 18.8, 160 20.
 //   * A share of the candidate brings one of each reference with it.  9 groups of 25 236 with three references of
 //     27 025: 480 4-grams 42.8, 1280 49.5, 320 50.0.
-//   * A 4-gram costs 1.6 times a pair, and a token, of which most are merged, half as much.
+//   * A 4-gram costs 1.6 times a pair, and a token, of which most are merged, half as much.  With more references,
+//     whose counters need more LDS, the table of tokens is the first that does not fit: smaller shares of them
+//     leave the others larger ones (19 groups of 20 809 with two references of 20 000 54.3 -> 51.4, two orders 38.8 ->
+//     34.2).
 //   * Tables of tokens and pairs at most half full: a wavefront probes as long as its unluckiest lane.  With up to
 //     two thirds, 22 groups of two times 17 000, two orders, 28.4 instead of 24.0, 4 of two times 50 000 29.3 instead
 //     of 26.9.
@@ -866,7 +869,7 @@ bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   // shares: positions whose n-grams are entered, as a partition of each kind may expect them
   const int64_t entries = p.all ? cap : cand_stride;
   auto fits = [&](int scale) {
-    int64_t share[kKinds] = {256 * scale, 128 * scale, 80 * scale};
+    int64_t share[kKinds] = {(R == 1 ? 256 : 192) * scale, 128 * scale, 80 * scale};
     int log2_slots[kKinds];
     p.all_parts = 0;
     for (int kind = 0; kind < kKinds; ++kind) {
