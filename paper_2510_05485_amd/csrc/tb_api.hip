@@ -324,25 +324,22 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
                    plan);
 }
 
-// Whether a call that the sorted runs take goes to the kernels that deal every position out once.  Lines by 600 drawn
-// shapes of 12 000 to 2 000 000 positions with 1 to 16 references, one to four orders.  BLEU: 0.82 of the sorted runs'
-// time on average of the shapes drawn with one to three references.  Below 65 536 positions in all both are a chain of
-// latencies, and the sorted runs' is the shorter one (one text of 13 121 and 10 863 tokens 15.3 us, 21.1 here; two of
-// two times 20 000 20.6, 19.2); a partition has all references of its share of the candidate, so that more than
-// four need more positions, and more than eight leave the partitions too few (three groups of 5700 with eight of 5123
-// 23.7, 31.5; one of 4728 with 16 23.3, 36.9; one of 51 059 with eight 34.1, 29.2); with three references or more
-// whose counters need 32 bits, tables take too much LDS (two groups of 131 072 with three 58.2, 124.6).  Two orders
-// have no third that goes along with a fourth: with more than one reference and 1 000 000 positions the sorted runs
-// are faster (19 groups of 20 809 with two of 21 000 34.9, 37.3; 13 of two times 63 000 with one 48.1, 41.7).  With
-// dictionary sizes, where the tables hold the references' n-grams, too, 0.88 of 35 shapes of up to four references (30
-// groups of two times 21 000 81.9, 64.1), 1.1 with eight (4 of 37 199 81.0, 100.7).  ROUGE-N has one kind of members,
-// whose order the sorted runs deal out by themselves as well, in longer chunks: with few positions a candidate, many
-// of them with more than 1 000 000 for ROUGE-2, or many references these are faster (two groups of two times 138 993
-// 25.2, 19.1; 21 of two times 40 393 29.7, 34.4; 84 of 7239 23.4, 30.9).
+// Whether a call that the sorted runs take goes to the kernels that deal every position out once (us, sorted runs /
+// dealt).  BLEU, 640 drawn shapes of 12 000 to 2 000 000 positions, one to 16 references, one to four orders: 0.835 of
+// the sorted runs' time on average over the 518 that go there, 1.02 over the 122 that do not.  Of few positions both are
+// a chain of latencies: below 65 536 0.98, at worst three of 7477 with one reference of 8070 15.9 / 18.8.  A partition
+// has all references of its share of the candidate, which many of them leave small: eight below 262 144 positions 1.08
+// (two of 4165 with eight of 3344 20.5 / 27.0), above 0.98; sixteen 1.03 (eight of 1289 with 16 of 1449 28.5 / 42.1).
+// Three references or more whose counters need 32 bits: 1.03, from four of 71 385 with three of 66 300 65.0 / 48.0 to
+// two of 131 072 with three of 150 200 63.9 / 123.3.  With dictionary sizes, where the tables hold the references'
+// n-grams, too: 0.88 over 31 shapes of up to four references (15 of 7157 with four of 7789 83.4 / 57.3), 1.06 over 17
+// of eight and 16 (four of 57 060 with eight of 50 911 99.3 / 134.9).  ROUGE-N has one kind of members, whose order the
+// sorted runs deal out by themselves as well, in longer chunks: rows below 12 000 tokens, fewer
+// than 98 304 positions or, for ROUGE-2, more than 1 000 000 stay with them (120 of 2216 with eight of 2379 50.7 /
+// 76.1; one of 174 600 with one of 193 745, ROUGE-1, 23.7 / 15.8).
 bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* plan) {
   const int64_t positions = pb.B * pb.group_cap;
   if (pb.R > 8 || positions < (pb.R <= 4 ? 65536 : 262144)) return false;
-  if (pb.N <= 2 && pb.R > 1 && positions > 1000000) return false;
   if (pb.R > 2 && (pb.cand_stride > 65535 || pb.ref_stride > 65535)) return false;
   if (group_distinct && (pb.R > 4 || positions < 98304)) return false;
   if (rouge && (pb.cand_stride < 12000 || positions < 98304 || (pb.N > 1 && positions > 1000000))) return false;
@@ -364,9 +361,9 @@ bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* pl
 // 12 400 to 24 500 positions with 1 to 62 references and 4 to 130 groups, one to six orders: on average
 // 0.5 % (ROUGE 0.2 %) behind the better kernel, more than a tenth behind in 2.3 % (0.5 %) of them.  (The
 // lines fitted before the kernel found n-grams without looking them up: 1.0 % and 17 %.)
-// Against the kernels that deal every position out once, BLEU's line is another: linear fit to 275 pairs of the
-// same shapes, 0.5 % behind the better kernel on average, more than a tenth behind in 1.5 %; 6 groups of 6235 with
-// three references of 5797 20 us there, 43.9 here; 60 of two times 8192 38, 27.
+// Against the kernels that deal every position out once, BLEU's line is another (dealt / fused): on average 0.6 %
+// behind the better kernel over 202 shapes of the same ranges, more than a tenth behind in five; five groups of 5804
+// with three references of 6020 18.7 / 45.4, 113 of 2541 with eight of 2673 112.0 / 34.4.
 // Against the partitioned kernels, which take what the sorted runs do not: 32.
 bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
                  FusedPlan* plan) {
