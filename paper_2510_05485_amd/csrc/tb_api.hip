@@ -325,24 +325,28 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
 }
 
 // Whether a call that the sorted runs take goes to the kernels that deal every position out once (us, sorted runs /
-// dealt).  BLEU, 640 drawn shapes of 12 000 to 2 000 000 positions, one to 16 references, one to four orders: 0.835 of
-// the sorted runs' time on average over the 518 that go there, 1.02 over the 122 that do not.  Of few positions both are
-// a chain of latencies: below 65 536 0.98, at worst three of 7477 with one reference of 8070 15.9 / 18.8.  A partition
-// has all references of its share of the candidate, which many of them leave small: eight below 262 144 positions 1.08
-// (two of 4165 with eight of 3344 20.5 / 27.0), above 0.98; sixteen 1.03 (eight of 1289 with 16 of 1449 28.5 / 42.1).
+// dealt).  BLEU, 640 drawn shapes of 12 000 to 2 000 000 positions, one to 16 references, one to four orders: 0.83 of
+// the sorted runs' time on average over the 505 that go there, 1.026 over the 135 that do not.  Of few
+// positions both are a chain of latencies: below 65 536 0.98, at worst three of 7477 with one reference of 8070 15.9 /
+// 18.8.  A partition has all references of its share of the candidate, which many of them leave small: eight below
+// 262 144 positions 1.08 (two of 4165 with eight of 3344 20.5 / 27.0), above 0.98, but with fewer than four orders 1.07
+// over 19 shapes of more than 1 000 000 (13 of 9513 with eight of 9856, three orders, 46.8 / 56.4) and 0.99 over 16 of
+// fewer; sixteen 1.03 (eight of 1289 with 16 of 1449 28.5 / 42.1).
 // Three references or more whose counters need 32 bits: 1.03, from four of 71 385 with three of 66 300 65.0 / 48.0 to
 // two of 131 072 with three of 150 200 63.9 / 123.3.  With dictionary sizes, where the tables hold the references'
 // n-grams, too: 0.88 over 31 shapes of up to four references (15 of 7157 with four of 7789 83.4 / 57.3), 1.06 over 17
 // of eight and 16 (four of 57 060 with eight of 50 911 99.3 / 134.9).  ROUGE-N has one kind of members, whose order the
-// sorted runs deal out by themselves as well, in longer chunks: rows below 12 000 tokens, fewer
-// than 98 304 positions or, for ROUGE-2, more than 1 000 000 stay with them (120 of 2216 with eight of 2379 50.7 /
-// 76.1; one of 174 600 with one of 193 745, ROUGE-1, 23.7 / 15.8).
+// sorted runs deal out by themselves as well, in longer chunks: ROUGE-1 0.89 over 246 shapes of up to eight
+// references (one of 235 166 with one of 191 043 25.7 / 16.7; 97 of 6303 with one of 7834 21.7 / 25.4), ROUGE-2 0.91
+// over 67 of rows of 12 000 and up to four (two of 128 592 with one of 121 506 28.3 / 20.7), 1.02 over the 150 others
+// (120 of 2216 with eight of 2379 50.7 / 76.1).
 bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* plan) {
   const int64_t positions = pb.B * pb.group_cap;
   if (pb.R > 8 || positions < (pb.R <= 4 ? 65536 : 262144)) return false;
   if (pb.R > 2 && (pb.cand_stride > 65535 || pb.ref_stride > 65535)) return false;
   if (group_distinct && (pb.R > 4 || positions < 98304)) return false;
-  if (rouge && (pb.cand_stride < 12000 || positions < 98304 || (pb.N > 1 && positions > 1000000))) return false;
+  if (rouge && pb.N > 1 && (pb.cand_stride < 12000 || pb.R > 4)) return false;
+  if (!rouge && pb.N < 4 && pb.R > 4) return false;
   return plan_deal(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.vocab, rouge, group_distinct, plan);
 }
 
