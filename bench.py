@@ -43,6 +43,7 @@ def algorithmic_bytes(w, lay, N, token_bytes=4):
         "count_clip": 4 * sum(G) + stats,
         "finalize": stats + 4 * w.B * (1 + w.R) + 4 * w.B,
         "fused": 4 * T + 4 * w.B + stats,
+        "dealt": 4 * T + 4 * w.B + stats,
         "sorted runs": 4 * T + 4 * w.B + stats,
     }
 
@@ -68,9 +69,12 @@ def kernel_names(fn, torch):
 
 
 def route_of(names, layout_path):
-    """Which kernels served a call: "fused", "sorted runs" or "global" (the staged kernels)."""
+    """Which kernels served a call: "fused", "dealt" (positions dealt out once), "sorted runs" or "global" (the
+    staged kernels)."""
     if names and any("fused_kernel" in n for n in names):
         return "fused"
+    if names and any("tally_kernel" in n for n in names):
+        return "dealt"
     if names and any("runs_count_kernel" in n for n in names):
         return "sorted runs"
     return "global" if names else {1: "fused", 2: "global"}[layout_path]

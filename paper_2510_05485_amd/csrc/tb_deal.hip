@@ -26,7 +26,7 @@
 // unit, and the 19 bytes a position that it writes.  Tallying: issue, 560 vector and 450 scalar instructions of a
 // wavefront's 9 us (a third of them exec masks of the probing loops), and the longest workgroups.
 //
-// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 33 -> 25; 11 groups of two
+// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 33.4 -> 25.8; 11 groups of two
 // times 90 000 96.7 -> 59; 50 of two times 20 000 80.4 -> 57; 16 of two times 12 500 32 -> 22.6; two of 174 762
 // with two references 65 -> 40.  Of these the scores inside the counting kernel, instead of in one of their own, and
 // arguments read where they are used (113 scalar registers were moved to lanes and back, now 33) 2 to 4 us each.
@@ -837,8 +837,8 @@ hipError_t launch_items(const DealArgs& a, const DealPlan& plan, hipStream_t s) 
 //     27 025: 480 4-grams 42.8, 1280 49.5, 320 50.0.
 //   * A 4-gram costs 1.6 times a pair, and a token, of which most are merged, half as much.  With more references,
 //     whose counters need more LDS, the table of tokens is the first that does not fit: smaller shares of them
-//     leave the others larger ones (19 groups of 20 809 with two references of 20 000 54.3 -> 51.4, two orders 38.8 ->
-//     34.2).
+//     leave the others larger ones (19 groups of 20 809 with two references of 20 000 54.4 -> 51.4, two orders 38.8 ->
+//     34.0).
 //   * Tables of tokens and pairs at most half full: a wavefront probes as long as its unluckiest lane.  With up to
 //     two thirds, 22 groups of two times 17 000, two orders, 28.4 instead of 24.0, 4 of two times 50 000 29.3 instead
 //     of 26.9.

@@ -1,4 +1,6 @@
-// Whole calls on groups beyond one LDS table (12 289 .. 2 097 152 n-gram slots), in two kernels:
+// Whole calls on groups beyond one LDS table (12 289 .. 2 097 152 n-gram slots) that the kernels which deal every
+// position out once (tb_deal.hip) do not take or are slower on (more than four orders or 20-bit tokens, few positions,
+// many references: takes_deal in tb_api.hip), in two kernels:
 //
 //   runs_sort_kernel   one workgroup per (group, order, chunk of 1024..4096 positions of one
 //                      sequence): builds the chunk's n-grams from the token row (Section 3.1),
@@ -28,7 +30,7 @@
 //     part is a table of its own, of 64 slots at the least: the plan has to leave it room for more than
 //     its share (has_room).
 //
-// Measured (us a call, before on the partitioned kernels -> now): one text of 262 144 tokens with its
+// Measured (us a call, before on the partitioned kernels -> here, whichever kernel takes them now): one text of 262 144 tokens with its
 // reference 110.7 -> 33 (sorting 12.5, counting 17.6, score 3); 16 groups of two times 8192 36 -> 22; 100 of
 // two times 20 000 276 -> 137 (sorting 55, counting 80); 300 of nine times 4096 1111 -> 354; 20 of nine
 // times 4096 with 18-bit tokens 147 -> 48; ROUGE-2 of one text of 100 000 80 -> 20.  The number of

@@ -40,3 +40,9 @@ def test_route_names():
     assert bench.route_of(["tb::runs_sort_kernel<4>", "tb::runs_count_kernel<4096>"], 2) == "sorted runs"
     assert bench.route_of(["tb::pack_kernel"], 1) == "global"
     assert bench.route_of(None, 1) == "fused" and bench.route_of(None, 2) == "global"
+
+
+def test_route_of_dealt_positions():
+    names = ["tb::deal_kernel<2>", "tb::tally_kernel<(tb::Counters)0>"]
+    assert bench.route_of(names, 2) == "dealt"
+    assert bench.route_of(["tb::deal_kernel<2>"], 2) == "global"      # (half of a call)
