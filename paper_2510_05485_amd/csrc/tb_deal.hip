@@ -842,6 +842,11 @@ hipError_t launch_items(const DealArgs& a, const DealPlan& plan, hipStream_t s) 
 //   * Tables of tokens and pairs at most half full: a wavefront probes as long as its unluckiest lane.  With up to
 //     two thirds, 22 groups of two times 17 000, two orders, 28.4 instead of 24.0, 4 of two times 50 000 29.3 instead
 //     of 26.9.
+//   * Where the partitions do not fit one round of 512 workgroups at that, shares grow as far as the LDS of two of them a
+//     unit lets them, up to 48 / (1 + R) steps.  It was 32, which left a third of the LDS unused with three references:
+//     of 89 shapes whose shares that changes 0.95 of the time on average (three references 0.93, two 0.99, the worst of
+//     all 1.08; 41 groups of 10 622 with three references of 12 054, two orders, 49.6 -> 45.0, 27 of 7687 with three
+//     of 8643 46.0 -> 38.5, 33 of 10 083 with one of 9617 35.6 -> 29.8).
 bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, bool rouge,
                bool group_distinct, DealPlan* plan) {
   DealPlan& p = *plan;
@@ -908,7 +913,7 @@ bool plan_deal(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
     p.lds_bytes = p.off_scratch + 4 * 17;
     return p.all_parts <= kMaxParts && chunks * p.all_parts <= (p.kinds - p.first_kind) * cap;
   };
-  const int most = 32 / (1 + R) < 2 ? 2 : 32 / (1 + R), least = (12 + R) / (1 + R) < 2 ? 2 : (12 + R) / (1 + R);
+  const int most = 48 / (1 + R) < 2 ? 2 : 48 / (1 + R), least = (12 + R) / (1 + R) < 2 ? 2 : (12 + R) / (1 + R);
   int scale = 0;
   for (int s = 1; s <= most; ++s) {
     if (!fits(s)) continue;
