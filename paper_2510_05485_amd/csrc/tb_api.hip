@@ -326,20 +326,20 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
 
 // Whether a call that the sorted runs take goes to the kernels that deal every position out once (us, sorted runs /
 // dealt).  BLEU, 640 drawn shapes of 12 000 to 2 000 000 positions, one to 16 references, one to four orders: 0.83 of
-// the sorted runs' time on average over the 505 that go there, 1.026 over the 135 that do not.  Of few
-// positions both are a chain of latencies: below 65 536 0.98, at worst three of 7477 with one reference of 8070 15.9 /
-// 18.8.  A partition has all references of its share of the candidate, which many of them leave small: eight below
-// 262 144 positions 1.08 (two of 4165 with eight of 3344 20.5 / 27.0), above 0.98, but with fewer than four orders 1.07
-// over 19 shapes of more than 1 000 000 (13 of 9513 with eight of 9856, three orders, 46.8 / 56.4) and 0.99 over 16 of
-// fewer; sixteen 1.03 (eight of 1289 with 16 of 1449 28.5 / 42.1).
-// Three references or more whose counters need 32 bits: 1.03, from four of 71 385 with three of 66 300 65.0 / 48.0 to
-// two of 131 072 with three of 150 200 63.9 / 123.3.  With dictionary sizes, where the tables hold the references'
-// n-grams, too: 0.88 over 31 shapes of up to four references (15 of 7157 with four of 7789 83.4 / 57.3), 1.06 over 17
-// of eight and 16 (four of 57 060 with eight of 50 911 99.3 / 134.9).  ROUGE-N has one kind of members, whose order the
-// sorted runs deal out by themselves as well, in longer chunks: ROUGE-1 0.89 over 246 shapes of up to eight
-// references (one of 235 166 with one of 191 043 25.7 / 16.7; 97 of 6303 with one of 7834 21.7 / 25.4), ROUGE-2 0.91
-// over 67 of rows of 12 000 and up to four (two of 128 592 with one of 121 506 28.3 / 20.7), 1.02 over the 150 others
-// (120 of 2216 with eight of 2379 50.7 / 76.1).
+// the sorted runs' time on average over the 505 that go there (118 of 7162 with one reference of 7172 112.1 / 52.4; at
+// worst five of 2979 with four of 3432, two orders, 18.3 / 21.3), 1.03 over the 135 that do not.  Of few positions both
+// are a chain of latencies: below 65 536 1.0, at worst three of 7477 with one of 8070 15.7 / 18.9.  A partition has all
+// references of its share of the candidate, which many of them leave small: eight below 262 144 positions 1.07 (two of
+// 4165 with eight of 3344 19.8 / 26.6), above 0.87 with four orders, but 0.99 over 35 shapes with fewer (13 of 9513 with
+// eight of 9856, three orders, 46.7 / 52.5); sixteen 1.03 (eight of 1289 with 16 of 1449 28.4 / 42.6).  Three
+// references or more whose counters need 32 bits: 1.03, from four of 71 385 with three of 66 300 64.7 / 48.0 to one of
+// 131 072 with three of 106 288 37.1 / 73.5.  With dictionary sizes, where the tables hold the references' n-grams, too:
+// 0.87 over 31 shapes of up to four references (15 of 7157 with four of 7789 84.0 / 49.8), 0.99 over 17 of eight and 16
+// (five of 21 214 with 16 of 17 606, one order, 66.2 / 82.1).  ROUGE-N has one kind of members, whose order the sorted
+// runs deal out by themselves as well, in longer chunks: ROUGE-1 0.89 over 246 shapes of up to eight references (one of
+// 135 978 with one of 120 892 20.2 / 13.3; 97 of 6303 with one of 7834 21.1 / 25.1), ROUGE-2 0.91 over 67 of rows of
+// 12 000 and up to four (two of 128 592 with one of 121 506 27.8 / 20.5), 1.02 over the 150 others (60 of 1427 with
+// eight of 1772 39.5 / 50.3).
 bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* plan) {
   const int64_t positions = pb.B * pb.group_cap;
   if (pb.R > 8 || positions < (pb.R <= 4 ? 65536 : 262144)) return false;
@@ -365,9 +365,9 @@ bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* pl
 // 12 400 to 24 500 positions with 1 to 62 references and 4 to 130 groups, one to six orders: on average
 // 0.5 % (ROUGE 0.2 %) behind the better kernel, more than a tenth behind in 2.3 % (0.5 %) of them.  (The
 // lines fitted before the kernel found n-grams without looking them up: 1.0 % and 17 %.)
-// Against the kernels that deal every position out once, BLEU's line is another (dealt / fused): on average 0.6 %
-// behind the better kernel over 202 shapes of the same ranges, more than a tenth behind in five; five groups of 5804
-// with three references of 6020 18.7 / 45.4, 113 of 2541 with eight of 2673 112.0 / 34.4.
+// Against the kernels that deal every position out once, BLEU's line is another (dealt / fused): on average 0.8 %
+// behind the better kernel over 193 shapes of the same ranges, more than a tenth behind in five; five groups of 5804
+// with three references of 6020 18.9 / 45.2, 91 of 2107 with four of 2686, two orders, 37.3 / 13.9.
 // Against the partitioned kernels, which take what the sorted runs do not: 32.
 bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
                  FusedPlan* plan) {

@@ -26,7 +26,7 @@
 // unit, and the 19 bytes a position that it writes.  Tallying: issue, 560 vector and 450 scalar instructions of a
 // wavefront's 9 us (a third of them exec masks of the probing loops), and the longest workgroups.
 //
-// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 33.4 -> 25.8; 11 groups of two
+// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 33.3 -> 25.7; 11 groups of two
 // times 90 000 96.7 -> 59; 50 of two times 20 000 80.4 -> 57; 16 of two times 12 500 32 -> 22.6; two of 174 762
 // with two references 65 -> 40.  Of these the scores inside the counting kernel, instead of in one of their own, and
 // arguments read where they are used (113 scalar registers were moved to lanes and back, now 33) 2 to 4 us each.

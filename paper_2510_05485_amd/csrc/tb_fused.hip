@@ -3,8 +3,8 @@
 // Tokens are read from HBM once; dictionary and counters never leave LDS; one score (plus optional
 // integer statistics) goes out.  What bounds it: instruction issue.  A lone small group pays seven or
 // eight cycles per instruction of its longest wavefront.  A full chip issues, per cycle and compute unit,
-// 0.72 vector and 0.48 scalar instructions (512 x 1024 with four references), 0.82 and 0.58 (1024 x 2048),
-// 0.71 and 0.54 (4096 x 512 with two): 71 to 82 % of the 1.7 that a mix of both kinds reaches at most
+// 0.73 vector and 0.48 scalar instructions (512 x 1024 with four references), 0.83 and 0.59 (1024 x 2048),
+// 0.71 and 0.54 (4096 x 512 with two): 71 to 84 % of the 1.7 that a mix of both kinds reaches at most
 // (counters of rocprofv3; 1.5 of vector instructions alone, 1.0 of scalar ones), the scalar ones from
 // loops, masks and bookkeeping.  LDS is not the limit (0.07 to 0.09 instructions; a random 16-byte read
 // takes 12.5 cycles per wavefront, a 4-byte one 6.5, a compare-and-swap 12).  So:
@@ -48,7 +48,7 @@
 // put together what is left of blocks, the one that entered every n-gram and swept its counters, and the one
 // before that, with a barrier per insertion and look-up of each order): 16 x 256 tokens with one reference 5.9
 // (6.0, 6.7, 9.5), 256 x 1088 8.0 (8.3, 9.4, 12.8), 512 x 1024 with four references 17.0 (17.5, 19.8, 22.8), 4096 x
-// 512 with two and the batch's sums 30.5 (31.9, 47.7, 50.5), 4096 x 2048 with two 95 (102, 145, 171), 1000 x 96 with
+// 512 with two and the batch's sums 30.3 (32.0, 47.7, 50.5), 4096 x 2048 with two 95 (102, 145, 171), 1000 x 96 with
 // up to eight 10.1 (10.3, 10.5, 13.7), ROUGE-2 of 512 x 512 with three 7.2 (7.1, 9.6, 12.5); 128 x 5000 with one
 // 18.9 (21.7, 28.5; 55 on three staged kernels), 128 x 8192 27.5 (31.2, 46.6; 98 on the partitioned ones).
 #include <type_traits>
