@@ -233,7 +233,11 @@ struct SymbolTable {
 
 // What a kernel is for.  With one or two references lengths, rows and counters of a block are known
 // without a look at other lanes, and no register holds what depends on the number of references.
-enum Mode { kOneReference, kTwoReferences, kReferences, kRouge };
+// kRouge: ROUGE-1 and -2, kRougeLonger the others.  (One kernel for both moved 19 to 24 scalar registers to lanes
+// of a vector register and back in ROUGE-1 and -2, too, and took a branch around the orders behind order 2: ROUGE-2
+// of 512 x 512 with three references 7.16 -> 6.87 us, of 700 x 512 8.63 -> 8.25, ROUGE-1 of 1435 x 503 with one 7.43 -> 7.23,
+// with three 10.44 -> 10.12.)
+enum Mode { kOneReference, kTwoReferences, kReferences, kRouge, kRougeLonger };
 
 // The value of sequence f.  (Arguments by value: a choice between variables that closures refer to is
 // made between their addresses, which keeps all of them in memory.)
@@ -257,7 +261,8 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   typedef const char __attribute__((address_space(4)))* Segment;
   const FusedArgs& a =
       *(const FusedArgs*)((Segment)__builtin_amdgcn_kernarg_segment_ptr() + kRegisterArgs);
-  constexpr bool ROUGE = MODE == kRouge, ONE = MODE == kOneReference, TWO = MODE == kTwoReferences;
+  constexpr bool ROUGE = MODE == kRouge || MODE == kRougeLonger, SHORT = MODE == kRouge;
+  constexpr bool ONE = MODE == kOneReference, TWO = MODE == kTwoReferences;
   constexpr bool FEW = ONE || TWO;
   typedef uint32_t Quad __attribute__((ext_vector_type(4)));
   const int cs = cand_shape & 0xFFFFu, R = ONE ? 1 : TWO ? 2 : (cand_shape >> 16) & 0xFFu;
@@ -528,7 +533,8 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
 
   // Counters: 16-bit fields, two a word, the words of all ids in one array per pair of fields.  A position
   // whose n-gram has the position's own id (its first occurrence) is not counted: no reference asks for
-  // other ids, so a field that nothing was added to stands for one occurrence in the candidate.
+  // other ids, so a field that nothing was added to stands for one occurrence in the candidate.  (ROUGE-1 and -2
+  // count every occurrence: with hardly an n-gram's second one behind it, the branch costs more than it saves.)
   //   * One reference, and ROUGE-N: a field is one less than the n-gram's count in the candidate, less
   //     what the reference has had of it so far (a negative lower half borrows from the upper one).  A
   //     reference's n-gram that does not find it negative is a match, and matches are all that is asked
@@ -537,6 +543,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   //   * Two references: the same less the reference's count, one field each; the smaller one is (one less
   //     than) what the candidate has beyond both.
   //   * More: one less than the count in the candidate, then the counts in the references.
+  constexpr bool EVERY = SHORT;
   constexpr bool matching = ONE || ROUGE;
   constexpr bool differences = MODE != kReferences;
   const int order_fields = differences ? R : R + 1;
@@ -561,9 +568,10 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     lds_add(at, unit);
     return 0u;
   };
-  // whether the field was not negative (low + 65536 * high, each within 32767)
+  // whether the field was not negative, with EVERY positive (low + 65536 * high, each within 32767)
   auto is_match = [&](int order, int f, uint32_t word) __attribute__((always_inline)) {
     const int odd = ((ROUGE ? 0 : order * order_fields) + first_ref + f) & 1;
+    if (EVERY) return int32_t(word << (odd ? 0 : 16)) > (odd ? 0x7FFF : 0);
     return int32_t(word << (odd ? 0 : 16)) >= (odd ? -0x8000 : 0);
   };
   // Of this lane, orders 1, 2 and the ones behind them that a stretch has: the reference's matches, and
@@ -583,7 +591,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
   const bool want_distinct = want;
 
   // What is left of blocks is put together to full ones (COMPACT; not where a wavefront has few).
-  constexpr bool COMPACT = BLOCKS > kApartBlocks;
+  constexpr bool COMPACT = BLOCKS > kApartBlocks && !SHORT;
   constexpr bool LISTED = COMPACT && !FEW;  // the references of positions are looked up
 
   // ---- order 1: tokens become symbols
@@ -594,12 +602,13 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       int32_t got = -1;
       if (v >= 0) {
         got = int32_t(table.claim<LOOK_FIRST>(uint32_t(v) * table.multiplier, id));
-        if (got != int32_t(id)) {
+        if (EVERY || got != int32_t(id)) {
           if (!ROUGE || N == 1) count_candidate(0, uint32_t(got));
           if (!ROUGE) ++repeat12;
         }
       }
       *lds<int16_t>(s) = int16_t(got);
+      if (SHORT) v = got;
       id += nt;
       s += sym_stride;
       b += nwaves;
@@ -633,6 +642,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
         const int of_block = __popcll(__builtin_amdgcn_ballot_w64(match));
         overlap += lane == f ? of_block : 0;
       }
+      if (SHORT) v = got;
       s += sym_stride;
       b += nwaves;
     });
@@ -807,7 +817,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
     // `next` on take such words.
     const bool dense = !KEEP || lo == 2;
     const int next = dense ? 3 : lo;
-    const bool deeper = KEEP || hi > 2;
+    const bool deeper = !SHORT && (KEEP || hi > 2);
     const uint32_t ahead = 2u * uint32_t(next - 1), other = sym_at + ahead;
     auto word_of = [](uint32_t position, uint32_t id) __attribute__((always_inline)) { return int32_t(position | id << 16); };
 
@@ -818,7 +828,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
                      auto&& repeated) __attribute__((always_inline)) {
       uint32_t id = prefix;
       if (last != implied) id = table.claim<LOOK>(hash_of(n, prefix, uint32_t(last)), position);
-      if (id == position) return;
+      if (!EVERY && id == position) return;
       if (!ROUGE || n == N) count_candidate(n - 1 - swept, id);
       repeated(id);
     };
@@ -893,7 +903,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       return left;
     };
     // A block's order 2, and without COMPACT the orders behind it at once.
-    const bool at_once = !COMPACT && hi > 2;
+    const bool at_once = !COMPACT && !SHORT && hi > 2;
     int i = 0, b = wave;
     uint32_t id = uint32_t(kWave * wave + lane), s = first_sym;
     auto enter_block = [&]() __attribute__((always_inline)) {
@@ -901,8 +911,8 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       const int32_t prefix = *lds<int16_t>(s), last = *lds<int16_t>(s + 2);
       int32_t lasts[DEPTH];
 #pragma unroll
-      for (int d = 0; !COMPACT && d < DEPTH; ++d) lasts[d] = *lds<int16_t>(s + 4 + 2u * d);
-      if (last >= 0 && prefix != int32_t(id)) {
+      for (int d = 0; !COMPACT && !SHORT && d < DEPTH; ++d) lasts[d] = *lds<int16_t>(s + 4 + 2u * d);
+      if (last >= 0 && (EVERY || prefix != int32_t(id))) {
         const int32_t implied = *lds<int16_t>(sym_at + 2u * uint32_t(prefix) + 2u);
         enter(2, id, uint32_t(prefix), last, implied, [&](uint32_t got) __attribute__((always_inline)) {
           if (!ROUGE) repeat12 += 0x10000u;
@@ -923,7 +933,7 @@ void fused_group(const void* cand, const int32_t* cand_lens, const void* refs,
       const int32_t prefix = *lds<int16_t>(own), last = *lds<int16_t>(own + 2);
       int32_t lasts[DEPTH];
 #pragma unroll
-      for (int d = 0; !COMPACT && d < DEPTH; ++d) lasts[d] = *lds<int16_t>(own + 4 + 2u * d);
+      for (int d = 0; !COMPACT && !SHORT && d < DEPTH; ++d) lasts[d] = *lds<int16_t>(own + 4 + 2u * d);
       int32_t left = -1;
       bool match = false;
       if ((int32_t(uint32_t(prefix) << id_bits) | last) >= 0) {
@@ -1192,7 +1202,12 @@ hipError_t launch_shape(const Problem& pb, const FusedArgs& a, const FusedPlan& 
 }
 template <int BLOCKS, bool KEEP, bool ALONE>
 hipError_t launch_mode(const Problem& pb, const FusedArgs& a, const FusedPlan& plan, hipStream_t s) {
-  if (a.rouge_prf) return launch_shape<BLOCKS, KEEP, kRouge, ALONE>(pb, a, plan, s);
+  if (a.rouge_prf) {
+    if constexpr (!KEEP) {
+      if (pb.N <= 2) return launch_shape<BLOCKS, KEEP, kRouge, ALONE>(pb, a, plan, s);
+    }
+    return launch_shape<BLOCKS, KEEP, kRougeLonger, ALONE>(pb, a, plan, s);
+  }
   return pb.R == 1   ? launch_shape<BLOCKS, KEEP, kOneReference, ALONE>(pb, a, plan, s)
          : pb.R == 2 ? launch_shape<BLOCKS, KEEP, kTwoReferences, ALONE>(pb, a, plan, s)
                      : launch_shape<BLOCKS, KEEP, kReferences, ALONE>(pb, a, plan, s);

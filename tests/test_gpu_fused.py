@@ -156,6 +156,14 @@ def test_every_kernel(kernel):
         check_row(690 + blocks, kernel[2], shape)
 
 
+@pytest.mark.parametrize("N", [1, 2, 3])
+@pytest.mark.parametrize("alone", [False, True])
+def test_rouge_kernels(alone, N):
+    # ROUGE-1 and -2 on kernels without what longer orders need, every number of blocks; ROUGE-3 beside them
+    for blocks, shape in fused_rows.ROUGE[alone].items():
+        check_row(740 + blocks, "rouge", (*shape, N))
+
+
 @pytest.mark.parametrize("way", list(fused_rows.PASSES))
 def test_every_way_to_divide_the_orders(way):
     for i, (alone, mode, shape) in enumerate(fused_rows.PASSES[way]):

@@ -172,6 +172,26 @@ def test_the_rows_reach_what_they_name(plans):
     assert len(fused_rows.KERNELS) == 16
 
 
+def test_rouge_shapes_reach_their_kernels(plans):
+    out = (ctypes.c_int64 * 9)()
+    kernels = (1, 2, 3, 4, 5, 6, 8, 12, 16, 24)
+    for alone, rows in fused_rows.ROUGE.items():
+        assert sorted(rows) == list(kernels[0 if alone else 1:])
+        for blocks, (B, R, cs, rs) in rows.items():
+            for N in (1, 2, 3):
+                assert plans.fused_plan(B, cs, rs, R, N, fused_rows.BITS, True, out)
+                assert B >= 100 or plans.fused_path(cs, rs, R, fused_rows.BITS)
+                assert (out[8], out[7]) == (alone, 0)
+                assert blocks == min(k for k in kernels if k >= out[6])
+    # ids are kept between passes from order 3 on only: ROUGE-1 and -2 need no kernels that keep them
+    rng = random.Random(41)
+    for _ in range(20000):
+        B, R, N = int(2 ** (13 * rng.random())), rng.choice((1, 2, 3, 8, 40, 62)), rng.randint(1, 2)
+        cs, rs = int(2 ** (13.6 * rng.random())), int(2 ** (14 * rng.random()))
+        if plans.fused_plan(B, cs, rs, R, N, rng.choice((1, 8, 16, 31)), True, out):
+            assert not out[7]
+
+
 def test_colliding_ids_walk_further_than_an_entry_counts(plans):
     # order 1 of the batch of test_gpu_fused.py: so many of the ids have the same bucket and the same step that
     # they fill more buckets than an entry can count
