@@ -36,7 +36,6 @@
 // 4 again, each on its own and in as many rounds as leave each its share (see tally_kind).  A table that is full
 // then (which takes tokens chosen to collide) is reported through TB_DEV_TABLE_OVERFLOW and scored NaN.
 #include <cmath>
-#include <type_traits>
 
 #include "tb_kernels.h"
 #include "tb_score.h"
@@ -52,6 +51,7 @@ constexpr int kTallyThreads = 1024;
 constexpr int kMaxDealChunks = kTallyThreads;  // per group: one thread each reads a run's place
 constexpr int kTokenBits = 20;
 constexpr uint32_t kNoToken = (1u << kTokenBits) - 1u;  // behind the end of a sequence
+constexpr uint32_t kGivenBack = ~0u;  // in the place of an id's token
 
 struct DealArgs {
   Problem pb;
@@ -325,8 +325,7 @@ __device__ __forceinline__ __attribute__((address_space(3))) T* lds(uint32_t off
   return (Ptr)(uintptr_t)(offset);
 }
 template <typename T>
-__device__ __forceinline__ T lds_cas(uint32_t at, T desired) {  // expects 0
-  T expected = 0;
+__device__ __forceinline__ T lds_cas(uint32_t at, T desired, T expected = 0) {
   __hip_atomic_compare_exchange_strong((T*)lds<T>(at), &expected, desired, __ATOMIC_RELAXED,
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
   return expected;
@@ -337,6 +336,9 @@ __device__ __forceinline__ uint32_t lds_add(uint32_t at, uint32_t v) {
 }
 __device__ __forceinline__ void lds_add_only(uint32_t at, uint32_t v) {
   __hip_atomic_fetch_add((uint32_t*)lds<uint32_t>(at), v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+}
+__device__ __forceinline__ uint32_t lds_peek(uint32_t at) {  // (as it is now)
+  return __hip_atomic_load((uint32_t*)lds<uint32_t>(at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 typedef uint32_t Quad __attribute__((ext_vector_type(4)));
 
@@ -374,7 +376,7 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
   const uint32_t cand_marks = KIND < 2 ? used_bytes : (a.off_lead + 4u * uint32_t(a.capacity) + 15u) & ~15u;
   const uint32_t ref_marks = cand_marks + 2u * uint32_t(window);
   clear(0, used_bytes);
-  clear(cand_marks, cand_marks + 4u * uint32_t(window));
+  clear(KIND < 2 ? cand_marks : a.off_lead, cand_marks + 4u * uint32_t(window));  // (no id is given back yet)
   clear(a.off_sums, a.off_places);
   // Members: those of the candidate's chunks, then those of the references'.
   auto scratch = [&](int i) __attribute__((always_inline)) { return lds<int>(a.off_scratch + 4u * uint32_t(i)); };
@@ -501,12 +503,26 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     return x.t0 == y.t0 && ((x.rest ^ y.rest) & mask) == 0ull;
   };
   auto last_of = [](const Item& x) __attribute__((always_inline)) { return uint32_t(x.rest >> (2 * kTokenBits)); };
+  // An id that a lane took and had no use for, where there are no new ones; `capacity`: none found.  (Each lane looks at
+  // places of its own: where lanes lose many ids, the first ones will do, and few lost are no use.)
+  auto id_given_back = [&]() __attribute__((always_inline)) {
+    uint32_t h = uint32_t(tid) * 0x85EBCA6Bu;
+#pragma unroll 1
+    for (int tries = 0; tries < 64 && !lds_peek(again_at); ++tries) {
+      h = h * 0x9E3779B1u + 0x7F4A7C15u;
+      const uint32_t id = __umulhi(h, capacity), at = a.off_lead + 4u * id;
+      if (lds_peek(at) == kGivenBack && lds_cas<uint32_t>(at, 0u, kGivenBack) == kGivenBack) return id;
+    }
+    *lds<uint32_t>(again_at) = 1u;
+    return capacity;
+  };
   // The id of the n-gram of order n (3 or 4) with hash h, and the item under it; it is entered if it is the
-  // candidate's and not there.  false: not there, or no id left for it.  Lanes that enter the n-gram that the first
-  // one of them does wait for its id, or each would use one up (a frequent beginning); `careful`: one n-gram is
-  // entered after the other.
-  auto resolve = [&](const Item& x, uint32_t h, int n, int f, uint32_t& id, Item& found, bool& is_new,
-                     auto careful) __attribute__((always_inline)) {
+  // candidate's and not there.  false: not there, or no id left for it.  Who enters one takes an id, writes the
+  // tokens under it and then swaps it in; where another lane was first, the id is given back.  (Ids that were lost
+  // there ran out on texts of few different tokens, which all lanes enter at once: two of 100 000, 13 different ones,
+  // 122 us a call, now 25.  The lanes with the n-gram of the first one used to wait for its id instead: that took
+  // longer than it saved, 50 groups of two times 20 000 61.1 us, now 60.2.)
+  auto resolve = [&](const Item& x, uint32_t h, int n, int f, uint32_t& id, Item& found, bool& is_new) __attribute__((always_inline)) {
     uint32_t s = ((h * parts) >> (30 - a.log2_item)) & bucket_mask;
     const uint32_t mine = h << (a.id_bits + 1) | uint32_t(n - 2) << a.id_bits;
     Quad e;
@@ -530,56 +546,39 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
       s = (s + 16u) & bucket_mask;
     }
     if (f > 0 && !ALL) return false;
-    while (true) {
-      const uint64_t going = __builtin_amdgcn_ballot_w64(true);
-      const int leader = __ffsll((unsigned long long)going) - 1;
-      const Item first{uint32_t(__builtin_amdgcn_readlane(int(x.t0), leader)),
-                       uint64_t(uint32_t(__builtin_amdgcn_readlane(int(x.rest >> 32), leader))) << 32 |
-                           uint32_t(__builtin_amdgcn_readlane(int(uint32_t(x.rest)), leader))};
-      const bool follows = lane != leader && same(first, x, n);
-      const bool waits = decltype(careful)::value && lane != leader;
-      id = ~0u;
-      if (!follows && !waits) {
-        const uint64_t entering = __builtin_amdgcn_ballot_w64(true);
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(entering >> 32),
-                                                        __builtin_amdgcn_mbcnt_lo(uint32_t(entering), 0u));
-        uint32_t next = 0;
-        if (rank == 0) next = lds_add(ids_at, uint32_t(__popcll(entering)));
-        const uint32_t own = uint32_t(__builtin_amdgcn_readfirstlane(int(next))) + rank;
-        if (own < capacity) {
-          *lds<uint64_t>(a.off_tokens + 8u * own) = x.rest;
-          *lds<uint32_t>(a.off_lead + 4u * own) = x.t0;
-          asm volatile("" ::: "memory");  // (a wavefront's LDS accesses happen in their order)
-          s += first_free_slot(e.x, e.y, e.z);
-          while (true) {
-            const uint32_t old = lds_cas<uint32_t>(s, mine + own);
-            if (old == 0u) {
-              is_new = true;
-              id = own;
-              found = x;
-              break;
-            }
-            id = old ^ mine;
-            if (id < id_limit) {
-              found = load_item(id);
-              if (same(found, x, n)) break;
-            }
-            s = (s + 4u) & (bucket_mask | 12u);
-          }
-        } else {
-          *lds<uint32_t>(again_at) = 1u;
-        }
-      }
-      const uint32_t leaders = uint32_t(__builtin_amdgcn_readlane(int(id), leader));
-      if (follows) {
-        id = leaders;
-        if (id < id_limit) found = load_item(id);
-      }
-      // (the slots from the first one that was free on are looked at one by one, so that what has been entered
-      // since is seen)
-      if (!decltype(careful)::value || follows || !waits) break;
+    const uint64_t entering = __builtin_amdgcn_ballot_w64(true);
+    const uint32_t rank = __builtin_amdgcn_mbcnt_hi(uint32_t(entering >> 32),
+                                                    __builtin_amdgcn_mbcnt_lo(uint32_t(entering), 0u));
+    uint32_t next = 0;
+    if (rank == 0) next = lds_add(ids_at, uint32_t(__popcll(entering)));
+    uint32_t own = uint32_t(__builtin_amdgcn_readfirstlane(int(next))) + rank;
+    if (__builtin_expect(own >= capacity, 0)) {
+      own = id_given_back();
+      if (own >= capacity) return false;
     }
-    return id < id_limit;
+    *lds<uint64_t>(a.off_tokens + 8u * own) = x.rest;
+    *lds<uint32_t>(a.off_lead + 4u * own) = x.t0;
+    asm volatile("" ::: "memory");  // (a wavefront's LDS accesses happen in their order)
+    // (the slots from the first one that was free on are looked at one by one, so that what has been entered
+    // since is seen)
+    s += first_free_slot(e.x, e.y, e.z);
+    while (true) {
+      const uint32_t old = lds_cas<uint32_t>(s, mine + own);
+      if (old == 0u) {
+        is_new = true;
+        id = own;
+        found = x;
+        break;
+      }
+      id = old ^ mine;
+      if (id < id_limit) {
+        found = load_item(id);
+        if (same(found, x, n)) break;
+      }
+      s = (s + 4u) & (bucket_mask | 12u);
+    }
+    *lds<uint32_t>(a.off_lead + 4u * own) = is_new ? x.t0 : kGivenBack;  // (a branch: 2 % of the call)
+    return true;
   };
   auto item_hash = [](const Item& x) __attribute__((always_inline)) {
     return hash3(x.t0, uint32_t(x.rest) & kNoToken, uint32_t(x.rest >> kTokenBits) & kNoToken);
@@ -592,14 +591,14 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     Item found;
     uint32_t id;
     bool is_new;
-    if (!resolve(x, h, 3, f, id, found, is_new, std::false_type{})) return;
+    if (!resolve(x, h, 3, f, id, found, is_new)) return;
     // (one that is new at order 3 is new at order 4, too)
     if (f == 0 && is_new && times == 1u && !ALL) return;
     if (ALL) created += is_new ? 1u : 0u;
     count(table_bytes + 4u * id, times, f, is_new, matches);
     // (behind the end there is no fourth token)
     if (N < 4 || last_of(x) == kNoToken) return;
-    if (last_of(x) != last_of(found) && !resolve(x, longer_hash(x, h), 4, f, id, found, is_new, std::false_type{}))
+    if (last_of(x) != last_of(found) && !resolve(x, longer_hash(x, h), 4, f, id, found, is_new))
       return;
     if (ALL) created4 += is_new ? 1u : 0u;
     count(counters4 + 4u * id, times, f, is_new, matches4);
@@ -685,12 +684,14 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
 #pragma unroll 1
     for (int n = 3; n <= N; ++n) {
       uint32_t part = 0;
-      int rounds = 2 + 2 * (ALL ? members : cand_members) / int(capacity);
+      const int first_rounds = 2 + 2 * (ALL ? members : cand_members) / int(capacity);
+      int rounds = first_rounds;
       created = 0;
 #pragma unroll 1
       for (int round = 0; round < rounds; ++round) {
         __syncthreads();
         clear(0, counters4);
+        clear(a.off_lead, cand_marks);
         if (tid == 0) *lds<uint32_t>(ids_at) = 0u, *lds<uint32_t>(again_at) = 0u;
         matches = 0;
 #pragma unroll 1
@@ -713,9 +714,14 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
             Item found;
             uint32_t id;
             bool is_new;
-            if (!resolve(x, h, n, m.f, id, found, is_new, std::true_type{})) continue;
-            if (ALL) created += is_new ? 1u : 0u;
-            count(table_bytes + 4u * id, (m.word >> kTokenBits) + 1u, m.f, is_new, matches);
+            // (in the end one lane of a wavefront after the other: sixteen ids at most are then taken in vain)
+            const int turns = rounds < 16 * first_rounds ? 1 : kWave;
+#pragma unroll 1
+            for (int turn = 0; turn < turns; ++turn) {
+              if ((turns > 1 && turn != lane) || !resolve(x, h, n, m.f, id, found, is_new)) continue;
+              if (ALL) created += is_new ? 1u : 0u;
+              count(table_bytes + 4u * id, (m.word >> kTokenBits) + 1u, m.f, is_new, matches);
+            }
           }
           if (refs == 0) i = cand_members + tid;
         }

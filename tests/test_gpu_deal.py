@@ -106,6 +106,13 @@ def test_repetition():
     check(w, 4)
 
 
+@pytest.mark.parametrize("vocab", [2, 4, 13])
+@pytest.mark.parametrize("B,R,L,N", [(2, 1, 60000, 4), (16, 2, 12500, 4), (9, 3, 9000, 4), (4, 1, 30000, 3)])
+def test_few_different_tokens(B, R, L, N, vocab):
+    # all lanes enter the same n-grams at once: ids are taken in vain, given back and used again
+    check(syn.random_small(991 + R, B=B, R=R, vocab=vocab, max_len=L, min_len=L - 100), N)
+
+
 @pytest.mark.parametrize("R,N", [(1, 4), (2, 4), (1, 3), (3, 4)])
 def test_more_ids_than_a_partition_has(R, N):
     # 4-grams of one beginning, a quarter of the text: counted in rounds
