@@ -113,6 +113,17 @@ def test_few_different_tokens(B, R, L, N, vocab):
     check(syn.random_small(991 + R, B=B, R=R, vocab=vocab, max_len=L, min_len=L - 100), N)
 
 
+@pytest.mark.parametrize("N", [3, 4])
+def test_equal_beginnings(N):
+    # n-grams that are merged by three tokens, but not by four, and those at the ends of rows
+    w = syn.random_small(996, B=12, R=1, vocab=900, max_len=6000, min_len=5000)
+    w.cand[:, ::4], w.cand[:, 1::4], w.cand[:, 2::4] = 3, 4, 5
+    w.refs[:, :, ::4], w.refs[:, :, 1::4], w.refs[:, :, 2::4] = 3, 4, 5
+    for i in range(12):
+        w.cand_len[i], w.ref_len[i, 0] = (1026, 2050, 4098)[i % 3] + i // 3, (2050, 4097)[i % 2] + i // 4
+    check(w, N)
+
+
 @pytest.mark.parametrize("R,N", [(1, 4), (2, 4), (1, 3), (3, 4)])
 def test_more_ids_than_a_partition_has(R, N):
     # 4-grams of one beginning, a quarter of the text: counted in rounds
