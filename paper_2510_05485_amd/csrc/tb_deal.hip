@@ -32,8 +32,8 @@
 // arguments read where they are used (113 scalar registers were moved to lanes and back, now 33) 2 to 4 us each.
 //
 // Keys are exact.  What the tables hold is bounded by the hashes whatever the tokens are, except for 4-grams:
-// where many different ones start with the same three tokens and ids run out, the partition counts orders 3 and
-// 4 again, each on its own and in as many rounds as leave each its share (see tally_kind).  A table that is full
+// where many different ones start with the same three tokens and ids run out, orders 3 and 4 are counted again, each
+// on its own, order 4 in shares that the group's workgroups take in turn (see tally_crowd).  A table that is full
 // then (which takes tokens chosen to collide) is reported through TB_DEV_TABLE_OVERFLOW and scored NaN.
 #include <cmath>
 
@@ -52,6 +52,8 @@ constexpr int kMaxDealChunks = kTallyThreads;  // per group: one thread each rea
 constexpr int kTokenBits = 20;
 constexpr uint32_t kNoToken = (1u << kTokenBits) - 1u;  // behind the end of a sequence
 constexpr uint32_t kGivenBack = ~0u;  // in the place of an id's token
+constexpr uint32_t kAlone = 3;  // shares of a crowded partition that its own workgroup takes by itself
+constexpr int kCrowds = 64;     // crowded partitions of a group whose shares others are told of
 
 struct DealArgs {
   Problem pb;
@@ -63,8 +65,13 @@ struct DealArgs {
   uint32_t* run_at;  // [B][chunks][parts of all kinds]: first of the run within its chunk | size << 16
   int32_t* overflow; // [B]
   int32_t* rouge_overlap;  // [B, R] or null
-  unsigned long long* arrived;  // [B, N]: sum of the partitions' matches | partitions << 40 | spoilt ones << 52
+  unsigned long long* arrived;  // [B, N]: sum of the partitions' matches | partitions and shares of them << 24 | shares
+                                // there are << 40 | spoilt ones << 52
   int32_t* complete;  // [B]: orders all of whose partitions have arrived
+  // Crowded partitions (see tally_crowd):
+  int32_t* crowds;      // [B]: how many
+  int32_t* crowd;       // [B][kCrowds]: partition << 16 | shares, or 0
+  int32_t* next_share;  // [B][kCrowds]: shares that have been taken
   ScoreParams sp;
   void* out;          // per-sentence scores, or null
   int first_kind, kinds, all_parts;  // kinds first_kind .. kinds - 1
@@ -74,6 +81,7 @@ struct DealArgs {
   // tally_kernel
   int words;         // per counter
   int capacity;      // ids of order 3 and 4 n-grams
+  uint32_t per_member;  // 2^32 / members of a share
   int window[kKinds];  // members of a kind that the marks are for, a multiple of 64
   int id_bits, log2_first, log2_pair, log2_item;
   // LDS: table and counters at 0, (4-grams: tokens under the ids,) marks, and for all kinds
@@ -176,7 +184,8 @@ __global__ __launch_bounds__(kThreads, 8) void deal_kernel(DealArgs a) {
       a.st.clipped[int64_t(g) * pb.N + tid] = 0;
       a.st.distinct[int64_t(g) * pb.N + tid] = 0;
     }
-    if (tid == 0) a.overflow[g] = a.complete[g] = 0;
+    if (tid == 0) a.overflow[g] = a.complete[g] = a.crowds[g] = 0;
+    if (tid < kCrowds) a.crowd[g * kCrowds + tid] = a.next_share[g * kCrowds + tid] = 0;
     if (tid < pb.N) a.arrived[int64_t(g) * pb.N + tid] = 0;
     if (a.rouge_overlap && tid < pb.R) a.rouge_overlap[int64_t(g) * pb.R + tid] = 0;
   }
@@ -359,98 +368,122 @@ typedef uint32_t Quad __attribute__((ext_vector_type(4)));
 // occurrence is counted.
 enum Counters { kOneReference, kHalves, kWords, kAllHalves, kAllWords };
 
-// One partition's members of one kind.
+// The kernel's arguments, read through the argument segment where they are used (loads of a by-value parameter all stand
+// at the entry and occupy scalar registers throughout); and read once more by who calls this again.
+__device__ __forceinline__ const DealArgs& arguments() {
+  typedef const char __attribute__((address_space(4)))* Segment;
+  Segment at = (Segment)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(at));
+  return *(const DealArgs*)at;
+}
+
+// What a workgroup of the tallying kernel works with.  (The rare parts below have an object of their own, from
+// arguments that are read again: shared with the usual part, their values took its scalar registers, 95 of which
+// were moved to lanes and back.)
 template <int KIND, Counters COUNTERS>
-__device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
-  constexpr bool ONE = COUNTERS == kOneReference, HALVES = COUNTERS == kHalves || COUNTERS == kAllHalves;
-  constexpr bool ALL = COUNTERS == kAllHalves || COUNTERS == kAllWords;
-  const Problem& pb = a.pb;
-  const int tid = threadIdx.x, lane = tid & (kWave - 1);
-  const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
-  const int g = blockIdx.y;
-  const int N = pb.N;
-  const uint32_t parts = uint32_t(a.parts[KIND]);
-  // (LDS: the table at 0, its counters behind it, then what follows here)
-  const uint32_t lost_at = a.off_sums, ids_at = lost_at + 4u, again_at = lost_at + 8u;
-
-  uint32_t place = 0;
-  if (tid < a.chunks) place = a.run_at[(int64_t(g) * a.chunks + tid) * a.all_parts + a.parts_before[KIND] + p];
-  auto clear = [&](uint32_t from, uint32_t to) __attribute__((always_inline)) {
-    for (uint32_t q = from + 16u * uint32_t(tid); q < to; q += 16u * kTallyThreads) *lds<Quad>(q) = Quad(0u);
-  };
-  const uint32_t table_bytes = KIND == 0 ? 4u << a.log2_first : KIND == 1 ? 8u << a.log2_pair : 4u << a.log2_item;
-  const uint32_t slots_bytes = KIND == 0 ? 4u << a.log2_first : KIND == 1 ? 4u << a.log2_pair : 4u * uint32_t(a.capacity);
-  const uint32_t counters4 = table_bytes + slots_bytes * uint32_t(ONE ? 1 : a.words);  // KIND 2: order 4's
-  const uint32_t used_bytes = KIND < 2 ? counters4 : counters4 + slots_bytes * uint32_t(N < 4 ? 0 : ONE ? 1 : a.words);
-  const int window = a.window[KIND];
-  const uint32_t cand_marks = KIND < 2 ? used_bytes : (a.off_lead + 4u * uint32_t(a.capacity) + 15u) & ~15u;
-  const uint32_t ref_marks = cand_marks + 2u * uint32_t(window);
-  clear(0, used_bytes);
-  clear(KIND < 2 ? cand_marks : a.off_lead, cand_marks + 4u * uint32_t(window));  // (no id is given back yet)
-  clear(a.off_sums, a.off_places);
-  // Members: those of the candidate's chunks, then those of the references'.
-  auto scratch = [&](int i) __attribute__((always_inline)) { return lds<int>(a.off_scratch + 4u * uint32_t(i)); };
-  constexpr int kWaves = kTallyThreads / kWave;
-  const int run_size = int(place >> 16);
-  int before = wave_inclusive_scan(run_size);
-  if (lane == kWave - 1) *scratch(wave) = before;
-  __syncthreads();
-  const int of_waves = row_inclusive_scan(*scratch(lane & (kWaves - 1)));
-  const int members = lane_value(of_waves, kWaves - 1);
-  if (wave > 0) before += __builtin_amdgcn_readlane(of_waves, (wave - 1) & 15);
-  before -= run_size;
-  if (tid == a.cand_chunks) *scratch(16) = before;
-  // where a run's members are: x + member; and whose they are
-  if (tid < a.chunks) {
-    int seq;
-    const int base = deal_base(a, deal_chunk(a, tid), &seq);
-    *lds<int>(a.off_places + 4u * uint32_t(tid)) = base + int(place & 0xFFFFu) - before;
-    if (KIND == 2) *lds<int>(a.off_places + 4u * uint32_t(a.chunks + tid)) = before;
-    if (!ONE) *lds<int>(a.off_places + 4u * uint32_t(2 * a.chunks + tid)) = seq;
-  }
-  // Windows of `window` members, in blocks of 64 that the wavefronts take in turn.  A run marks its first member
-  // in the window and every member at a multiple of 64: the largest mark up to a lane is its run.
-  auto mark = [&](uint32_t marks, int begin, int size) __attribute__((always_inline)) {
-    const int lo = max(before - begin, 0), hi = min(before + run_size - begin, size);
-#pragma unroll 1
-    for (int i = lo; i < hi; i = (i | (kWave - 1)) + 1) *lds<uint16_t>(marks + 2u * uint32_t(i)) = uint16_t(tid + 1);
-  };
-  __syncthreads();
-  const int cand_members = __builtin_amdgcn_readfirstlane(*scratch(16));
-  mark(cand_marks, 0, min(cand_members, window));
-  mark(ref_marks, cand_members, min(members - cand_members, window));
-  __syncthreads();
-
-  const int64_t slots = int64_t(g) * pb.group_cap;
+struct Tally {
+  static constexpr bool ONE = COUNTERS == kOneReference, HALVES = COUNTERS == kHalves || COUNTERS == kAllHalves;
+  static constexpr bool ALL = COUNTERS == kAllHalves || COUNTERS == kAllWords;
+  static constexpr int kWaves = kTallyThreads / kWave;
   struct Member {
     uint64_t key;   // pair, or the rest of a 4-gram
     uint32_t word;  // token, or the first one of a 4-gram
     int f;
   };
-  auto load = [&](int i, int run, bool cand) __attribute__((always_inline)) {
+  struct Item {
+    uint32_t t0;
+    uint64_t rest;
+  };
+
+  const DealArgs& a;
+  const int tid, lane, wave, g, N;
+  const uint32_t parts;
+  // (LDS: the table at 0, its counters behind it, then what follows here)
+  const uint32_t lost_at, ids_at, again_at;
+  const uint32_t table_bytes, slots_bytes;
+  const uint32_t counters4, used_bytes;  // KIND 2: order 4's
+  const int window;
+  const uint32_t cand_marks, ref_marks;
+  const int64_t slots;
+  // 4-grams: ids, and the tokens under them
+  const uint32_t id_limit, capacity, bucket_mask;
+  int run_size, before, members, cand_members;
+  uint32_t matches = 0, matches4 = 0;  // (4-grams)
+
+  __device__ __forceinline__ explicit Tally(const DealArgs& args)
+      : a(args), tid(threadIdx.x), lane(tid & (kWave - 1)), wave(__builtin_amdgcn_readfirstlane(tid / kWave)),
+        g(blockIdx.y), N(a.pb.N), parts(uint32_t(a.parts[KIND])),
+        lost_at(a.off_sums), ids_at(lost_at + 4u), again_at(lost_at + 8u),
+        table_bytes(KIND == 0 ? 4u << a.log2_first : KIND == 1 ? 8u << a.log2_pair : 4u << a.log2_item),
+        slots_bytes(KIND == 0 ? 4u << a.log2_first : KIND == 1 ? 4u << a.log2_pair : 4u * uint32_t(a.capacity)),
+        counters4(table_bytes + slots_bytes * uint32_t(ONE ? 1 : a.words)),
+        used_bytes(KIND < 2 ? counters4 : counters4 + slots_bytes * uint32_t(N < 4 ? 0 : ONE ? 1 : a.words)),
+        window(a.window[KIND]),
+        cand_marks(KIND < 2 ? used_bytes : (a.off_lead + 4u * uint32_t(a.capacity) + 15u) & ~15u),
+        ref_marks(cand_marks + 2u * uint32_t(window)), slots(int64_t(g) * a.pb.group_cap),
+        id_limit(1u << a.id_bits), capacity(uint32_t(a.capacity)), bucket_mask(((4u << a.log2_item) - 1u) & ~15u) {}
+
+  __device__ __forceinline__ auto scratch(int i) const { return lds<int>(a.off_scratch + 4u * uint32_t(i)); }
+  __device__ __forceinline__ auto place_of(int run) const { return lds<int>(a.off_places + 4u * uint32_t(run)); }
+  __device__ __forceinline__ auto before_of(int run) const { return place_of(a.chunks + run); }
+  __device__ __forceinline__ auto seq_of(int run) const { return place_of(2 * a.chunks + run); }
+  __device__ __forceinline__ void clear(uint32_t from, uint32_t to) const {
+    for (uint32_t q = from + 16u * uint32_t(tid); q < to; q += 16u * kTallyThreads) *lds<Quad>(q) = Quad(0u);
+  }
+  __device__ __forceinline__ uint32_t load_place(int partition) const {
+    if (tid >= a.chunks) return 0u;
+    return a.run_at[(int64_t(g) * a.chunks + tid) * a.all_parts + a.parts_before[KIND] + partition];
+  }
+
+  // Members: those of the candidate's chunks, then those of the references'.
+  __device__ __forceinline__ void gather(uint32_t place) {
+    run_size = int(place >> 16);
+    before = wave_inclusive_scan(run_size);
+    if (lane == kWave - 1) *scratch(wave) = before;
+    __syncthreads();
+    const int of_waves = row_inclusive_scan(*scratch(lane & (kWaves - 1)));
+    members = lane_value(of_waves, kWaves - 1);
+    if (wave > 0) before += __builtin_amdgcn_readlane(of_waves, (wave - 1) & 15);
+    before -= run_size;
+    if (tid == a.cand_chunks) *scratch(16) = before;
+    // where a run's members are: x + member; and whose they are
+    if (tid < a.chunks) {
+      int seq;
+      const int base = deal_base(a, deal_chunk(a, tid), &seq);
+      *place_of(tid) = base + int(place & 0xFFFFu) - before;
+      if (KIND == 2) *before_of(tid) = before;
+      if (!ONE) *seq_of(tid) = seq;
+    }
+  }
+  // Windows of `window` members, in blocks of 64 that the wavefronts take in turn.  A run marks its first member
+  // in the window and every member at a multiple of 64: the largest mark up to a lane is its run.
+  __device__ __forceinline__ void mark(uint32_t marks, int begin, int size) const {
+    const int lo = max(before - begin, 0), hi = min(before + run_size - begin, size);
+#pragma unroll 1
+    for (int i = lo; i < hi; i = (i | (kWave - 1)) + 1) *lds<uint16_t>(marks + 2u * uint32_t(i)) = uint16_t(tid + 1);
+  }
+  __device__ __forceinline__ Member load(int i, int run, bool cand) const {
     Member m;
-    const int64_t at = slots + i + *lds<int>(a.off_places + 4u * uint32_t(run));
-    m.f = cand ? 0 : ONE ? 1 : *lds<int>(a.off_places + 4u * uint32_t(2 * a.chunks + run));
+    const int64_t at = slots + i + *place_of(run);
+    m.f = cand ? 0 : ONE ? 1 : *seq_of(run);
     m.key = 0;
     m.word = 0;
     if (KIND == 0) m.word = a.first[at];
     if (KIND == 1) m.key = a.pair[at];
     if (KIND == 2) m.key = a.rest[at], m.word = a.lead[at];
     return m;
-  };
+  }
   // block of a window of `size` > 64 * block members from `begin` on
-  auto fetch = [&](uint32_t marks, int begin, int size, int block, bool cand) __attribute__((always_inline)) {
+  __device__ __forceinline__ Member fetch(uint32_t marks, int begin, int size, int block, bool cand) const {
     const uint32_t mark = marks + 2u * uint32_t(block * kWave + lane);
     const int run = wave_inclusive_max(*lds<uint16_t>(mark)) - 1;
     *lds<uint16_t>(mark) = 0;  // (for the next window)
     // (behind the last member: the last one again)
     return load(begin + min(block * kWave + lane, size - 1), run, cand);
-  };
+  }
 
-  uint32_t matches = 0, matches4 = 0;  // (4-grams)
-  uint32_t created = 0, created4 = 0;
   // Adds `times` occurrences in sequence f to the counter; `is_new`: the candidate's first.
-  auto count = [&](uint32_t at, uint32_t times, int f, bool is_new, uint32_t& matched) __attribute__((always_inline)) {
+  __device__ __forceinline__ void count(uint32_t at, uint32_t times, int f, bool is_new, uint32_t& matched) const {
     if (f == 0) {
       lds_add_only(at, times - (is_new && !ALL ? 1u : 0u));
     } else if (ONE) {
@@ -459,10 +492,10 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     } else {
       lds_add_only(at + uint32_t(HALVES ? f >> 1 : f) * slots_bytes, HALVES ? times << (16 * (f & 1)) : times);
     }
-  };
+  }
   // Tables of whole keys, probed slot by slot.
-  auto do_key = [&](auto key, uint32_t s, uint32_t times, int f) __attribute__((always_inline)) {
-    typedef decltype(key) Key;
+  template <typename Key>
+  __device__ __forceinline__ void do_key(Key key, uint32_t s, uint32_t times, int f) {
     constexpr uint32_t kSize = sizeof(Key);
     Key old = *lds<Key>(s);
     if (f > 0 && !ALL) {
@@ -485,54 +518,50 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
         return;
       }
     }
-    if (ALL) created += old == 0 ? 1u : 0u;
     count(table_bytes + s / (kSize / 4u), times, f, old == 0, matches);
-  };
-  auto do_first = [&](uint32_t word, int f) __attribute__((always_inline)) {
+  }
+  __device__ __forceinline__ void do_first(uint32_t word, int f) {
     const uint32_t t = word & kNoToken;
-    do_key(uint32_t(t + 1u), (hash1(t) * parts) >> (32 - a.log2_first) << 2, (word >> kTokenBits) + 1u, f);
-  };
-  auto do_pair = [&](uint64_t word, int f) __attribute__((always_inline)) {
+    do_key<uint32_t>(t + 1u, (hash1(t) * parts) >> (32 - a.log2_first) << 2, (word >> kTokenBits) + 1u, f);
+  }
+  __device__ __forceinline__ void do_pair(uint64_t word, int f) {
     const uint32_t h = hash2(uint32_t(word) & kNoToken, uint32_t(word >> kTokenBits) & kNoToken);
-    do_key(uint64_t((word & ((1ull << (2 * kTokenBits)) - 1ull)) | 1ull << 63), (h * parts) >> (32 - a.log2_pair) << 3,
-           uint32_t(word >> (2 * kTokenBits)) + 1u, f);
-  };
+    do_key<uint64_t>((word & ((1ull << (2 * kTokenBits)) - 1ull)) | 1ull << 63, (h * parts) >> (32 - a.log2_pair) << 3,
+                     uint32_t(word >> (2 * kTokenBits)) + 1u, f);
+  }
 
-  // ---- 4-grams: ids, and the tokens under them
-  const uint32_t id_limit = 1u << a.id_bits, capacity = uint32_t(a.capacity);
-  const uint32_t bucket_mask = ((4u << a.log2_item) - 1u) & ~15u;
-  struct Item {
-    uint32_t t0;
-    uint64_t rest;
-  };
-  auto load_item = [&](uint32_t id) __attribute__((always_inline)) {
+  __device__ __forceinline__ Item load_item(uint32_t id) const {
     return Item{*lds<uint32_t>(a.off_lead + 4u * id), *lds<uint64_t>(a.off_tokens + 8u * id)};
-  };
-  auto same = [](const Item& x, const Item& y, int n) __attribute__((always_inline)) {
+  }
+  static __device__ __forceinline__ bool same(const Item& x, const Item& y, int n) {
     const uint64_t mask = n == 3 ? (1ull << (2 * kTokenBits)) - 1ull : ~0ull;
     return x.t0 == y.t0 && ((x.rest ^ y.rest) & mask) == 0ull;
-  };
-  auto last_of = [](const Item& x) __attribute__((always_inline)) { return uint32_t(x.rest >> (2 * kTokenBits)); };
+  }
+  static __device__ __forceinline__ uint32_t last_of(const Item& x) { return uint32_t(x.rest >> (2 * kTokenBits)); }
+  static __device__ __forceinline__ uint32_t item_hash(const Item& x) {
+    return hash3(x.t0, uint32_t(x.rest) & kNoToken, uint32_t(x.rest >> kTokenBits) & kNoToken);
+  }
   // An id that a lane took and had no use for, where there are no new ones; `capacity`: none found.  (Each lane looks at
   // places of its own: where lanes lose many ids, the first ones will do, and few lost are no use.)
-  auto id_given_back = [&]() __attribute__((always_inline)) {
+  __device__ __forceinline__ uint32_t id_given_back() const {
     uint32_t h = uint32_t(tid) * 0x85EBCA6Bu;
 #pragma unroll 1
-    for (int tries = 0; tries < 64 && !lds_peek(again_at); ++tries) {
+    for (int tries = 0; tries < 24 && !lds_peek(again_at); ++tries) {
       h = h * 0x9E3779B1u + 0x7F4A7C15u;
       const uint32_t id = __umulhi(h, capacity), at = a.off_lead + 4u * id;
       if (lds_peek(at) == kGivenBack && lds_cas<uint32_t>(at, 0u, kGivenBack) == kGivenBack) return id;
     }
     *lds<uint32_t>(again_at) = 1u;
     return capacity;
-  };
+  }
   // The id of the n-gram of order n (3 or 4) with hash h, and the item under it; it is entered if it is the
   // candidate's and not there.  false: not there, or no id left for it.  Who enters one takes an id, writes the
   // tokens under it and then swaps it in; where another lane was first, the id is given back.  (Ids that were lost
   // there ran out on texts of few different tokens, which all lanes enter at once: two of 100 000, 13 different ones,
   // 122 us a call, now 25.  The lanes with the n-gram of the first one used to wait for its id instead: that took
   // longer than it saved, 50 groups of two times 20 000 61.1 us, now 60.2.)
-  auto resolve = [&](const Item& x, uint32_t h, int n, int f, uint32_t& id, Item& found, bool& is_new) __attribute__((always_inline)) {
+  __device__ __forceinline__ bool resolve(const Item& x, uint32_t h, int n, int f, uint32_t& id, Item& found,
+                                          bool& is_new) const {
     uint32_t s = ((h * parts) >> (30 - a.log2_item)) & bucket_mask;
     const uint32_t mine = h << (a.id_bits + 1) | uint32_t(n - 2) << a.id_bits;
     Quad e;
@@ -589,12 +618,8 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     }
     *lds<uint32_t>(a.off_lead + 4u * own) = is_new ? x.t0 : kGivenBack;  // (a branch: 2 % of the call)
     return true;
-  };
-  auto item_hash = [](const Item& x) __attribute__((always_inline)) {
-    return hash3(x.t0, uint32_t(x.rest) & kNoToken, uint32_t(x.rest >> kTokenBits) & kNoToken);
-  };
-  auto longer_hash = [&](const Item& x, uint32_t h) __attribute__((always_inline)) { return hash4(h, last_of(x)); };
-  auto do_item = [&](uint64_t rest, uint32_t lead, int f) __attribute__((always_inline)) {
+  }
+  __device__ __forceinline__ void do_item(uint64_t rest, uint32_t lead, int f) {
     const uint32_t times = (lead >> kTokenBits) + 1u;
     const Item x{lead & kNoToken, rest};
     const uint32_t h = item_hash(x);
@@ -604,17 +629,15 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
     if (!resolve(x, h, 3, f, id, found, is_new)) return;
     // (one that is new at order 3 is new at order 4, too)
     if (f == 0 && is_new && times == 1u && !ALL) return;
-    if (ALL) created += is_new ? 1u : 0u;
     count(table_bytes + 4u * id, times, f, is_new, matches);
     // (behind the end there is no fourth token)
     if (N < 4 || last_of(x) == kNoToken) return;
-    if (last_of(x) != last_of(found) && !resolve(x, longer_hash(x, h), 4, f, id, found, is_new))
-      return;
-    if (ALL) created4 += is_new ? 1u : 0u;
+    if (last_of(x) != last_of(found) && !resolve(x, hash4(h, last_of(x)), 4, f, id, found, is_new)) return;
     count(counters4 + 4u * id, times, f, is_new, matches4);
-  };
+  }
 
-  auto side = [&](bool cand, Member m) __attribute__((always_inline)) {
+  // The candidate's members, or the references'; m: the wavefront's first block.
+  __device__ __forceinline__ void side(bool cand, Member m) {
     const uint32_t marks = cand ? cand_marks : ref_marks;
     int begin = cand ? 0 : cand_members;
     const int end = cand ? cand_members : members;
@@ -636,21 +659,14 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
       if (begin >= end) break;
       const int next = min(end - begin, window);
       __syncthreads();
+      if (KIND == 2 && lds_peek(again_at)) break;  // uniform: what is counted is of no use
       mark(marks, begin, next);
       __syncthreads();
       if (wave * kWave < next) m = fetch(marks, begin, next, wave, cand);
     }
-  };
-  Member m{0, 0, 0}, later{0, 0, 0};
-  const int refs_size = min(members - cand_members, window);
-  if (wave * kWave < min(cand_members, window)) m = fetch(cand_marks, 0, min(cand_members, window), wave, true);
-  // (on their way while the candidate's are entered)
-  if (wave * kWave < refs_size) later = fetch(ref_marks, cand_members, refs_size, wave, false);
-  side(true, m);
-  __syncthreads();
-  side(false, later);
-  __syncthreads();
-  auto sweep = [&](uint32_t at) __attribute__((always_inline)) {
+  }
+  // The candidate's n-grams clipped; `there`: the entries (of which every occurrence is counted).
+  __device__ __forceinline__ uint32_t sweep(uint32_t at, uint32_t& there) const {
     uint32_t part = 0;
     for (uint32_t k = at + 4u * uint32_t(tid); k < at + slots_bytes; k += 4u * kTallyThreads) {
       const uint32_t head = *lds<uint32_t>(k);
@@ -661,145 +677,372 @@ __device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
         most = max(most, HALVES ? max(word & 0xFFFFu, word >> 16) : word);
       }
       part += min(of_cand, most);
+      if (ALL) there += (of_cand | most) != 0u ? 1u : 0u;
     }
     return part;
-  };
-  auto add_to = [&](uint32_t at, uint32_t part) __attribute__((always_inline)) {
+  }
+  __device__ __forceinline__ void add_to(uint32_t at, uint32_t part) const {
     const int sum = wave_sum(int(part));
     if (lane == 0 && sum) lds_add_only(at, uint32_t(sum));
-  };
-  auto add_up = [&](int n, uint32_t part, uint32_t sizes) __attribute__((always_inline)) {
-    add_to(lost_at + 12u + 4u * uint32_t(n), part);
-    if (ALL) add_to(lost_at + 28u + 4u * uint32_t(n), sizes);
-  };
-  const bool rouge = KIND < 2 && a.rouge_overlap;  // uniform
-  const uint32_t overlaps_at = lost_at + 64u;
-  if (rouge && !ONE) {  // the overlap with each reference
-    for (int f = 1; f <= pb.R; ++f) {
-      uint32_t part = 0;
-      for (uint32_t k = table_bytes + 4u * uint32_t(tid); k < table_bytes + slots_bytes; k += 4u * kTallyThreads) {
-        const uint32_t head = *lds<uint32_t>(k), word = *lds<uint32_t>(k + uint32_t(HALVES ? f >> 1 : f) * slots_bytes);
-        part += HALVES ? min((head & 0xFFFFu) + 1u, f & 1 ? word >> 16 : word & 0xFFFFu) : min(head + 1u, word);
+  }
+  // Order n's sums, of the counters at `at` or as matched.
+  __device__ __forceinline__ void add_up(int n, uint32_t at, uint32_t matched) const {
+    uint32_t there = 0;
+    add_to(lost_at + 12u + 4u * uint32_t(n), ONE ? matched : sweep(at, there));
+    if (ALL) add_to(lost_at + 28u + 4u * uint32_t(n), there);
+  }
+  __device__ __forceinline__ uint32_t report_loss() const {
+    const uint32_t lost = *lds<uint32_t>(lost_at);  // uniform
+    if (tid == 0 && lost) {
+      if (a.pb.status) atomicOr(a.pb.status, TB_DEV_TABLE_OVERFLOW);
+      a.overflow[g] = 1;
+    }
+    return lost;
+  }
+  // (wavefront 0) The partition's sums, from LDS; of a share of order 4 (not `own`): that order's.
+  // The last partition (or share of one) of an order to arrive writes the order's statistics, and the last of these
+  // scores the sentence: one round trip to memory for a workgroup, three for the last one, where a kernel of its own
+  // took 3.5 us.  Everything that passes between workgroups goes through atomics whose answers are awaited.
+  __device__ __forceinline__ void arrive(uint32_t lost, bool own) const {
+    const Problem& pb = a.pb;
+    const int n0 = KIND + lane;  // order n0 + 1
+    const int64_t stat = int64_t(g) * N + n0;
+    bool last = false;
+    if (lane < (KIND == 2 ? 2 : 1) && n0 < N && (own || n0 == 3)) {
+      if (ALL) atomicAdd(&a.st.distinct[stat], int(*lds<uint32_t>(lost_at + 32u + 4u * uint32_t(n0))));
+      const unsigned long long add = *lds<uint32_t>(lost_at + 16u + 4u * uint32_t(n0)) | 1ull << 24 | (lost ? 1ull << 52 : 0ull);
+      const unsigned long long all = add + __hip_atomic_fetch_add(&a.arrived[stat], add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const uint32_t shares = uint32_t(all >> 40) & 0xFFFu;  // (of order 4)
+      if (KIND == 2 && shares) *lds<uint32_t>(called_at()) = 1u;
+      if ((uint32_t(all >> 24) & 0xFFFFu) == parts + shares) {
+        const int len = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, nullptr);
+        a.st.clipped[stat] = int32_t(all & 0xFFFFFFull);
+        a.st.total[stat] = max(len - n0, 0);
+        if (a.out)
+          last = __hip_atomic_fetch_add(&a.complete[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == N - 1;
       }
-      add_to(overlaps_at + 4u * uint32_t(f), part);
+    }
+    if (!__builtin_amdgcn_ballot_w64(last)) return;  // uniform
+    unsigned long long all = 0;
+    if (lane < N) all = __hip_atomic_load(&a.arrived[int64_t(g) * N + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const int c = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, pb.status);
+    const RefRows rows = ref_rows(pb, g, true);
+    const int r = closest_ref_len(c, pb.ref_len + rows.row0, rows.used, pb.ref_stride, pb.status);
+    const float brevity = expf(1.0f - float(r) / float(c));
+    const float score = bleu_from_stats_wave<int>(int(all & 0xFFFFFFull), max(c - lane, 0), c, r, brevity, lane_weight(a.sp), a.sp);
+    const bool spoilt = __builtin_amdgcn_ballot_w64(all >> 52 != 0) != 0;
+    if (lane == 0) {
+      a.st.closest[g] = r;
+      store_score(a.out, g, spoilt ? __int_as_float(0x7FC00000) : score, a.sp.out_bf16);
     }
   }
-  const bool again = KIND == 2 && *lds<uint32_t>(again_at);  // uniform
-  if (!again) {
-    if (ONE || !rouge) add_up(KIND + 1, ONE ? matches : sweep(table_bytes), created);
-    if (KIND == 2 && N > 3) add_up(4, ONE ? matches4 : sweep(counters4), created4);
-  } else {
-    // Orders 3 and 4, each on its own, in rounds of the n-grams whose hash falls into the round; more rounds where
-    // one has too many all the same.
+
+  // ---- 4-grams where ids run out (see tally_crowd).
+  // LDS words: whether there are shares of crowded partitions to be taken; and for what is passed on to all threads.
+  __device__ __forceinline__ uint32_t called_at() const { return lost_at + 48u; }
+  __device__ __forceinline__ uint32_t told_at() const { return lost_at + 52u; }
+  // Members that take up ids.
+  __device__ __forceinline__ uint32_t entries() const { return uint32_t(ALL ? members : cand_members); }
+
+  // One order on its own: n-grams whose hash falls into the share, in `pieces` rounds, and in more of them where one
+  // has too many all the same.  Each wavefront takes a sixteenth of the members, one behind the other, whose runs then
+  // need no search.  It requests several blocks at a time (most of the time is the way from memory) and puts those
+  // members that are the share's together to full blocks, which are then entered or looked up.
+  __device__ __forceinline__ void count_alone(int n, uint32_t index, uint32_t of, uint32_t pieces) {
+    constexpr int kAhead = 4;
+    constexpr uint64_t kTokens = (1ull << (3 * kTokenBits)) - 1ull;
+    const uint32_t first_pieces = pieces;
+    auto hash_of = [&](const Item& x) { return n == 3 ? item_hash(x) : hash4(item_hash(x), last_of(x)); };
+    auto move = [&](int place, uint32_t v) { return uint32_t(__builtin_amdgcn_ds_permute(place << 2, int(v))); };
 #pragma unroll 1
-    for (int n = 3; n <= N; ++n) {
-      uint32_t part = 0;
-      const int first_rounds = 2 + 2 * (ALL ? members : cand_members) / int(capacity);
-      int rounds = first_rounds;
-      created = 0;
+    for (uint32_t done = 0; done < pieces;) {
+      __syncthreads();
+      clear(0, counters4);
+      clear(a.off_lead, cand_marks);
+      if (tid == 0) *lds<uint32_t>(ids_at) = 0u, *lds<uint32_t>(again_at) = 0u;
+      matches = 0;
+      const uint32_t all = of * pieces, mine = index * pieces + done;
+      // (in the end one lane of a wavefront after the other: sixteen ids at most are then taken in vain)
+      const int turns = pieces < 16u * first_pieces ? 1 : kWave;
 #pragma unroll 1
-      for (int round = 0; round < rounds; ++round) {
+      for (int refs = 0; refs < 2; ++refs) {
+        const int begin = refs ? cand_members : 0, end = refs ? members : cand_members;
+        const int blocks = (end - begin + kWave - 1) / kWave;
+        int at = begin + wave * blocks / kWaves * kWave;  // (uniform)
+        const int stop = min(begin + (wave + 1) * blocks / kWaves * kWave, end);
+        int run = 0;
+        if (at < stop) {
+#pragma unroll 1
+          for (int step = kMaxDealChunks / 2; step; step /= 2)
+            if (run + step < a.chunks && *before_of(run + step) <= min(at + lane, stop - 1)) run += step;
+        }
+        // An n-gram that many lanes have met: what a lane sees of it is added up in a register first.
+        uint32_t often0 = ~0u, often1 = 0, often2 = 0;  // its tokens
+        uint32_t often_at = 0, times_often = 0;
+        int f = 0;
+        // Lanes 0 .. pending - 1: members to be entered or looked up (the sequence from bit 60 of the key on).
+        uint64_t key = 0;
+        uint32_t word = 0;
+        int pending = 0;
         __syncthreads();
-        clear(0, counters4);
-        clear(a.off_lead, cand_marks);
-        if (tid == 0) *lds<uint32_t>(ids_at) = 0u, *lds<uint32_t>(again_at) = 0u;
-        matches = 0;
+        uint64_t next_key[kAhead];
+        uint32_t next_word[kAhead];
+        int loaded = 0;
 #pragma unroll 1
-        for (int i = tid, refs = 0; refs < 2; ++refs) {
-          __syncthreads();
+        while (at < stop || pending > 0) {
+          uint64_t more_key = 0;
+          uint32_t more_word = 0;
+          if (at < stop) {
+            if (loaded == 0) {
+#pragma unroll
+              for (int k = 0; k < kAhead; ++k) {
+                const int i = min(at + k * kWave + lane, stop - 1);
 #pragma unroll 1
-          for (; i < (refs ? members : cand_members); i += kTallyThreads) {
-            int run = 0;
-#pragma unroll 1
-            for (int step = kMaxDealChunks / 2; step; step /= 2)
-              if (run + step < a.chunks && *lds<int>(a.off_places + 4u * uint32_t(a.chunks + run + step)) <= i) run += step;
-            const Member m = load(i, run, refs == 0);
-            const Item x{m.word & kNoToken, m.key};
-            uint32_t h = item_hash(x);
-            if (n == 4) {
-              if (last_of(x) == kNoToken) continue;
-              h = longer_hash(x, h);
+                while (run + 1 < a.chunks && *before_of(run + 1) <= i) ++run;
+                const Member m = load(i, run, refs == 0);
+                next_key[k] = m.key | uint64_t(m.f) << (3 * kTokenBits);
+                next_word[k] = m.word;
+              }
+              loaded = kAhead;
             }
-            if (int(__umulhi(h * 0x9E3779B1u, uint32_t(rounds))) != round) continue;
-            Item found;
-            uint32_t id;
-            bool is_new;
-            // (in the end one lane of a wavefront after the other: sixteen ids at most are then taken in vain)
-            const int turns = rounds < 16 * first_rounds ? 1 : kWave;
+            bool counts = at + lane < stop;
+            const uint64_t own = next_key[0];
+            const uint32_t own_word = next_word[0];
+            --loaded;
+            at += kWave;
+#pragma unroll
+            for (int k = 0; k + 1 < kAhead; ++k) next_key[k] = next_key[k + 1], next_word[k] = next_word[k + 1];
+            const Item x{own_word & kNoToken, own & kTokens};
+            const int of_seq = refs ? ONE ? 1 : int(own >> (3 * kTokenBits)) : 0;
+            if (times_often && of_seq != f) {
+              count(often_at, times_often, f, false, matches);
+              times_often = 0;
+            }
+            f = of_seq;
+            if (n == 4) {
+              counts &= last_of(x) != kNoToken;
+            } else if (counts && same(x, Item{often0, uint64_t(often2) << 32 | often1}, 3)) {
+              times_often += (own_word >> kTokenBits) + 1u;
+              counts = false;
+            }
+            if (all > 1u) counts &= __umulhi(hash_of(x) * 0x9E3779B1u, all) == mine;
+            const uint64_t going = __builtin_amdgcn_ballot_w64(counts);
+            if (going) {
+              // Lanes that have one move it behind those waiting, the others theirs behind these (a permutation).
+              const int rank = int(__builtin_amdgcn_mbcnt_hi(uint32_t(going >> 32),
+                                                             __builtin_amdgcn_mbcnt_lo(uint32_t(going), 0u)));
+              const int place = pending + (counts ? rank : __popcll(going) + lane - rank);
+              more_key = uint64_t(move(place, uint32_t(own >> 32))) << 32 | move(place, uint32_t(own));
+              more_word = move(place, own_word);
+              if (lane >= pending) key = more_key, word = more_word;
+              pending += __popcll(going);
+            }
+            if (pending < kWave && at < stop) continue;
+          }
+          const bool counts = lane < pending;
+          const Item x{word & kNoToken, key & kTokens};
+          const uint32_t times = (word >> kTokenBits) + 1u;
+          const int seq = refs ? ONE ? 1 : int(key >> (3 * kTokenBits)) : 0;
+          const uint32_t h = hash_of(x);
+          key = more_key, word = more_word;  // (lanes 0 .. pending - 65)
+          pending = max(pending - kWave, 0);
 #pragma unroll 1
-            for (int turn = 0; turn < turns; ++turn) {
-              if ((turns > 1 && turn != lane) || !resolve(x, h, n, m.f, id, found, is_new)) continue;
-              if (ALL) created += is_new ? 1u : 0u;
-              count(table_bytes + 4u * id, (m.word >> kTokenBits) + 1u, m.f, is_new, matches);
+          for (int turn = 0; turn < turns; ++turn) {
+            bool there = false, is_new;
+            uint32_t id = 0;
+            if (counts && (turns == 1 || turn == lane)) {
+              Item found;
+              there = resolve(x, h, n, seq, id, found, is_new);
+              if (there) count(table_bytes + 4u * id, times, seq, is_new, matches);
+            }
+            if (n == 3) {
+              const uint64_t have = __builtin_amdgcn_ballot_w64(there);
+              if (!have) continue;
+              const int first = __ffsll((unsigned long long)have) - 1;
+              const uint32_t first_id = uint32_t(__builtin_amdgcn_readlane(int(id), first));
+              if (__popcll(__builtin_amdgcn_ballot_w64(there && id == first_id)) < kWave / 4) continue;
+              if (times_often) count(often_at, times_often, f, false, matches);
+              times_often = 0;
+              often_at = table_bytes + 4u * first_id;
+              const Item often = load_item(first_id);
+              often0 = uint32_t(__builtin_amdgcn_readfirstlane(int(often.t0)));
+              often1 = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(often.rest))));
+              often2 = uint32_t(__builtin_amdgcn_readfirstlane(int(often.rest >> 32)));
             }
           }
-          if (refs == 0) i = cand_members + tid;
+        }
+        if (times_often) count(often_at, times_often, f, false, matches);
+      }
+      __syncthreads();
+      if (!*lds<uint32_t>(again_at)) {  // uniform
+        add_up(n, table_bytes, matches);
+        ++done;
+      } else if (pieces < first_pieces << 8) {
+        pieces *= 2;
+        done *= 2;
+      } else {
+        if (tid == 0) *lds<uint32_t>(lost_at) = 1u;
+        break;
+      }
+    }
+  }
+};
+
+// What is left to do where ids ran out.  Many different 4-grams with the same first three tokens crowd a partition: a
+// twentieth of a text of 262 144 tokens behind one beginning are 13 000 ids, where a partition has 1900.  The workgroup
+// of such a partition (`own`) counts order 3 on its own, where they are one n-gram, and divides order 4 into shares by
+// the hash of all four tokens.  Of more than kAlone it makes them known before it arrives, and every workgroup of the
+// group's 4-grams that sees with its own arrival that there are some takes shares until none is left.  Nobody waits for
+// another one: who makes shares known takes what is left of them.
+//
+// Measured (us a call; one text of 262 144 tokens, so much of it behind one beginning with another token behind it each
+// time; the partition's workgroup counting in rounds -> this; the sorted runs take 40): 0.5 % 243 -> 79, 1 % 342 -> 96,
+// 5 % 1940 -> 69, an eighth 7780 -> 92, a quarter 22 960 -> 123; 50 texts of 20 000, a quarter 740 -> 102 (84).  A pass
+// over few members is a chain of latencies, the first one with instructions that no other workgroup has brought along.
+// Told of at the start by the dealing kernel, or by the number of members, shares come earlier (0.5 % 49), but either
+// took the usual texts 1 to 3 %, or texts of few different tokens with as many members for crowded ones.
+template <Counters COUNTERS>
+__device__ __forceinline__ void tally_crowd(int p, int members, int cand_members, bool own) {
+  typedef Tally<2, COUNTERS> T;
+  if (own) {
+    uint32_t pieces;
+    {
+      T t(arguments());
+      t.members = members;
+      t.cand_members = cand_members;
+      pieces = 1u + __umulhi(t.entries(), t.a.per_member);
+      if (t.N > 3 && pieces > kAlone) {
+        __syncthreads();
+        if (t.tid == 0) {
+          const int e = __hip_atomic_fetch_add(&t.a.crowds[t.g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          if (e < kCrowds) {
+            // (answers awaited: known before it is counted, counted before the partition arrives)
+            const int was = __hip_atomic_exchange(&t.a.crowd[t.g * kCrowds + e], p << 16 | int(pieces), __ATOMIC_RELAXED,
+                                                  __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long add = (unsigned long long)(pieces + uint32_t(was)) << 40;  // (it was 0)
+            const unsigned long long before = __hip_atomic_fetch_add(&t.a.arrived[int64_t(t.g) * t.N + 3], add,
+                                                                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            *lds<uint32_t>(t.called_at()) = uint32_t((before + add) >> 40);
+          }
+          *lds<int>(t.told_at()) = e;
         }
         __syncthreads();
-        if (!*lds<uint32_t>(again_at)) {  // uniform
-          part += ONE ? matches : sweep(table_bytes);
-        } else if (rounds < 1 << 14) {
-          rounds *= 2;
-          part = created = 0;
-          round = -1;
-        } else {
-          if (tid == 0) *lds<uint32_t>(lost_at) = 1u;
-          round = rounds;
-        }
+        if (*lds<int>(t.told_at()) < kCrowds) pieces = 0;  // uniform
       }
-      add_up(n, part, created);
+      t.count_alone(3, 0u, 1u, 1u);
     }
+    if (pieces && arguments().pb.N > 3) {  // (more crowded partitions than can be told of)
+      T t(arguments());
+      t.members = members;
+      t.cand_members = cand_members;
+      t.count_alone(4, 0u, 1u, pieces);
+    }
+    const T t(arguments());
+    __syncthreads();
+    const uint32_t lost = t.report_loss();
+    if (t.wave == 0) t.arrive(lost, true);
+    __syncthreads();
+    if (!*lds<uint32_t>(t.called_at())) return;  // uniform
   }
+#pragma unroll 1
+  for (int e = 0; e < kCrowds;) {
+    T t(arguments());
+    __syncthreads();
+    if (t.tid == 0) {  // (one thread looks: another one might see something else already)
+      const int crowds = __hip_atomic_load(&t.a.crowds[t.g], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      const int crowd = __hip_atomic_load(&t.a.crowd[t.g * kCrowds + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      int share = e < crowds ? 0xFFFF : -1;  // (not told of yet: its own workgroup comes to it; none)
+      if (crowd) share = __hip_atomic_fetch_add(&t.a.next_share[t.g * kCrowds + e], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      *lds<int>(t.told_at()) = crowd;
+      *lds<int>(t.told_at() + 4u) = share;
+      *lds<uint32_t>(t.lost_at) = *lds<uint32_t>(t.lost_at + 28u) = *lds<uint32_t>(t.lost_at + 44u) = 0u;
+    }
+    __syncthreads();
+    const int crowd = __builtin_amdgcn_readfirstlane(*lds<int>(t.told_at()));
+    const int share = __builtin_amdgcn_readfirstlane(*lds<int>(t.told_at() + 4u));
+    if (share < 0) return;
+    if (share >= (crowd & 0xFFFF)) {
+      ++e;
+      continue;
+    }
+    t.gather(t.load_place(crowd >> 16));
+    __syncthreads();
+    t.cand_members = __builtin_amdgcn_readfirstlane(*t.scratch(16));
+    t.count_alone(4, uint32_t(share), uint32_t(crowd & 0xFFFF), 1u);
+    __syncthreads();
+    const uint32_t lost = t.report_loss();
+    if (t.wave == 0) t.arrive(lost, false);
+  }
+}
+
+// One partition's members of one kind.
+template <int KIND, Counters COUNTERS>
+__device__ __forceinline__ void tally_kind(const DealArgs& a, int p) {
+  typedef Tally<KIND, COUNTERS> T;
+  typedef typename T::Member Member;
+  constexpr bool ONE = T::ONE, HALVES = T::HALVES;
+  T t(a);
+  const uint32_t place = t.load_place(p);
+  t.clear(0, t.used_bytes);
+  t.clear(KIND < 2 ? t.cand_marks : a.off_lead, t.cand_marks + 4u * uint32_t(t.window));  // (no id is given back yet)
+  t.clear(a.off_sums, a.off_places);
+  t.gather(place);
   __syncthreads();
-  const uint32_t lost = *lds<uint32_t>(lost_at);  // uniform
-  if (tid == 0 && lost) {
-    if (pb.status) atomicOr(pb.status, TB_DEV_TABLE_OVERFLOW);
-    a.overflow[g] = 1;
-  }
-  if (rouge) {
-    const uint32_t at = ONE ? lost_at + 16u + 4u * uint32_t(KIND) : overlaps_at + 4u * uint32_t(tid + 1);
-    if (tid < pb.R && *lds<uint32_t>(at)) atomicAdd(&a.rouge_overlap[int64_t(g) * pb.R + tid], int(*lds<uint32_t>(at)));
-    return;
-  }
-  if (wave != 0) return;
-  // The last partition of an order to arrive writes the order's statistics, and the last of these scores the
-  // sentence: one round trip to memory for a workgroup, three for the last one, where a kernel of its own took
-  // 3.5 us.  Everything that passes between workgroups goes through atomics whose answers are awaited.
-  const int n0 = KIND + lane;  // order n0 + 1
-  const int64_t stat = int64_t(g) * N + n0;
-  bool last = false;
-  if (lane < (KIND == 2 ? 2 : 1) && n0 < N) {
-    if (ALL) atomicAdd(&a.st.distinct[stat], int(*lds<uint32_t>(lost_at + 32u + 4u * uint32_t(n0))));
-    const unsigned long long add = *lds<uint32_t>(lost_at + 16u + 4u * uint32_t(n0)) | 1ull << 40 | (lost ? 1ull << 52 : 0ull);
-    const unsigned long long all = add + __hip_atomic_fetch_add(&a.arrived[stat], add, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if ((all >> 40 & 0xFFFu) == parts) {
-      const int len = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, nullptr);
-      a.st.clipped[stat] = int32_t(all & 0xFFFFFFFFull);
-      a.st.total[stat] = max(len - n0, 0);
-      if (a.out)
-        last = __hip_atomic_fetch_add(&a.complete[g], 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == N - 1;
+  t.cand_members = __builtin_amdgcn_readfirstlane(*t.scratch(16));
+  t.mark(t.cand_marks, 0, min(t.cand_members, t.window));
+  t.mark(t.ref_marks, t.cand_members, min(t.members - t.cand_members, t.window));
+  __syncthreads();
+  // (of so many members ids run out: not tried first)
+  bool counted = KIND < 2 || 2u * t.entries() <= 5u * t.capacity;  // uniform
+  if (counted) {
+    Member m{0, 0, 0}, later{0, 0, 0};
+    const int cand_size = min(t.cand_members, t.window), refs_size = min(t.members - t.cand_members, t.window);
+    if (t.wave * kWave < cand_size) m = t.fetch(t.cand_marks, 0, cand_size, t.wave, true);
+    // (on their way while the candidate's are entered)
+    if (t.wave * kWave < refs_size) later = t.fetch(t.ref_marks, t.cand_members, refs_size, t.wave, false);
+    t.side(true, m);
+    __syncthreads();
+    // (uniform: only what is entered can set it; with ALL the references' n-grams are, too)
+    if (KIND == 2 && !T::ALL) counted = !lds_peek(t.again_at);
+    if (counted) {
+      t.side(false, later);
+      __syncthreads();
+      if (KIND == 2 && T::ALL) counted = !lds_peek(t.again_at);  // uniform
     }
   }
-  if (!__builtin_amdgcn_ballot_w64(last)) return;  // uniform
-  unsigned long long all = 0;
-  if (lane < N) all = __hip_atomic_load(&a.arrived[int64_t(g) * N + lane], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const int c = clamped_len(uniform_load(pb.cand_len, g), pb.cand_stride, pb.status);
-  const RefRows rows = ref_rows(pb, g, true);
-  const int r = closest_ref_len(c, pb.ref_len + rows.row0, rows.used, pb.ref_stride, pb.status);
-  const float brevity = expf(1.0f - float(r) / float(c));
-  const float score = bleu_from_stats_wave<int>(int(all & 0xFFFFFFFFull), max(c - lane, 0), c, r, brevity, lane_weight(a.sp), a.sp);
-  const bool spoilt = __builtin_amdgcn_ballot_w64(all >> 52 != 0) != 0;
-  if (lane == 0) {
-    a.st.closest[g] = r;
-    store_score(a.out, g, spoilt ? __int_as_float(0x7FC00000) : score, a.sp.out_bf16);
+  if (counted) {
+    const bool rouge = KIND < 2 && a.rouge_overlap;  // uniform
+    const uint32_t overlaps_at = t.lost_at + 64u;
+    if (rouge && !ONE) {  // the overlap with each reference
+      for (int f = 1; f <= a.pb.R; ++f) {
+        uint32_t part = 0;
+        for (uint32_t k = t.table_bytes + 4u * uint32_t(t.tid); k < t.table_bytes + t.slots_bytes; k += 4u * kTallyThreads) {
+          const uint32_t head = *lds<uint32_t>(k), word = *lds<uint32_t>(k + uint32_t(HALVES ? f >> 1 : f) * t.slots_bytes);
+          part += HALVES ? min((head & 0xFFFFu) + 1u, f & 1 ? word >> 16 : word & 0xFFFFu) : min(head + 1u, word);
+        }
+        t.add_to(overlaps_at + 4u * uint32_t(f), part);
+      }
+    }
+    if (ONE || !rouge) t.add_up(KIND + 1, t.table_bytes, t.matches);
+    if (KIND == 2 && t.N > 3) t.add_up(4, t.counters4, t.matches4);
+    __syncthreads();
+    const uint32_t lost = t.report_loss();
+    if (rouge) {
+      const uint32_t at = ONE ? t.lost_at + 16u + 4u * uint32_t(KIND) : overlaps_at + 4u * uint32_t(t.tid + 1);
+      if (t.tid < a.pb.R && *lds<uint32_t>(at))
+        atomicAdd(&a.rouge_overlap[int64_t(t.g) * a.pb.R + t.tid], int(*lds<uint32_t>(at)));
+      return;
+    }
+    if (t.wave == 0) t.arrive(lost, true);
+    if (KIND < 2 || t.N < 4) return;
+    __syncthreads();
+    if (!*lds<uint32_t>(t.called_at())) return;  // uniform
   }
+  if constexpr (KIND == 2) tally_crowd<COUNTERS>(p, t.members, t.cand_members, !counted);
 }
 template <Counters COUNTERS>
 __global__ __launch_bounds__(kTallyThreads, 8) void tally_kernel(DealArgs by_value) {
-  // (read through the argument segment where its fields are used: loads of a by-value parameter all stand at the
-  // entry and occupy scalar registers throughout)
-  typedef const char __attribute__((address_space(4)))* Segment;
-  const DealArgs& a = *(const DealArgs*)(Segment)__builtin_amdgcn_kernarg_segment_ptr();
+  const DealArgs& a = arguments();
   int p = blockIdx.x;  // (the kind with the most work first)
   if (a.kinds > 2) {
     if (p < a.parts[2]) return tally_kind<2, COUNTERS>(a, p);
@@ -958,6 +1201,10 @@ hipError_t launch_deal(const Problem& pb, const DealPlan& plan, const RunsBuffer
   a.rouge_overlap = rouge_overlap;
   a.arrived = reinterpret_cast<unsigned long long*>(buffers.times);  // (N * n words there)
   a.complete = reinterpret_cast<int32_t*>(a.arrived + size_t(pb.B) * pb.N);
+  a.crowds = a.complete + pb.B;
+  a.crowd = a.crowds + pb.B;  // (a group has more than 12 288 slots)
+  a.next_share = a.crowd + size_t(pb.B) * kCrowds;
+  a.per_member = uint32_t((int64_t(20) << 32) / (17 * int64_t(plan.capacity)));
   a.sp = sp;
   a.out = out_bleu_or_null;
   a.first_kind = plan.first_kind;

@@ -140,6 +140,58 @@ def test_more_ids_than_a_partition_has(R, N):
     check(w, N)
 
 
+# What chooses a 4-gram's partition (of its first three tokens) and, where order 4 is counted in shares, its share.
+def hashes(t0, t1, t2, t3):
+    M = np.uint64(0xFFFFFFFF)
+    mul = lambda x, c: (np.asarray(x, dtype=np.uint64) * np.uint64(c)) & M
+    mix = lambda h: mul(h ^ (h >> np.uint64(15)), 0xC2B2AE3D)
+    h3 = mix((mul(t0, 0x9E3779B1) + mul(t1, 0x85EBCA6B) + mul(t2, 0x27D4EB2F)) & M)
+    return h3, mul(mix((h3 + mul(t3, 0x165667B1)) & M), 0x9E3779B1)
+
+
+def behind_beginnings(seed, B, R, L, vocab, each, beginnings, ids=None):
+    """Texts with `each` 4-grams behind each of the beginnings (b, b, b), another token behind it every time, a half of
+    them in the references, too; the rest random."""
+    w = syn.random_small(seed, B=B, R=R, vocab=vocab, max_len=L, min_len=L - 50)
+    rng = np.random.default_rng(seed)
+    for i in range(B):
+        at = 4 * rng.permutation(L // 4)[:each * beginnings]
+        x = rng.permutation(vocab if ids is None else ids)[:each]
+        for k in range(3):
+            w.cand[i, at + k] = 1 + np.repeat(np.arange(beginnings), each)
+        w.cand[i, at + 3] = np.resize(x, len(at))
+        for j in range(R):
+            w.refs[i, j] = np.where(rng.random(L) < 0.5, w.cand[i], w.refs[i, j])
+            some = at[rng.random(len(at)) < 0.5]
+            for k in range(4):
+                w.refs[i, j, some + k] = w.cand[i, some + k]
+    return w
+
+
+@pytest.mark.parametrize("B,R,L,each,beginnings", [
+    (4, 1, 30000, 1200, 1),     # 784 ids: three shares, by the partition's workgroup alone
+    (4, 3, 30000, 900, 2),      # 592 ids
+    (4, 1, 30000, 2500, 2),     # more shares, told of
+    (2, 3, 30000, 6000, 1),
+    (4, 8, 9000, 2000, 1),      # five counter words
+    (2, 2, 70000, 3000, 4),     # counters of 32 bits
+    (1, 1, 262144, 1500, 1),    # 1936 ids
+    (1, 1, 262144, 15000, 3),
+])
+def test_crowded_partitions(B, R, L, each, beginnings):
+    check(behind_beginnings(1001 + L + each, B, R, L, 50257, each, beginnings), 4)
+
+
+@pytest.mark.parametrize("part,each", [(16, 900), (100, 1200)])
+def test_shares_of_uneven_size(part, each):
+    # all 4-grams of the beginning in the first sixteenth or hundredth of the hashes: shares are divided several times,
+    # in the end one lane of a wavefront goes after the other
+    vocab = (1 << 20) - 2
+    x = np.arange(10, vocab)
+    ids = x[hashes(1, 1, 1, x)[1] < (1 << 32) // part].astype(np.int32)
+    check(behind_beginnings(1011, 2, 1, 30000, vocab, each, 1, ids), 4)
+
+
 def test_members_beyond_a_window():
     # pairs and 4-grams of few tokens: unmerged in part, far more of them in a partition than its share
     w = syn.random_small(951, B=2, R=1, vocab=13, max_len=60000, min_len=60000)
