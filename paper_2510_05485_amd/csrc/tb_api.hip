@@ -369,26 +369,37 @@ bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* pl
 // behind the better kernel over 193 shapes of the same ranges, more than a tenth behind in five; five groups of 5804
 // with three references of 6020 18.9 / 45.2, 91 of 2107 with four of 2686, two orders, 37.3 / 13.9.
 // Against the partitioned kernels, which take what the sorted runs do not: 32.
-bool takes_fused(const Call& c, const tb_config_t* cfg, const tb_stats_t* stats, bool rouge,
+bool takes_fused(const Call& c, const tb_config_t* cfg, bool rouge, bool group_distinct, bool runs, bool dealt,
                  FusedPlan* plan) {
   const Problem& pb = c.pb;
   if (c.plans.layout.path != TB_PATH_FUSED) {
-    if (cfg->force_path != TB_PATH_AUTO || cfg->workspace_tables) return false;
-    if (stats && stats->group_distinct) return false;
-    RunsPlan runs;
-    DealPlan deal;
+    if (cfg->force_path != TB_PATH_AUTO || cfg->workspace_tables || group_distinct) return false;
+    const int64_t refs = pb.R * pb.ref_stride;
     int64_t few = 32;
-    if (takes_runs(c, cfg, rouge, false, &runs)) {
-      const int64_t refs = pb.R * pb.ref_stride;
-      if (!rouge && takes_deal(pb, false, false, &deal))
-        few = pb.cand_stride / 300 + refs / 700 + 6 * pb.N - 36;
-      else
-        few = rouge ? pb.N * pb.cand_stride / 260 + pb.N * refs / 1400 - 5 * pb.R / 2 - 33
-                    : pb.cand_stride / 200 + refs / 700 - pb.R / 2 + 5 * pb.N - 33;
-    }
+    if (dealt && !rouge)
+      few = pb.cand_stride / 300 + refs / 700 + 6 * pb.N - 36;
+    else if (runs)
+      few = rouge ? pb.N * pb.cand_stride / 260 + pb.N * refs / 1400 - 5 * pb.R / 2 - 33
+                  : pb.cand_stride / 200 + refs / 700 - pb.R / 2 + 5 * pb.N - 33;
     if (c.plans.use_part && pb.B < few) return false;
   }
   return plan_fused(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.bits, rouge, plan);
+}
+
+// The kernels of a whole call, with their plan.
+struct Routed {
+  Route route;
+  FusedPlan fused;
+  DealPlan deal;
+  RunsPlan runs;
+};
+void choose_route(const Call& c, const tb_config_t* cfg, bool rouge, bool group_distinct, Routed* r) {
+  const bool runs = c.plans.layout.path == TB_PATH_GLOBAL && takes_runs(c, cfg, rouge, group_distinct, &r->runs);
+  const bool dealt = runs && takes_deal(c.pb, rouge, group_distinct, &r->deal);
+  r->route = takes_fused(c, cfg, rouge, group_distinct, runs, dealt, &r->fused) ? Route::kFused
+             : dealt                                                            ? Route::kDealt
+             : runs                                                             ? Route::kRuns
+                                                                                : Route::kStaged;
 }
 
 int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
@@ -400,12 +411,12 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
                    workspace, workspace_bytes, hip_stream, true, TB_PATH_AUTO, &c);
   if (rc != TB_OK || B == 0) return rc;
   if (!out_bleu) return TB_ERR_INVALID_ARG;
-  FusedPlan plan;
-  const bool fused = takes_fused(c, cfg, stats, false, &plan);
-  if (!fused && c.plans.layout.path == TB_PATH_FUSED) return TB_ERR_UNSUPPORTED;
   const bool group_distinct = stats && stats->group_distinct;
-  if (fused) {
-    rc = hip_rc(launch_fused(c.pb, plan, c.st, c.sp, corpus ? nullptr : out_bleu, group_distinct,
+  Routed r;
+  choose_route(c, cfg, false, group_distinct, &r);
+  if (r.route != Route::kFused && c.plans.layout.path == TB_PATH_FUSED) return TB_ERR_UNSUPPORTED;
+  if (r.route == Route::kFused) {
+    rc = hip_rc(launch_fused(c.pb, r.fused, c.st, c.sp, corpus ? nullptr : out_bleu, group_distinct,
                              c.stream));
     if (rc != TB_OK) return rc;
     if (corpus || c.want_corpus_stats) {
@@ -417,13 +428,11 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
     }
     return TB_OK;
   }
-  RunsPlan runs;
-  if (takes_runs(c, cfg, false, group_distinct, &runs)) {
+  if (r.route == Route::kDealt || r.route == Route::kRuns) {
     const RunsBuffers buffers = runs_buffers(c.pb, c.ws, c.plans.part);
-    DealPlan deal;
-    const bool dealt = takes_deal(c.pb, false, group_distinct, &deal);  // (scores the sentences, too)
-    rc = hip_rc(dealt ? launch_deal(c.pb, deal, buffers, c.st, c.sp, corpus ? nullptr : out_bleu, nullptr, c.stream)
-                      : launch_runs(c.pb, runs, buffers, c.st, group_distinct, nullptr, c.stream));
+    const bool dealt = r.route == Route::kDealt;  // (scores the sentences, too)
+    rc = hip_rc(dealt ? launch_deal(c.pb, r.deal, buffers, c.st, c.sp, corpus ? nullptr : out_bleu, nullptr, c.stream)
+                      : launch_runs(c.pb, r.runs, buffers, c.st, group_distinct, nullptr, c.stream));
     if (rc != TB_OK || (dealt && !corpus && !c.want_corpus_stats)) return rc;
     return hip_rc(launch_finalize(c.pb, c.st, c.sp, !corpus && !dealt, corpus || c.want_corpus_stats, corpus,
                                   out_bleu, c.stream, c.ws.overflow, dealt && !corpus));
@@ -443,6 +452,27 @@ int run_all(const void* cand, int64_t cand_stride, const int32_t* cand_len,
 }
 
 }  // namespace
+
+namespace tb {
+
+Route route_of_call(int32_t B, int32_t R, int64_t cand_stride, int64_t ref_stride, const tb_config_t* cfg, bool rouge,
+                    bool group_distinct) {
+  Call c{};
+  if (make_plans(B, R, cand_stride, ref_stride, cfg, &c.plans) != TB_OK) return Route::kStaged;
+  c.pb.B = B;
+  c.pb.R = R;
+  c.pb.N = cfg->max_n;
+  c.pb.cand_stride = cand_stride;
+  c.pb.ref_stride = ref_stride;
+  c.pb.group_cap = c.plans.layout.group_cap;
+  c.pb.bits = c.plans.layout.bits;
+  c.pb.vocab = cfg->vocab_size;
+  Routed r;
+  choose_route(c, cfg, rouge, group_distinct, &r);
+  return r.route;
+}
+
+}  // namespace tb
 
 extern "C" {
 
@@ -502,9 +532,10 @@ int tensorrouge_n(const void* cand, int64_t cand_stride, const int32_t* cand_len
   c.st.total = reinterpret_cast<int32_t*>(w + L.total_off);
   c.st.closest = reinterpret_cast<int32_t*>(w + L.closest_off);
   c.st.distinct = reinterpret_cast<int32_t*>(w + L.distinct_off);
-  FusedPlan plan;
-  if (takes_fused(c, cfg, nullptr, true, &plan))
-    return hip_rc(launch_fused(c.pb, plan, c.st, c.sp, nullptr, false, c.stream, &ro));
+  Routed r;
+  choose_route(c, cfg, true, false, &r);
+  if (r.route == Route::kFused)
+    return hip_rc(launch_fused(c.pb, r.fused, c.st, c.sp, nullptr, false, c.stream, &ro));
   if (L.path == TB_PATH_FUSED) return TB_ERR_UNSUPPORTED;
   // GLOBAL: pack and dictionary as for BLEU (the keys of order n build on the ids of the orders
   // below), then the count pass for order n alone, which also sums the per-reference overlaps
@@ -512,13 +543,11 @@ int tensorrouge_n(const void* cand, int64_t cand_stride, const int32_t* cand_len
   // cfg->workspace_tables set)
   if (!c.plans.use_hier && !c.plans.use_part && !c.plans.use_big) return TB_ERR_UNSUPPORTED;
   int32_t* ov = reinterpret_cast<int32_t*>(w + L.overlap_off);
-  RunsPlan runs;
-  if (takes_runs(c, cfg, true, false, &runs)) {
+  if (r.route == Route::kDealt || r.route == Route::kRuns) {
     const RunsBuffers buffers = runs_buffers(c.pb, c.ws, c.plans.part);
-    DealPlan deal;
-    rc = hip_rc(takes_deal(c.pb, true, false, &deal)
-                    ? launch_deal(c.pb, deal, buffers, c.st, c.sp, nullptr, ov, c.stream)
-                    : launch_runs(c.pb, runs, buffers, c.st, false, ov, c.stream));
+    rc = hip_rc(r.route == Route::kDealt
+                    ? launch_deal(c.pb, r.deal, buffers, c.st, c.sp, nullptr, ov, c.stream)
+                    : launch_runs(c.pb, r.runs, buffers, c.st, false, ov, c.stream));
     if (rc != TB_OK) return rc;
     return hip_rc(launch_rouge_finalize(c.pb, c.sp, ov, ro, c.stream));
   }

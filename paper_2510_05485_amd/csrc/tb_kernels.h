@@ -201,6 +201,12 @@ bool plan_fused(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
 // Whether the plan's workgroups have a compute unit each, and with it the kernel that has more registers.
 bool fused_alone(int64_t B, const FusedPlan& plan);
 
+// The kernels that serve a whole call: the fused one, those for dealt positions or for sorted runs, or the GLOBAL path's
+// stages.
+enum class Route { kFused, kDealt, kRuns, kStaged };
+Route route_of_call(int32_t B, int32_t R, int64_t cand_stride, int64_t ref_stride, const tb_config_t* cfg, bool rouge,
+                    bool group_distinct);
+
 hipError_t launch_pack(const Problem& pb, const GlobalWs& ws, hipStream_t s);
 hipError_t launch_dictionary(const Problem& pb, const GlobalWs& ws, const DictPlan& plan,
                              int32_t* distinct, hipStream_t s);

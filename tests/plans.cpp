@@ -17,6 +17,19 @@ bool runs_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N,
   return true;
 }
 
+// of the same plan: positions per thread of the sorting kernel, counter words, whether counters have 32 bits, bits of
+// an n-gram that choose a part of the table
+bool runs_shape(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int bits, bool group_distinct,
+                int32_t* out) {
+  tb::RunsPlan p;
+  if (!tb::plan_runs(B, cand_stride, ref_stride, R, N, bits, false, group_distinct, &p)) return false;
+  out[0] = p.items;
+  out[1] = p.words;
+  out[2] = p.wide_fields;
+  out[3] = p.sub_bits;
+  return true;
+}
+
 // kinds; partitions, slots and candidate's positions of each; ids; slots of their table; members in a window (of any kind);
 // partitions of all kinds; chunks; LDS bytes; first kind; false: no such plan
 bool deal_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N, int32_t vocab, bool rouge,
@@ -54,6 +67,15 @@ bool fused_plan(int64_t B, int64_t cand_stride, int64_t ref_stride, int R, int N
   out[7] = p.keep;
   out[8] = tb::fused_alone(B, p);
   return true;
+}
+
+// which kernels serve a whole call: 0 the fused one, 1 dealt positions, 2 sorted runs, 3 stages
+int route(int32_t B, int32_t R, int64_t cand_stride, int64_t ref_stride, int N, int32_t vocab, bool rouge,
+          bool group_distinct) {
+  tb_config_t cfg{};
+  cfg.max_n = N;
+  cfg.vocab_size = vocab;
+  return int(tb::route_of_call(B, R, cand_stride, ref_stride, &cfg, rouge, group_distinct));
 }
 
 bool fused_path(int64_t cand_stride, int64_t ref_stride, int R, int bits) {

@@ -10,6 +10,7 @@ import pytest
 from scipy import stats
 
 import fused_rows
+import long_rows
 import paper_2510_05485_amd as tb
 from paper_2510_05485_amd import build
 
@@ -35,6 +36,9 @@ def plans(tmp_path_factory):
     lib.fused_plan.restype = lib.fused_path.restype = flag
     lib.fused_plan.argtypes = [i64, i64, i64, i32, i32, i32, flag, ctypes.POINTER(i64)]
     lib.fused_path.argtypes = [i64, i64, i32, i32]
+    lib.route.argtypes = [i32, i32, i64, i64, i32, i32, flag, flag]
+    lib.runs_shape.restype = flag
+    lib.runs_shape.argtypes = [i64, i64, i64, i32, i32, i32, flag, ctypes.POINTER(i32)]
     lib.first_free_slot.restype = ctypes.c_uint32
     lib.first_free_slot.argtypes = [ctypes.c_uint32] * 3
     return lib
@@ -98,6 +102,23 @@ def test_dealt_partitions_leave_their_tables_room(plans):
     assert not plans.deal_plan(4, 20000, 20000, 1, 5, 1000, False, False, out)
     chance = stats.binom.logsf(slots, mean, 1.0 / np.array(tables, dtype=np.float64))
     assert chance.max() <= -40.0
+
+
+def test_long_shapes_reach_their_kernels(plans):
+    dealt, runs = 1, 2
+    for (B, R, L, Lr, vocab, N), calls in long_rows.DEALT.items():
+        for call, (n, rouge, sizes) in {"b": (N, False, False), "d": (N, False, True), "1": (1, True, False),
+                                        "2": (2, True, False)}.items():
+            assert (plans.route(B, R, L, Lr, n, vocab, rouge, sizes) == dealt) == (call in calls), (B, R, L, Lr, call)
+    for B, R, L, N in long_rows.FEW_TOKENS + [(*row[:3], 4) for row in long_rows.CROWDED]:
+        assert plans.route(B, R, L, L, N, 50257, False, False) == dealt, (B, R, L)
+    out = (ctypes.c_int32 * 4)()
+    for (B, R, L, Lr, vocab, N), (items, words, wide) in long_rows.RUNS.items():
+        bits = (vocab - 1).bit_length()
+        for sizes in (False, True):
+            assert plans.route(B, R, L, Lr, N, vocab, False, sizes) == runs, (B, R, L, Lr, sizes)
+            assert plans.runs_shape(B, L, Lr, R, N, bits, sizes, out)
+            assert list(out[:3]) == [items, words, wide] and (out[3] > 0) == (vocab == 262144), (B, R, L, Lr)
 
 
 def fused_table(plans, *shape):
