@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import long_rows
 import oracle
 import paper_2510_05485_amd as tb
 import synth_inputs as syn
@@ -57,21 +58,7 @@ def check(w, N, int64=False, lists=None, counts=None):
         check_rouge(want, overlap.cpu().numpy(), best.cpu().numpy(), prf.cpu().numpy(), TOL)
 
 
-@pytest.mark.parametrize("B,R,L,Lr,vocab,N", [
-    (3, 1, 20000, 20481, 50257, 4),          # 1024 positions a chunk
-    (20, 1, 15360, 15361, 50257, 4),         # 2048 a chunk; rows that end with one and one behind it
-    (20, 2, 10000, 10100, 3000, 4),          # counters of 16 bits, two words
-    (9, 8, 4097, 4100, 900, 4),              # five words
-    (4, 4, 12100, 9000, 900, 4),             # three, also with dictionary sizes and for ROUGE
-    (2, 2, 70000, 66000, 1000, 4),           # of 32 bits, three words
-    (2, 1, 70000, 66000, 2, 4),              # sixteen 4-grams: counts beyond 16 bits
-    (4, 1, 14000, 14000, (1 << 20) - 2, 4),  # the largest vocabulary
-    (5, 2, 9000, 9001, 300, 3),
-    (5, 3, 9000, 9001, 50257, 2),
-    (5, 1, 30000, 30000, 50257, 1),
-    (1, 1, 600, 120000, 500, 4),             # candidate much shorter than the reference
-    (1, 1, 120000, 600, 500, 4),
-])
+@pytest.mark.parametrize("B,R,L,Lr,vocab,N", list(long_rows.DEALT))
 def test_shapes(B, R, L, Lr, vocab, N):
     w = syn.random_small(911 + L, B=B, R=R, vocab=vocab, max_len=min(L, Lr), min_len=min(L, Lr) // 2,
                          cand_stride=L, ref_stride=Lr)
@@ -107,7 +94,7 @@ def test_repetition():
 
 
 @pytest.mark.parametrize("vocab", [2, 4, 13])
-@pytest.mark.parametrize("B,R,L,N", [(2, 1, 60000, 4), (16, 2, 12500, 4), (9, 3, 9000, 4), (4, 1, 30000, 3)])
+@pytest.mark.parametrize("B,R,L,N", long_rows.FEW_TOKENS)
 def test_few_different_tokens(B, R, L, N, vocab):
     # all lanes enter the same n-grams at once: ids are taken in vain, given back and used again
     check(syn.random_small(991 + R, B=B, R=R, vocab=vocab, max_len=L, min_len=L - 100), N)
@@ -126,7 +113,8 @@ def test_equal_beginnings(N):
 
 @pytest.mark.parametrize("R,N", [(1, 4), (2, 4), (1, 3), (3, 4)])
 def test_more_ids_than_a_partition_has(R, N):
-    # 4-grams of one beginning, a quarter of the text: counted in rounds
+    # 4-grams of one beginning, a quarter of the text: counted in shares (with three orders the beginnings are merged,
+    # and there are enough ids)
     w = syn.random_small(941, B=2, R=R, vocab=50257, max_len=30000, min_len=29000)
     rng = np.random.default_rng(941)
     for i in range(2):
@@ -168,16 +156,7 @@ def behind_beginnings(seed, B, R, L, vocab, each, beginnings, ids=None):
     return w
 
 
-@pytest.mark.parametrize("B,R,L,each,beginnings", [
-    (4, 1, 30000, 1200, 1),     # 784 ids: three shares, by the partition's workgroup alone
-    (4, 3, 30000, 900, 2),      # 592 ids
-    (4, 1, 30000, 2500, 2),     # more shares, told of
-    (2, 3, 30000, 6000, 1),
-    (4, 8, 9000, 2000, 1),      # five counter words
-    (2, 2, 70000, 3000, 4),     # counters of 32 bits
-    (1, 1, 262144, 1500, 1),    # 1936 ids
-    (1, 1, 262144, 15000, 3),
-])
+@pytest.mark.parametrize("B,R,L,each,beginnings", long_rows.CROWDED)
 def test_crowded_partitions(B, R, L, each, beginnings):
     check(behind_beginnings(1001 + L + each, B, R, L, 50257, each, beginnings), 4)
 
@@ -222,6 +201,41 @@ def test_tokens_outside_the_vocabulary_are_reported():
         assert st.device_status.item() == tb.TB_DEV_TOKEN_RANGE
         ref = oracle.bleu(w.cand, w.cand_len, w.refs, w.ref_len, smoothing="exp", threads=4)
         np.testing.assert_array_equal(st.clipped.cpu().numpy(), ref.clipped)
+
+
+@pytest.mark.parametrize("R", [1, 2])
+def test_scores_are_those_of_the_stages(R):
+    # bit by bit: of the same whole numbers, by the same steps
+    w = syn.random_small(1021, B=20, R=R, vocab=900, max_len=12000, min_len=6000)
+    args = [dev(a) for a in (w.cand, w.cand_len, w.refs, w.ref_len)]
+    for smoothing, param in (("none", 0.0), ("floor", 0.1), ("add-k", 1.0), ("exp", 0.0)):
+        for fn in (tb.tensorbleu_sentence, tb.tensorbleu_corpus):
+            here, there = (fn(*args, tb.make_config(vocab_size=w.vocab, smoothing=smoothing, smooth_param=param, path=path))
+                           for path in ("auto", "global"))
+            assert torch.equal(here.view(torch.int32), there.view(torch.int32))
+
+
+def test_a_table_that_tokens_fill_is_reported():
+    # 5000 tokens of one partition, whose table has 4096 slots: reported, that sentence scored NaN, and the corpus
+    vocab = (1 << 20) - 2
+    tokens = np.arange(vocab, dtype=np.uint64)
+    ids = tokens[((tokens * np.uint64(0x9E3779B1) + np.uint64(0x6A09E667)) & np.uint64(0xFFFFFFFF)) < (1 << 32) // 16]
+    w = syn.random_small(1031, B=4, R=1, vocab=vocab, max_len=20000, min_len=20000)
+    w.cand[2, 100:5100] = ids[:5000]
+    args = [dev(a) for a in (w.cand, w.cand_len, w.refs, w.ref_len)]
+    ref = oracle.bleu(w.cand, w.cand_len, w.refs, w.ref_len, max_n=1)
+    for fn in (tb.tensorbleu_sentence, tb.tensorbleu_corpus):
+        st = tb.Stats.allocate(4, 1, DEV)
+        st.group_distinct = None
+        out = fn(*args, tb.make_config(max_n=1, vocab_size=vocab), stats=st).cpu().numpy()
+        assert st.device_status.item() == tb.TB_DEV_TABLE_OVERFLOW
+        if fn is tb.tensorbleu_corpus:
+            assert np.isnan(out[0])
+        else:
+            assert np.isnan(out[2]) and np.abs(np.delete(out - ref.bleu, 2)).max() <= TOL
+    cfg = tb.make_config(max_n=1, vocab_size=vocab)
+    cfg.workspace_tables = 1                 # the way to re-issue the call
+    assert abs(tb.tensorbleu_sentence(*args, cfg).cpu().numpy()[2] - ref.bleu[2]) <= TOL
 
 
 def test_replays_of_a_captured_call():

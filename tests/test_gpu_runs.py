@@ -5,6 +5,7 @@ import numpy as np
 import pytest
 import torch
 
+import long_rows
 import oracle
 import paper_2510_05485_amd as tb
 import synth_inputs as syn
@@ -77,6 +78,20 @@ def test_shapes(B, R, L, Lr, vocab, N):
     if B > 1:                          # empty rows, and rows shorter than an n-gram
         w.cand_len[0], w.ref_len[1, 0] = 2, 0
     check(w, N, int64=B % 2 == 0, rouge_n=N if vocab == 10000 else 2)
+
+
+@pytest.mark.parametrize("B,R,L,Lr,vocab,N", list(long_rows.RUNS))
+def test_shapes_that_are_not_dealt(B, R, L, Lr, vocab, N):
+    # (many of the shapes above go to the kernels for dealt positions on AUTO)
+    w = syn.random_small(815 + L, B=B, R=R, vocab=vocab, max_len=min(L, Lr), min_len=min(L, Lr) // 2,
+                         cand_stride=L, ref_stride=Lr)
+    if B > 1:
+        w.cand_len[0], w.ref_len[1, 0] = 2, 0
+    check(w, N, int64=B % 2 == 0)
+
+
+def test_frequent_tokens_of_five_orders():
+    check(syn.long_form(B=1, L=100000, vocab=9000), 5)
 
 
 @pytest.mark.parametrize("B,R,L,Lr,vocab,N", [
