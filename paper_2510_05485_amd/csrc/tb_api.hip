@@ -339,7 +339,10 @@ bool takes_runs(const Call& c, const tb_config_t* cfg, bool rouge, bool group_di
 // runs deal out by themselves as well, in longer chunks: ROUGE-1 0.89 over 246 shapes of up to eight references (one of
 // 135 978 with one of 120 892 20.2 / 13.3; 97 of 6303 with one of 7834 21.1 / 25.1), ROUGE-2 0.91 over 67 of rows of
 // 12 000 and up to four (two of 128 592 with one of 121 506 27.8 / 20.5), 1.02 over the 150 others (60 of 1427 with
-// eight of 1772 39.5 / 50.3).
+// eight of 1772 39.5 / 50.3).  BLEU of one order is one kind of members, too: with two
+// references or more it is 0.90 of up to 1 600 000 positions (137 shapes; 0.99 from 1 300 000 on), 1.05 above (49
+// shapes, 0.86 to 1.25: 114 of 11 095 with two of 11 414 44.0 / 35.7, 31 of 20 106 with three of 17 022 29.7 / 30.5),
+// with one reference 0.92 above (ten shapes).
 bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* plan) {
   const int64_t positions = pb.B * pb.group_cap;
   if (pb.R > 8 || positions < (pb.R <= 4 ? 65536 : 262144)) return false;
@@ -347,6 +350,7 @@ bool takes_deal(const Problem& pb, bool rouge, bool group_distinct, DealPlan* pl
   if (group_distinct && (pb.R > 4 || positions < 98304)) return false;
   if (rouge && pb.N > 1 && (pb.cand_stride < 12000 || pb.R > 4)) return false;
   if (!rouge && pb.N < 4 && pb.R > 4) return false;
+  if (!rouge && pb.N == 1 && pb.R > 1 && positions > 1600000) return false;
   return plan_deal(pb.B, pb.cand_stride, pb.ref_stride, pb.R, pb.N, pb.vocab, rouge, group_distinct, plan);
 }
 

@@ -112,6 +112,10 @@ def test_long_shapes_reach_their_kernels(plans):
             assert (plans.route(B, R, L, Lr, n, vocab, rouge, sizes) == dealt) == (call in calls), (B, R, L, Lr, call)
     for B, R, L, N in long_rows.FEW_TOKENS + [(*row[:3], 4) for row in long_rows.CROWDED]:
         assert plans.route(B, R, L, L, N, 50257, False, False) == dealt, (B, R, L)
+    # one order, many positions: with one reference only
+    assert plans.route(12, 2, 48662, 50090, 1, 300, False, False) == runs
+    assert plans.route(10, 2, 48662, 50090, 1, 300, False, False) == dealt
+    assert plans.route(51, 1, 25511, 26000, 1, 300, False, False) == dealt
     out = (ctypes.c_int32 * 4)()
     for (B, R, L, Lr, vocab, N), (items, words, wide) in long_rows.RUNS.items():
         bits = (vocab - 1).bit_length()
