@@ -23,13 +23,15 @@
 // there, and those equal to it add themselves to its count; any other is passed on as it is.
 //
 // What bounds it.  Dealing: 7.7 us a workgroup, six barriers' worth of LDS and memory latency, two of them on a
-// unit, and the 19 bytes a position that it writes.  Tallying: issue, 560 vector and 450 scalar instructions of a
-// wavefront's 9 us (a third of them exec masks of the probing loops), and the longest workgroups.
+// unit, and the 19 bytes a position that it writes.  Tallying: latency, too (one text of 262 144 tokens: 356 vector and
+// 347 scalar instructions of a wavefront, which waits 64 % of its cycles; 37 MB fetched for the 11.5 that were
+// written: a partition's places lie a row of partitions apart), and the longest workgroups.
 //
-// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 33.3 -> 25.7; 11 groups of two
+// Measured (us a call, sorted runs -> this): one text of 262 144 tokens with its reference 32.6 -> 25.8; 11 groups of two
 // times 90 000 96.7 -> 59; 50 of two times 20 000 80.4 -> 57; 16 of two times 12 500 32 -> 22.6; two of 174 762
 // with two references 65 -> 40.  Of these the scores inside the counting kernel, instead of in one of their own, and
-// arguments read where they are used (113 scalar registers were moved to lanes and back, now 33) 2 to 4 us each.
+// arguments read where they are used 2 to 4 us each (113 scalar registers were moved to lanes and back, then 33; with the
+// code for crowded partitions 84 to 102).
 //
 // Keys are exact.  What the tables hold is bounded by the hashes whatever the tokens are, except for 4-grams:
 // where many different ones start with the same three tokens and ids run out, orders 3 and 4 are counted again, each

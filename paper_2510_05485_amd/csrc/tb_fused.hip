@@ -49,8 +49,9 @@
 // before that, with a barrier per insertion and look-up of each order): 16 x 256 tokens with one reference 5.9
 // (6.0, 6.7, 9.5), 256 x 1088 8.0 (8.3, 9.4, 12.8), 512 x 1024 with four references 17.0 (17.5, 19.8, 22.8), 4096 x
 // 512 with two and the batch's sums 30.3 (32.0, 47.7, 50.5), 4096 x 2048 with two 95 (102, 145, 171), 1000 x 96 with
-// up to eight 10.1 (10.3, 10.5, 13.7), ROUGE-2 of 512 x 512 with three 7.2 (7.1, 9.6, 12.5); 128 x 5000 with one
-// 18.9 (21.7, 28.5; 55 on three staged kernels), 128 x 8192 27.5 (31.2, 46.6; 98 on the partitioned ones).
+// up to eight 10.1 (10.3, 10.5, 13.7), ROUGE-2 of 512 x 512 with three 6.9 (7.1, 9.6, 12.5; 7.2 on
+// one kernel with the other orders); 128 x 5000 with one 18.9 (21.7, 28.5; 55 on three staged kernels), 128 x 8192 27.5
+// (31.2, 46.6; 98 on the partitioned ones).
 #include <type_traits>
 
 #include "tb_kernels.h"
